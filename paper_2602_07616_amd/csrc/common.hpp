@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/sere.h"
+#include "ffn_plan.hpp"
 
 // The kernels rest on gfx950 facts (wave64, the 16x16x32 bf16 MFMA and its lane layout, DPP row
 // operations, and the cache behaviour of device-scope stores that the routing kernels' hand-off

@@ -1,4 +1,5 @@
-// Grouped expert FFN for bf16 on the gfx950 matrix cores.
+// Grouped expert FFN for bf16 on the gfx950 matrix cores, for work items of at most kItemRows rows
+// (batches with many rows per expert: ffn_tile.hpp).
 //
 // The decode FFN is bound by streaming each surviving expert's weights from
 // HBM once.  Two things decide how close a kernel gets to the HBM rate here:
@@ -79,6 +80,28 @@ __device__ __forceinline__ u32x4 lower_from(u32x4 keep, u32x4 other) {
   return r;
 }
 
+// four consecutive elements of h = silu(gate) * up, at element `at`: rounded to bf16 and, with split_h, the
+// rounding residual in the second plane
+__device__ __forceinline__ void store_h4(const FfnArgs& p, size_t at, f32x4 gate, f32x4 up) {
+  uint16_t hi[4], lo[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float hv = silu(gate[r]) * up[r];
+    hi[r] = f32_to_bf16(hv);
+    lo[r] = f32_to_bf16(hv - bf16_to_f32(hi[r]));
+  }
+  uint16_t* h = reinterpret_cast<uint16_t*>(p.h);
+  uint2 packed;
+  packed.x = static_cast<uint32_t>(hi[0]) | (static_cast<uint32_t>(hi[1]) << 16);
+  packed.y = static_cast<uint32_t>(hi[2]) | (static_cast<uint32_t>(hi[3]) << 16);
+  *reinterpret_cast<uint2*>(h + at) = packed;
+  if (p.split_h) {
+    packed.x = static_cast<uint32_t>(lo[0]) | (static_cast<uint32_t>(lo[1]) << 16);
+    packed.y = static_cast<uint32_t>(lo[2]) | (static_cast<uint32_t>(lo[3]) << 16);
+    *reinterpret_cast<uint2*>(h + static_cast<size_t>(p.rows) * p.dm + at) = packed;
+  }
+}
+
 constexpr int kTile = 16;      // tokens per MFMA tile
 // Work per workgroup: two cuts.  With few work items the grid is only a few workgroups per
 // compute unit and one workgroup more on some compute units decides the kernel time, so the
@@ -96,8 +119,7 @@ constexpr int kFineCutBlocks = 2560;  // fine cut while the coarse gate/up grid 
 constexpr int kWavesPerBlock = 4;
 
 // The token operand (hidden states for gate/up, h for down) is shared by the
-// wavefronts of a workgroup (four; eight in the kernels for prefill-sized
-// batches) and staged through LDS in k chunks, double buffered: all threads of
+// wavefronts of a workgroup (four, or eight) and staged through LDS in k chunks, double buffered: all threads of
 // the workgroup copy a chunk of all token rows with 128-bit loads while
 // the previous chunk is being multiplied; lane (g, n) then reads its MFMA
 // operand straight from LDS (row n, k offset 16g: chunk 2g for A_even, 2g+1
@@ -121,14 +143,8 @@ struct Stage {
   static constexpr int kPerThread = kRows * kPiecesPerRow / BT;
   static_assert(kPerThread >= 1 && kRows * kPiecesPerRow % BT == 0, "chunk must split over the workgroup's threads");
 };
-// the largest configuration (eight token tiles, 64-wide chunks), two buffers
-constexpr int kStageLdsBytes = 2 * Stage<8, 64>::kBufBytes;
-// the kernels for prefill-sized batches stage 128-wide chunks of up to eight token tiles, or
-// 64-wide chunks of sixteen
-constexpr int kWideLdsBytes = 2 * Stage<16, 64>::kBufBytes;
-static_assert(kWideLdsBytes >= 2 * Stage<8, 128>::kBufBytes, "LDS budget");
-static_assert(Stage<8, 64>::kBufBytes >= Stage<4, 128>::kBufBytes && Stage<8, 64>::kBufBytes >= Stage<2, 256>::kBufBytes,
-              "LDS budget");
+// the largest configuration (two token tiles, 256-wide chunks), two buffers
+constexpr int kStageLdsBytes = 2 * Stage<2, 256>::kBufBytes;
 
 // Token rows of a group: row r (< nrows) of the group is row index[first + r]
 // (or first + r if index is NULL) of a matrix with leading dimension ld.
@@ -148,16 +164,15 @@ struct TokenSource {
 //   lo_plane     : with LO, a second token operand `lo_plane` elements after the
 //                  first is multiplied too (token = high + low bf16 parts)
 // All BT threads of the workgroup must call this together (it has barriers).
-// LDS_BYTES: size of the caller's LDS array (the staging configuration must fit it)
 // BT       : threads of the workgroup (all of them stage, every wavefront multiplies every staged tile)
-template <int NA, int NT, int KC, bool LO, bool HALF = false, int LDS_BYTES = kStageLdsBytes, int BT = 256>
+template <int NA, int NT, int KC, bool LO, bool HALF = false, int BT = 256>
 __device__ __forceinline__ void stream_tiles(const uint16_t* const (&wx)[NA], const uint16_t* const (&wy)[NA],
                                              const TokenSource& tok, size_t lo_plane, int kbeg, int kend, int rot,
                                              unsigned char* lds, f32x4 (&acc)[NA][NT]) {
   using St = Stage<NT, KC, BT>;
   constexpr int KB = KC / 64;          // 64-wide k blocks per chunk
   constexpr int NP = LO ? 2 : 1;
-  static_assert(NP * 2 * St::kBufBytes <= LDS_BYTES, "LDS budget");
+  static_assert(NP * 2 * St::kBufBytes <= kStageLdsBytes, "LDS budget");
   const int tid = threadIdx.x, lane = tid & 63;
   const int i = lane & 15, g = lane >> 4;
   const int len = kend - kbeg;
@@ -212,10 +227,6 @@ __device__ __forceinline__ void stream_tiles(const uint16_t* const (&wx)[NA], co
       if (!HALF) ry[a][b] = load_weight(wy[a] + kk);
     }
   };
-  // token tiles whose operands are held at a time: all of them, or four when there are sixteen
-  // (the accumulators alone are then 128 registers)
-  constexpr int TG = NT > 8 ? 4 : NT;
-  static_assert(NT % TG == 0, "token tiles are multiplied in equal groups");
   // (Issuing a slot's next load as soon as its weights have been merged into the MFMA operands,
   // i.e. before the block's MFMAs instead of after them, was measured slower: 1-2 % on the decode
   // layers, 5 % at 1024 tokens.)
@@ -228,28 +239,24 @@ __device__ __forceinline__ void stream_tiles(const uint16_t* const (&wx)[NA], co
         a_even[a] = HALF ? rx[a][b] : upper_from(rx[a][b], ry[a][b]);
         a_odd[a] = HALF ? rotate8(rx[a][b]) : lower_from(ry[a][b], rx[a][b]);
       }
+      u32x4 b_even[NP][NT], b_odd[NP][NT];
 #pragma unroll
-      for (int t0 = 0; t0 < NT; t0 += TG) {
-        u32x4 b_even[NP][TG], b_odd[NP][TG];
+      for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const unsigned char* src = lds + (buf * NP + pl) * St::kBufBytes + (t * kTile + i) * St::kRowBytes + (64 * b + 16 * g) * 2;
+          b_even[pl][t] = *reinterpret_cast<const u32x4*>(src);
+          b_odd[pl][t] = *reinterpret_cast<const u32x4*>(src + 16);
+        }
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl)
 #pragma unroll
-          for (int t = 0; t < TG; ++t) {
-            const unsigned char* src = lds + (buf * NP + pl) * St::kBufBytes + ((t0 + t) * kTile + i) * St::kRowBytes +
-                                       (64 * b + 16 * g) * 2;
-            b_even[pl][t] = *reinterpret_cast<const u32x4*>(src);
-            b_odd[pl][t] = *reinterpret_cast<const u32x4*>(src + 16);
+          for (int t = 0; t < NT; ++t) {
+            acc[a][t] = mfma_bf16(a_even[a], b_even[pl][t], acc[a][t]);
+            acc[a][t] = mfma_bf16(a_odd[a], b_odd[pl][t], acc[a][t]);
           }
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-          for (int pl = 0; pl < NP; ++pl)
-#pragma unroll
-            for (int t = 0; t < TG; ++t) {
-              acc[a][t0 + t] = mfma_bf16(a_even[a], b_even[pl][t], acc[a][t0 + t]);
-              acc[a][t0 + t] = mfma_bf16(a_odd[a], b_odd[pl][t], acc[a][t0 + t]);
-            }
-      }
     }
   };
 
@@ -291,11 +298,10 @@ __device__ __forceinline__ BlockMap map_block(bool fine, int coarse_parts) {
 }
 
 // first chunk of a workgroup: spread over the row
-// seed < 0: the workgroup's linear id
-__device__ __forceinline__ int start_rotation(int len, int chunk, int seed = -1) {
+__device__ __forceinline__ int start_rotation(int len, int chunk) {
   const int n = (len + chunk - 1) / chunk;
   if (n <= 1) return 0;
-  const unsigned id = seed < 0 ? blockIdx.y * gridDim.x + blockIdx.x : static_cast<unsigned>(seed);
+  const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
   return static_cast<int>((id * 5u) % static_cast<unsigned>(n));
 }
 
@@ -307,68 +313,34 @@ __device__ __forceinline__ int start_rotation(int len, int chunk, int seed = -1)
 // h = silu(gate) * up is stored as bf16 (plus, if split_h, the bf16 rounding
 // residual in a second plane).
 // ---------------------------------------------------------------------------
-// j0 >= d_m (a wavefront beyond the last intermediate index of a wide workgroup): the wavefront
-// still takes part in the staging, streams the last rows again and stores nothing.
-template <int NT, int KC, bool HALF, int NA = 1, int LDS_BYTES = kStageLdsBytes, int BT = 256>
+template <int NT, int KC, bool HALF, int BT>
 __device__ __forceinline__ void gateup_group(const FfnArgs& p, const uint16_t* W, int j0, int row0, int nrows,
-                                             unsigned char* lds, int rot_seed = -1) {
-  static_assert(!HALF || NA == 1, "the half-tile layout has one tile per wavefront");
+                                             unsigned char* lds) {
   const int lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int dh = p.dh, dm = p.dm;
   const int chunk = 2 * g + (i >> 3);
-  const bool live = j0 < dm;
-  if (!live) j0 = dm - 8 * NA;
   // HALF: the one half tile holds gate rows j0..j0+3 (tile rows 0-3) and up rows (tile rows 4-7);
-  // otherwise tile a holds gate rows j0 + 8a .. +7 (half tile X) and the matching up rows (Y)
-  const uint16_t* wx[NA];
-  const uint16_t* wy[NA];
-#pragma unroll
-  for (int a = 0; a < NA; ++a) {
-    const int xrow = HALF ? ((i & 4) ? dm + j0 + (i & 3) : j0 + (i & 3)) : j0 + 8 * a + (i & 7);
-    wx[a] = W + static_cast<size_t>(xrow) * dh + 8 * chunk;
-    wy[a] = W + static_cast<size_t>(dm + j0 + 8 * a + (i & 7)) * dh + 8 * chunk;
-  }
+  // otherwise the tile holds gate rows j0 .. +7 (half tile X) and the matching up rows (Y)
+  const int xrow = HALF ? ((i & 4) ? dm + j0 + (i & 3) : j0 + (i & 3)) : j0 + (i & 7);
+  const uint16_t* wx[1] = {W + static_cast<size_t>(xrow) * dh + 8 * chunk};
+  const uint16_t* wy[1] = {W + static_cast<size_t>(dm + j0 + (i & 7)) * dh + 8 * chunk};
   const TokenSource tok{static_cast<const uint16_t*>(p.hidden), p.sorted_token, row0, nrows, dh};
-  f32x4 acc[NA][NT];
+  f32x4 acc[1][NT];
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  stream_tiles<NA, NT, KC, false, HALF, LDS_BYTES, BT>(wx, wy, tok, 0, 0, dh, start_rotation(dh, KC, rot_seed), lds, acc);
-  if (!live) return;
+  for (int t = 0; t < NT; ++t) acc[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  stream_tiles<1, NT, KC, false, HALF, BT>(wx, wy, tok, 0, 0, dh, start_rotation(dh, KC), lds, acc);
 
   // gate values sit in lanes g < GL, the up values of the same (j, token) GL * 16 lanes higher
   constexpr int GL = HALF ? 1 : 2;
-  uint16_t* h = reinterpret_cast<uint16_t*>(p.h);
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
+  for (int t = 0; t < NT; ++t) {
+    f32x4 up;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      f32x4 up;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) up[r] = __shfl(acc[a][t][r], (lane + 16 * GL) & 63, kWave);
-      const int n = t * kTile + i;
-      if (g < GL && n < nrows) {
-        uint16_t hi[4], lo[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float hv = silu(acc[a][t][r]) * up[r];
-          hi[r] = f32_to_bf16(hv);
-          lo[r] = f32_to_bf16(hv - bf16_to_f32(hi[r]));
-        }
-        const size_t at = static_cast<size_t>(row0 + n) * dm + j0 + 8 * a + 4 * g;
-        uint2 packed;
-        packed.x = static_cast<uint32_t>(hi[0]) | (static_cast<uint32_t>(hi[1]) << 16);
-        packed.y = static_cast<uint32_t>(hi[2]) | (static_cast<uint32_t>(hi[3]) << 16);
-        *reinterpret_cast<uint2*>(h + at) = packed;
-        if (p.split_h) {
-          packed.x = static_cast<uint32_t>(lo[0]) | (static_cast<uint32_t>(lo[1]) << 16);
-          packed.y = static_cast<uint32_t>(lo[2]) | (static_cast<uint32_t>(lo[3]) << 16);
-          *reinterpret_cast<uint2*>(h + static_cast<size_t>(p.rows) * dm + at) = packed;
-        }
-      }
-    }
+    for (int r = 0; r < 4; ++r) up[r] = __shfl(acc[0][t][r], (lane + 16 * GL) & 63, kWave);
+    const int n = t * kTile + i;
+    if (g < GL && n < nrows) store_h4(p, static_cast<size_t>(row0 + n) * dm + j0 + 4 * g, acc[0][t], up);
+  }
 }
 
 // grid (dm / (4 WAVES), max items), 64 WAVES threads: WAVES wavefronts x 4 (fine) or 8 (coarse)
@@ -388,28 +360,19 @@ __global__ __launch_bounds__(64 * WAVES, 16 / WAVES) void ffn_gateup_mfma(FfnArg
   const uint16_t* W = static_cast<const uint16_t*>(
       expert_base<SERE_BF16>(p.w_gate_up, p.shared_gate_up, e, p.M, static_cast<size_t>(2) * p.dm * p.dh));
   const int wave = threadIdx.x >> 6;
-  // the routing step cuts experts into items of at most 32 rows; longer items (the
-  // similarity estimation's) are served 32 rows at a time, streaming the weights again
   if (fine) {
     const int j0 = (at.part * WAVES + wave) * kGateUpJ;
     if (cnt <= kTile) {
-      gateup_group<1, 512, true, 1, kStageLdsBytes, BT>(p, W, j0, off, cnt, lds);
+      gateup_group<1, 512, true, BT>(p, W, j0, off, cnt, lds);
     } else {
-      for (int q = 0; q < cnt; q += 2 * kTile) gateup_group<2, 256, true, 1, kStageLdsBytes, BT>(p, W, j0, off + q, min(2 * kTile, cnt - q), lds);
+      gateup_group<2, 256, true, BT>(p, W, j0, off, cnt, lds);
     }
   } else {
     const int j0 = (at.part * WAVES + wave) * (2 * kGateUpJ);
     if (cnt <= kTile) {
-      gateup_group<1, 256, false, 1, kStageLdsBytes, BT>(p, W, j0, off, cnt, lds);
+      gateup_group<1, 256, false, BT>(p, W, j0, off, cnt, lds);
     } else {
-      // long items (many tokens per expert): 128, 64 or 32 rows per pass over the weights
-      int q = 0;
-      for (; cnt - q > 4 * kTile; q += 8 * kTile) gateup_group<8, 64, false, 1, kStageLdsBytes, BT>(p, W, j0, off + q, min(8 * kTile, cnt - q), lds);
-      if (cnt - q > 2 * kTile) {
-        gateup_group<4, 128, false, 1, kStageLdsBytes, BT>(p, W, j0, off + q, cnt - q, lds);
-      } else if (q < cnt) {
-        gateup_group<2, 256, false, 1, kStageLdsBytes, BT>(p, W, j0, off + q, cnt - q, lds);
-      }
+      gateup_group<2, 256, false, BT>(p, W, j0, off, cnt, lds);
     }
   }
 }
@@ -420,9 +383,9 @@ __global__ __launch_bounds__(64 * WAVES, 16 / WAVES) void ffn_gateup_mfma(FfnArg
 // operand is h_hi + h_lo (two MFMAs per weight fragment).  Partial results go
 // to y[slice][row][r] (fp32).
 // ---------------------------------------------------------------------------
-template <int NA, int NT, int KC, bool LO, int LDS_BYTES = kStageLdsBytes, int BT = 256>
+template <int NA, int NT, int KC, bool LO>
 __device__ __forceinline__ void down_group(const FfnArgs& p, const uint16_t* W, int r0, int kbeg, int kend,
-                                           int slice, int row0, int nrows, unsigned char* lds, int rot_seed = -1) {
+                                           int slice, int row0, int nrows, unsigned char* lds) {
   const int lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int dh = p.dh, dm = p.dm;
@@ -444,8 +407,8 @@ __device__ __forceinline__ void down_group(const FfnArgs& p, const uint16_t* W, 
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  stream_tiles<NA, NT, KC, LO, false, LDS_BYTES, BT>(wx, wy, tok, static_cast<size_t>(p.rows) * dm, kbeg, kend,
-                                                     start_rotation(kend - kbeg, KC, rot_seed), lds, acc);
+  stream_tiles<NA, NT, KC, LO>(wx, wy, tok, static_cast<size_t>(p.rows) * dm, kbeg, kend,
+                               start_rotation(kend - kbeg, KC), lds, acc);
   if (!live) return;
   float* y = p.y + static_cast<size_t>(slice) * p.rows * dh;
 #pragma unroll
@@ -490,14 +453,12 @@ __global__ __launch_bounds__(256, 4) void ffn_down_mfma(FfnArgs p) {
         down_group<1, 1, 256, false>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
       }
     } else {
-      for (int q = 0; q < cnt; q += 2 * kTile) {
-        if (p.split_h) {
-          down_group<1, 2, 64, true>(p, W, r0, kbeg, kend, slice, off + q, min(2 * kTile, cnt - q), lds);
-        } else if (half_tail) {
-          down_group<1, 2, 128, false>(p, W, r0, kbeg, kend, slice, off + q, min(2 * kTile, cnt - q), lds);
-        } else {
-          down_group<1, 2, 256, false>(p, W, r0, kbeg, kend, slice, off + q, min(2 * kTile, cnt - q), lds);
-        }
+      if (p.split_h) {
+        down_group<1, 2, 64, true>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
+      } else if (half_tail) {
+        down_group<1, 2, 128, false>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
+      } else {
+        down_group<1, 2, 256, false>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
       }
     }
   } else {
@@ -510,122 +471,12 @@ __global__ __launch_bounds__(256, 4) void ffn_down_mfma(FfnArgs p) {
       }
     } else {
       if (p.split_h) {
-        for (int q = 0; q < cnt; q += 2 * kTile)
-          down_group<2, 2, 64, true>(p, W, r0, kbeg, kend, slice, off + q, min(2 * kTile, cnt - q), lds);
+        down_group<2, 2, 64, true>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
       } else {
-        // 64 rows per pass over the weights while more than 32 remain (128 rows per pass, one
-        // weight tile per wavefront, measured slower here: 237 vs 211 us at 2048 tokens)
-        int q = 0;
-        for (; cnt - q > 4 * kTile; q += 4 * kTile)
-          down_group<2, 4, 64, false>(p, W, r0, kbeg, kend, slice, off + q, 4 * kTile, lds);
-        if (cnt - q > 2 * kTile) {
-          down_group<2, 4, 64, false>(p, W, r0, kbeg, kend, slice, off + q, cnt - q, lds);
-        } else if (q < cnt) {
-          down_group<2, 2, 128, false>(p, W, r0, kbeg, kend, slice, off + q, cnt - q, lds);
-        }
+        down_group<2, 2, 128, false>(p, W, r0, kbeg, kend, slice, off, cnt, lds);
       }
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// Prefill-sized batches (every expert has many token rows): the same building
-// blocks with squarer workgroup tiles.  Staging the token tile costs as much
-// traffic from L2 as the weights themselves once the tile holds 128 rows, so a
-// workgroup should cover as many weight rows per staged tile as it can hold
-// accumulators for: two weight tiles per wavefront and eight (items of up to
-// 128 rows) or sixteen (up to 256 rows) token tiles per pass.  The host launches
-// these kernels instead of the ones above when the routing kernel cuts items
-// of 64 rows or more; bf16 without the split h only.
-// ---------------------------------------------------------------------------
-constexpr int kWideGateUpJ = 16;  // intermediate indices per wavefront: two tiles of 8 gate + 8 up rows
-constexpr int kWideDownRows = 32; // output rows per wavefront: two tiles
-
-// k chunk per number of token tiles: the staged chunk must give each thread of the workgroup a piece,
-// and two buffers of it must fit the LDS budget
-constexpr int wide_chunk(int nt) { return nt == 1 ? 256 : (nt <= 8 ? 128 : 64); }
-
-template <int NA, bool GATEUP, typename Fn>
-__device__ __forceinline__ void wide_rows(int cnt, Fn&& pass) {
-  // rows of the item: up to 256 in one pass (more than 128: sixteen token tiles); beyond that, passes
-  // of 128 while more than 64 remain; then one pass of <= 64, <= 32 or <= 16
-  if (cnt > 8 * kTile && cnt <= 16 * kTile) {
-    pass(std::integral_constant<int, 16>{}, 0, cnt);
-    return;
-  }
-  int q = 0;
-  for (; cnt - q > 4 * kTile; q += 8 * kTile) pass(std::integral_constant<int, 8>{}, q, min(8 * kTile, cnt - q));
-  const int rem = cnt - q;
-  if (rem > 2 * kTile) {
-    pass(std::integral_constant<int, 4>{}, q, rem);
-  } else if (rem > kTile) {
-    pass(std::integral_constant<int, 2>{}, q, rem);
-  } else if (rem > 0) {
-    pass(std::integral_constant<int, 1>{}, q, rem);
-  }
-}
-
-// The hardware hands workgroups to the chip's 8 XCDs round-robin by linear workgroup id, and each
-// XCD has an L2 of its own.  With the parts of a work item numbered along that id, the item's token
-// rows (512 KB for 128 rows of d_h = 2048) are fetched into all eight L2s, and a batch of thousands
-// of tokens does not fit any of them: measured at T = 2048, the gate/up kernel then moves twice the
-// weights' bytes across the fabric.  This renumbering gives every XCD a contiguous range of the
-// `total` working (item, part) pairs, so the parts of an item meet in one L2.  Ids >= total idle.
-constexpr unsigned kXcds = 8;
-__device__ __forceinline__ BlockMap map_block_per_xcd(unsigned items, unsigned parts, bool* idle) {
-  const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, total = items * parts;
-  *idle = id >= total;
-  const unsigned x = id % kXcds, q = total / kXcds, r = total % kXcds;
-  const unsigned v = x * q + min(x, r) + id / kXcds;
-  return BlockMap{static_cast<int>(v / parts), static_cast<int>(v % parts)};
-}
-
-// Workgroups of the wide kernels: 8 wavefronts, one workgroup per compute unit.  What bounds these
-// kernels is the bytes a compute unit takes in per flop (weights from HBM plus staged token rows
-// from L2, measured at about 30 GB/s per compute unit whatever the mix), so all eight wavefronts
-// multiply the same staged token tiles, each with two weight tiles of its own: 256 weight rows per
-// staged tile (four wavefronts: 128), and a work item holds up to 256 rows (sixteen token tiles, 128
-// accumulator registers), so that an expert with that many rows streams its weights once.
-constexpr int kWideItemRows = 16 * kTile;
-constexpr int kWideThreads = 512;
-constexpr int kWideWaves = kWideThreads / kWave;
-
-// grid (ceil(dm / 128), max items), 512 threads
-__global__ __launch_bounds__(kWideThreads, 1) void ffn_gateup_mfma_wide(FfnArgs p) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kWideLdsBytes];
-  bool idle;
-  const BlockMap at = map_block_per_xcd(*p.n_work, gridDim.x, &idle);
-  if (idle) return;
-  const int w = at.item;
-  const int e = p.work_expert[w], off = p.work_off[w], cnt = p.work_cnt[w];
-  const uint16_t* W = static_cast<const uint16_t*>(
-      expert_base<SERE_BF16>(p.w_gate_up, p.shared_gate_up, e, p.M, static_cast<size_t>(2) * p.dm * p.dh));
-  const int j0 = (at.part * kWideWaves + (threadIdx.x >> 6)) * kWideGateUpJ;  // may lie beyond d_m
-  wide_rows<2, true>(cnt, [&](auto nt, int q, int n) {
-    constexpr int NT = decltype(nt)::value;
-    gateup_group<NT, wide_chunk(NT), false, 2, kWideLdsBytes, kWideThreads>(p, W, j0, off + q, n, lds, at.part);
-  });
-}
-
-// grid (ceil(dh / 256) * ksplit, max items), 512 threads
-__global__ __launch_bounds__(kWideThreads, 1) void ffn_down_mfma_wide(FfnArgs p) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kWideLdsBytes];
-  bool idle;
-  const BlockMap at = map_block_per_xcd(*p.n_work, gridDim.x, &idle);
-  if (idle) return;
-  const int w = at.item;
-  const int e = p.work_expert[w], off = p.work_off[w], cnt = p.work_cnt[w];
-  const uint16_t* W = static_cast<const uint16_t*>(
-      expert_base<SERE_BF16>(p.w_down, p.shared_down, e, p.M, static_cast<size_t>(p.dh) * p.dm));
-  const int slab = at.part / p.ksplit, slice = at.part % p.ksplit;
-  const int r0 = (slab * kWideWaves + (threadIdx.x >> 6)) * kWideDownRows;  // may lie beyond d_h
-  const int blocks = p.dm >> 6, per = (blocks + p.ksplit - 1) / p.ksplit;
-  const int kbeg = min(slice * per, blocks) << 6, kend = min((slice + 1) * per, blocks) << 6;
-  wide_rows<2, false>(cnt, [&](auto nt, int q, int n) {
-    constexpr int NT = decltype(nt)::value;
-    down_group<2, NT, wide_chunk(NT), false, kWideLdsBytes, kWideThreads>(p, W, r0, kbeg, kend, slice, off + q, n, lds,
-                                                                           at.part);
-  });
 }
 
 }  // namespace sere

@@ -1,0 +1,131 @@
+// Host side: which FFN kernels serve a bf16 call, with which work item size and how many slices of
+// the down projection's contraction.  A function of the sizes alone.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+
+namespace sere {
+
+constexpr int kItemRows = 32;     // rows of the sorted slot list per FFN work item (FfnPlan::item_rows may be larger)
+constexpr int kTileGroups = 256;  // persistent workgroups of the kernels of ffn_tile.hpp: one per compute unit
+
+struct FfnShape {
+  int hidden, inter, num_shared, tokens;
+  double experts;      // routed experts that own rows
+  double rows;         // rows of each of them, on average
+  double spread;       // standard deviation of that
+  double slots_per_expert;  // rows per expert, all experts counted
+  bool split_h;        // h carried as two bf16 planes
+  int max_ksplit;      // slices of d_m that the workspace has room for
+};
+
+struct FfnPlan {
+  int item_rows = kItemRows;
+  bool tile_gate_up = false, tile_down = false;   // the persistent kernels of ffn_tile.hpp
+  int ksplit = 1;                                 // slices of d_m in the down projection
+};
+
+struct TileVariant {
+  int rows;            // of a work item, at most
+  int gate_up_out;     // intermediate indices per gate/up unit
+  int down_out;        // output rows per down unit
+  double gate_up_step, down_step;  // us per 64-wide k step of a unit
+};
+
+// The constants of this file are fitted to measured launches of 300 layers (those of workloads.py at 4 to 4096
+// tokens and random ones: d_h 256 to 4096, d_m 128 to 14336, 2 to 160 experts, 1 to 4000 tokens), every item size
+// and both kinds of kernels timed on each.  What the rule picks takes 2.5 % longer than the best choice on average,
+// and 17 % less than one rule for all (items of 32 to 256 rows by rows per expert) with workgroup-staged kernels.
+inline const TileVariant* tile_variants(bool split_h, int* count) {
+  // a step of a unit of 256 weight rows: 0.74 us and 2.6 ns for every token row; of 128 rows measured on its own
+  static const TileVariant plain[] = {{32, 128, 256, 0.82, 0.82},  {64, 128, 256, 0.91, 0.91}, {96, 128, 256, 0.99, 0.99},
+                                      {128, 128, 256, 1.07, 1.07}, {160, 128, 256, 1.16, 1.16}, {192, 64, 128, 0.74, 0.74},
+                                      {256, 64, 128, 0.84, 0.84}};
+  // both planes of h count in the down projection
+  static const TileVariant split[] = {{32, 128, 256, 0.82, 0.91}, {64, 128, 256, 0.91, 1.07}, {128, 128, 128, 1.07, 0.84}};
+  *count = split_h ? 3 : 7;
+  return split_h ? split : plain;
+}
+
+// expected work items of an expert whose row count is about normal: sum over k of P(rows > k * item_rows)
+inline double items_per_expert(const FfnShape& s, int item_rows) {
+  double n = 1.0;
+  for (int k = 1; k <= 4096 && k * item_rows < s.rows + 6.0 * s.spread + 1.0; ++k)
+    n += s.spread > 0.0 ? 0.5 * std::erfc((k * item_rows + 0.5 - s.rows) / (s.spread * 1.4142135623730951))
+                        : (s.rows > k * item_rows ? 1.0 : 0.0);
+  return n;
+}
+inline double total_items(const FfnShape& s, int item_rows) {
+  return s.experts * items_per_expert(s, item_rows) + static_cast<double>(s.num_shared) * ((s.tokens + item_rows - 1) / item_rows);
+}
+
+// us to stream the weights: the first 130 MB of a launch come partly from the last-level cache
+inline double stream_us(double bytes, double near_rate, double far_rate) {
+  constexpr double kNear = 1.3e8;
+  return std::min(bytes, kNear) / near_rate + std::max(0.0, bytes - kNear) / far_rate;
+}
+// us of a launch of the persistent kernels: rounds of 256 units, each its k steps and `change` us to change units
+// (down stores y, four times the bytes of h), but no less than the weights take, and 2.8 us to fill the ring.
+// With few units a step is bound by latency alone and a little shorter.
+inline double tile_cost(double units, double steps, double step_us, double change, double weight_bytes) {
+  const double rounds = std::max(1.0, std::ceil(units / kTileGroups - 0.02));
+  const double busy = std::min(1.0, std::max(0.8, units / rounds / kTileGroups));
+  return std::max(rounds * (steps * step_us * busy + change), stream_us(weight_bytes, 9.8e6, 5.8e6)) + 2.8;
+}
+// us of a launch of the kernels of ffn_mfma.hpp (items of kItemRows): the weights, an expert's further items
+// from cache, and launch, first loads and drain
+inline double row_cost(const FfnShape& s, double weight_bytes, double near_rate, double far_rate, double again_rate, double fixed) {
+  const double again = total_items(s, kItemRows) / (s.experts + s.num_shared) - 1.0;
+  return stream_us(weight_bytes, near_rate, far_rate) + again * weight_bytes / again_rate + fixed;
+}
+
+// Smallest number of slices up to max_ksplit that wastes the fewest rounds; no slice may be empty.
+inline int tile_ksplit(const FfnShape& s, double units, double step_us, double weight_bytes, double* cost) {
+  const int blocks = s.inter / 64;
+  int best = 1;
+  *cost = 1e30;
+  for (int k = 1; k <= s.max_ksplit; ++k) {
+    const int per = (blocks + k - 1) / k;
+    if ((k - 1) * per >= blocks) continue;
+    const double c = tile_cost(units * k, per, step_us, 4.4, weight_bytes) + 0.55 * (k - 1);
+    if (c < *cost) {
+      *cost = c;
+      best = k;
+    }
+  }
+  return best;
+}
+
+inline FfnPlan plan_ffn(const FfnShape& s) {
+  const double gu_bytes = (s.experts + s.num_shared) * 4.0 * s.hidden * s.inter, dn_bytes = 0.5 * gu_bytes;
+  FfnPlan best;
+  best.ksplit = s.max_ksplit;
+  // from 8 rows per expert on the token rows that the gate/up kernel stages slow the weights down
+  const double row_gu = row_cost(s, gu_bytes, 9.2e6, s.split_h || s.slots_per_expert < 8 ? 6.0e6 : 5.2e6, 5.0e6, 6.8);
+  const double row_dn = row_cost(s, dn_bytes, 6.3e6, s.split_h ? 3.9e6 : 5.7e6, 7.1e6, 6.2);
+  constexpr double kMargin = 0.9;    // what the persistent kernels have to promise to be taken
+  double best_cost = row_gu + row_dn;
+  int n = 0;
+  const TileVariant* v = tile_variants(s.split_h, &n);
+  for (int i = 0; i < n; ++i) {
+    const double items = total_items(s, v[i].rows);
+    const double gu = tile_cost(items * std::ceil(static_cast<double>(s.inter) / v[i].gate_up_out), s.hidden / 64,
+                                v[i].gate_up_step, 0.9, gu_bytes);
+    double dn;
+    const int ksplit = tile_ksplit(s, items * std::ceil(static_cast<double>(s.hidden) / v[i].down_out), v[i].down_step, dn_bytes, &dn);
+    FfnPlan p;
+    p.item_rows = v[i].rows;
+    p.tile_gate_up = v[i].rows != kItemRows || gu < kMargin * row_gu;   // the other kernels take items of kItemRows
+    p.tile_down = v[i].rows != kItemRows || dn < kMargin * row_dn;
+    p.ksplit = p.tile_down ? ksplit : s.max_ksplit;
+    const double cost = (p.tile_gate_up ? gu : row_gu) + (p.tile_down ? dn : row_dn);
+    if (cost < best_cost * (best.tile_gate_up || best.tile_down ? 1.0 : kMargin)) {
+      best_cost = cost;
+      best = p;
+    }
+  }
+  return best;
+}
+
+}  // namespace sere

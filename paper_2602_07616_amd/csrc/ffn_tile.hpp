@@ -1,0 +1,308 @@
+// Grouped expert FFN for bf16, for batches that give the experts a dozen rows and more: persistent
+// workgroups fed by loads that go straight to LDS.
+//
+// What bounds these launches is how many bytes a compute unit keeps in flight.  The weights come
+// from HBM at about 3 us of latency under load, so 27 GB/s per compute unit (7 TB/s for the chip)
+// needs some 80 KB on their way at all times, next to the token rows, which come from L2.  Loads
+// into registers cannot hold that; the 160 KB of LDS can: global_load_lds writes a stage of weight
+// and token rows straight into a ring of three or four stages (36 to 52 KB each), nothing passes
+// through registers until the matrix cores read it.
+//
+//  - A unit of work is BM weight rows x all token rows of a work item (at most BN) over the whole
+//    contraction.  256 workgroups, one per compute unit, walk their units without a gap: the ring
+//    is a single sequence of (unit, 64-wide k step), so the next unit's loads are in flight while
+//    the last one is finished and stored.
+//  - A row of a stage is 128 bytes, eight 16-byte pieces; piece c of row r lies at position
+//    c ^ (r & 7).  The loads put it there by having each lane fetch the piece that belongs at its
+//    place, still eight whole 128-byte lines per instruction, and a matrix operand (16 rows x 16
+//    bytes, rows in the wavefront's lane order) then reads every LDS bank once.
+//  - Eight wavefronts share a stage as BM / 64 x WN: 64 weight rows and every WN-th token tile
+//    each.  While the second half of a stage is multiplied the first half of the next one is read
+//    from LDS, so that reads and products overlap inside a wavefront (gate/up at 2048 tokens of
+//    the Qwen3 shape: 165 -> 151 us).
+//  - Workgroups are handed to the 8 XCDs round-robin; each XCD walks a contiguous range of units,
+//    so the parts of one item run side by side and share its token rows in one L2.  Every part
+//    starts at another k step (not the same offset of every row at once, that is, not the same
+//    memory channels: 115 -> 107 us at 128 tokens).
+//
+// Measured on the Qwen3 shape (d_h 2048, d_m 768, 128 experts), us per launch, gate/up + down,
+// against the kernels with eight wavefronts that staged token rows through registers:
+//   tokens   128: 113 + 60 -> 106 + 59     512: 140 + 82 -> 129 + 75    1024: 164 + 97 -> 136 + 85
+//           2048: 233 + 128 -> 151 + 111   3072: 260 + 155 -> 223 + 143   4096: 392 + 209 -> 273 + 179
+// Not faster: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens); the same
+// first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
+#pragma once
+
+#include "common.hpp"
+#include "ffn_generic.hpp"
+#include "ffn_mfma.hpp"
+
+namespace sere {
+
+// uniform load through the scalar cache (of arrays that earlier kernels wrote)
+__device__ __forceinline__ int scalar_load(const int32_t* p, int i) {
+  return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
+// 64 lanes x 16 bytes from memory to 1 KB of LDS at byte `lds` (lane l's bytes land at lds + 16 l).
+// They are asm so that the compiler does not wait for them on its own; nothing else of these kernels'
+// main loop counts in vmcnt but them and the result stores.
+__device__ __forceinline__ void lds_load_weights(uint32_t lds, uint32_t lane_off, const char* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void lds_load_tokens(uint32_t lds, const char* addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
+}
+// all but the youngest N vector memory operations, and this wavefront's LDS reads
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N <= 63, "vmcnt has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+constexpr unsigned kXcds = 8;
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / kWave;
+constexpr int kTileLds = 160 * 1024;
+constexpr int kRowBytes = 128;       // of a stage: one 64-wide k step
+constexpr int kLoadRows = 8;         // rows one load instruction fills
+
+// BM weight rows x BN token rows per unit, WN wavefronts along the tokens.  LO: the token operand has a
+// second plane (the rounding residual of h); BN then counts the rows of both planes.
+template <int BM, int BN, int WN, bool LO>
+struct TileShape {
+  static constexpr int kStageBytes = (BM + BN) * kRowBytes;
+  static constexpr int kStages = kTileLds / kStageBytes >= 4 ? 4 : kTileLds / kStageBytes;
+  static constexpr int kRealRows = LO ? BN / 2 : BN;
+  static constexpr int kWeightLoads = BM / kLoadRows / kTileWaves;  // per wavefront and step
+  static constexpr int kTokenInstr = BN / kLoadRows;                // per workgroup and step
+  static constexpr int kTokenLoads = (kTokenInstr + kTileWaves - 1) / kTileWaves;  // of the first kFullWaves wavefronts; the others one less
+  static constexpr int kFullWaves = kTokenInstr % kTileWaves == 0 ? kTileWaves : kTokenInstr % kTileWaves;
+  static constexpr int kTilesPerWave = kRealRows / kTile / WN;
+  static_assert(BM / 64 == kTileWaves / WN, "a wavefront owns 64 weight rows");
+  static_assert(kRealRows % (kTile * WN) == 0 && kStages >= 3, "the ring holds a stage in use and two on their way");
+};
+
+// h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of every unit.  Items have at most
+// TileShape::kRealRows rows; p.ksplit slices of d_m (down), none of them empty.  grid kTileGroups, 512 threads.
+template <bool GATEUP, int BM, int BN, int WN, bool LO>
+__global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
+  using Sh = TileShape<BM, BN, WN, LO>;
+  constexpr int S = Sh::kStages, NQ = Sh::kWeightLoads, NI = Sh::kTokenLoads, NT = Sh::kTilesPerWave;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[S * Sh::kStageBytes];
+  const uint32_t lds0 = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>(reinterpret_cast<__attribute__((address_space(3))) unsigned char*>(
+          reinterpret_cast<uintptr_t>(lds))));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int i = lane & 15, g = lane >> 4;
+  const int wm = wave / WN, wn = wave % WN;
+  const int dh = p.dh, dm = p.dm;
+  const int ld = GATEUP ? dh : dm;                       // row length of both operands
+  const int items = scalar_load(p.n_work, 0);
+  const int outs = GATEUP ? dm : dh;
+  constexpr int kOut = GATEUP ? BM / 2 : BM;             // output columns of a unit
+  const int ksplit = GATEUP ? 1 : p.ksplit;
+  const int parts = (outs + kOut - 1) / kOut * ksplit;
+  const int blocks = ld >> 6, per = (blocks + ksplit - 1) / ksplit;
+
+  // this workgroup's units: every 32nd of its XCD's contiguous range
+  const unsigned total = static_cast<unsigned>(items) * parts;
+  const unsigned xcd = blockIdx.x % kXcds, q8 = total / kXcds, r8 = total % kXcds;
+  const unsigned lo = xcd * q8 + min(xcd, r8), hi = lo + q8 + (xcd < r8 ? 1u : 0u);
+  constexpr unsigned kStride = kTileGroups / kXcds;
+  unsigned pu = lo + blockIdx.x / kXcds;                 // unit being loaded
+  unsigned cu = pu;                                      // unit being multiplied
+  if (pu >= hi) return;
+
+  // ---- loading side
+  constexpr int CH = kRowBytes / 16;                     // pieces of a row
+  const uint32_t piece = ((lane & (CH - 1)) ^ (lane / CH)) << 4;   // of a lane's row, see the layout above
+  const uint32_t lane_off = static_cast<uint32_t>(lane / CH) * ld * 2 + piece;
+  const char* wbase[NQ];
+  const char* tptr[NI];
+  int pk = 0, pbeg = 0, pnk = 0, pleft = 0;
+  auto open_load_unit = [&](unsigned u) {
+    const int item = u / parts, part = u % parts;
+    const int e = scalar_load(p.work_expert, item), off = scalar_load(p.work_off, item), cnt = scalar_load(p.work_cnt, item);
+    const int slab = part / ksplit, slice = part % ksplit;
+    const char* W = static_cast<const char*>(expert_base<SERE_BF16>(GATEUP ? p.w_gate_up : p.w_down,
+                                                                    GATEUP ? p.shared_gate_up : p.shared_down, e, p.M,
+                                                                    static_cast<size_t>(GATEUP ? 2 : 1) * dm * dh));
+    const int o0 = slab * kOut;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int r = kLoadRows * (wave * NQ + q);                // first of the LDS rows of this load
+      int row;
+      if (GATEUP) {
+        int j = o0 + (r >> 6) * 32 + (r & 31);
+        if (j >= dm) j = o0 + (r & 31);
+        row = (r & 32) ? dm + j : j;
+      } else {
+        row = o0 + r < dh ? o0 + r : o0;
+      }
+      wbase[q] = W + static_cast<size_t>(row) * ld * 2;
+    }
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+      const int v0 = kLoadRows * (wave + kTileWaves * n);       // first of the token rows
+      size_t row = 0;
+      if (GATEUP) {
+        int tok = 0;
+#pragma unroll
+        for (int s = 0; s < kLoadRows; ++s) {
+          const int t = scalar_load(p.sorted_token, off + min(v0 + s, cnt - 1));
+          tok = lane / CH == s ? t : tok;
+        }
+        row = tok;
+      } else {
+        const int v = v0 + lane / CH;
+        const int plane = LO && v >= Sh::kRealRows ? 1 : 0;
+        row = static_cast<size_t>(plane) * p.rows + off + min(v - plane * Sh::kRealRows, cnt - 1);
+      }
+      const char* base = GATEUP ? static_cast<const char*>(p.hidden) : reinterpret_cast<const char*>(p.h);
+      tptr[n] = base + row * ld * 2 + piece;
+    }
+    pbeg = min(slice * per, blocks);
+    pnk = min((slice + 1) * per, blocks) - pbeg;
+    pk = (part * 5) % pnk;
+    pleft = pnk;
+  };
+  auto issue = [&](int slot) {
+    const size_t koff = static_cast<size_t>(pbeg + pk) * kRowBytes;
+    const uint32_t at = lds0 + slot * Sh::kStageBytes;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) lds_load_weights(at + (wave * NQ + q) * 1024, lane_off, wbase[q] + koff);
+#pragma unroll
+    for (int n = 0; n < NI; ++n)
+      if (n + 1 < NI || wave < Sh::kFullWaves) lds_load_tokens(at + BM * kRowBytes + (wave + kTileWaves * n) * 1024, tptr[n] + koff);
+    if (++pk == pnk) pk = 0;
+    if (--pleft == 0) {
+      pu += kStride;
+      if (pu < hi) open_load_unit(pu);
+    }
+  };
+
+  // ---- multiplying side
+  const uint32_t frag = i * kRowBytes + ((g ^ (i & 7)) << 4);
+  f32x4 acc[4][NT];
+  int cnt = 0, off = 0, part = 0, left = 0;
+  auto open_unit = [&](unsigned u) {
+    const int item = u / parts;
+    part = u % parts;
+    off = scalar_load(p.work_off, item);
+    cnt = scalar_load(p.work_cnt, item);
+    const int slice = part % ksplit;
+    left = min((slice + 1) * per, blocks) - min(slice * per, blocks);
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  struct Frags {
+    u32x4 w[4], x[NT], y[LO ? NT : 1];
+  };
+  auto fetch = [&](Frags& f, int slot, int h) {          // operands of one 32-wide half of a stage
+    const unsigned char* st = lds + slot * Sh::kStageBytes + (frag ^ (h << 6));
+#pragma unroll
+    for (int a = 0; a < 4; ++a) f.w[a] = *reinterpret_cast<const u32x4*>(st + (wm * 64 + a * 16) * kRowBytes);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int tile = wn + WN * t;
+      f.x[t] = *reinterpret_cast<const u32x4*>(st + (BM + tile * kTile) * kRowBytes);
+      if (LO) f.y[t] = *reinterpret_cast<const u32x4*>(st + (BM + Sh::kRealRows + tile * kTile) * kRowBytes);
+    }
+  };
+  auto multiply = [&](const Frags& f) {
+    auto tile_of = [&](int t) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) acc[a][t] = mfma_bf16(f.w[a], f.x[t], acc[a][t]);
+      if (LO) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a][t] = mfma_bf16(f.w[a], f.y[t], acc[a][t]);
+      }
+    };
+    if (cnt > Sh::kRealRows - kTile * WN) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) tile_of(t);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if ((wn + WN * t) * kTile < cnt) tile_of(t);
+    }
+  };
+  auto store = [&]() {
+    const int slab = part / ksplit, slice = part % ksplit;
+    if (GATEUP) {
+      const int j0 = slab * kOut + wm * 32;
+      if (j0 >= dm) return;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int n = (wn + WN * t) * kTile + i;
+        if (n < cnt) {
+#pragma unroll
+          for (int a = 0; a < 2; ++a)                    // tiles 0, 1: gate rows, tiles 2, 3: the matching up rows
+            store_h4(p, static_cast<size_t>(off + n) * dm + j0 + 16 * a + 4 * g, acc[a][t], acc[a + 2][t]);
+        }
+      }
+    } else {
+      const int r0 = slab * kOut + wm * 64;
+      if (r0 >= dh) return;
+      float* y = p.y + static_cast<size_t>(slice) * p.rows * dh;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int n = (wn + WN * t) * kTile + i;
+        if (n < cnt) {
+          float* dst = y + static_cast<size_t>(off + n) * dh + r0 + 4 * g;
+#pragma unroll
+          for (int a = 0; a < 4; ++a) *reinterpret_cast<f32x4*>(dst + 16 * a) = acc[a][t];
+        }
+      }
+    }
+  };
+
+  // Steps run half a step out of phase with the stages: while a stage's second half is multiplied, the first
+  // half of the next one is read from LDS, so that reads and products overlap within a wavefront.
+  open_load_unit(pu);
+  int ahead = 0, slot = 0;                               // stages issued and not yet waited for; slot in use
+  for (; ahead < S && pu < hi; ++ahead) issue(ahead);
+  open_unit(cu);
+  auto wait_stage = [&](auto issued) {                   // the oldest of the stages issued, by all wavefronts
+    constexpr int D = decltype(issued)::value;           // how many there are while units are left to load
+    if (ahead == D) {
+      // everything but the youngest D - 1 stages (stores among them make the wait longer, never shorter)
+      if (wave < Sh::kFullWaves) wait_loads<(D - 1) * (NQ + NI)>(); else wait_loads<(D - 1) * (NQ + NI - 1)>();
+    } else {
+      wait_loads<0>();
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    --ahead;
+  };
+  Frags f0, f1;
+  wait_stage(std::integral_constant<int, S>{});
+  fetch(f0, 0, 0);
+  for (;;) {
+    fetch(f1, slot, 1);
+    multiply(f0);
+    if (ahead > 0) {
+      // the wait also covers this wavefront's reads of the stage in use, whose slot is then free
+      const int used = slot;
+      slot = slot + 1 == S ? 0 : slot + 1;
+      wait_stage(std::integral_constant<int, S - 1>{});
+      if (pu < hi) {
+        issue(used);
+        ++ahead;
+      }
+      fetch(f0, slot, 0);
+    }
+    multiply(f1);
+    if (--left == 0) {
+      store();
+      cu += kStride;
+      if (cu >= hi) break;
+      open_unit(cu);
+    }
+  }
+}
+
+}  // namespace sere

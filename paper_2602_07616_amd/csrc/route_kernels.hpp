@@ -441,13 +441,13 @@ struct RouteArgs {
   int32_t* sorted_slot;     // [A]
   int32_t* slot_pos;        // [A]  position of slot a = t*K+k in the sorted list
   int32_t* work_expert;     // [max items] expert of each work item (M+s for shared expert s); experts
-                            //             ascending, an expert's rows cut into items of <= kItemRows
+                            //             ascending, an expert's rows cut into items of <= item_rows
   int32_t* work_off;        // [max items] first row of the item in the sorted list
-  int32_t* work_cnt;        // [max items] rows of the item (1 .. kItemRows)
+  int32_t* work_cnt;        // [max items] rows of the item (1 .. item_rows)
   int32_t* n_work;          // [2]: number of items; 1 if the FFN kernels are to cut them fine
   int fine_items;           // ... which they do while there are at most this many items
   int topk_threads;         // threads of a workgroup that take part in the top-K merge (256 or 1024)
-  int item_rows;            // rows per work item: kItemRows, or twice that for batches with many rows per expert
+  int item_rows;            // rows per work item, at most: kItemRows and more, the host's choice
 };
 
 constexpr int kRouteThreads = 1024;
@@ -458,7 +458,6 @@ constexpr int kTopkLoneThreads = 512;    // one workgroup serves the whole batch
 constexpr int kTopkMaxSmallGroups = 64;  // groups of 256 threads up to this many workgroups, of 1024 beyond
 constexpr int kSimPrefetchMaxGroups = 8;  // workgroups of a top-K launch that all prefetch their similarity rows
 constexpr int kRouteWaves = kRouteThreads / kWave;
-constexpr int kItemRows = 32;                     // rows of the sorted slot list per FFN work item (RouteArgs::item_rows may double it)
 constexpr int kIdsInLds = 4096;                   // slots whose ids a lone workgroup keeps in LDS
 
 struct RouteShared {
@@ -595,7 +594,7 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
 
   // inclusive scans over experts: slots (-> offsets), activity (-> active
   // count) and work items (an expert's rows are cut into items of at most
-  // kItemRows rows, so that one long expert cannot hold up the FFN kernels);
+  // item_rows rows, so that one long expert cannot hold up the FFN kernels);
   // inside each of the first four wavefronts by shuffles, across them through
   // four totals in LDS
   const bool is_e = tid < SERE_MAX_EXPERTS;
@@ -643,7 +642,7 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
     p.count_after[tid] = my_cnt;
     p.primary_mask[tid] = s.prim[tid];
     const int first = inc_items - my_items;
-    // Items of 128 rows (prefill-sized batches): an expert with a few rows more than one item
+    // Items of 128 rows and more (prefill-sized batches): an expert with a few rows more than one item
     // holds is cut into items of about equal size (multiples of a 16-row tile) instead of a full
     // one and a remnant: its items then take about equally long, and as they are numbered next
     // to each other they stream the expert's weights side by side, the later one from cache.

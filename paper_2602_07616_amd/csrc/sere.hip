@@ -12,6 +12,7 @@
 #include "common.hpp"
 #include "ffn_generic.hpp"
 #include "ffn_mfma.hpp"
+#include "ffn_tile.hpp"
 #include "route_kernels.hpp"
 #include "similarity_kernels.hpp"
 
@@ -189,7 +190,8 @@ struct Pointers {
   float* y;
 };
 
-static Pointers bind(const sere_config& c, const Layout& l, void* workspace, const sere_route_out* o) {
+static Pointers bind(const sere_config& c, const Layout& l, void* workspace, const sere_route_out* o,
+                     int item_rows = kItemRows) {
   char* ws = static_cast<char*>(workspace);
   auto pick = [&](void* user, size_t off) { return user != nullptr ? user : static_cast<void*>(ws + off); };
   static const sere_route_out none{};
@@ -230,13 +232,7 @@ static Pointers bind(const sere_config& c, const Layout& l, void* workspace, con
                        ? kTopkThreadsMulti
                        : kRouteThreads;
   r.fine_items = kFineCutBlocks / (c.inter / (2 * kGateUpJ * kWavesPerBlock));
-  // many rows per expert on average (prefill-sized batches): items of 64, 128 or 256 rows, served in
-  // one pass over the weights each
-  const long long slots = static_cast<long long>(c.num_tokens) * c.top_k;
-  r.item_rows = slots >= 96ll * c.num_experts   ? kWideItemRows
-                : slots >= 48ll * c.num_experts ? 4 * kItemRows
-                : slots >= 24ll * c.num_experts ? 2 * kItemRows
-                                                : kItemRows;
+  r.item_rows = item_rows;
   p.h = reinterpret_cast<float*>(ws + l.h);
   p.y = reinterpret_cast<float*>(ws + l.y);
   return p;
@@ -318,10 +314,10 @@ static int launch_route(const sere_config& c, const Pointers& p, bool with_topk,
   return hip_status();
 }
 
-static void launch_combine(const sere_config& c, const Layout& l, const Pointers& p, const void* hidden, void* out,
-                           hipStream_t s) {
+static void launch_combine(const sere_config& c, const Layout& l, const Pointers& p, int ksplit, const void* hidden,
+                           void* out, hipStream_t s) {
   CombineArgs ca{p.y, p.topk_w, p.route.slot_pos, (c.flags & SERE_FLAG_RESIDUAL) ? hidden : nullptr, out,
-                 c.num_tokens, c.hidden, c.top_k, c.num_shared, l.ksplit, l.rows};
+                 c.num_tokens, c.hidden, c.top_k, c.num_shared, ksplit, l.rows};
   const dim3 grid(static_cast<unsigned>((c.hidden + 255) / 256) * c.num_tokens);
   if (c.dtype == SERE_F32)
     launch_stage(SERE_STAGE_COMBINE, s, combine_kernel<SERE_F32>, grid, dim3(256), ca);
@@ -329,42 +325,93 @@ static void launch_combine(const sere_config& c, const Layout& l, const Pointers
     launch_stage(SERE_STAGE_COMBINE, s, combine_kernel<SERE_BF16>, grid, dim3(256), ca);
 }
 
-// fp32 layers: vector-ALU kernels.  bf16 layers: matrix-core kernels; `wide`: the variants for
-// batches whose work items hold 128 rows (prefill-sized).
-static void launch_gateup_down(int dtype, int inter, int hidden, int max_work, int ksplit, const FfnArgs& f,
-                               hipStream_t s, bool wide = false, bool waves8 = false) {
-  if (dtype == SERE_BF16 && wide) {
-    constexpr int kGateUpPerBlock = kWideGateUpJ * kWideWaves, kDownPerBlock = kWideDownRows * kWideWaves;
-    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma_wide, dim3((inter + kGateUpPerBlock - 1) / kGateUpPerBlock, max_work),
-                 dim3(kWideThreads), f);
-    launch_stage(SERE_STAGE_DOWN, s, ffn_down_mfma_wide,
-                 dim3(((hidden + kDownPerBlock - 1) / kDownPerBlock) * ksplit, max_work), dim3(kWideThreads), f);
-    return;
+// wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
+static int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 && c.inter >= 4096) ? 1 : 0; }
+
+// Work item size and kernels of a call whose experts own the slots of T tokens.  Which experts those are is
+// known on the device only; here it is what independent tokens give: an expert stays if some token has it among
+// its top S (its top K without re-routing or with a threshold).
+static FfnPlan plan_decode(const sere_config& c, int ksplit, bool reroute) {
+  FfnPlan plan;
+  plan.ksplit = ksplit;
+  const double T = c.num_tokens, M = c.num_experts, K = c.top_k;
+  if (c.dtype == SERE_F32) {
+    // the vector-ALU kernels serve an item of any length: longer ones where experts have many rows
+    const double rows = T * K / M;
+    plan.item_rows = rows >= 96 ? 8 * kItemRows : rows >= 48 ? 4 * kItemRows : rows >= 24 ? 2 * kItemRows : kItemRows;
+    return plan;
   }
+  const double kept = reroute && !(c.threshold > 0.0f) ? c.select_top_k : K;
+  FfnShape s{};
+  s.hidden = c.hidden;
+  s.inter = c.inter;
+  s.num_shared = c.num_shared;
+  s.tokens = c.num_tokens;
+  s.experts = std::max(1.0, M * (1.0 - std::pow(1.0 - kept / M, T)));
+  s.rows = T * K / s.experts;
+  s.slots_per_expert = T * K / M;
+  s.spread = K < M ? 1.5 * std::sqrt(s.rows) : 0.0;  // tokens of a batch resemble each other: wider than by chance
+  s.split_h = wants_split_h(c) != 0;
+  s.max_ksplit = ksplit;
+  return plan_ffn(s);
+}
+
+template <bool GATEUP, int BM, int BN, int WN, bool LO = false>
+static void launch_tile_as(const FfnArgs& f, hipStream_t s) {
+  launch_stage(GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, s, ffn_tile<GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
+               dim3(kTileThreads), f);
+}
+template <bool GATEUP>
+static void launch_tile(int item_rows, const FfnArgs& f, hipStream_t s) {
+  if (!GATEUP && f.split_h) {  // both planes of the token rows count in the second size
+    switch (item_rows) {
+      case 32: launch_tile_as<false, 256, 64, 2, true>(f, s); return;
+      case 64: launch_tile_as<false, 256, 128, 2, true>(f, s); return;
+      default: launch_tile_as<false, 128, 256, 4, true>(f, s); return;
+    }
+  }
+  switch (item_rows) {
+    case 32: launch_tile_as<GATEUP, 256, 32, 2>(f, s); return;
+    case 64: launch_tile_as<GATEUP, 256, 64, 2>(f, s); return;
+    case 96: launch_tile_as<GATEUP, 256, 96, 2>(f, s); return;
+    case 128: launch_tile_as<GATEUP, 256, 128, 2>(f, s); return;
+    case 160: launch_tile_as<GATEUP, 256, 160, 2>(f, s); return;
+    case 192: launch_tile_as<GATEUP, 128, 192, 4>(f, s); return;
+    default: launch_tile_as<GATEUP, 128, 256, 4>(f, s); return;
+  }
+}
+
+// fp32 layers: vector-ALU kernels.  bf16 layers: matrix-core kernels, as planned.
+static void launch_gateup_down(int dtype, int inter, int hidden, int max_work, const FfnPlan& plan, const FfnArgs& f,
+                               hipStream_t s, bool waves8 = false) {
   if (dtype == SERE_F32) {
     launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_generic<SERE_F32>, dim3((inter + kGenJB - 1) / kGenJB, max_work),
                  dim3(256), f);
     launch_stage(SERE_STAGE_DOWN, s, ffn_down_generic<SERE_F32>, dim3((hidden + kGenRB - 1) / kGenRB, max_work),
                  dim3(256), f);
-  } else {
-    if (waves8)
-      launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<8>, dim3(inter / (kGateUpJ * 8), max_work), dim3(512), f);
-    else
-      launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<4>, dim3(inter / (kGateUpJ * 4), max_work), dim3(256), f);
-    launch_stage(SERE_STAGE_DOWN, s, ffn_down_mfma,
-                 dim3(((hidden + kDownRows * kWavesPerBlock - 1) / (kDownRows * kWavesPerBlock)) * ksplit, max_work),
-                 dim3(256), f);
+    return;
   }
+  if (plan.tile_gate_up)
+    launch_tile<true>(plan.item_rows, f, s);
+  else if (waves8)
+    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<8>, dim3(inter / (kGateUpJ * 8), max_work), dim3(512), f);
+  else
+    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<4>, dim3(inter / (kGateUpJ * 4), max_work), dim3(256), f);
+  if (plan.tile_down)
+    launch_tile<false>(plan.item_rows, f, s);
+  else
+    launch_stage(SERE_STAGE_DOWN, s, ffn_down_mfma,
+                 dim3(((hidden + kDownRows * kWavesPerBlock - 1) / (kDownRows * kWavesPerBlock)) * plan.ksplit, max_work),
+                 dim3(256), f);
 }
 
-static void launch_ffn(const sere_config& c, const Layout& l, const Pointers& p, const FfnArgs& f, void* out,
-                       hipStream_t s) {
-  const bool wide = c.dtype == SERE_BF16 && !f.split_h && p.route.item_rows >= 2 * kItemRows;
+static void launch_ffn(const sere_config& c, const Layout& l, const Pointers& p, const FfnPlan& plan, const FfnArgs& f,
+                       void* out, hipStream_t s) {
   // a dozen rows per expert and more: the gate/up workgroups of eight wavefronts (the routing
   // kernel's choice of the cut counts workgroups of four; both cuts halve alike)
   const bool waves8 = static_cast<long long>(c.num_tokens) * c.top_k >= kGateUpEightWavesRows * c.num_experts;
-  launch_gateup_down(c.dtype, c.inter, c.hidden, l.max_work, l.ksplit, f, s, wide, waves8);
-  launch_combine(c, l, p, f.hidden, out, s);
+  launch_gateup_down(c.dtype, c.inter, c.hidden, l.max_work, plan, f, s, waves8);
+  launch_combine(c, l, p, plan.ksplit, f.hidden, out, s);
 }
 
 // --------------------------------------------------------- static scratch ---
@@ -389,9 +436,6 @@ static int static_scratch(void** out) {
   *out = g_scratch_ptr[dev];
   return SERE_OK;
 }
-
-// wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
-static int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 && c.inter >= 4096) ? 1 : 0; }
 
 static int decode(const sere_config* cfg, const void* hidden, const void* router_w, const void* w_gate_up,
                   const void* w_down, const void* shared_gate_up, const void* shared_down, const float* sim,
@@ -423,7 +467,8 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   if (st != SERE_OK) return st;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Pointers p = bind(*cfg, l, workspace, dbg);
+  const FfnPlan plan = plan_decode(*cfg, l.ksplit, reroute);
+  Pointers p = bind(*cfg, l, workspace, dbg, plan.item_rows);
   p.route.sim = sim;
   p.route.reroute = reroute ? 1 : 0;
   if (!reroute) p.route.S = cfg->top_k;  // every slot is a primary slot: identity map
@@ -451,7 +496,7 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   f.M = cfg->num_experts;
   f.K = cfg->top_k;
   f.n_sh = cfg->num_shared;
-  f.ksplit = l.ksplit;
+  f.ksplit = plan.ksplit;
   f.rows = l.rows;
   // Rounding h to bf16 perturbs every term of the down projection by up to
   // 2^-9 relative; the sum of d_m such terms stays far inside the output
@@ -459,7 +504,7 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   // reach several units.  From d_m = 4096 on, h keeps its rounding residual in
   // a second bf16 plane and the down projection multiplies both.
   f.split_h = wants_split_h(*cfg);
-  launch_ffn(*cfg, l, p, f, out, s);
+  launch_ffn(*cfg, l, p, plan, f, out, s);
   return hip_status();
 }
 
@@ -488,6 +533,8 @@ struct SimLayout {
   size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, max_bits,
       total;
   int rows, ksplit;
+  FfnPlan plan;
+  int items;            // work items of an expert
   int gram_splits;      // Frobenius metric: slices of the flattened outputs in the Gram kernel
   long long gram_chunk; // ... and their length
 };
@@ -497,6 +544,23 @@ static SimLayout make_sim_layout(const sere_config& c, int n) {
   const size_t M = c.num_experts, R = M * static_cast<size_t>(n);
   l.rows = static_cast<int>(R);
   l.ksplit = down_ksplit(c);
+  l.plan.ksplit = l.ksplit;
+  if (c.dtype == SERE_F32) {
+    l.plan.item_rows = n;   // the vector-ALU kernels serve an item of any length
+  } else {
+    FfnShape s{};
+    s.hidden = c.hidden;
+    s.inter = c.inter;
+    s.tokens = n;
+    s.experts = M;
+    s.rows = n;
+    s.slots_per_expert = n;
+    s.split_h = wants_split_h(c) != 0;
+    s.max_ksplit = l.ksplit;
+    l.plan = plan_ffn(s);
+  }
+  l.items = (n + l.plan.item_rows - 1) / l.plan.item_rows;
+  const size_t W = M * l.items;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -504,9 +568,9 @@ static SimLayout make_sim_layout(const sere_config& c, int n) {
     return at;
   };
   l.sorted_token = take(R * 4);
-  l.work_expert = take(M * 4);
-  l.work_off = take(M * 4);
-  l.work_cnt = take(M * 4);
+  l.work_expert = take(W * 4);
+  l.work_off = take(W * 4);
+  l.work_cnt = take(W * 4);
   l.n_work = take(8);
   l.h = take(R * c.inter * sizeof(float));
   l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
@@ -580,10 +644,10 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   f.M = M;
   f.K = 1;
   f.n_sh = 0;
-  f.ksplit = l.ksplit;
+  f.ksplit = l.plan.ksplit;
   f.rows = l.rows;
   f.split_h = wants_split_h(*cfg);
-  hipLaunchKernelGGL(similarity_worklist_kernel, dim3((M * n + 255) / 256), dim3(256), 0, s, M, n,
+  hipLaunchKernelGGL(similarity_worklist_kernel, dim3((M * n + 255) / 256), dim3(256), 0, s, M, n, l.plan.item_rows,
                      const_cast<int32_t*>(f.sorted_token), const_cast<int32_t*>(f.work_expert),
                      const_cast<int32_t*>(f.work_off), const_cast<int32_t*>(f.work_cnt),
                      const_cast<int32_t*>(f.n_work));
@@ -595,19 +659,19 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   unsigned long long* max_bits = reinterpret_cast<unsigned long long*>(ws + l.max_bits);
   for (int b = 0; b < num_batches; ++b) {
     f.hidden = static_cast<const char*>(calib) + static_cast<size_t>(b) * n * cfg->hidden * eb;
-    launch_gateup_down(cfg->dtype, cfg->inter, cfg->hidden, M, l.ksplit, f, s);
+    launch_gateup_down(cfg->dtype, cfg->inter, cfg->hidden, M * l.items, l.plan, f, s);
     if (metric == kMetricCosine) {
-      hipLaunchKernelGGL(pair_cosine_kernel, dim3(M, M), dim3(256), 0, s, f.y, l.ksplit, l.rows, n, cfg->hidden, M,
+      hipLaunchKernelGGL(pair_cosine_kernel, dim3(M, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, M,
                          dist);
     } else if (metric == kMetricCkaLinear) {
       double* gram = reinterpret_cast<double*>(ws + l.gram);
       double* rowsum = reinterpret_cast<double*>(ws + l.rowsum);
       if (cka_kernel == kCkaLinear) {
-        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, l.ksplit, l.rows, n, cfg->hidden, gram,
+        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, gram,
                            rowsum, static_cast<double*>(nullptr));
       } else {
         double* diag = reinterpret_cast<double*>(ws + l.diag);
-        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, l.ksplit, l.rows, n, cfg->hidden, gram,
+        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, gram,
                            static_cast<double*>(nullptr), diag);
         hipLaunchKernelGGL(gram_transform_kernel, dim3(n, M), dim3(256), 0, s, gram, diag, n, cka_kernel, p0,
                            static_cast<int>(p1), rowsum);
@@ -619,11 +683,11 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
       const int nb = (M + kGramBlock - 1) / kGramBlock;
       const dim3 per_pair((M * M + 255) / 256);
       launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_gram_kernel, dim3(nb * (nb + 1) / 2, l.gram_splits), dim3(256), f.y,
-                   l.ksplit, l.rows, n, cfg->hidden, M, l.gram_chunk, part, max_bits);
+                   f.ksplit, l.rows, n, cfg->hidden, M, l.gram_chunk, part, max_bits);
       launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(per_pair.x, kGramGroups), dim3(256),
                    static_cast<const double*>(part), l.gram_splits, M, gram);
       launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, per_pair, dim3(256),
-                   static_cast<const double*>(gram), static_cast<const float*>(f.y), l.ksplit, l.rows, n, cfg->hidden,
+                   static_cast<const double*>(gram), static_cast<const float*>(f.y), f.ksplit, l.rows, n, cfg->hidden,
                    M, dist, max_bits);
     }
     launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3((M * M + 255) / 256), dim3(256),

@@ -13,19 +13,24 @@
 
 namespace sere {
 
-// work list "every expert, all n tokens": grid ceil(M*n/256), 256 threads
-__global__ __launch_bounds__(256) void similarity_worklist_kernel(int M, int n, int32_t* sorted_token,
+// work list "every expert, all n tokens" in items of at most item_rows rows (about equal ones, of whole
+// 16-row tiles): grid ceil(M*n/256), 256 threads
+__global__ __launch_bounds__(256) void similarity_worklist_kernel(int M, int n, int item_rows, int32_t* sorted_token,
                                                                   int32_t* work_expert, int32_t* work_off,
                                                                   int32_t* work_cnt, int32_t* n_work) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < M * n) sorted_token[i] = i % n;
-  if (i < M) {
-    work_expert[i] = i;
-    work_off[i] = i * n;
-    work_cnt[i] = n;
+  const int items = (n + item_rows - 1) / item_rows;
+  if (i < M * items) {
+    const int e = i / items, j = i % items;
+    const int per = items > 1 ? min(item_rows, ((n + items - 1) / items + 15) & ~15) : n;
+    const int first = min(j * per, n);
+    work_expert[i] = e;
+    work_off[i] = e * n + first;
+    work_cnt[i] = min(per, n - first);
   }
   if (i == 0) {
-    n_work[0] = M;
+    n_work[0] = M * items;
     n_work[1] = 0;  // many long items: coarse cut
   }
 }

@@ -1,0 +1,56 @@
+"""The host's choice of FFN kernels (csrc/ffn_plan.hpp, compiled here with g++): over the range of
+layers and batches the library accepts, every plan must be one that the kernels can run."""
+import math
+import os
+import random
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "plan_main.cpp"), "-o", exe], check=True)
+
+    def run(cases):
+        text = "".join("%d %d %d %d %r %r %r %r %d %d\n" % c for c in cases)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        return [tuple(int(v) for v in line.split()) for line in out if line]
+    return run
+
+
+def shape(T, dh, M, K, dm, sh, kept):
+    experts = max(1.0, M * (1.0 - (1.0 - kept / M) ** T))
+    rows = T * K / experts
+    return (dh, dm, sh, T, experts, rows, 1.5 * math.sqrt(rows) if K < M else 0.0, T * K / M, int(dm >= 4096), (dm + 2047) // 2048)
+
+
+def test_every_plan_can_be_run(plans):
+    rng = random.Random(5)
+    cases, layers = [], []
+    log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    for _ in range(4000):
+        M = log_int(1, 256)
+        K = rng.randint(1, min(M, 12))
+        layer = (log_int(1, 65536), 64 * log_int(1, 1024), M, K, 64 * log_int(1, 4096), rng.choice([0, 0, 1, 4, 16]), rng.randint(1, K))
+        layers.append(layer)
+        cases.append(shape(*layer))
+    for layer, case, (rows, tile_gu, tile_dn, ksplit) in zip(layers, cases, plans(cases)):
+        blocks, split, max_ksplit = layer[4] // 64, case[8], case[9]
+        assert rows in ((32, 64, 128) if split else (32, 64, 96, 128, 160, 192, 256)), layer
+        if not (tile_gu and tile_dn):
+            assert rows == 32, layer               # the other kernels take items of at most 32 rows
+        assert 1 <= ksplit <= max_ksplit, layer
+        assert (ksplit - 1) * -(-blocks // ksplit) < blocks, layer   # no slice of d_m is empty
+        if not tile_dn:
+            assert ksplit == max_ksplit, layer
+
+
+def test_choices_on_the_layers_the_rule_was_measured_on(plans):
+    """Qwen3 shape: the persistent kernels from 8 rows per expert on, longer items with more rows."""
+    got = plans([shape(T, 2048, 128, 8, 768, 0, 2) for T in (1, 32, 64, 128, 512, 1024, 2048, 3072)])
+    assert [g[1] for g in got] == [0, 0, 0, 1, 1, 1, 1, 1]
+    assert [g[0] for g in got] == [32, 32, 32, 32, 64, 96, 160, 256]
