@@ -1,4 +1,4 @@
-// Grouped expert FFN on the vector ALU (any dtype, any tokens-per-expert) and
+// Grouped expert FFN on the vector ALU (fp32 layers, batches of a few tokens) and
 // the weighted combine.  Expert equations: appendix "Preliminaries on MoEs"
 // (E(x) = (silu(x W_gate) * (x W_up)) W_down, y = sum_i P_i E_i(x)).
 //

@@ -81,8 +81,16 @@ __device__ __forceinline__ u32x4 lower_from(u32x4 keep, u32x4 other) {
 }
 
 // four consecutive elements of h = silu(gate) * up, at element `at`: rounded to bf16 and, with split_h, the
-// rounding residual in the second plane
+// rounding residual in the second plane; fp32 layers keep it as it is
+template <int DT = SERE_BF16>
 __device__ __forceinline__ void store_h4(const FfnArgs& p, size_t at, f32x4 gate, f32x4 up) {
+  if constexpr (DT == SERE_F32) {
+    f32x4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = silu(gate[r]) * up[r];
+    *reinterpret_cast<f32x4*>(p.h + at) = v;
+    return;
+  }
   uint16_t hi[4], lo[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {

@@ -128,4 +128,23 @@ inline FfnPlan plan_ffn(const FfnShape& s) {
   return best;
 }
 
+// fp32 layers: the persistent kernels take 128 weight rows a unit (20 KB a stage, eight stages), 32-wide k steps
+// and items of 32 rows; the matrix cores' fp32 rate bounds them from some 20 rows per expert on, so longer items
+// would gain nothing (measured with 256 x 64 units: 54 + 38 -> 93 + 65 us at 96 tokens of a 1024-wide layer).  The
+// vector-ALU kernels serve 8 rows in one pass and start faster: they keep batches of at most 8 tokens whose
+// contractions are long and whose experts are few (one token, d_h 1472: 27 against 37 us; 8 tokens, d_h 256: 24
+// against 14 us; 96 tokens, d_h 1024: 264 against 108 us).  Both sides fitted to 45 measured layers.
+constexpr int kTileF32Rows = 128;
+inline FfnPlan plan_ffn_f32(const FfnShape& s) {
+  const double experts = s.experts + s.num_shared;
+  const double gu_units = total_items(s, kItemRows) * std::ceil(s.inter / (0.5 * kTileF32Rows));
+  const double dn_units = total_items(s, kItemRows) * std::ceil(s.hidden / (1.0 * kTileF32Rows));
+  const double tile = std::ceil(gu_units / kTileGroups) * (s.hidden / 32 * 0.62 + 2.5) +
+                      std::ceil(dn_units / kTileGroups) * (s.inter / 32 * 0.62 + 2.5);
+  const double rows = 22.0 + experts * 12.0 * s.hidden * s.inter / 3.5e6;
+  FfnPlan p;
+  p.tile_gate_up = p.tile_down = s.tokens > 8 || tile < rows;
+  return p;
+}
+
 }  // namespace sere

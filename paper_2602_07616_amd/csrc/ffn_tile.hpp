@@ -1,5 +1,5 @@
-// Grouped expert FFN for bf16, for batches that give the experts a dozen rows and more: persistent
-// workgroups fed by loads that go straight to LDS.
+// Grouped expert FFN for batches that give the experts a dozen rows and more (bf16), and for most fp32
+// layers: persistent workgroups fed by loads that go straight to LDS.
 //
 // What bounds these launches is how many bytes a compute unit keeps in flight.  The weights come
 // from HBM at about 3 us of latency under load, so 27 GB/s per compute unit (7 TB/s for the chip)
@@ -9,15 +9,15 @@
 // through registers until the matrix cores read it.
 //
 //  - A unit of work is BM weight rows x all token rows of a work item (at most BN) over the whole
-//    contraction.  256 workgroups, one per compute unit, walk their units without a gap: the ring
+//    contraction, 128 bytes of every row a step.  256 workgroups, one per compute unit, walk their units without a gap: the ring
 //    is a single sequence of (unit, 64-wide k step), so the next unit's loads are in flight while
 //    the last one is finished and stored.
 //  - A row of a stage is 128 bytes, eight 16-byte pieces; piece c of row r lies at position
 //    c ^ (r & 7).  The loads put it there by having each lane fetch the piece that belongs at its
 //    place, still eight whole 128-byte lines per instruction, and a matrix operand (16 rows x 16
 //    bytes, rows in the wavefront's lane order) then reads every LDS bank once.
-//  - Eight wavefronts share a stage as BM / 64 x WN: 64 weight rows and every WN-th token tile
-//    each.  While the second half of a stage is multiplied the first half of the next one is read
+//  - Eight wavefronts share a stage as 8 / WN x WN: 64 (or 32) weight rows and every WN-th token
+//    tile each.  While the second half of a stage is multiplied the first half of the next one is read
 //    from LDS, so that reads and products overlap inside a wavefront (gate/up at 2048 tokens of
 //    the Qwen3 shape: 165 -> 151 us).
 //  - Workgroups are handed to the 8 XCDs round-robin; each XCD walks a contiguous range of units,
@@ -29,6 +29,8 @@
 // against the kernels with eight wavefronts that staged token rows through registers:
 //   tokens   128: 113 + 60 -> 106 + 59     512: 140 + 82 -> 129 + 75    1024: 164 + 97 -> 136 + 85
 //           2048: 233 + 128 -> 151 + 111   3072: 260 + 155 -> 223 + 143   4096: 392 + 209 -> 273 + 179
+// fp32 layers against the vector-ALU kernels: 154 + 110 -> 66 + 42 us at 96 tokens (d_h 1024, d_m 704, 32 experts),
+// 182 + 130 -> 35 + 18 at 180 tokens (d_h 1024, d_m 192, 15 experts); relative error of the layer 1.8e-7 -> 1.4e-7.
 // Not faster: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens); the same
 // first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
 #pragma once
@@ -64,7 +66,7 @@ constexpr unsigned kXcds = 8;
 constexpr int kTileThreads = 512;
 constexpr int kTileWaves = kTileThreads / kWave;
 constexpr int kTileLds = 160 * 1024;
-constexpr int kRowBytes = 128;       // of a stage: one 64-wide k step
+constexpr int kRowBytes = 128;       // of a stage: one k step, 64 wide in bf16, 32 in fp32
 constexpr int kLoadRows = 8;         // rows one load instruction fills
 
 // BM weight rows x BN token rows per unit, WN wavefronts along the tokens.  LO: the token operand has a
@@ -72,22 +74,26 @@ constexpr int kLoadRows = 8;         // rows one load instruction fills
 template <int BM, int BN, int WN, bool LO>
 struct TileShape {
   static constexpr int kStageBytes = (BM + BN) * kRowBytes;
-  static constexpr int kStages = kTileLds / kStageBytes >= 4 ? 4 : kTileLds / kStageBytes;
+  static constexpr int kStages = kTileLds / kStageBytes >= 8 ? 8 : kTileLds / kStageBytes;
   static constexpr int kRealRows = LO ? BN / 2 : BN;
   static constexpr int kWeightLoads = BM / kLoadRows / kTileWaves;  // per wavefront and step
   static constexpr int kTokenInstr = BN / kLoadRows;                // per workgroup and step
   static constexpr int kTokenLoads = (kTokenInstr + kTileWaves - 1) / kTileWaves;  // of the first kFullWaves wavefronts; the others one less
   static constexpr int kFullWaves = kTokenInstr % kTileWaves == 0 ? kTileWaves : kTokenInstr % kTileWaves;
   static constexpr int kTilesPerWave = kRealRows / kTile / WN;
-  static_assert(BM / 64 == kTileWaves / WN, "a wavefront owns 64 weight rows");
+  static constexpr int kWaveRows = BM * WN / kTileWaves;            // weight rows of a wavefront
+  static constexpr int kWeightTiles = kWaveRows / kTile;
+  static_assert(kWeightTiles % 2 == 0 && BM % (kLoadRows * kTileWaves) == 0, "gate and up rows pair up inside a wavefront");
   static_assert(kRealRows % (kTile * WN) == 0 && kStages >= 3, "the ring holds a stage in use and two on their way");
 };
 
 // h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of every unit.  Items have at most
 // TileShape::kRealRows rows; p.ksplit slices of d_m (down), none of them empty.  grid kTileGroups, 512 threads.
-template <bool GATEUP, int BM, int BN, int WN, bool LO>
+template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO>
 __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   using Sh = TileShape<BM, BN, WN, LO>;
+  static_assert(DT == SERE_BF16 || !LO, "fp32 keeps h as it is");
+  constexpr int EB = Store<DT>::bytes;
   constexpr int S = Sh::kStages, NQ = Sh::kWeightLoads, NI = Sh::kTokenLoads, NT = Sh::kTilesPerWave;
   __shared__ __attribute__((aligned(16))) unsigned char lds[S * Sh::kStageBytes];
   const uint32_t lds0 = static_cast<uint32_t>(
@@ -95,7 +101,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
           reinterpret_cast<uintptr_t>(lds))));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
-  const int wm = wave / WN, wn = wave % WN;
+  // the wavefronts of one SIMD (w and w + 4) differ in wn: an item of few rows keeps all four SIMDs busy
+  constexpr int WM = kTileWaves / WN, RW = Sh::kWaveRows, NA = Sh::kWeightTiles;
+  const int wm = wave % WM, wn = wave / WM;
   const int dh = p.dh, dm = p.dm;
   const int ld = GATEUP ? dh : dm;                       // row length of both operands
   const int items = scalar_load(p.n_work, 0);
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   constexpr int kOut = GATEUP ? BM / 2 : BM;             // output columns of a unit
   const int ksplit = GATEUP ? 1 : p.ksplit;
   const int parts = (outs + kOut - 1) / kOut * ksplit;
-  const int blocks = ld >> 6, per = (blocks + ksplit - 1) / ksplit;
+  const int blocks = ld * EB / kRowBytes, per = (blocks + ksplit - 1) / ksplit;
 
   // this workgroup's units: every 32nd of its XCD's contiguous range
   const unsigned total = static_cast<unsigned>(items) * parts;
@@ -117,7 +125,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   // ---- loading side
   constexpr int CH = kRowBytes / 16;                     // pieces of a row
   const uint32_t piece = ((lane & (CH - 1)) ^ (lane / CH)) << 4;   // of a lane's row, see the layout above
-  const uint32_t lane_off = static_cast<uint32_t>(lane / CH) * ld * 2 + piece;
+  const uint32_t lane_off = static_cast<uint32_t>(lane / CH) * ld * EB + piece;
   const char* wbase[NQ];
   const char* tptr[NI];
   int pk = 0, pbeg = 0, pnk = 0, pleft = 0;
@@ -125,22 +133,23 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     const int item = u / parts, part = u % parts;
     const int e = scalar_load(p.work_expert, item), off = scalar_load(p.work_off, item), cnt = scalar_load(p.work_cnt, item);
     const int slab = part / ksplit, slice = part % ksplit;
-    const char* W = static_cast<const char*>(expert_base<SERE_BF16>(GATEUP ? p.w_gate_up : p.w_down,
-                                                                    GATEUP ? p.shared_gate_up : p.shared_down, e, p.M,
-                                                                    static_cast<size_t>(GATEUP ? 2 : 1) * dm * dh));
+    const char* W = static_cast<const char*>(expert_base<DT>(GATEUP ? p.w_gate_up : p.w_down,
+                                                             GATEUP ? p.shared_gate_up : p.shared_down, e, p.M,
+                                                             static_cast<size_t>(GATEUP ? 2 : 1) * dm * dh));
     const int o0 = slab * kOut;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int r = kLoadRows * (wave * NQ + q);                // first of the LDS rows of this load
       int row;
       if (GATEUP) {
-        int j = o0 + (r >> 6) * 32 + (r & 31);
-        if (j >= dm) j = o0 + (r & 31);
-        row = (r & 32) ? dm + j : j;
+        // of a wavefront's RW rows the first half are gate rows, the second half the matching up rows
+        int j = o0 + r / RW * (RW / 2) + r % (RW / 2);
+        if (j >= dm) j = o0 + r % (RW / 2);
+        row = r % RW >= RW / 2 ? dm + j : j;
       } else {
         row = o0 + r < dh ? o0 + r : o0;
       }
-      wbase[q] = W + static_cast<size_t>(row) * ld * 2;
+      wbase[q] = W + static_cast<size_t>(row) * ld * EB;
     }
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         row = static_cast<size_t>(plane) * p.rows + off + min(v - plane * Sh::kRealRows, cnt - 1);
       }
       const char* base = GATEUP ? static_cast<const char*>(p.hidden) : reinterpret_cast<const char*>(p.h);
-      tptr[n] = base + row * ld * 2 + piece;
+      tptr[n] = base + row * ld * EB + piece;
     }
     pbeg = min(slice * per, blocks);
     pnk = min((slice + 1) * per, blocks) - pbeg;
@@ -184,7 +193,8 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
 
   // ---- multiplying side
   const uint32_t frag = i * kRowBytes + ((g ^ (i & 7)) << 4);
-  f32x4 acc[4][NT];
+  f32x4 acc[NA][NT];
+  f32x4 low[DT == SERE_F32 ? NA : 1][DT == SERE_F32 ? NT : 1];   // what acc has lost (fp32)
   int cnt = 0, off = 0, part = 0, left = 0;
   auto open_unit = [&](unsigned u) {
     const int item = u / parts;
@@ -194,17 +204,20 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     const int slice = part % ksplit;
     left = min((slice + 1) * per, blocks) - min(slice * per, blocks);
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < NT; ++t) {
+        acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (DT == SERE_F32) low[a][t] = acc[a][t];
+      }
   };
   struct Frags {
-    u32x4 w[4], x[NT], y[LO ? NT : 1];
+    u32x4 w[NA], x[NT], y[LO ? NT : 1];
   };
   auto fetch = [&](Frags& f, int slot, int h) {          // operands of one 32-wide half of a stage
     const unsigned char* st = lds + slot * Sh::kStageBytes + (frag ^ (h << 6));
 #pragma unroll
-    for (int a = 0; a < 4; ++a) f.w[a] = *reinterpret_cast<const u32x4*>(st + (wm * 64 + a * 16) * kRowBytes);
+    for (int a = 0; a < NA; ++a) f.w[a] = *reinterpret_cast<const u32x4*>(st + (wm * RW + a * 16) * kRowBytes);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int tile = wn + WN * t;
@@ -212,16 +225,42 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
       if (LO) f.y[t] = *reinterpret_cast<const u32x4*>(st + (BM + Sh::kRealRows + tile * kTile) * kRowBytes);
     }
   };
-  auto multiply = [&](const Frags& f) {
+  f32x4 sums[4][DT == SERE_F32 ? NA : 1][DT == SERE_F32 ? NT : 1];
+  auto multiply = [&](const Frags& f, auto which) {
     auto tile_of = [&](int t) {
+      if constexpr (DT == SERE_F32) {
+        // 16 of the step's 32 k: lane (g, i) has four consecutive k of its rows, one product each.  The matrix
+        // cores add one after the other; a chain over the whole contraction would round more than a sum over
+        // 64 lanes does (2.6e-7 against 1.8e-7 relative error at d_h = 1024).  So every 8 products are summed
+        // on their own, a step's four sums pairwise, and the step's sum is added to the unit's with
+        // compensation (Kahan).
 #pragma unroll
-      for (int a = 0; a < 4; ++a) acc[a][t] = mfma_bf16(f.w[a], f.x[t], acc[a][t]);
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            f32x4& sum = sums[2 * decltype(which)::value + j / 2][a][t];
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(f.w[a][j]), __uint_as_float(f.x[t][j]),
+                                                       j % 2 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
+          }
+        if constexpr (decltype(which)::value == 1) {
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            const f32x4 add = ((sums[0][a][t] + sums[1][a][t]) + (sums[2][a][t] + sums[3][a][t])) - low[a][t];
+            const f32x4 next = acc[a][t] + add;
+            low[a][t] = (next - acc[a][t]) - add;
+            acc[a][t] = next;
+          }
+        }
+        return;
+      }
+#pragma unroll
+      for (int a = 0; a < NA; ++a) acc[a][t] = mfma_bf16(f.w[a], f.x[t], acc[a][t]);
       if (LO) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) acc[a][t] = mfma_bf16(f.w[a], f.y[t], acc[a][t]);
+        for (int a = 0; a < NA; ++a) acc[a][t] = mfma_bf16(f.w[a], f.y[t], acc[a][t]);
       }
     };
-    if (cnt > Sh::kRealRows - kTile * WN) {
+    if ((wn + WN * (NT - 1)) * kTile < cnt) {
 #pragma unroll
       for (int t = 0; t < NT; ++t) tile_of(t);
     } else {
@@ -233,19 +272,19 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   auto store = [&]() {
     const int slab = part / ksplit, slice = part % ksplit;
     if (GATEUP) {
-      const int j0 = slab * kOut + wm * 32;
+      const int j0 = slab * kOut + wm * (RW / 2);
       if (j0 >= dm) return;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int n = (wn + WN * t) * kTile + i;
         if (n < cnt) {
 #pragma unroll
-          for (int a = 0; a < 2; ++a)                    // tiles 0, 1: gate rows, tiles 2, 3: the matching up rows
-            store_h4(p, static_cast<size_t>(off + n) * dm + j0 + 16 * a + 4 * g, acc[a][t], acc[a + 2][t]);
+          for (int a = 0; a < NA / 2; ++a)               // gate tiles, then the matching up tiles
+            store_h4<DT>(p, static_cast<size_t>(off + n) * dm + j0 + 16 * a + 4 * g, acc[a][t], acc[a + NA / 2][t]);
         }
       }
     } else {
-      const int r0 = slab * kOut + wm * 64;
+      const int r0 = slab * kOut + wm * RW;
       if (r0 >= dh) return;
       float* y = p.y + static_cast<size_t>(slice) * p.rows * dh;
 #pragma unroll
@@ -254,7 +293,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         if (n < cnt) {
           float* dst = y + static_cast<size_t>(off + n) * dh + r0 + 4 * g;
 #pragma unroll
-          for (int a = 0; a < 4; ++a) *reinterpret_cast<f32x4*>(dst + 16 * a) = acc[a][t];
+          for (int a = 0; a < NA; ++a) *reinterpret_cast<f32x4*>(dst + 16 * a) = acc[a][t];
         }
       }
     }
@@ -283,7 +322,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   fetch(f0, 0, 0);
   for (;;) {
     fetch(f1, slot, 1);
-    multiply(f0);
+    multiply(f0, std::integral_constant<int, 0>{});
     if (ahead > 0) {
       // the wait also covers this wavefront's reads of the stage in use, whose slot is then free
       const int used = slot;
@@ -295,7 +334,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
       }
       fetch(f0, slot, 0);
     }
-    multiply(f1);
+    multiply(f1, std::integral_constant<int, 1>{});
     if (--left == 0) {
       store();
       cu += kStride;

@@ -332,15 +332,7 @@ static int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 &&
 // known on the device only; here it is what independent tokens give: an expert stays if some token has it among
 // its top S (its top K without re-routing or with a threshold).
 static FfnPlan plan_decode(const sere_config& c, int ksplit, bool reroute) {
-  FfnPlan plan;
-  plan.ksplit = ksplit;
   const double T = c.num_tokens, M = c.num_experts, K = c.top_k;
-  if (c.dtype == SERE_F32) {
-    // the vector-ALU kernels serve an item of any length: longer ones where experts have many rows
-    const double rows = T * K / M;
-    plan.item_rows = rows >= 96 ? 8 * kItemRows : rows >= 48 ? 4 * kItemRows : rows >= 24 ? 2 * kItemRows : kItemRows;
-    return plan;
-  }
   const double kept = reroute && !(c.threshold > 0.0f) ? c.select_top_k : K;
   FfnShape s{};
   s.hidden = c.hidden;
@@ -353,37 +345,42 @@ static FfnPlan plan_decode(const sere_config& c, int ksplit, bool reroute) {
   s.spread = K < M ? 1.5 * std::sqrt(s.rows) : 0.0;  // tokens of a batch resemble each other: wider than by chance
   s.split_h = wants_split_h(c) != 0;
   s.max_ksplit = ksplit;
-  return plan_ffn(s);
+  return c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
 }
 
-template <bool GATEUP, int BM, int BN, int WN, bool LO = false>
+template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO = false>
 static void launch_tile_as(const FfnArgs& f, hipStream_t s) {
-  launch_stage(GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, s, ffn_tile<GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
+  launch_stage(GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, s, ffn_tile<DT, GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
                dim3(kTileThreads), f);
 }
 template <bool GATEUP>
 static void launch_tile(int item_rows, const FfnArgs& f, hipStream_t s) {
   if (!GATEUP && f.split_h) {  // both planes of the token rows count in the second size
     switch (item_rows) {
-      case 32: launch_tile_as<false, 256, 64, 2, true>(f, s); return;
-      case 64: launch_tile_as<false, 256, 128, 2, true>(f, s); return;
-      default: launch_tile_as<false, 128, 256, 4, true>(f, s); return;
+      case 32: launch_tile_as<SERE_BF16, false, 256, 64, 2, true>(f, s); return;
+      case 64: launch_tile_as<SERE_BF16, false, 256, 128, 2, true>(f, s); return;
+      default: launch_tile_as<SERE_BF16, false, 128, 256, 4, true>(f, s); return;
     }
   }
   switch (item_rows) {
-    case 32: launch_tile_as<GATEUP, 256, 32, 2>(f, s); return;
-    case 64: launch_tile_as<GATEUP, 256, 64, 2>(f, s); return;
-    case 96: launch_tile_as<GATEUP, 256, 96, 2>(f, s); return;
-    case 128: launch_tile_as<GATEUP, 256, 128, 2>(f, s); return;
-    case 160: launch_tile_as<GATEUP, 256, 160, 2>(f, s); return;
-    case 192: launch_tile_as<GATEUP, 128, 192, 4>(f, s); return;
-    default: launch_tile_as<GATEUP, 128, 256, 4>(f, s); return;
+    case 32: launch_tile_as<SERE_BF16, GATEUP, 256, 32, 2>(f, s); return;
+    case 64: launch_tile_as<SERE_BF16, GATEUP, 256, 64, 2>(f, s); return;
+    case 96: launch_tile_as<SERE_BF16, GATEUP, 256, 96, 2>(f, s); return;
+    case 128: launch_tile_as<SERE_BF16, GATEUP, 256, 128, 2>(f, s); return;
+    case 160: launch_tile_as<SERE_BF16, GATEUP, 256, 160, 2>(f, s); return;
+    case 192: launch_tile_as<SERE_BF16, GATEUP, 128, 192, 4>(f, s); return;
+    default: launch_tile_as<SERE_BF16, GATEUP, 128, 256, 4>(f, s); return;
   }
 }
 
-// fp32 layers: vector-ALU kernels.  bf16 layers: matrix-core kernels, as planned.
+// fp32 layers: the persistent kernels, or the vector-ALU ones.  bf16 layers: matrix-core kernels.  As planned.
 static void launch_gateup_down(int dtype, int inter, int hidden, int max_work, const FfnPlan& plan, const FfnArgs& f,
                                hipStream_t s, bool waves8 = false) {
+  if (dtype == SERE_F32 && plan.tile_gate_up) {
+    launch_tile_as<SERE_F32, true, kTileF32Rows, kItemRows, 2>(f, s);
+    launch_tile_as<SERE_F32, false, kTileF32Rows, kItemRows, 2>(f, s);
+    return;
+  }
   if (dtype == SERE_F32) {
     launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_generic<SERE_F32>, dim3((inter + kGenJB - 1) / kGenJB, max_work),
                  dim3(256), f);
@@ -544,21 +541,16 @@ static SimLayout make_sim_layout(const sere_config& c, int n) {
   const size_t M = c.num_experts, R = M * static_cast<size_t>(n);
   l.rows = static_cast<int>(R);
   l.ksplit = down_ksplit(c);
-  l.plan.ksplit = l.ksplit;
-  if (c.dtype == SERE_F32) {
-    l.plan.item_rows = n;   // the vector-ALU kernels serve an item of any length
-  } else {
-    FfnShape s{};
-    s.hidden = c.hidden;
-    s.inter = c.inter;
-    s.tokens = n;
-    s.experts = M;
-    s.rows = n;
-    s.slots_per_expert = n;
-    s.split_h = wants_split_h(c) != 0;
-    s.max_ksplit = l.ksplit;
-    l.plan = plan_ffn(s);
-  }
+  FfnShape s{};
+  s.hidden = c.hidden;
+  s.inter = c.inter;
+  s.tokens = n;
+  s.experts = M;
+  s.rows = n;
+  s.slots_per_expert = n;
+  s.split_h = wants_split_h(c) != 0;
+  s.max_ksplit = l.ksplit;
+  l.plan = c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
   l.items = (n + l.plan.item_rows - 1) / l.plan.item_rows;
   const size_t W = M * l.items;
   size_t o = 0;

@@ -15,9 +15,9 @@ def plans(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("plan") / "plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "plan_main.cpp"), "-o", exe], check=True)
 
-    def run(cases):
+    def run(cases, *args):
         text = "".join("%d %d %d %d %r %r %r %r %d %d\n" % c for c in cases)
-        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        out = subprocess.run([exe, *args], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
         return [tuple(int(v) for v in line.split()) for line in out if line]
     return run
 
@@ -54,3 +54,12 @@ def test_choices_on_the_layers_the_rule_was_measured_on(plans):
     got = plans([shape(T, 2048, 128, 8, 768, 0, 2) for T in (1, 32, 64, 128, 512, 1024, 2048, 3072)])
     assert [g[1] for g in got] == [0, 0, 0, 1, 1, 1, 1, 1]
     assert [g[0] for g in got] == [32, 32, 32, 32, 64, 96, 160, 256]
+
+
+def test_fp32_plans(plans):
+    """fp32 layers: items of 32 rows, no slices; batches of more than 8 tokens run on the persistent kernels."""
+    layers = [(T, dh, 17, 4, dm, sh, 4) for T in (1, 2, 8, 9, 96, 4096) for dh in (64, 256, 1472) for dm in (64, 704) for sh in (0, 2)]
+    cases = [shape(*layer)[:9] + (1,) for layer in layers]
+    for layer, (rows, tile_gu, tile_dn, ksplit) in zip(layers, plans(cases, "f32")):
+        assert (rows, ksplit) == (32, 1) and tile_gu == tile_dn, layer
+        assert tile_gu or layer[0] <= 8, layer

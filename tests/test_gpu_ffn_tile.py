@@ -57,6 +57,33 @@ def test_every_item_size(dev, case):  # noqa: F811
         assert (layer.out == first).all()          # the same bits again
 
 
+F32_CASES = [
+    # T, d_h, M, K, d_m, shared: the vector-ALU kernels below 9 tokens with long contractions, else the persistent ones
+    (1, 1472, 17, 4, 192, 1), (8, 1472, 5, 2, 704, 0), (8, 256, 16, 2, 128, 0), (9, 1472, 5, 2, 704, 1),
+    (33, 64, 2, 2, 64, 1), (70, 320, 3, 1, 448, 0), (300, 704, 8, 2, 1088, 2),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: "x".join(str(v) for v in c))
+def test_fp32_layers(dev, case):  # noqa: F811
+    """Every token against fp64; an fp32 sum of n products of independent terms rounds to about sqrt(n) 2^-24 of
+    its size at worst, and the compensated sums stay near 2e-7: 1e-6 relative leaves a factor of five."""
+    T, dh, M, K, dm, n_sh = case
+    spec = wk.custom_spec("f32tile" + "x".join(map(str, case)), wk.F32, dh, M, K, dm, n_sh, T, 5400 + T + dm, clusters=3,
+                          calib_batches=1, calib_tokens=4)
+    wl = wk.make_workload(spec)
+    sim = pins.rand_sim(5400 + T, M)
+    layer = dev.DeviceLayer.from_workload(wl, sim, 1, 0.3)
+    print(f"fp32 {case}", flush=True)
+    ref = oracle.layer(wl.hidden, wl.router_w, wl.w_gate_up, wl.w_down, wl.shared_gate_up, wl.shared_down, wk.F32, K, sim, 1, 0.3)
+    assert ref.min_gap > 1e-9
+    layer.run_decode()
+    check_routing(layer.routing_to_host(), ref, layer.cfg)
+    got = layer.out_to_host_f64()
+    assert np.linalg.norm(got - ref.out_sere) <= 1e-6 * np.linalg.norm(ref.out_sere)
+    assert np.abs(got - ref.out_sere).max() <= 1e-5 * np.abs(ref.out_sere).max()
+
+
 # 40 experts own 1, 15, 16, 17, ... rows up to two and three items (average about 90: items of 96 rows)
 EDGE_COUNTS = [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 79, 80, 81, 95, 96, 97, 111, 112, 113, 127, 128, 129,
                159, 160, 161, 191, 192, 193, 223, 288, 289, 90, 90, 90, 90, 90, 91]
