@@ -253,7 +253,9 @@ int sere_moe_decode_static(const sere_config *cfg, const void *hidden, const voi
  * kernels, so for SERE_BF16 the activations carry bf16-level rounding (as a
  * bf16 model forward does); similarities agree with an fp64 evaluation to a
  * few 1e-3.  batch_tokens: 1 .. 4096, num_batches: 1 .. 4096.
- * Workspace: sere_similarity_workspace_bytes(cfg, batch_tokens).
+ * Workspace: sere_similarity_workspace_bytes(cfg, batch_tokens), which has room
+ * for several batches at once (the experts' weights are then streamed once for
+ * all of them); a smaller one is accepted as long as one batch fits.
  */
 size_t sere_similarity_workspace_bytes(const sere_config *cfg, int32_t batch_tokens);
 int sere_similarity(const sere_config *cfg, const void *calib, int32_t num_batches,

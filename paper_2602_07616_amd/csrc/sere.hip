@@ -526,32 +526,41 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* __restric
 }
 
 // ------------------------------------------------------------- similarity ---
+// Calibration batches are served in groups of about kSimGroupRows tokens (more rows per expert make the forward
+// pass no faster per token), within kSimGroupBytes of workspace, so that an expert's weights are streamed once per
+// group: 32 tokens of the Qwen3 shape 201 us alone, 110 / 66 / 53 us a batch in groups of 2 / 4 / 8.  A layer whose experts fit the chip's
+// L2s takes one batch at a time: its weights are streamed from there.  A call with less workspace, or with fewer
+// batches, runs smaller groups.
+constexpr int kSimGroupRows = 256, kSimGroupMax = 16;
+constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{32} << 20;
+
 struct SimLayout {
-  size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, max_bits,
+  size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, inv_norm, max_bits,
       total;
   int rows, ksplit;
   FfnPlan plan;
   int items;            // work items of an expert
-  int gram_splits;      // Frobenius metric: slices of the flattened outputs in the Gram kernel
+  int gram_splits;      // slices of the flattened outputs in the Gram kernel
   long long gram_chunk; // ... and their length
 };
 
-static SimLayout make_sim_layout(const sere_config& c, int n) {
+// layout of groups of g batches of n tokens
+static SimLayout make_sim_layout(const sere_config& c, int n, int g) {
   SimLayout l{};
-  const size_t M = c.num_experts, R = M * static_cast<size_t>(n);
+  const size_t M = c.num_experts, R = M * static_cast<size_t>(n) * g;
   l.rows = static_cast<int>(R);
   l.ksplit = down_ksplit(c);
   FfnShape s{};
   s.hidden = c.hidden;
   s.inter = c.inter;
-  s.tokens = n;
+  s.tokens = n * g;
   s.experts = M;
-  s.rows = n;
-  s.slots_per_expert = n;
+  s.rows = n * g;
+  s.slots_per_expert = n * g;
   s.split_h = wants_split_h(c) != 0;
   s.max_ksplit = l.ksplit;
   l.plan = c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
-  l.items = (n + l.plan.item_rows - 1) / l.plan.item_rows;
+  l.items = (n * g + l.plan.item_rows - 1) / l.plan.item_rows;
   const size_t W = M * l.items;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -559,36 +568,51 @@ static SimLayout make_sim_layout(const sere_config& c, int n) {
     o = align_up(o + bytes);
     return at;
   };
+  l.acc = take(M * M * sizeof(double));  // first: the same place for groups of every size
   l.sorted_token = take(R * 4);
   l.work_expert = take(W * 4);
   l.work_off = take(W * 4);
   l.work_cnt = take(W * 4);
   l.n_work = take(8);
-  l.h = take(R * c.inter * sizeof(float));
+  l.dist = take(g * M * M * sizeof(double));
+  l.max_bits = take(g * 8);
   l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
-  l.dist = take(M * M * sizeof(double));
-  l.acc = take(M * M * sizeof(double));
-  l.max_bits = take(8);
+  l.h = take(R * c.inter * sizeof(float));
   if (c.flags & SERE_FLAG_SIM_CKA_LINEAR) {  // Gram matrix and its row sums per expert
     l.gram = take(R * n * sizeof(double));
     l.rowsum = take(R * sizeof(double));
     l.diag = take(R * sizeof(double));
-  }
-  if ((c.flags & (SERE_FLAG_SIM_CKA_LINEAR | SERE_FLAG_SIM_COSINE)) == 0) {  // Frobenius: partial Gram matrices of the experts
+  } else {                                   // partial Gram matrices of the experts' flattened outputs
+    // the cosine metric keeps them in the place of h, which is no longer needed when they are written
+    const bool in_h = (c.flags & SERE_FLAG_SIM_COSINE) != 0;
+    const size_t end = o;
+    if (in_h) {
+      o = l.h;
+      l.inv_norm = take(R * sizeof(double));
+    }
     const long long L = static_cast<long long>(n) * c.hidden;
-    // enough splits that blocks x splits fill the chip (about 512 workgroups), 16 .. 128 of them,
-    // each a multiple of the Gram kernel's 64-wide load group
+    // about three workgroups for every compute unit, 16 .. 256 splits, each a multiple of the Gram kernel's
+    // 64-wide load group
     const int nb = static_cast<int>((M + kGramBlock - 1) / kGramBlock);
-    const int want = std::min(128, std::max(16, 512 / (nb * (nb + 1) / 2)));
+    const int want = std::min(256, std::max(16, 768 / (nb * (nb + 1) / 2 * g)));
     long long chunk = (L + want - 1) / want;
     chunk = std::max<long long>(256, (chunk + 63) / 64 * 64);
     l.gram_chunk = chunk;
     l.gram_splits = static_cast<int>((L + chunk - 1) / chunk);
-    l.gram_part = take(static_cast<size_t>(l.gram_splits) * gram_part_stride(static_cast<int>(M)) * sizeof(double));
-    l.gram = take(kGramGroups * M * M * sizeof(double));
+    l.gram_part = take(static_cast<size_t>(g) * l.gram_splits * gram_part_stride(static_cast<int>(M)) * sizeof(double));
+    l.gram = take(static_cast<size_t>(g) * kGramGroups * M * M * sizeof(double));
+    if (in_h) o = std::max(end, o);
   }
   l.total = o;
   return l;
+}
+
+// batches of a group that a workspace is sized for
+static int sim_group(const sere_config& c, int n) {
+  const size_t weights = static_cast<size_t>(c.num_experts) * 3 * c.hidden * c.inter * (c.dtype == SERE_F32 ? 4 : 2);
+  int g = weights <= kSimGroupWeights ? 1 : std::max(1, std::min(kSimGroupMax, kSimGroupRows / n));
+  while (g > 1 && make_sim_layout(c, n, g).total > kSimGroupBytes) --g;
+  return g;
 }
 
 constexpr int kCkaMinTokens = 4, kCkaMaxTokens = 512;  // the estimator's lower limit; M*n*n doubles of workspace
@@ -597,6 +621,80 @@ static int check_similarity_sizes(const sere_config& c, int32_t num_batches, int
   if (num_batches < 1 || num_batches > 4096 || n < 1 || n > 4096) return SERE_ERR_BAD_SHAPE;
   if ((c.flags & SERE_FLAG_SIM_CKA_LINEAR) && (n < kCkaMinTokens || n > kCkaMaxTokens)) return SERE_ERR_BAD_SHAPE;
   return SERE_OK;
+}
+
+// One group: g batches from calibration batch b0 on.
+static void similarity_group(const sere_config& c, const SimLayout& l, const char* calib, int b0, int g, bool new_list, int num_batches,
+                             int n, const void* w_gate_up, const void* w_down, int cka_kernel, double p0, double p1, float* sim,
+                             char* ws, hipStream_t s) {
+  const int M = c.num_experts, dh = c.hidden;
+  FfnArgs f{};
+  f.w_gate_up = w_gate_up;
+  f.w_down = w_down;
+  f.sorted_token = reinterpret_cast<int32_t*>(ws + l.sorted_token);
+  f.work_expert = reinterpret_cast<int32_t*>(ws + l.work_expert);
+  f.work_off = reinterpret_cast<int32_t*>(ws + l.work_off);
+  f.work_cnt = reinterpret_cast<int32_t*>(ws + l.work_cnt);
+  f.n_work = reinterpret_cast<int32_t*>(ws + l.n_work);
+  f.h = reinterpret_cast<float*>(ws + l.h);
+  f.y = reinterpret_cast<float*>(ws + l.y);
+  f.T = n * g;
+  f.dh = dh;
+  f.dm = c.inter;
+  f.M = M;
+  f.K = 1;
+  f.n_sh = 0;
+  f.ksplit = l.plan.ksplit;
+  f.rows = l.rows;
+  f.split_h = wants_split_h(c);
+  f.hidden = calib + static_cast<size_t>(b0) * n * dh * (c.dtype == SERE_F32 ? 4 : 2);
+  if (new_list)
+    hipLaunchKernelGGL(similarity_worklist_kernel, dim3((l.rows + 255) / 256), dim3(256), 0, s, M, n * g, l.plan.item_rows,
+                       const_cast<int32_t*>(f.sorted_token), const_cast<int32_t*>(f.work_expert),
+                       const_cast<int32_t*>(f.work_off), const_cast<int32_t*>(f.work_cnt), const_cast<int32_t*>(f.n_work));
+  launch_gateup_down(c.dtype, c.inter, dh, M * l.items, l.plan, f, s);
+
+  const int metric = (c.flags & SERE_FLAG_SIM_COSINE)
+                         ? kMetricCosine
+                         : ((c.flags & SERE_FLAG_SIM_CKA_LINEAR) ? kMetricCkaLinear : kMetricFrobenius);
+  double* dist = reinterpret_cast<double*>(ws + l.dist);
+  double* gram = reinterpret_cast<double*>(ws + l.gram);
+  unsigned long long* max_bits = reinterpret_cast<unsigned long long*>(ws + l.max_bits);
+  const unsigned entries = (M * M + 255) / 256;
+  if (metric == kMetricCkaLinear) {
+    double* rowsum = reinterpret_cast<double*>(ws + l.rowsum);
+    const bool linear = cka_kernel == kCkaLinear;
+    double* diag = linear ? nullptr : reinterpret_cast<double*>(ws + l.diag);
+    hipLaunchKernelGGL(gram_kernel, dim3(n, M * g), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, dh, gram,
+                       linear ? rowsum : static_cast<double*>(nullptr), diag);
+    if (!linear)
+      hipLaunchKernelGGL(gram_transform_kernel, dim3(n, M * g), dim3(256), 0, s, gram, diag, n, cka_kernel, p0,
+                         static_cast<int>(p1), rowsum);
+    hipLaunchKernelGGL(pair_hsic_kernel, dim3(M, M, g), dim3(256), 0, s, gram, rowsum, n, M, dist);
+  } else {
+    double* part = reinterpret_cast<double*>(ws + l.gram_part);
+    const int nb = (M + kGramBlock - 1) / kGramBlock;
+    const dim3 blocks(nb * (nb + 1) / 2, l.gram_splits, g);
+    if (metric == kMetricCosine) {
+      double* inv_norm = reinterpret_cast<double*>(ws + l.inv_norm);
+      hipLaunchKernelGGL(row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), 0, s, f.y, f.ksplit, l.rows, dh, inv_norm);
+      hipLaunchKernelGGL(pair_gram_kernel<true>, blocks, dim3(256), 0, s, f.y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part,
+                         inv_norm, max_bits);
+    } else {
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<false>, blocks, dim3(256), f.y, f.ksplit, l.rows, n, dh, M,
+                   l.gram_chunk, part, static_cast<const double*>(nullptr), max_bits);
+    }
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(entries, kGramGroups, g), dim3(256),
+                 static_cast<const double*>(part), l.gram_splits, M, gram);
+    if (metric == kMetricCosine)
+      hipLaunchKernelGGL(cosine_mean_kernel, dim3(entries, g), dim3(256), 0, s, gram, n, M, dist);
+    else
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
+                   static_cast<const double*>(gram), static_cast<const float*>(f.y), f.ksplit, l.rows, n, dh, M, dist, max_bits);
+  }
+  launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), M,
+               b0, g, num_batches, metric, static_cast<const unsigned long long*>(max_bits),
+               reinterpret_cast<double*>(ws + l.acc), sim);
 }
 
 static int similarity(const sere_config* cfg, const void* calib, int32_t num_batches, int32_t batch_tokens,
@@ -612,79 +710,20 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   pc.need(w_down);
   pc.need(sim);
   if (pc.status != SERE_OK) return pc.status;
-  const SimLayout l = make_sim_layout(*cfg, batch_tokens);
   if (workspace == nullptr) return SERE_ERR_NULL_PTR;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return SERE_ERR_MISALIGNED;
+  int group = std::min(sim_group(*cfg, batch_tokens), num_batches);
+  while (group > 1 && make_sim_layout(*cfg, batch_tokens, group).total > workspace_bytes) --group;
+  const SimLayout l = make_sim_layout(*cfg, batch_tokens, group);
   if (workspace_bytes < l.total) return SERE_ERR_WORKSPACE_TOO_SMALL;
 
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  char* ws = static_cast<char*>(workspace);
-  const int M = cfg->num_experts, n = batch_tokens;
-  FfnArgs f{};
-  f.w_gate_up = w_gate_up;
-  f.w_down = w_down;
-  f.sorted_token = reinterpret_cast<int32_t*>(ws + l.sorted_token);
-  f.work_expert = reinterpret_cast<int32_t*>(ws + l.work_expert);
-  f.work_off = reinterpret_cast<int32_t*>(ws + l.work_off);
-  f.work_cnt = reinterpret_cast<int32_t*>(ws + l.work_cnt);
-  f.n_work = reinterpret_cast<int32_t*>(ws + l.n_work);
-  f.h = reinterpret_cast<float*>(ws + l.h);
-  f.y = reinterpret_cast<float*>(ws + l.y);
-  f.T = n;
-  f.dh = cfg->hidden;
-  f.dm = cfg->inter;
-  f.M = M;
-  f.K = 1;
-  f.n_sh = 0;
-  f.ksplit = l.plan.ksplit;
-  f.rows = l.rows;
-  f.split_h = wants_split_h(*cfg);
-  hipLaunchKernelGGL(similarity_worklist_kernel, dim3((M * n + 255) / 256), dim3(256), 0, s, M, n, l.plan.item_rows,
-                     const_cast<int32_t*>(f.sorted_token), const_cast<int32_t*>(f.work_expert),
-                     const_cast<int32_t*>(f.work_off), const_cast<int32_t*>(f.work_cnt),
-                     const_cast<int32_t*>(f.n_work));
-  const size_t eb = cfg->dtype == SERE_F32 ? 4 : 2;
-  const int metric = (cfg->flags & SERE_FLAG_SIM_COSINE)
-                         ? kMetricCosine
-                         : ((cfg->flags & SERE_FLAG_SIM_CKA_LINEAR) ? kMetricCkaLinear : kMetricFrobenius);
-  double* dist = reinterpret_cast<double*>(ws + l.dist);
-  unsigned long long* max_bits = reinterpret_cast<unsigned long long*>(ws + l.max_bits);
-  for (int b = 0; b < num_batches; ++b) {
-    f.hidden = static_cast<const char*>(calib) + static_cast<size_t>(b) * n * cfg->hidden * eb;
-    launch_gateup_down(cfg->dtype, cfg->inter, cfg->hidden, M * l.items, l.plan, f, s);
-    if (metric == kMetricCosine) {
-      hipLaunchKernelGGL(pair_cosine_kernel, dim3(M, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, M,
-                         dist);
-    } else if (metric == kMetricCkaLinear) {
-      double* gram = reinterpret_cast<double*>(ws + l.gram);
-      double* rowsum = reinterpret_cast<double*>(ws + l.rowsum);
-      if (cka_kernel == kCkaLinear) {
-        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, gram,
-                           rowsum, static_cast<double*>(nullptr));
-      } else {
-        double* diag = reinterpret_cast<double*>(ws + l.diag);
-        hipLaunchKernelGGL(gram_kernel, dim3(n, M), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, cfg->hidden, gram,
-                           static_cast<double*>(nullptr), diag);
-        hipLaunchKernelGGL(gram_transform_kernel, dim3(n, M), dim3(256), 0, s, gram, diag, n, cka_kernel, p0,
-                           static_cast<int>(p1), rowsum);
-      }
-      hipLaunchKernelGGL(pair_hsic_kernel, dim3(M, M), dim3(256), 0, s, gram, rowsum, n, M, dist);
-    } else {
-      double* part = reinterpret_cast<double*>(ws + l.gram_part);
-      double* gram = reinterpret_cast<double*>(ws + l.gram);
-      const int nb = (M + kGramBlock - 1) / kGramBlock;
-      const dim3 per_pair((M * M + 255) / 256);
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_gram_kernel, dim3(nb * (nb + 1) / 2, l.gram_splits), dim3(256), f.y,
-                   f.ksplit, l.rows, n, cfg->hidden, M, l.gram_chunk, part, max_bits);
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(per_pair.x, kGramGroups), dim3(256),
-                   static_cast<const double*>(part), l.gram_splits, M, gram);
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, per_pair, dim3(256),
-                   static_cast<const double*>(gram), static_cast<const float*>(f.y), f.ksplit, l.rows, n, cfg->hidden,
-                   M, dist, max_bits);
-    }
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3((M * M + 255) / 256), dim3(256),
-                 static_cast<const double*>(dist), M, b, static_cast<int>(num_batches), metric,
-                 static_cast<const unsigned long long*>(max_bits), reinterpret_cast<double*>(ws + l.acc), sim);
+  const int rest = num_batches % group;
+  const SimLayout last = rest != 0 ? make_sim_layout(*cfg, batch_tokens, rest) : l;
+  for (int b = 0; b < num_batches; b += group) {
+    const bool whole = b + group <= num_batches;
+    similarity_group(*cfg, whole ? l : last, static_cast<const char*>(calib), b, whole ? group : rest, b == 0 || !whole, num_batches, batch_tokens,
+                     w_gate_up, w_down, cka_kernel, p0, p1, sim, static_cast<char*>(workspace),
+                     static_cast<hipStream_t>(hip_stream));
   }
   return hip_status();
 }
@@ -772,7 +811,7 @@ int sere_moe_decode_baseline(const sere_config* cfg, const void* hidden, const v
 
 size_t sere_similarity_workspace_bytes(const sere_config* cfg, int32_t batch_tokens) {
   if (check_config(cfg) != SERE_OK || check_similarity_sizes(*cfg, 1, batch_tokens) != SERE_OK) return 0;
-  return make_sim_layout(*cfg, batch_tokens).total;
+  return make_sim_layout(*cfg, batch_tokens, sim_group(*cfg, batch_tokens)).total;
 }
 
 int sere_similarity(const sere_config* cfg, const void* calib, int32_t num_batches, int32_t batch_tokens,

@@ -7,13 +7,19 @@
 // mean over tokens of the cosine between the two experts' outputs, or linear
 // CKA of the experts' Gram matrices; Sim is accumulated over batches and
 // averaged.
+//
+// Calibration batches are taken in groups of g: an expert's weights are streamed once for the g * n
+// tokens of a group (a batch of 32 tokens of the Qwen3 shape: forward pass 201 us alone, 66 us in a
+// group of four), and every kernel of the pair stage serves the whole group in one
+// launch.  Rows of y: expert-major, then batch, then token; V_e of a batch is n * d_h consecutive
+// numbers, and the same batch of the next expert lies g * n * d_h further.
 #pragma once
 
 #include "common.hpp"
 
 namespace sere {
 
-// work list "every expert, all n tokens" in items of at most item_rows rows (about equal ones, of whole
+// work list "every expert, all n tokens" (n: of a group) in items of at most item_rows rows (about equal ones, of whole
 // 16-row tiles): grid ceil(M*n/256), 256 threads
 __global__ __launch_bounds__(256) void similarity_worklist_kernel(int M, int n, int item_rows, int32_t* sorted_token,
                                                                   int32_t* work_expert, int32_t* work_off,
@@ -67,12 +73,19 @@ __device__ __forceinline__ void gram_block_of(int index, int nb, int& bp, int& b
 // upper-triangular 64 x 64 blocks.  grid (nb (nb + 1) / 2, nsplit), 256 threads; lane l of a
 // wavefront holds row l % 16 of each of its tiles, and of every 16 consecutive k the four
 // 4 (l / 16) ... + 3 (the order of k inside the sum is free as long as both operands agree).
-// `chunk` (the split's length) is a multiple of 2 * 16 * kGramSteps (= 64, as L is).
-__global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n,
-                                                             int dh, int M, long long chunk,
-                                                             double* __restrict__ part,
-                                                             unsigned long long* __restrict__ max_bits) {
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *max_bits = 0ull;   // for frobenius_distance_kernel
+// `chunk` (the split's length) is a multiple of 2 * 16 * kGramSteps (= 64, as L is).  blockIdx.z: batch of
+// the group.
+// 43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us a batch; the fp64 matrix cores reach 69 in a large
+// product).  Neither more workgroups (three for every compute unit instead of one and a half) nor four
+// independent sums between two products of one changed that: it waits for its operands.
+// COSINE: every row of A is divided by its length first (inv_norm[row], 0 for a zero row), so the entries
+// are sums over tokens of cosines.
+template <bool COSINE>
+__global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n,
+                                                        int dh, int M, long long chunk, double* __restrict__ part,
+                                                        const double* __restrict__ inv_norm,
+                                                        unsigned long long* __restrict__ max_bits) {
+  if (!COSINE && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) max_bits[blockIdx.z] = 0ull;   // for frobenius_distance_kernel
   const int nb = (M + kGramBlock - 1) / kGramBlock;
   int bp, bq;
   gram_block_of(blockIdx.x, nb, bp, bq);
@@ -81,12 +94,19 @@ __global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __rest
   const int p0 = bp * kGramBlock + (wave >> 1) * 32, q0 = bq * kGramBlock + (wave & 1) * 32;
   const long long L = static_cast<long long>(n) * dh;             // multiple of 64
   const size_t slice = static_cast<size_t>(rows) * dh;
+  const int g = gridDim.z, batch = blockIdx.z;
   const float* ap[2];
   const float* aq[2];
+  const double* ip[2];
+  const double* iq[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {   // rows beyond M repeat the last one (their results are not stored)
-    ap[t] = y + static_cast<size_t>(min(p0 + 16 * t + r16, M - 1)) * L + 4 * kq;
-    aq[t] = y + static_cast<size_t>(min(q0 + 16 * t + r16, M - 1)) * L + 4 * kq;
+    const size_t rp = static_cast<size_t>(min(p0 + 16 * t + r16, M - 1)) * g + batch;
+    const size_t rq = static_cast<size_t>(min(q0 + 16 * t + r16, M - 1)) * g + batch;
+    ap[t] = y + rp * L + 4 * kq;
+    aq[t] = y + rq * L + 4 * kq;
+    ip[t] = inv_norm + rp * n;
+    iq[t] = inv_norm + rq * n;
   }
   const long long kbeg = blockIdx.y * chunk, kend = min(kbeg + chunk, L);
   auto fetch = [&](const float* row, long long k) {
@@ -105,7 +125,16 @@ __global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __rest
   // groups of kGramSteps steps, double buffered: the loads of the next group are in flight while
   // the current one is multiplied (the split's length is a multiple of 2 * 16 * kGramSteps)
   float4 va[2][kGramSteps][2], vb[2][kGramSteps][2];
+  double sa[2][2], sb[2][2];   // COSINE: the group's row factors (a group of 32 consecutive k lies in one token: d_h % 64 == 0)
   auto fetch_group = [&](int buf, long long k) {
+    if constexpr (COSINE) {
+      const int token = static_cast<int>(k) / dh;   // L is below 2^29
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        sa[buf][t] = ip[t][token];
+        sb[buf][t] = iq[t][token];
+      }
+    }
 #pragma unroll
     for (int st = 0; st < kGramSteps; ++st)
 #pragma unroll
@@ -118,15 +147,22 @@ __global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __rest
 #pragma unroll
     for (int st = 0; st < kGramSteps; ++st)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int j = 0; j < 4; ++j) {   // four independent sums between two products of one
+        double x[2], w[2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const float4 x = va[buf][st][a], w = vb[buf][st][b];
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(x.x), static_cast<double>(w.x), acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(x.y), static_cast<double>(w.y), acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(x.z), static_cast<double>(w.z), acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(x.w), static_cast<double>(w.w), acc[a][b], 0, 0, 0);
+        for (int t = 0; t < 2; ++t) {
+          x[t] = static_cast<double>(reinterpret_cast<const float*>(&va[buf][st][t])[j]);
+          w[t] = static_cast<double>(reinterpret_cast<const float*>(&vb[buf][st][t])[j]);
+          if constexpr (COSINE) {
+            x[t] *= sa[buf][t];
+            w[t] *= sb[buf][t];
+          }
         }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a], w[b], acc[a][b], 0, 0, 0);
+      }
   };
   constexpr int kGroup = 16 * kGramSteps;
   fetch_group(0, kbeg);
@@ -137,7 +173,7 @@ __global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __rest
     multiply_group(1);
   }
   // lane l holds D[l / 16 + 4 r][l % 16], r = 0..3 (the fp64 tile interleaves its row blocks)
-  double* out = part + static_cast<size_t>(blockIdx.y) * gram_part_stride(M);
+  double* out = part + (static_cast<size_t>(batch) * gridDim.y + blockIdx.y) * gram_part_stride(M);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -152,7 +188,7 @@ __global__ __launch_bounds__(256) void frobenius_gram_kernel(const float* __rest
 // The partial Gram matrices are added in two fixed-order levels: group r of kGramGroups takes the
 // splits r, r + kGramGroups, ... (this kernel; entries below the block diagonal are read from
 // their mirror image), and the distance kernel adds the kGramGroups group sums.
-// grid (ceil(M * M / 256), kGramGroups), 256 threads.
+// grid (ceil(M * M / 256), kGramGroups, g), 256 threads.
 constexpr int kGramGroups = 8;
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, int nsplit, int M,
                                                           double* __restrict__ gram) {
@@ -165,10 +201,10 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
     b = t;
   }
   const size_t mm = gram_part_stride(M);
-  const double* src = part + static_cast<size_t>(a) * M + b;
+  const double* src = part + static_cast<size_t>(blockIdx.z) * nsplit * mm + static_cast<size_t>(a) * M + b;
   double g = 0.0;
   for (int s = blockIdx.y; s < nsplit; s += kGramGroups) g += src[s * mm];
-  gram[static_cast<size_t>(blockIdx.y) * M * M + idx] = g;
+  gram[(static_cast<size_t>(blockIdx.z) * kGramGroups + blockIdx.y) * M * M + idx] = g;
 }
 
 // dist[p][q] = sqrt(G_pp + G_qq - 2 G_pq), G = the sum of the group sums `gram`.  A pair whose squared distance is below
@@ -176,14 +212,17 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
 // digits) is recomputed as a direct difference sqrt(sum_i (A_p[i] - A_q[i])^2) by the whole
 // wavefront, one such pair after the other.  The largest distance of the batch is gathered in
 // *max_bits (the bits of a non-negative double order like the number; cleared by the Gram kernel).
-// grid ceil(M * M / 256), 256 threads.
+// grid (ceil(M * M / 256), g), 256 threads.
 __global__ __launch_bounds__(256) void frobenius_distance_kernel(const double* __restrict__ gram,
                                                                  const float* __restrict__ y, int ksplit, int rows,
                                                                  int n, int dh, int M, double* __restrict__ dist,
                                                                  unsigned long long* __restrict__ max_bits) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
+  const int g = gridDim.y, batch = blockIdx.y;
   const bool valid = idx < M * M;
+  gram += static_cast<size_t>(batch) * kGramGroups * M * M;
+  dist += static_cast<size_t>(batch) * M * M;
   const int p = valid ? idx / M : 0, q = valid ? idx % M : 0;
   double d = 0.0;
   bool twin = false;
@@ -206,8 +245,8 @@ __global__ __launch_bounds__(256) void frobenius_distance_kernel(const double* _
     const int src = __ffsll(static_cast<long long>(todo)) - 1;
     todo &= todo - 1ull;
     const int tp = __shfl(p, src, kWave), tq = __shfl(q, src, kWave);
-    const float* ap = y + static_cast<size_t>(tp) * len;
-    const float* aq = y + static_cast<size_t>(tq) * len;
+    const float* ap = y + (static_cast<size_t>(tp) * g + batch) * len;
+    const float* aq = y + (static_cast<size_t>(tq) * g + batch) * len;
     double acc = 0.0;
     for (size_t i = static_cast<size_t>(lane) * 4; i < len; i += 256) {
       float4 a = *reinterpret_cast<const float4*>(ap + i), b = *reinterpret_cast<const float4*>(aq + i);
@@ -228,52 +267,51 @@ __global__ __launch_bounds__(256) void frobenius_distance_kernel(const double* _
   double m = d;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, kWave));
-  if (lane == 0 && m > 0.0) atomicMax(max_bits, static_cast<unsigned long long>(__double_as_longlong(m)));
+  if (lane == 0 && m > 0.0) atomicMax(max_bits + batch, static_cast<unsigned long long>(__double_as_longlong(m)));
 }
 
-// Cosine metric (appendix "Cosine Similarity"): out[p][q] = (1/n) sum over tokens i of
-// <A_p[i], A_q[i]> / (|A_p[i]| |A_q[i]|); a token where either output is the zero vector
-// contributes 0.  A_e as above.  grid (M, M), 256 threads: wavefront w takes tokens w, w+4, ...;
-// fp64 accumulation, the four partial sums added in fixed order.
-__global__ __launch_bounds__(256) void pair_cosine_kernel(const float* __restrict__ y, int ksplit, int rows, int n,
-                                                          int dh, int M, double* __restrict__ out) {
-  __shared__ double part[4];
-  const int p = blockIdx.y, q = blockIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Cosine metric (appendix "Cosine Similarity"): Sim(p, q) = (1/n) sum over tokens i of <A_p[i], A_q[i]> /
+// (|A_p[i]| |A_q[i]|); a token where either output is the zero vector contributes 0.  With every row divided
+// by its length that sum is an entry of the Gram matrix of the flattened outputs, so it takes the Frobenius
+// metric's kernels: M * M / 2 products on the fp64 matrix cores instead of a workgroup per ordered pair that
+// reads both experts' outputs from cache (two batches of 32 tokens, 128 experts, d_h 2048, forward pass
+// included: 1278 -> 358 us).
+// inv_norm[row] = 1 / |y[row]|, 0 for a zero row; grid ceil(rows / 4), 256 threads: a wavefront per row.
+__global__ __launch_bounds__(256) void row_norm_kernel(const float* __restrict__ y, int ksplit, int rows, int dh,
+                                                       double* __restrict__ inv_norm) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= rows) return;
   const size_t slice = static_cast<size_t>(rows) * dh;
-  double total = 0.0;
-  for (int i = wave; i < n; i += 4) {
-    const float* ap = y + (static_cast<size_t>(p) * n + i) * dh;
-    const float* aq = y + (static_cast<size_t>(q) * n + i) * dh;
-    double dot = 0.0, np2 = 0.0, nq2 = 0.0;
-    for (int c = lane * 4; c < dh; c += 256) {
-      float4 a = *reinterpret_cast<const float4*>(ap + c), b = *reinterpret_cast<const float4*>(aq + c);
-      for (int s = 1; s < ksplit; ++s) {
-        const float4 a2 = *reinterpret_cast<const float4*>(ap + s * slice + c);
-        const float4 b2 = *reinterpret_cast<const float4*>(aq + s * slice + c);
-        a.x += a2.x; a.y += a2.y; a.z += a2.z; a.w += a2.w;
-        b.x += b2.x; b.y += b2.y; b.z += b2.z; b.w += b2.w;
-      }
-      const double ax = a.x, ay = a.y, az = a.z, aw = a.w, bx = b.x, by = b.y, bz = b.z, bw = b.w;
-      dot += ax * bx + ay * by + az * bz + aw * bw;
-      np2 += ax * ax + ay * ay + az * az + aw * aw;
-      nq2 += bx * bx + by * by + bz * bz + bw * bw;
+  const float* a = y + static_cast<size_t>(row) * dh;
+  double sum = 0.0;
+  for (int c = lane * 4; c < dh; c += 256) {
+    float4 v = *reinterpret_cast<const float4*>(a + c);
+    for (int s = 1; s < ksplit; ++s) {
+      const float4 w = *reinterpret_cast<const float4*>(a + s * slice + c);
+      v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
     }
-    dot = wave_sum(dot);
-    np2 = wave_sum(np2);
-    nq2 = wave_sum(nq2);
-    const double den = sqrt(np2) * sqrt(nq2);
-    if (den > 0.0) total += dot / den;
+    const double x = v.x, yy = v.y, z = v.z, w = v.w;
+    sum += x * x + yy * yy + z * z + w * w;
   }
-  if (lane == 0) part[wave] = total;
-  __syncthreads();
-  if (threadIdx.x == 0) out[static_cast<size_t>(p) * M + q] = ((part[0] + part[1]) + (part[2] + part[3])) / n;
+  sum = wave_sum(sum);
+  if (lane == 0) inv_norm[row] = sum > 0.0 ? 1.0 / sqrt(sum) : 0.0;
+}
+
+// dist[batch][p][q] = (1/n) sum of the group sums; grid (ceil(M * M / 256), g), 256 threads
+__global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restrict__ gram, int n, int M,
+                                                          double* __restrict__ dist) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= M * M) return;
+  double sum = 0.0;
+#pragma unroll
+  for (int r = 0; r < kGramGroups; ++r) sum += gram[(static_cast<size_t>(blockIdx.y) * kGramGroups + r) * M * M + idx];
+  dist[static_cast<size_t>(blockIdx.y) * M * M + idx] = sum / n;
 }
 
 // Linear CKA (appendix "Centered Kernel Alignment"), step 1: the Gram matrix of every expert's
 // outputs with its diagonal set to zero, gram[e][i][j] = <A_e[i], A_e[j]> (i != j), and its row
 // sums.  Entries (i, j) and (j, i) are formed by the same operations in the same order, so the
-// matrix is symmetric to the bit.  grid (n, M), 256 threads: wavefront w takes j = w, w+4, ...;
+// matrix is symmetric to the bit.  grid (n, M * g), 256 threads (e: expert and batch): wavefront w takes j = w, w+4, ...;
 // fp64 accumulation.
 // With `diag` (RBF and polynomial kernels) the diagonal <A_e[i], A_e[i]> goes there and the row
 // sums are left to gram_transform_kernel (rowsum == nullptr).
@@ -321,7 +359,7 @@ constexpr int kCkaLinear = 0, kCkaRbf = 1, kCkaPoly = 2;  // SERE_CKA_* of the h
 //   RBF:        K_ij = exp(-(G_ii + G_jj - 2 G_ij) / (2 sigma^2)),  sigma = p0
 //   polynomial: K_ij = (G_ij + c)^d,  c = p0, d = degree (repeated multiplication)
 // The diagonal stays 0 (the HSIC estimator ignores it); (i, j) and (j, i) take the same operations
-// on the same values, so the matrix stays symmetric to the bit.  grid (n, M), 256 threads.
+// on the same values, so the matrix stays symmetric to the bit.  grid (n, M * g), 256 threads.
 __global__ __launch_bounds__(256) void gram_transform_kernel(double* __restrict__ gram,
                                                              const double* __restrict__ diag, int n, int kernel,
                                                              double p0, int degree,
@@ -357,19 +395,20 @@ __global__ __launch_bounds__(256) void gram_transform_kernel(double* __restrict_
 // the O(n^2) estimator the appendix refers to), from the zero-diagonal Gram matrices Kt_p, Kt_q:
 //   hsic[p][q] = [ tr(Kt_p Kt_q) + (1'Kt_p 1)(1'Kt_q 1) / ((n-1)(n-2)) - 2 (1'Kt_p Kt_q 1) / (n-2) ] / (n (n-3))
 // with tr(Kt_p Kt_q) = sum_ij Kt_p[i][j] Kt_q[i][j] (symmetric matrices) and 1'Kt_p Kt_q 1 = the
-// dot product of the two row-sum vectors.  grid (M, M), 256 threads; n >= 4.
+// dot product of the two row-sum vectors.  grid (M, M, g), 256 threads; n >= 4.
 __global__ __launch_bounds__(256) void pair_hsic_kernel(const double* __restrict__ gram,
                                                         const double* __restrict__ rowsum, int n, int M,
                                                         double* __restrict__ hsic) {
   __shared__ double part[4][4];
-  const int p = blockIdx.y, q = blockIdx.x;
+  const int batch = blockIdx.z;
+  const size_t p = static_cast<size_t>(blockIdx.y) * gridDim.z + batch, q = static_cast<size_t>(blockIdx.x) * gridDim.z + batch;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const double* kp = gram + static_cast<size_t>(p) * n * n;
-  const double* kq = gram + static_cast<size_t>(q) * n * n;
+  const double* kp = gram + p * n * n;
+  const double* kq = gram + q * n * n;
   double tr = 0.0, cross = 0.0, sp = 0.0, sq = 0.0;
   for (int i = threadIdx.x; i < n * n; i += 256) tr += kp[i] * kq[i];
   for (int i = threadIdx.x; i < n; i += 256) {
-    const double rp = rowsum[static_cast<size_t>(p) * n + i], rq = rowsum[static_cast<size_t>(q) * n + i];
+    const double rp = rowsum[p * n + i], rq = rowsum[q * n + i];
     cross += rp * rq;
     sp += rp;
     sq += rq;
@@ -389,7 +428,7 @@ __global__ __launch_bounds__(256) void pair_hsic_kernel(const double* __restrict
     double v[4];
     for (int k = 0; k < 4; ++k) v[k] = (part[k][0] + part[k][1]) + (part[k][2] + part[k][3]);
     const double dn = n;
-    hsic[static_cast<size_t>(p) * M + q] =
+    hsic[(static_cast<size_t>(batch) * M + blockIdx.y) * M + blockIdx.x] =
         (v[0] + v[2] * v[3] / ((dn - 1.0) * (dn - 2.0)) - 2.0 * v[1] / (dn - 2.0)) / (dn * (dn - 3.0));
   }
 }
@@ -399,28 +438,31 @@ constexpr int kMetricFrobenius = 0, kMetricCosine = 1, kMetricCkaLinear = 2;
 // Frobenius: acc[p][q] (+)= 1 - dist/max(dist), the maximum of the batch given as the bits of a
 // double in *max_bits; cosine: acc[p][q] (+)= dist[p][q] (the pair kernel's value as it is); linear
 // CKA: acc[p][q] (+)= dist[p][q] / sqrt(dist[p][p] dist[q][q]), dist holding the HSIC estimates (0
-// where a self-term is not positive: the quotient is undefined there).  On the last batch
-// sim = acc / N.  grid ceil(M * M / 256), 256 threads.
+// where a self-term is not positive: the quotient is undefined there).  The g batches of the group are added
+// in order.  With the last batch sim = acc / N.  grid ceil(M * M / 256), 256 threads.
 __global__ __launch_bounds__(256) void similarity_accumulate_kernel(const double* __restrict__ dist, int M,
-                                                                    int batch, int num_batches, int metric,
+                                                                    int batch0, int g, int num_batches, int metric,
                                                                     const unsigned long long* __restrict__ max_bits,
                                                                     double* __restrict__ acc,
                                                                     float* __restrict__ sim) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= M * M) return;
-  double sv;
-  if (metric == kMetricCosine) {
-    sv = dist[i];
-  } else if (metric == kMetricCkaLinear) {
-    const double hp = dist[static_cast<size_t>(i / M) * M + i / M], hq = dist[static_cast<size_t>(i % M) * M + i % M];
-    sv = (hp > 0.0 && hq > 0.0) ? dist[i] / sqrt(hp * hq) : 0.0;
-  } else {
-    const double mx = __longlong_as_double(static_cast<long long>(*max_bits));
-    sv = mx > 0.0 ? 1.0 - dist[i] / mx : 1.0;  // all pairs identical: Sim = 1
+  double a = batch0 == 0 ? 0.0 : acc[i];
+  for (int b = 0; b < g; ++b, dist += static_cast<size_t>(M) * M) {
+    double sv;
+    if (metric == kMetricCosine) {
+      sv = dist[i];
+    } else if (metric == kMetricCkaLinear) {
+      const double hp = dist[static_cast<size_t>(i / M) * M + i / M], hq = dist[static_cast<size_t>(i % M) * M + i % M];
+      sv = (hp > 0.0 && hq > 0.0) ? dist[i] / sqrt(hp * hq) : 0.0;
+    } else {
+      const double mx = __longlong_as_double(static_cast<long long>(max_bits[b]));
+      sv = mx > 0.0 ? 1.0 - dist[i] / mx : 1.0;  // all pairs identical: Sim = 1
+    }
+    a += sv;
   }
-  const double a = (batch == 0 ? 0.0 : acc[i]) + sv;
   acc[i] = a;
-  if (batch == num_batches - 1) sim[i] = static_cast<float>(a / num_batches);
+  if (batch0 + g == num_batches) sim[i] = static_cast<float>(a / num_batches);
 }
 
 }  // namespace sere
