@@ -13,7 +13,8 @@
 // Two launches: (1) router logits, delivered per token as sorted lists of 16;
 // (2) top-K per token as a merge of the list heads; the workgroup that finishes
 // last (a ticket in global memory, cleared by launch 1) then runs the
-// batch-wide step, so no third launch is needed.
+// batch-wide step, so no third launch is needed.  From kChunkedSlots slots on
+// the batch-wide step is a launch of its own, shared by many workgroups.
 #pragma once
 
 #include "common.hpp"
@@ -423,7 +424,8 @@ __device__ __forceinline__ void topk_merge(const uint64_t* __restrict__ list_key
 }
 
 // ---------------------------------------------------------------------------
-// Batch-wide re-routing and compaction by ONE workgroup of 1024 threads.
+// Batch-wide re-routing and compaction by ONE workgroup of 1024 threads (smaller batches), and the
+// parts of it that the shared form uses too.
 // ---------------------------------------------------------------------------
 struct RouteArgs {
   const int32_t* topk_ids;  // [A]  I
@@ -439,6 +441,7 @@ struct RouteArgs {
   int32_t* expert_offsets;  // [M+1]
   int32_t* sorted_token;    // [A + n_sh*T]
   int32_t* sorted_slot;     // [A]
+  int32_t* sorted_token_out; // [A]  the caller's copy of the routed part of sorted_token, or NULL
   int32_t* slot_pos;        // [A]  position of slot a = t*K+k in the sorted list
   int32_t* work_expert;     // [max items] expert of each work item (M+s for shared expert s); experts
                             //             ascending, an expert's rows cut into items of <= item_rows
@@ -447,6 +450,9 @@ struct RouteArgs {
   int32_t* n_work;          // [2]: number of items; 1 if the FFN kernels are to cut them fine
   int fine_items;           // ... which they do while there are at most this many items
   int topk_threads;         // threads of a workgroup that take part in the top-K merge (256 or 1024)
+  int32_t* chunk_hist;      // [chunks][2][M] slots per expert of every chunk of tokens, primary / secondary slots
+                            //             (NULL: the batch-wide step runs in the last workgroup of the top-K)
+  int chunk_tokens;         // tokens of a chunk
   int item_rows;            // rows per work item, at most: kItemRows and more, the host's choice
 };
 
@@ -458,7 +464,12 @@ constexpr int kTopkLoneThreads = 512;    // one workgroup serves the whole batch
 constexpr int kTopkMaxSmallGroups = 64;  // groups of 256 threads up to this many workgroups, of 1024 beyond
 constexpr int kSimPrefetchMaxGroups = 8;  // workgroups of a top-K launch that all prefetch their similarity rows
 constexpr int kRouteWaves = kRouteThreads / kWave;
-constexpr int kIdsInLds = 4096;                   // slots whose ids a lone workgroup keeps in LDS
+constexpr int kIdsInLds = 4096;                   // slots whose ids a workgroup keeps in LDS
+// Batches from this many slots on: the batch-wide step as a launch of many workgroups.  sere_route / sere_reroute,
+// us per call with one workgroup against many: 128 experts, K = 8: 1024 slots 19.0 / 8.0 against 19.5 / 8.2, 1536
+// slots 22.4 / 9.1 against 21.2 / 8.9, 4096 slots 35.7 / 14.3 against 25.5 / 8.7, 8000 slots 50.5 / 24.5 against
+// 31.1 / 9.3; 64 experts, K = 6: 1536 slots 20.8 / 7.5 against 19.8 / 7.5.
+constexpr int kChunkedSlots = 1536;
 
 struct RouteShared {
   int cnt_b[SERE_MAX_EXPERTS];
@@ -513,90 +524,57 @@ __device__ __forceinline__ void simmax_step(float& sv, int& iv) {
   }
 }
 
-template <bool IDS_IN_LDS, int NC>
-__device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf,
-                                            bool prefetched = true) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int M = p.M, K = p.K, S = p.S;
-  const int A = p.T * K;
-  // ids read from memory may be a caller's (sere_reroute): clamped into [0, M) so that an id outside
-  // that range, a broken precondition, cannot send any access out of bounds
-  // (device-scope loads: the ids may have been written by other workgroups of this launch)
-  auto id_at = [&](int a) -> int {
-    return IDS_IN_LDS ? static_cast<int>(s.ids8[a])
-                      : min(max(__hip_atomic_load(p.topk_ids + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0), M - 1);
-  };
-
-  if (tid < SERE_MAX_EXPERTS) {
-    s.cnt_b[tid] = 0;
-    s.cnt_a[tid] = 0;
-    s.prim[tid] = 0;
-    s.remap[tid] = tid;
-  }
-  for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
-  lds_barrier();
-
-  // Step 1: activation histogram and primary mask (union of every token's top-S)
-  for (int a = tid; a < A; a += kRouteThreads) {
-    const int e = id_at(a);
-    atomicAdd(&s.cnt_b[e], 1);
-    if (a % K < S) s.prim[e] = 1;
-  }
-  lds_barrier();
-
-  // Step 2: per secondary expert u (activated, not primary): most similar
-  // primary v*.  Each lane keeps the first maximum of its own columns in
-  // ascending order with strict '>' (start value (-inf, expert 0)); lanes are
-  // merged preferring the larger similarity, then the lower index: together
-  // the first maximum of an ascending scan, as the paper's algorithm finds it.
-  // The expert is kept as critical iff rho > 0 and sim* < rho.
-  if (p.reroute) {
-    const int q = lane >> 4, i = lane & 15;
+// Step 2: per secondary expert u (activated, not primary): most similar
+// primary v*.  Each lane keeps the first maximum of its own columns in
+// ascending order with strict '>' (start value (-inf, expert 0)); lanes are
+// merged preferring the larger similarity, then the lower index: together
+// the first maximum of an ascending scan, as the paper's algorithm finds it.
+// The expert is kept as critical iff rho > 0 and sim* < rho.
+template <int NC>
+__device__ __forceinline__ void remap_secondary(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf, bool prefetched) {
+  if (!p.reroute) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, M = p.M;
+  const int q = lane >> 4, i = lane & 15;
 #pragma unroll
-    for (int r = 0; r < SimPrefetch<NC>::NR; ++r) {
-      const int u = 4 * wave + q + 64 * r;
-      const bool sec = u < M && s.cnt_b[u] > 0 && !s.prim[u];
-      if (__ballot(sec) == 0) continue;  // wave-uniform
-      float bs = -INFINITY;
-      int bv = 0;
+  for (int r = 0; r < SimPrefetch<NC>::NR; ++r) {
+    const int u = 4 * wave + q + 64 * r;
+    const bool sec = u < M && s.cnt_b[u] > 0 && !s.prim[u];
+    if (__ballot(sec) == 0) continue;  // wave-uniform
+    float bs = -INFINITY;
+    int bv = 0;
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int v = i + 16 * c;
-        if (v < M) {
-          float sv;
-          if (r < SimPrefetch<NC>::PR && prefetched)   // prefetched: uniform over the workgroup
-            sv = pf.v[(r < SimPrefetch<NC>::PR ? r : 0) * NC + c];
-          else
-            sv = sec ? p.sim[static_cast<size_t>(u) * M + v] : 0.0f;
-          if (s.prim[v] && sv > bs) {
-            bs = sv;
-            bv = v;
-          }
+    for (int c = 0; c < NC; ++c) {
+      const int v = i + 16 * c;
+      if (v < M) {
+        float sv;
+        if (r < SimPrefetch<NC>::PR && prefetched)   // prefetched: uniform over the workgroup
+          sv = pf.v[(r < SimPrefetch<NC>::PR ? r : 0) * NC + c];
+        else
+          sv = sec ? p.sim[static_cast<size_t>(u) * M + v] : 0.0f;
+        if (s.prim[v] && sv > bs) {
+          bs = sv;
+          bv = v;
         }
       }
-      simmax_step<0>(bs, bv);
-      simmax_step<1>(bs, bv);
-      simmax_step<2>(bs, bv);
-      simmax_step<3>(bs, bv);
-      if (sec && i == 0) s.remap[u] = (p.rho > 0.0f && bs < p.rho) ? u : bv;
     }
+    simmax_step<0>(bs, bv);
+    simmax_step<1>(bs, bv);
+    simmax_step<2>(bs, bv);
+    simmax_step<3>(bs, bv);
+    if (sec && i == 0) s.remap[u] = (p.rho > 0.0f && bs < p.rho) ? u : bv;
   }
-  lds_barrier();
+}
 
-  // Step 3: rewrite secondary slots, count the new map
-  for (int a = tid; a < A; a += kRouteThreads) {
-    const int e = id_at(a);
-    const int e2 = (a % K >= S) ? s.remap[e] : e;
-    p.rerouted_ids[a] = e2;
-    atomicAdd(&s.cnt_a[e2], 1);
-  }
-  lds_barrier();
-
-  // inclusive scans over experts: slots (-> offsets), activity (-> active
-  // count) and work items (an expert's rows are cut into items of at most
-  // item_rows rows, so that one long expert cannot hold up the FFN kernels);
-  // inside each of the first four wavefronts by shuffles, across them through
-  // four totals in LDS
+// Per-expert results from the counts in s.cnt_b, s.cnt_a and the mask in s.prim: s.cursor[e] = offset of expert e
+// in the sorted list and, if `write`, the output arrays and the FFN work list.
+// inclusive scans over experts: slots (-> offsets), activity (-> active
+// count) and work items (an expert's rows are cut into items of at most
+// item_rows rows, so that one long expert cannot hold up the FFN kernels);
+// inside each of the first four wavefronts by shuffles, across them through
+// four totals in LDS
+__device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s, bool write) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int M = p.M, A = p.T * p.K;
   const bool is_e = tid < SERE_MAX_EXPERTS;
   const int my_cnt = (is_e && tid < M) ? s.cnt_a[tid] : 0;
   const int my_act = my_cnt > 0 ? 1 : 0;
@@ -637,24 +615,27 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
   if (is_e && tid < M) {
     const int off = inc_cnt - my_cnt;
     s.cursor[tid] = off;
-    p.expert_offsets[tid] = off;
-    p.count_before[tid] = s.cnt_b[tid];
-    p.count_after[tid] = my_cnt;
-    p.primary_mask[tid] = s.prim[tid];
-    const int first = inc_items - my_items;
-    // Items of 128 rows and more (prefill-sized batches): an expert with a few rows more than one item
-    // holds is cut into items of about equal size (multiples of a 16-row tile) instead of a full
-    // one and a remnant: its items then take about equally long, and as they are numbered next
-    // to each other they stream the expert's weights side by side, the later one from cache.
-    int per = item_rows;
-    if (item_rows >= 4 * kItemRows && my_items >= 2 && my_items <= 4)
-      per = ((my_cnt + my_items - 1) / my_items + 15) & ~15;
-    for (int j = 0; j < my_items; ++j) {
-      p.work_expert[first + j] = tid;
-      p.work_off[first + j] = off + j * per;
-      p.work_cnt[first + j] = min(per, my_cnt - j * per);
+    if (write) {
+      p.expert_offsets[tid] = off;
+      p.count_before[tid] = s.cnt_b[tid];
+      p.count_after[tid] = my_cnt;
+      p.primary_mask[tid] = s.prim[tid];
+      const int first = inc_items - my_items;
+      // Items of 128 rows and more (prefill-sized batches): an expert with a few rows more than one item
+      // holds is cut into items of about equal size (multiples of a 16-row tile) instead of a full
+      // one and a remnant: its items then take about equally long, and as they are numbered next
+      // to each other they stream the expert's weights side by side, the later one from cache.
+      int per = item_rows;
+      if (item_rows >= 4 * kItemRows && my_items >= 2 && my_items <= 4)
+        per = ((my_cnt + my_items - 1) / my_items + 15) & ~15;
+      for (int j = 0; j < my_items; ++j) {
+        p.work_expert[first + j] = tid;
+        p.work_off[first + j] = off + j * per;
+        p.work_cnt[first + j] = min(per, my_cnt - j * per);
+      }
     }
   }
+  if (!write) return;
   const int sh_items = (p.T + item_rows - 1) / item_rows;  // per shared expert
   if (tid == 0) {
     p.expert_offsets[M] = A;
@@ -669,25 +650,30 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
     p.work_off[n_items + i] = A + sh * p.T + j * item_rows;
     p.work_cnt[n_items + i] = min(item_rows, p.T - j * item_rows);
   }
-  for (int i = tid; i < p.n_sh * p.T; i += kRouteThreads) p.sorted_token[A + i] = i % p.T;
-  lds_barrier();
+}
 
-  // Stable regrouping by expert: slots keep ascending (token, slot) order
-  // inside each expert.  A round covers 1024 consecutive slots, one wavefront
-  // per 64; rank inside the wavefront from ballots, rank across wavefronts
-  // through the per-round table.
-  for (int base = 0; base < A; base += kRouteThreads) {
+// Stable regrouping by expert of slots [begin, end): slots keep ascending (token, slot) order
+// inside each expert, from position s.cursor[e] on.  A round covers 1024 consecutive slots, one wavefront
+// per 64; rank inside the wavefront from ballots, rank across wavefronts
+// through the per-round table.  s.round_cnt must be zero at the start.
+template <typename IdAt>
+__device__ __forceinline__ void regroup_slots(const RouteArgs& p, RouteShared& s, int begin, int end, IdAt&& id_at, bool write_ids) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int M = p.M, K = p.K, S = p.S;
+  const bool is_e = tid < SERE_MAX_EXPERTS;
+  for (int base = begin; base < end; base += kRouteThreads) {
     const int a = base + tid;
-    const bool valid = a < A;
+    const bool valid = a < end;
     int e = 0;
     if (valid) {
       const int e0 = id_at(a);
       e = (a % K >= S) ? s.remap[e0] : e0;
+      if (write_ids) p.rerouted_ids[a] = e;
     }
     // lanes of this wavefront holding the same expert: intersect, over the 8
     // bits of e, the ballot of lanes that agree with this lane on that bit
     int rank = 0, same = 0;
-    if (base + wave * kWave < A) {  // wave-uniform: this wavefront has slots
+    if (base + wave * kWave < end) {  // wave-uniform: this wavefront has slots
       uint64_t peers = __ballot(valid);
 #pragma unroll
       for (int bit = 0; bit < 8; ++bit) {
@@ -706,8 +692,9 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
       p.sorted_token[pos] = a / K;
       p.sorted_slot[pos] = a % K;
       p.slot_pos[a] = pos;
+      if (p.sorted_token_out != nullptr) p.sorted_token_out[pos] = a / K;
     }
-    if (base + kRouteThreads < A) {  // another round follows: advance the cursors
+    if (base + kRouteThreads < end) {  // another round follows: advance the cursors
       lds_barrier();
       if (is_e && tid < M) {
         int add = 0;
@@ -720,6 +707,138 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
       lds_barrier();
     }
   }
+}
+
+template <bool IDS_IN_LDS, int NC>
+__device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf,
+                                            bool prefetched = true) {
+  const int tid = threadIdx.x;
+  const int M = p.M, K = p.K, S = p.S;
+  const int A = p.T * K;
+  // ids read from memory may be a caller's (sere_reroute): clamped into [0, M) so that an id outside
+  // that range, a broken precondition, cannot send any access out of bounds
+  // (device-scope loads: the ids may have been written by other workgroups of this launch)
+  auto id_at = [&](int a) -> int {
+    return IDS_IN_LDS ? static_cast<int>(s.ids8[a])
+                      : min(max(__hip_atomic_load(p.topk_ids + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0), M - 1);
+  };
+
+  if (tid < SERE_MAX_EXPERTS) {
+    s.cnt_b[tid] = 0;
+    s.cnt_a[tid] = 0;
+    s.prim[tid] = 0;
+    s.remap[tid] = tid;
+  }
+  for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
+  lds_barrier();
+
+  // Step 1: activation histogram and primary mask (union of every token's top-S)
+  for (int a = tid; a < A; a += kRouteThreads) {
+    const int e = id_at(a);
+    atomicAdd(&s.cnt_b[e], 1);
+    if (a % K < S) s.prim[e] = 1;
+  }
+  lds_barrier();
+  remap_secondary(p, s, pf, prefetched);
+  lds_barrier();
+
+  // Step 3: rewrite secondary slots, count the new map
+  for (int a = tid; a < A; a += kRouteThreads) {
+    const int e = id_at(a);
+    const int e2 = (a % K >= S) ? s.remap[e] : e;
+    p.rerouted_ids[a] = e2;
+    atomicAdd(&s.cnt_a[e2], 1);
+  }
+  lds_barrier();
+
+  scan_experts(p, s, true);
+  for (int i = tid; i < p.n_sh * p.T; i += kRouteThreads) p.sorted_token[A + i] = i % p.T;
+  lds_barrier();
+  regroup_slots(p, s, 0, A, id_at, false);
+}
+
+// ---------------------------------------------------------------------------
+// The batch-wide step shared by many workgroups (batches of thousands of slots, where one workgroup
+// took 40 us of the 51 us of top-K and re-routing at 2048 tokens of the Qwen3 shape: now 17 in all, 20
+// instead of 91 at 4096).  Where a slot goes
+// depends on its expert and on whether it is a primary slot (k < S) only, so two counts per expert and
+// chunk of tokens are all that workgroups have to tell each other: the launch before this one writes
+// them (chunk_hist), and every workgroup here derives the mask, the map, the new counts, the offsets
+// and its own chunk's starting positions from them, then regroups its own slots.
+// ---------------------------------------------------------------------------
+
+// counts of the slots whose ids are in s.ids8 (n tokens' worth): hist[0][e] primary slots, hist[1][e] secondary
+// ones; all threads of the workgroup
+__device__ __forceinline__ void write_chunk_hist(const RouteArgs& p, RouteShared& s, int slots, int32_t* hist) {
+  for (int i = threadIdx.x; i < SERE_MAX_EXPERTS; i += blockDim.x) s.cnt_a[i] = s.cnt_b[i] = 0;
+  __syncthreads();
+  for (int a = threadIdx.x; a < slots; a += blockDim.x) atomicAdd((a % p.K < p.S) ? &s.cnt_a[s.ids8[a]] : &s.cnt_b[s.ids8[a]], 1);
+  __syncthreads();
+  for (int i = threadIdx.x; i < p.M; i += blockDim.x) {
+    hist[i] = s.cnt_a[i];
+    hist[p.M + i] = s.cnt_b[i];
+  }
+}
+
+// chunk counts of given ids (sere_reroute); grid chunks, 1024 threads
+__global__ __launch_bounds__(kRouteThreads) void route_hist_kernel(RouteArgs p) {
+  __shared__ RouteShared s;
+  const int begin = blockIdx.x * p.chunk_tokens * p.K, slots = min(p.chunk_tokens * p.K, p.T * p.K - begin);
+  for (int a = threadIdx.x; a < slots; a += kRouteThreads)
+    s.ids8[a] = static_cast<uint8_t>(min(max(p.topk_ids[begin + a], 0), p.M - 1));
+  __syncthreads();
+  write_chunk_hist(p, s, slots, p.chunk_hist + static_cast<size_t>(blockIdx.x) * 2 * p.M);
+}
+
+// grid chunks (ceil(T / chunk_tokens)), 1024 threads
+template <int NC>
+__global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p) {
+  __shared__ RouteShared s;
+  __shared__ int s_total[2 * SERE_MAX_EXPERTS], s_before[2 * SERE_MAX_EXPERTS];  // of all chunks / of the chunks before this one
+  const int tid = threadIdx.x, M = p.M, chunks = gridDim.x, chunk = blockIdx.x;
+  SimPrefetch<NC> pf;
+  prefetch_sim(p, pf);
+  for (int i = tid; i < 2 * SERE_MAX_EXPERTS; i += kRouteThreads) s_total[i] = s_before[i] = 0;
+  for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
+  lds_barrier();
+  // the 2 M counts of the chunks, kRouteThreads / (2 M) chunks at a time
+  const int per_pass = kRouteThreads / (2 * M);  // >= 2
+  const int c = tid % (2 * M);
+  if (tid < per_pass * 2 * M) {
+    int total = 0, before = 0;
+    for (int g = tid / (2 * M); g < chunks; g += per_pass) {
+      const int n = p.chunk_hist[static_cast<size_t>(g) * 2 * M + c];
+      total += n;
+      before += g < chunk ? n : 0;
+    }
+    atomicAdd(&s_total[c], total);
+    atomicAdd(&s_before[c], before);
+  }
+  lds_barrier();
+  if (tid < SERE_MAX_EXPERTS) {
+    const bool is_e = tid < M;
+    s.cnt_b[tid] = is_e ? s_total[tid] + s_total[M + tid] : 0;
+    s.prim[tid] = is_e && s_total[tid] > 0 ? 1 : 0;
+    s.remap[tid] = tid;
+    s.cnt_a[tid] = is_e ? s_total[tid] : 0;   // primary slots stay; the secondary ones are added below
+  }
+  lds_barrier();
+  remap_secondary(p, s, pf, true);
+  lds_barrier();
+  if (tid < M) {  // an expert's secondary slots all go to remap[e]
+    const int v = s.remap[tid], n = s_total[M + tid], b = s_before[M + tid];
+    if (n > 0) atomicAdd(&s.cnt_a[v], n);
+    if (b > 0) atomicAdd(&s_before[v], b);
+  }
+  lds_barrier();
+  scan_experts(p, s, chunk == 0);
+  lds_barrier();
+  if (tid < M) s.cursor[tid] += s_before[tid];
+  lds_barrier();
+  const int A = p.T * p.K, begin = chunk * p.chunk_tokens * p.K;
+  regroup_slots(p, s, begin, min(begin + p.chunk_tokens * p.K, A),
+                [&](int a) { return min(max(p.topk_ids[a], 0), M - 1); }, true);
+  for (int i = chunk * kRouteThreads + tid; i < p.n_sh * p.T; i += chunks * kRouteThreads) p.sorted_token[A + i] = i % p.T;
 }
 
 // Re-routing alone (indices in, indices out): grid 1, 1024 threads.
@@ -752,7 +871,7 @@ __global__ __launch_bounds__(kRouteThreads) void topk_route_kernel(const uint64_
   // known yet: with a handful of workgroups every one of them asks (the lines come from L2), with
   // many the step is long anyway and the rows are loaded where they are needed instead.
   SimPrefetch<NC> pf;
-  prefetch_sim(p, pf, gridDim.x <= kSimPrefetchMaxGroups);
+  prefetch_sim(p, pf, gridDim.x <= kSimPrefetchMaxGroups && p.chunk_hist == nullptr);
   const int nlists = (p.M + 15) >> 4;
   const int t = blockIdx.x * group_tokens + threadIdx.x / LP;
   const bool lone = gridDim.x == 1 && p.T * p.K <= kIdsInLds;
@@ -762,7 +881,15 @@ __global__ __launch_bounds__(kRouteThreads) void topk_route_kernel(const uint64_
   if (static_cast<int>(threadIdx.x & ~63u) < group_tokens * LP && first_of_wave < p.T) {  // wave-uniform: the wavefront has a token
     const size_t tt = has ? t : 0;
     topk_merge<LP, KS, KEEP>(list_key + tt * nlists * 16, list_id + tt * nlists * 16, has, nlists, topk_ids + tt * p.K,
-                       topk_w + tt * p.K, lone ? s.ids8 + tt * p.K : nullptr, p.K);
+                       topk_w + tt * p.K,
+                       lone ? s.ids8 + tt * p.K
+                            : (p.chunk_hist != nullptr ? s.ids8 + (threadIdx.x / LP) * p.K : nullptr), p.K);
+  }
+  if (p.chunk_hist != nullptr) {  // the batch-wide step is a launch of its own: leave this chunk's counts
+    __syncthreads();
+    const int tokens = min(group_tokens, p.T - static_cast<int>(blockIdx.x) * group_tokens);
+    write_chunk_hist(p, s, tokens * p.K, p.chunk_hist + static_cast<size_t>(blockIdx.x) * 2 * p.M);
+    return;
   }
   if (lone) {
     __syncthreads();

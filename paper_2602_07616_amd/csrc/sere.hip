@@ -190,8 +190,10 @@ struct Pointers {
   float* y;
 };
 
+constexpr int kRerouteChunkSlots = 1024;  // slots of a chunk when the ids are given (sere_reroute): one regrouping round
+
 static Pointers bind(const sere_config& c, const Layout& l, void* workspace, const sere_route_out* o,
-                     int item_rows = kItemRows) {
+                     bool with_topk = true, int item_rows = kItemRows) {
   char* ws = static_cast<char*>(workspace);
   auto pick = [&](void* user, size_t off) { return user != nullptr ? user : static_cast<void*>(ws + off); };
   static const sere_route_out none{};
@@ -217,6 +219,7 @@ static Pointers bind(const sere_config& c, const Layout& l, void* workspace, con
   r.num_active = static_cast<int32_t*>(pick(o->num_active, l.num_active));
   r.expert_offsets = static_cast<int32_t*>(pick(o->expert_offsets, l.offsets));
   r.sorted_token = reinterpret_cast<int32_t*>(ws + l.sorted_token);  // holds shared rows too
+  r.sorted_token_out = o->sorted_token;                              // the routed part, for the caller
   r.sorted_slot = static_cast<int32_t*>(pick(o->sorted_slot, l.sorted_slot));
   r.slot_pos = reinterpret_cast<int32_t*>(ws + l.slot_pos);
   r.work_expert = reinterpret_cast<int32_t*>(ws + l.work_expert);
@@ -231,6 +234,13 @@ static Pointers bind(const sere_config& c, const Layout& l, void* workspace, con
   r.topk_threads = (merge_threads > kTopkLoneThreads && merge_threads <= kTopkMaxSmallGroups * kTopkThreadsMulti)
                        ? kTopkThreadsMulti
                        : kRouteThreads;
+  // Batches of thousands of slots: the batch-wide step runs in a launch of its own, in chunks of the tokens that a
+  // top-K workgroup serves.  Their counts live in the place of y, which no kernel before the FFN uses:
+  // 2 M integers for 16 tokens and more are less than those tokens' rows of y (64 columns and more).
+  r.chunk_tokens = with_topk ? r.topk_threads / (lists <= 4 ? 4 : (lists <= 8 ? 8 : 16)) : std::max(1, kRerouteChunkSlots / c.top_k);
+  const bool chunked = static_cast<long long>(c.num_tokens) * c.top_k >= kChunkedSlots && c.num_tokens > r.chunk_tokens &&
+                       r.chunk_tokens * c.top_k <= kIdsInLds;
+  r.chunk_hist = chunked ? reinterpret_cast<int32_t*>(ws + l.y) : nullptr;
   r.fine_items = kFineCutBlocks / (c.inter / (2 * kGateUpJ * kWavesPerBlock));
   r.item_rows = item_rows;
   p.h = reinterpret_cast<float*>(ws + l.h);
@@ -280,8 +290,8 @@ static int launch_router(const sere_config& c, const Pointers& p, const void* hi
   return hip_status();
 }
 
-static int launch_route(const sere_config& c, const Pointers& p, bool with_topk, hipStream_t s,
-                        const sere_route_out* o, size_t sorted_token_bytes) {
+static int launch_route(const sere_config& c, const Pointers& p, bool with_topk, hipStream_t s) {
+  const unsigned chunks = (c.num_tokens + p.route.chunk_tokens - 1) / p.route.chunk_tokens;  // see bind()
   if (with_topk) {
     // lanes per token = lists per token rounded up to 4, 8 or 16; K <= KS * lanes
     const int lists = (c.num_experts + 15) / 16;
@@ -304,13 +314,19 @@ static int launch_route(const sere_config& c, const Pointers& p, bool with_topk,
       else SERE_LAUNCH_TOPK(16, 16, 16);
     }
 #undef SERE_LAUNCH_TOPK
+  } else if (p.route.chunk_hist != nullptr) {
+    launch_stage(SERE_STAGE_ROUTE, s, route_hist_kernel, dim3(chunks), dim3(kRouteThreads), p.route);
   } else {
     launch_stage(SERE_STAGE_ROUTE, s, route_kernel, dim3(1), dim3(kRouteThreads), p.route);
   }
-  // the internal sorted_token list also carries the shared experts' rows; a
-  // caller-visible copy holds the routed part only
-  if (o != nullptr && o->sorted_token != nullptr)
-    (void)hipMemcpyAsync(o->sorted_token, p.route.sorted_token, sorted_token_bytes, hipMemcpyDeviceToDevice, s);
+  if (p.route.chunk_hist != nullptr) {
+    if (c.num_experts <= 64)
+      launch_stage(SERE_STAGE_ROUTE, s, route_chunks_kernel<4>, dim3(chunks), dim3(kRouteThreads), p.route);
+    else if (c.num_experts <= 128)
+      launch_stage(SERE_STAGE_ROUTE, s, route_chunks_kernel<8>, dim3(chunks), dim3(kRouteThreads), p.route);
+    else
+      launch_stage(SERE_STAGE_ROUTE, s, route_chunks_kernel<16>, dim3(chunks), dim3(kRouteThreads), p.route);
+  }
   return hip_status();
 }
 
@@ -465,13 +481,13 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const FfnPlan plan = plan_decode(*cfg, l.ksplit, reroute);
-  Pointers p = bind(*cfg, l, workspace, dbg, plan.item_rows);
+  Pointers p = bind(*cfg, l, workspace, dbg, true, plan.item_rows);
   p.route.sim = sim;
   p.route.reroute = reroute ? 1 : 0;
   if (!reroute) p.route.S = cfg->top_k;  // every slot is a primary slot: identity map
   st = launch_router(*cfg, p, hidden, router_w, s);
   if (st != SERE_OK) return st;
-  st = launch_route(*cfg, p, true, s, dbg, static_cast<size_t>(cfg->num_tokens) * cfg->top_k * 4);
+  st = launch_route(*cfg, p, true, s);
   if (st != SERE_OK) return st;
 
   FfnArgs f{};
@@ -758,7 +774,7 @@ int sere_route(const sere_config* cfg, const void* hidden, const void* router_w,
   p.route.reroute = 1;
   st = launch_router(*cfg, p, hidden, router_w, s);
   if (st != SERE_OK) return st;
-  return launch_route(*cfg, p, true, s, out, static_cast<size_t>(cfg->num_tokens) * cfg->top_k * 4);
+  return launch_route(*cfg, p, true, s);
 }
 
 int sere_reroute(const sere_config* cfg, const int32_t* topk_ids, const float* sim, const sere_route_out* out,
@@ -778,11 +794,11 @@ int sere_reroute(const sere_config* cfg, const int32_t* topk_ids, const float* s
   if (out != nullptr) o = *out;
   o.topk_ids = nullptr;
   o.topk_weights = nullptr;
-  Pointers p = bind(*cfg, l, workspace, &o);
+  Pointers p = bind(*cfg, l, workspace, &o, false);
   p.route.topk_ids = topk_ids;
   p.route.sim = sim;
   p.route.reroute = 1;
-  return launch_route(*cfg, p, false, s, &o, static_cast<size_t>(cfg->num_tokens) * cfg->top_k * 4);
+  return launch_route(*cfg, p, false, s);
 }
 
 int sere_moe_decode(const sere_config* cfg, const void* hidden, const void* router_w, const void* w_gate_up,
