@@ -106,17 +106,6 @@ struct Raw8<SERE_BF16> {
   }
 };
 
-template <int DT>
-__device__ __forceinline__ void store1(void* base, size_t idx, float v);
-template <>
-__device__ __forceinline__ void store1<SERE_F32>(void* base, size_t idx, float v) {
-  static_cast<float*>(base)[idx] = v;
-}
-template <>
-__device__ __forceinline__ void store1<SERE_BF16>(void* base, size_t idx, float v) {
-  static_cast<uint16_t*>(base)[idx] = f32_to_bf16(v);
-}
-
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);

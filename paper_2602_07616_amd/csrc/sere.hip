@@ -334,11 +334,20 @@ static void launch_combine(const sere_config& c, const Layout& l, const Pointers
                            void* out, hipStream_t s) {
   CombineArgs ca{p.y, p.topk_w, p.route.slot_pos, (c.flags & SERE_FLAG_RESIDUAL) ? hidden : nullptr, out,
                  c.num_tokens, c.hidden, c.top_k, c.num_shared, ksplit, l.rows};
-  const dim3 grid(static_cast<unsigned>((c.hidden + 255) / 256) * c.num_tokens);
-  if (c.dtype == SERE_F32)
-    launch_stage(SERE_STAGE_COMBINE, s, combine_kernel<SERE_F32>, grid, dim3(256), ca);
-  else
-    launch_stage(SERE_STAGE_COMBINE, s, combine_kernel<SERE_BF16>, grid, dim3(256), ca);
+  const bool small = static_cast<int64_t>(c.num_tokens) * c.hidden <= kCombineColumns;
+  const dim3 grid(small ? static_cast<unsigned>((c.hidden + 255) / 256) * c.num_tokens
+                        : (static_cast<unsigned>(c.num_tokens) * (c.hidden / 4) + 255) / 256);
+#define SERE_LAUNCH_COMBINE(KERNEL)                                            \
+  if (c.dtype == SERE_F32)                                                     \
+    launch_stage(SERE_STAGE_COMBINE, s, KERNEL<SERE_F32>, grid, dim3(256), ca); \
+  else                                                                         \
+    launch_stage(SERE_STAGE_COMBINE, s, KERNEL<SERE_BF16>, grid, dim3(256), ca)
+  if (small) {
+    SERE_LAUNCH_COMBINE(combine_columns_kernel);
+  } else {
+    SERE_LAUNCH_COMBINE(combine_kernel);
+  }
+#undef SERE_LAUNCH_COMBINE
 }
 
 // wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
