@@ -565,6 +565,7 @@ struct SimLayout {
   int rows, ksplit;
   FfnPlan plan;
   int items;            // work items of an expert
+  bool gram_staged;     // Frobenius: the Gram kernel that stages through LDS
   int gram_splits;      // slices of the flattened outputs in the Gram kernel
   long long gram_chunk; // ... and their length
 };
@@ -619,7 +620,11 @@ static SimLayout make_sim_layout(const sere_config& c, int n, int g) {
     // about three workgroups for every compute unit, 16 .. 256 splits, each a multiple of the Gram kernel's
     // 64-wide load group
     const int nb = static_cast<int>((M + kGramBlock - 1) / kGramBlock);
-    const int want = std::min(256, std::max(16, 768 / (nb * (nb + 1) / 2 * g)));
+    // (staged kernel: one workgroup to a compute unit at a time; a single triangle: one even wave of them)
+    l.gram_staged = !in_h && l.ksplit == 1 && M > kGramBlock;
+    const int blocks = l.gram_staged ? gram_triangles(static_cast<int>(M)) + gram_squares(static_cast<int>(M))
+                                     : nb * (nb + 1) / 2;
+    const int want = std::min(256, std::max(16, (l.gram_staged && blocks == 1 ? 256 : 768) / (blocks * g)));
     long long chunk = (L + want - 1) / want;
     chunk = std::max<long long>(256, (chunk + 63) / 64 * 64);
     l.gram_chunk = chunk;
@@ -705,6 +710,9 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
       hipLaunchKernelGGL(row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), 0, s, f.y, f.ksplit, l.rows, dh, inv_norm);
       hipLaunchKernelGGL(pair_gram_kernel<true>, blocks, dim3(256), 0, s, f.y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part,
                          inv_norm, max_bits);
+    } else if (l.gram_staged) {
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_staged_kernel, dim3(gram_triangles(M) + gram_squares(M), l.gram_splits, g),
+                   dim3(kGramStagedThreads), static_cast<const float*>(f.y), n, dh, M, l.gram_chunk, part, max_bits);
     } else {
       launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<false>, blocks, dim3(256), f.y, f.ksplit, l.rows, n, dh, M,
                    l.gram_chunk, part, static_cast<const double*>(nullptr), max_bits);

@@ -16,6 +16,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "ffn_tile.hpp"
 
 namespace sere {
 
@@ -75,8 +76,8 @@ __device__ __forceinline__ void gram_block_of(int index, int nb, int& bp, int& b
 // 4 (l / 16) ... + 3 (the order of k inside the sum is free as long as both operands agree).
 // `chunk` (the split's length) is a multiple of 2 * 16 * kGramSteps (= 64, as L is).  blockIdx.z: batch of
 // the group.
-// 43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us a batch; the fp64 matrix cores reach 69 in a large
-// product).  Neither more workgroups (three for every compute unit instead of one and a half) nor four
+// Serves the cosine metric, up to 64 experts, and y in slices.  43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us
+// a batch; the fp64 matrix cores reach 69 in a large product).  Neither more workgroups (three for every compute unit instead of one and a half) nor four
 // independent sums between two products of one changed that: it waits for its operands.
 // COSINE: every row of A is divided by its length first (inv_norm[row], 0 for a zero row), so the entries
 // are sums over tokens of cosines.
@@ -185,26 +186,191 @@ __global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict_
       }
 }
 
+// The same partial Gram matrices (Frobenius metric, more than 64 experts, y in one slice) with the operands
+// staged through LDS: a workgroup takes a triangle of 128 experts, or a square of 64 x 64 between two such
+// triangles, and a range of L, and reads each of its 128 rows once, in whole 128-byte lines that go straight to a
+// ring of kGramRing stages (128 rows x 32 k; 16-byte piece c of a row lies at c ^ (row & 7), so that the reads are
+// free of bank conflicts).  In the kernel above every row is read by two blocks and by two wavefronts of each, 64
+// bytes at a time, and a diagonal block computes its lower half as well.
+// 8 wavefronts: wavefront w takes the 16 k of half w / 4 of each stage and, of the triangle's 8 x 8 tiles, the
+// cyclic share b = 2 (w & 3): (b, b + d) and (b + 1, b + 1 + d) for d = 0..3 and one of the four tiles at
+// d = 4 (rows modulo 8), nine tiles each; of a square's 4 x 4 tiles row w & 3.  The two halves are added at the end.
+// Bound by the fp64 matrix cores and the conversions between their products: 128 experts, 128 tokens, d_h 2048 take
+// 91 us a batch (4.8 GFLOP of fp64: 53 TFLOP/s; the kernel above: 147 us for 6.4 GFLOP); reading a stage from LDS
+// while the one before it is multiplied changed nothing.  Up to 64 experts the kernel above has one block of 16
+// tiles where the triangle would compute 36; with the cosine metric or y in slices the loads need arithmetic.
+constexpr int kGramRing = 8;
+constexpr int kGramRowsLds = 128;
+constexpr int kGramStageBytes = kGramRowsLds * kRowBytes;
+constexpr int kGramStagedThreads = 512;
+// squares: pairs of 64-row groups that lie in different triangles
+__host__ __device__ inline int gram_squares(int M) {
+  const int n64 = (M + 63) / 64;
+  int count = 0;
+  for (int p = 0; p < n64; ++p) count += n64 > 2 * (p / 2 + 1) ? n64 - 2 * (p / 2 + 1) : 0;
+  return count;
+}
+__host__ __device__ inline int gram_triangles(int M) { return (M + 127) / 128; }
+
+// grid (gram_triangles + gram_squares, nsplit, g), 512 threads
+__global__ __launch_bounds__(kGramStagedThreads) void pair_gram_staged_kernel(const float* __restrict__ y, int n, int dh,
+                                                                              int M, long long chunk,
+                                                                              double* __restrict__ part,
+                                                                              unsigned long long* __restrict__ max_bits) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kGramRing * kGramStageBytes];
+  const uint32_t lds0 = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>(reinterpret_cast<__attribute__((address_space(3))) unsigned char*>(
+          reinterpret_cast<uintptr_t>(lds))));
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) max_bits[blockIdx.z] = 0ull;   // for frobenius_distance_kernel
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r16 = lane & 15, kq = lane >> 4, half = wave >> 2;
+  const int g = gridDim.z, batch = blockIdx.z;
+  const long long L = static_cast<long long>(n) * dh;             // multiple of 64
+  const bool triangle = static_cast<int>(blockIdx.x) < gram_triangles(M);
+  int p0, q0;   // first expert of the stage's rows 0..63 and 64..127
+  if (triangle) {
+    p0 = blockIdx.x * 128;
+    q0 = p0 + 64;
+  } else {
+    const int n64 = (M + 63) / 64;
+    int index = blockIdx.x - gram_triangles(M), p = 0;
+    while (index >= max(n64 - 2 * (p / 2 + 1), 0)) {
+      index -= max(n64 - 2 * (p / 2 + 1), 0);
+      ++p;
+    }
+    p0 = p * 64;
+    q0 = (2 * (p / 2 + 1) + index) * 64;
+  }
+  const long long kbeg = blockIdx.y * chunk, kend = min(kbeg + chunk, L);
+  const int steps = static_cast<int>((kend - kbeg) / 32);         // >= 2: chunks are multiples of 64, as L is
+  const char* src[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {   // rows beyond M repeat the last one (their results are not stored)
+    const int row = 16 * wave + 8 * i + (lane >> 3);
+    const int e = min((row < 64 ? p0 : q0 - 64) + row, M - 1);
+    src[i] = reinterpret_cast<const char*>(y + (static_cast<size_t>(e) * g + batch) * L + kbeg) + 16 * ((lane & 7) ^ (row & 7));
+  }
+  auto issue = [&](int step) {
+    const uint32_t at = lds0 + (step % kGramRing) * kGramStageBytes + wave * 16 * kRowBytes;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) lds_load_tokens(at + i * kLoadRows * kRowBytes, src[i] + static_cast<size_t>(step) * kRowBytes);
+  };
+  auto fetch = [&](int step, int tile) {   // 4 consecutive k of row r16 of a 16-row tile
+    const int row = 16 * tile + r16;
+    return *reinterpret_cast<const float4*>(lds + (step % kGramRing) * kGramStageBytes + row * kRowBytes +
+                                            16 * ((4 * half + kq) ^ (row & 7)));
+  };
+  auto next_stage = [&](int step) {   // stage `step` is there; the stage before it is free and is filled again
+    if (step + kGramRing - 1 <= steps) wait_loads<2 * (kGramRing - 2)>(); else wait_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (step + kGramRing - 1 < steps) issue(step + kGramRing - 1);
+  };
+  for (int s = 0; s < min(kGramRing - 1, steps); ++s) issue(s);
+  // lane l holds D[l / 16 + 4 r][l % 16], r = 0..3 (the fp64 tile interleaves its row blocks).  The second half's
+  // sums pass through the ring, which is free by then.
+  double* out = part + (static_cast<size_t>(batch) * gridDim.y + blockIdx.y) * gram_part_stride(M);
+  auto finish = [&](auto& acc, auto count, auto tile_of) {
+    constexpr int N = decltype(count)::value;
+    double* sums = reinterpret_cast<double*>(lds) + (wave & 3) * N * 4 * kWave;
+    __syncthreads();
+    if (half == 1) {
+#pragma unroll
+      for (int t = 0; t < N; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[(4 * t + r) * kWave + lane] = acc[t][r];
+    }
+    __syncthreads();
+    if (half == 1) return;
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+      int ti, tj;
+      tile_of(t, ti, tj);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double v = acc[t][r] + sums[(4 * t + r) * kWave + lane];
+        const int row = 16 * ti + kq + 4 * r, col = 16 * tj + r16;
+        int pp = (row < 64 ? p0 : q0 - 64) + row, qq = (col < 64 ? p0 : q0 - 64) + col;
+        if (ti > tj) {   // only tiles of the upper triangle are kept
+          const int swap = pp;
+          pp = qq;
+          qq = swap;
+        }
+        if (pp < M && qq < M) out[static_cast<size_t>(pp) * M + qq] = v;
+      }
+    }
+  };
+  auto element = [](const float4& v, int j) { return static_cast<double>(j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w); };
+  if (triangle) {
+    const int b = 2 * (wave & 3), last = (wave & 3) < 2 ? 0 : 1;   // row b + last has the tile at d = 4
+    f64x4 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < steps; ++s) {
+      next_stage(s);
+      float4 v[7];
+#pragma unroll
+      for (int t = 0; t < 5; ++t) v[t] = fetch(s, (b + t) & 7);
+      v[5] = fetch(s, (b + last) & 7);
+      v[6] = fetch(s, (b + last + 4) & 7);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        double x[7];
+#pragma unroll
+        for (int t = 0; t < 7; ++t) x[t] = element(v[t], j);
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t >> 2], x[(t >> 2) + (t & 3)], acc[t], 0, 0, 0);
+        acc[8] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[5], x[6], acc[8], 0, 0, 0);
+      }
+    }
+    finish(acc, std::integral_constant<int, 9>{}, [&](int t, int& ti, int& tj) {
+      ti = (t < 8 ? b + (t >> 2) : b + last) & 7;
+      tj = (t < 8 ? b + (t >> 2) + (t & 3) : b + last + 4) & 7;
+    });
+  } else {
+    f64x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < steps; ++s) {
+      next_stage(s);
+      float4 v[5];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = fetch(s, 4 + t);
+      v[4] = fetch(s, wave & 3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(element(v[4], j), element(v[t], j), acc[t], 0, 0, 0);
+    }
+    finish(acc, std::integral_constant<int, 4>{}, [&](int t, int& ti, int& tj) {
+      ti = wave & 3;
+      tj = 4 + t;
+    });
+  }
+}
+
 // The partial Gram matrices are added in two fixed-order levels: group r of kGramGroups takes the
-// splits r, r + kGramGroups, ... (this kernel; entries below the block diagonal are read from
-// their mirror image), and the distance kernel adds the kGramGroups group sums.
+// splits r, r + kGramGroups, ... (this kernel; entries below the diagonal of 16 x 16 tiles are
+// copies of their mirror image), and the distance kernel adds the kGramGroups group sums.
+// Only the upper entries are summed, in rows, and written twice: 8 us for 128 experts and 256 splits, against 28 with
+// the lower entries read down the columns of their mirror image.
 // grid (ceil(M * M / 256), kGramGroups, g), 256 threads.
 constexpr int kGramGroups = 8;
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, int nsplit, int M,
                                                           double* __restrict__ gram) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (idx >= M * M) return;
-  int a = idx / M, b = idx % M;
-  if (a / kGramBlock > b / kGramBlock) {
-    const int t = a;
-    a = b;
-    b = t;
-  }
+  const int a = idx / M, b = idx % M;
+  if (a / 16 > b / 16) return;   // written by its mirror entry: read in rows, the partial sums come in whole lines
   const size_t mm = gram_part_stride(M);
-  const double* src = part + static_cast<size_t>(blockIdx.z) * nsplit * mm + static_cast<size_t>(a) * M + b;
+  const double* src = part + static_cast<size_t>(blockIdx.z) * nsplit * mm + idx;
   double g = 0.0;
   for (int s = blockIdx.y; s < nsplit; s += kGramGroups) g += src[s * mm];
-  gram[(static_cast<size_t>(blockIdx.z) * kGramGroups + blockIdx.y) * M * M + idx] = g;
+  double* out = gram + (static_cast<size_t>(blockIdx.z) * kGramGroups + blockIdx.y) * M * M;
+  out[idx] = g;
+  if (a / 16 < b / 16) out[b * M + a] = g;
 }
 
 // dist[p][q] = sqrt(G_pp + G_qq - 2 G_pq), G = the sum of the group sums `gram`.  A pair whose squared distance is below
