@@ -193,7 +193,8 @@ class Runner:
         return total_ms * 1e3 / steps, per_round, wall * 1e6 / steps, label
 
     def stage_times(self, mode, steps):
-        """Average duration of each kernel stage (HIP events attached to each dispatch on the launch stream)."""
+        """Average duration of each kernel stage in a step, all its launches (HIP events attached to each dispatch on
+        the launch stream)."""
         from paper_2602_07616_amd import binding as B
         n = len(self.layers)
         with self.torch.cuda.stream(self.stream):
@@ -203,15 +204,15 @@ class Runner:
             B.sere_stage_timing(True)
             for i in range(steps):
                 self._call(self.layers[i % n], mode)
-            ms, cnt = B.sere_stage_timing_read()
+            ms, _ = B.sere_stage_timing_read()
             B.sere_stage_timing(False)
-        return {s: (ms[s] * 1e3 / cnt[s] if cnt[s] else 0.0) for s in ms}
+        return {s: ms[s] * 1e3 / steps for s in ms}
 
     def similarity_timing(self):
         """The set-up step (sere_similarity, Frobenius metric) once more with per-kernel events: us per
         calibration batch of the experts' forward pass and of the pair stage (Gram matrix of the
         experts' outputs on the fp64 matrix cores, distances, accumulation), and the pair stage's
-        share of the fp64 MFMA peak: 2 * (upper-triangular 64 x 64 blocks) * n * d_h flop per batch."""
+        share of the fp64 MFMA peak: 2 * 16 * 16 * (upper-triangular 16 x 16 tiles) * n * d_h flop per batch."""
         from paper_2602_07616_amd import binding as B, device
         sp = self.wl.spec
         batches, n = self.wl.calib.shape[0], self.wl.calib.shape[1]
@@ -219,8 +220,8 @@ class Runner:
         device.similarity_on_device(self.wl, self.layers[0].weights())
         ms, cnt = B.sere_stage_timing_read()
         B.sere_stage_timing(False)
-        nb = (sp.experts + 63) // 64
-        flop = 2.0 * (nb * (nb + 1) // 2) * 64 * 64 * n * sp.hidden
+        nb = (sp.experts + 15) // 16
+        flop = 2.0 * (nb * (nb + 1) // 2) * 16 * 16 * n * sp.hidden
         pair_us = ms["sim_pairs"] * 1e3 / batches
         return {"calibration_batches": batches, "tokens_per_batch": n,
                 "forward_us_per_batch": round((ms["gate_up"] + ms["down"]) * 1e3 / batches, 2),
