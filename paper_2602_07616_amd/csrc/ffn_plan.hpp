@@ -4,8 +4,20 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
+
+#include "../../include/sere.h"
 
 namespace sere {
+
+inline size_t align_up(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }   // of a buffer in the workspace
+
+// bf16 down projection: d_m is cut into slices of at most 2048 so that one
+// wavefront streams at most 64 KB of weights whatever the expert width
+inline int down_ksplit(const sere_config& c) { return c.dtype == SERE_BF16 ? (c.inter + 2047) / 2048 : 1; }
+
+// wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
+inline int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 && c.inter >= 4096) ? 1 : 0; }
 
 constexpr int kItemRows = 32;     // rows of the sorted slot list per FFN work item (FfnPlan::item_rows may be larger)
 constexpr int kTileGroups = 256;  // persistent workgroups of the kernels of ffn_tile.hpp: one per compute unit

@@ -15,6 +15,7 @@
 #include "ffn_tile.hpp"
 #include "route_kernels.hpp"
 #include "similarity_kernels.hpp"
+#include "similarity_plan.hpp"
 
 namespace sere {
 
@@ -26,14 +27,6 @@ struct Layout {
   int ksplit;    // slices of d_m in the down projection
   int max_work;  // upper bound on FFN work items (the FFN grids are sized for it)
 };
-
-static size_t align_up(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
-
-// bf16 down projection: d_m is cut into slices of at most 2048 so that one
-// wavefront streams at most 64 KB of weights whatever the expert width
-static int down_ksplit(const sere_config& c) {
-  return c.dtype == SERE_BF16 ? (c.inter + 2047) / 2048 : 1;
-}
 
 static Layout make_layout(const sere_config& c) {
   Layout l{};
@@ -350,9 +343,6 @@ static void launch_combine(const sere_config& c, const Layout& l, const Pointers
 #undef SERE_LAUNCH_COMBINE
 }
 
-// wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
-static int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 && c.inter >= 4096) ? 1 : 0; }
-
 // Work item size and kernels of a call whose experts own the slots of T tokens.  Which experts those are is
 // known on the device only; here it is what independent tokens give: an expert stays if some token has it among
 // its top S (its top K without re-routing or with a threshold).
@@ -551,100 +541,6 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* __restric
 }
 
 // ------------------------------------------------------------- similarity ---
-// Calibration batches are served in groups of about kSimGroupRows tokens (more rows per expert make the forward
-// pass no faster per token), within kSimGroupBytes of workspace, so that an expert's weights are streamed once per
-// group: 32 tokens of the Qwen3 shape 201 us alone, 110 / 66 / 53 us a batch in groups of 2 / 4 / 8.  A layer whose experts fit the chip's
-// L2s takes one batch at a time: its weights are streamed from there.  A call with less workspace, or with fewer
-// batches, runs smaller groups.
-constexpr int kSimGroupRows = 256, kSimGroupMax = 16;
-constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{32} << 20;
-
-struct SimLayout {
-  size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, inv_norm, max_bits,
-      total;
-  int rows, ksplit;
-  FfnPlan plan;
-  int items;            // work items of an expert
-  bool gram_staged;     // Frobenius: the Gram kernel that stages through LDS
-  int gram_splits;      // slices of the flattened outputs in the Gram kernel
-  long long gram_chunk; // ... and their length
-};
-
-// layout of groups of g batches of n tokens
-static SimLayout make_sim_layout(const sere_config& c, int n, int g) {
-  SimLayout l{};
-  const size_t M = c.num_experts, R = M * static_cast<size_t>(n) * g;
-  l.rows = static_cast<int>(R);
-  l.ksplit = down_ksplit(c);
-  FfnShape s{};
-  s.hidden = c.hidden;
-  s.inter = c.inter;
-  s.tokens = n * g;
-  s.experts = M;
-  s.rows = n * g;
-  s.slots_per_expert = n * g;
-  s.split_h = wants_split_h(c) != 0;
-  s.max_ksplit = l.ksplit;
-  l.plan = c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
-  l.items = (n * g + l.plan.item_rows - 1) / l.plan.item_rows;
-  const size_t W = M * l.items;
-  size_t o = 0;
-  auto take = [&](size_t bytes) {
-    size_t at = o;
-    o = align_up(o + bytes);
-    return at;
-  };
-  l.acc = take(M * M * sizeof(double));  // first: the same place for groups of every size
-  l.sorted_token = take(R * 4);
-  l.work_expert = take(W * 4);
-  l.work_off = take(W * 4);
-  l.work_cnt = take(W * 4);
-  l.n_work = take(8);
-  l.dist = take(g * M * M * sizeof(double));
-  l.max_bits = take(g * 8);
-  l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
-  l.h = take(R * c.inter * sizeof(float));
-  if (c.flags & SERE_FLAG_SIM_CKA_LINEAR) {  // Gram matrix and its row sums per expert
-    l.gram = take(R * n * sizeof(double));
-    l.rowsum = take(R * sizeof(double));
-    l.diag = take(R * sizeof(double));
-  } else {                                   // partial Gram matrices of the experts' flattened outputs
-    // the cosine metric keeps them in the place of h, which is no longer needed when they are written
-    const bool in_h = (c.flags & SERE_FLAG_SIM_COSINE) != 0;
-    const size_t end = o;
-    if (in_h) {
-      o = l.h;
-      l.inv_norm = take(R * sizeof(double));
-    }
-    const long long L = static_cast<long long>(n) * c.hidden;
-    // about three workgroups for every compute unit, 16 .. 256 splits, each a multiple of the Gram kernel's
-    // 64-wide load group
-    const int nb = static_cast<int>((M + kGramBlock - 1) / kGramBlock);
-    // (staged kernel: one workgroup to a compute unit at a time; a single triangle: one even wave of them)
-    l.gram_staged = !in_h && l.ksplit == 1 && M > kGramBlock;
-    const int blocks = l.gram_staged ? gram_triangles(static_cast<int>(M)) + gram_squares(static_cast<int>(M))
-                                     : nb * (nb + 1) / 2;
-    const int want = std::min(256, std::max(16, (l.gram_staged && blocks == 1 ? 256 : 768) / (blocks * g)));
-    long long chunk = (L + want - 1) / want;
-    chunk = std::max<long long>(256, (chunk + 63) / 64 * 64);
-    l.gram_chunk = chunk;
-    l.gram_splits = static_cast<int>((L + chunk - 1) / chunk);
-    l.gram_part = take(static_cast<size_t>(g) * l.gram_splits * gram_part_stride(static_cast<int>(M)) * sizeof(double));
-    l.gram = take(static_cast<size_t>(g) * kGramGroups * M * M * sizeof(double));
-    if (in_h) o = std::max(end, o);
-  }
-  l.total = o;
-  return l;
-}
-
-// batches of a group that a workspace is sized for
-static int sim_group(const sere_config& c, int n) {
-  const size_t weights = static_cast<size_t>(c.num_experts) * 3 * c.hidden * c.inter * (c.dtype == SERE_F32 ? 4 : 2);
-  int g = weights <= kSimGroupWeights ? 1 : std::max(1, std::min(kSimGroupMax, kSimGroupRows / n));
-  while (g > 1 && make_sim_layout(c, n, g).total > kSimGroupBytes) --g;
-  return g;
-}
-
 constexpr int kCkaMinTokens = 4, kCkaMaxTokens = 512;  // the estimator's lower limit; M*n*n doubles of workspace
 
 static int check_similarity_sizes(const sere_config& c, int32_t num_batches, int32_t n) {

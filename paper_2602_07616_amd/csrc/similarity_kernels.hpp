@@ -17,6 +17,7 @@
 
 #include "common.hpp"
 #include "ffn_tile.hpp"
+#include "similarity_plan.hpp"
 
 namespace sere {
 
@@ -52,12 +53,7 @@ __global__ __launch_bounds__(256) void similarity_worklist_kernel(int M, int n, 
 // squared norm: harmless for every pair but near-identical twins, which are recomputed as a
 // direct difference by the wavefront that finds them.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int kGramBlock = 64;     // experts per side of a workgroup's block: 2 x 2 wavefronts, each 2 x 2 tiles of 16 x 16
 constexpr int kGramSteps = 2;      // 16-wide k steps per load group (two groups are in flight)
-// partial Gram matrices lie M * M + kGramPad doubles apart: a power-of-two distance would put the
-// same entry of every split on the same memory channel
-constexpr int kGramPad = 96;
-__host__ __device__ inline size_t gram_part_stride(int M) { return static_cast<size_t>(M) * M + kGramPad; }
 constexpr double kGramTwinThreshold = 1e-9;  // x_pq^2 below this fraction of <V_p,V_p> + <V_q,V_q>: recompute directly
 
 // upper-triangular blocks (bp <= bq) numbered row by row
@@ -203,14 +199,6 @@ constexpr int kGramRing = 8;
 constexpr int kGramRowsLds = 128;
 constexpr int kGramStageBytes = kGramRowsLds * kRowBytes;
 constexpr int kGramStagedThreads = 512;
-// squares: pairs of 64-row groups that lie in different triangles
-__host__ __device__ inline int gram_squares(int M) {
-  const int n64 = (M + 63) / 64;
-  int count = 0;
-  for (int p = 0; p < n64; ++p) count += n64 > 2 * (p / 2 + 1) ? n64 - 2 * (p / 2 + 1) : 0;
-  return count;
-}
-__host__ __device__ inline int gram_triangles(int M) { return (M + 127) / 128; }
 
 // grid (gram_triangles + gram_squares, nsplit, g), 512 threads
 __global__ __launch_bounds__(kGramStagedThreads) void pair_gram_staged_kernel(const float* __restrict__ y, int n, int dh,
@@ -357,7 +345,6 @@ __global__ __launch_bounds__(kGramStagedThreads) void pair_gram_staged_kernel(co
 // Only the upper entries are summed, in rows, and written twice: 8 us for 128 experts and 256 splits, against 28 with
 // the lower entries read down the columns of their mirror image.
 // grid (ceil(M * M / 256), kGramGroups, g), 256 threads.
-constexpr int kGramGroups = 8;
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, int nsplit, int M,
                                                           double* __restrict__ gram) {
   const int idx = blockIdx.x * 256 + threadIdx.x;

@@ -1,0 +1,62 @@
+"""The host's plan of a similarity estimation (csrc/similarity_plan.hpp, compiled here with g++): a call checks its
+workspace against the largest group of batches that it launches, so the layouts of all smaller groups, the last one of
+a call among them, have to fit into the same bytes."""
+import math
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2602_07616_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+METRICS = (0, B.SERE_FLAG_SIM_COSINE, B.SERE_FLAG_SIM_CKA_LINEAR)
+
+
+@pytest.fixture(scope="module")
+def layouts(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("simplan") / "plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "similarity_plan_main.cpp"), "-o", exe],
+                   check=True)
+
+    def run(cases):
+        out = subprocess.run([exe], input="".join("%d %d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
+                             check=True).stdout.split("\n")
+        return [[tuple(int(v) for v in g.split()) for g in line.split(";") if g] for line in out if line]
+    return run
+
+
+def draws(count, seed):
+    rng = random.Random(seed)
+    log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    # the sizes at which a last group of 15 batches once needed more than a group of 16, for all metrics
+    cases = [(dtype, 768, M, 64, 7, f) for dtype in (B.SERE_F32, B.SERE_BF16) for M in range(120, 130) for f in METRICS]
+    for _ in range(count):
+        f = rng.choice(METRICS)
+        cases.append((rng.choice((B.SERE_F32, B.SERE_BF16)), 64 * log_int(1, 64), log_int(1, 256), 64 * log_int(1, 224),
+                      log_int(4 if f == B.SERE_FLAG_SIM_CKA_LINEAR else 1, 400), f))
+    return cases
+
+
+def test_no_group_needs_more_than_a_larger_one(layouts):
+    cases = draws(6000, 11)
+    grouped = 0
+    for case, groups in zip(cases, layouts(cases)):
+        totals = [g[0] for g in groups]
+        assert totals == sorted(totals), (case, totals)
+        grouped += len(groups) > 1
+    assert grouped > 1000      # otherwise the draw would say nothing
+
+
+def test_plans_of_groups_can_be_run(layouts):
+    """Items hold every row of a group, longer items than the decode kernels take go to the persistent ones, and the
+    work list and the partial Gram matrices fit their places."""
+    cases = draws(2000, 12)
+    for case, groups in zip(cases, layouts(cases)):
+        M, n, blocks = case[2], case[4], case[3] // 64
+        for g, (_, items, rows, tile_gu, tile_dn, ksplit, splits, _, item_bytes, part_bytes) in enumerate(groups, 1):
+            assert M * items * 4 <= item_bytes and g * splits * (M * M + 96) * 8 <= part_bytes, case
+            assert (items - 1) * rows < n * g <= items * rows, case
+            assert rows == 32 or (tile_gu and tile_dn), case
+            assert (ksplit - 1) * -(-blocks // ksplit) < blocks, case
