@@ -232,8 +232,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         // 16 of the step's 32 k: lane (g, i) has four consecutive k of its rows, one product each.  The matrix
         // cores add one after the other; a chain over the whole contraction would round more than a sum over
         // 64 lanes does (2.6e-7 against 1.8e-7 relative error at d_h = 1024).  So every 8 products are summed
-        // on their own, a step's four sums pairwise, and the step's sum is added to the unit's with
-        // compensation (Kahan).
+        // on their own, a step's four sums pairwise, and what each addition of a step's sum to the unit's
+        // rounds away is kept in a sum of its own, which is added at the end.  It never enters the running
+        // sum: once that is infinite the rounded-away part is a NaN.
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -245,9 +246,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         if constexpr (decltype(which)::value == 1) {
 #pragma unroll
           for (int a = 0; a < NA; ++a) {
-            const f32x4 add = ((sums[0][a][t] + sums[1][a][t]) + (sums[2][a][t] + sums[3][a][t])) - low[a][t];
+            const f32x4 add = (sums[0][a][t] + sums[1][a][t]) + (sums[2][a][t] + sums[3][a][t]);
             const f32x4 next = acc[a][t] + add;
-            low[a][t] = (next - acc[a][t]) - add;
+            low[a][t] += add - (next - acc[a][t]);
             acc[a][t] = next;
           }
         }
@@ -270,6 +271,15 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     }
   };
   auto store = [&]() {
+    if constexpr (DT == SERE_F32) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (fabsf(low[a][t][r]) < INFINITY) acc[a][t][r] += low[a][t][r];
+    }
     const int slab = part / ksplit, slice = part % ksplit;
     if (GATEUP) {
       const int j0 = slab * kOut + wm * (RW / 2);

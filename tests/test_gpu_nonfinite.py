@@ -1,0 +1,67 @@
+"""Infinities and NaN in the experts' weights or from overflow: what a layer returns where a plain sum gives one.
+(Hidden states, router and similarities have to be finite; expert weights need not be.)"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2602_07616_amd import workloads as wk
+from . import pins
+from .test_gpu_parity import dev  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+HUGE = np.float32(2.5e38)    # finite; the sum of two is not
+
+
+def f32_layer(wl, ref):
+    """The layer in numpy, every projection rounded to fp32 (which is where a sum becomes infinite)."""
+    out = np.zeros(wl.hidden.shape, dtype=np.float64)
+    x = wl.hidden.astype(np.float64)
+    dm = wl.spec.inter
+    with np.errstate(all="ignore"):
+        for e in range(wl.spec.experts):
+            t, k = np.nonzero(ref.rerouted_ids == e)
+            if len(t) == 0:
+                continue
+            gu = np.einsum("tk,jk->tj", x[t], wl.w_gate_up[e].astype(np.float64)).astype(np.float32)
+            g, u = gu[:, :dm], gu[:, dm:]
+            h = (g / (1.0 + np.exp(-g.astype(np.float64)))).astype(np.float32) * u
+            y = np.einsum("tj,rj->tr", h.astype(np.float64), wl.w_down[e].astype(np.float64)).astype(np.float32)
+            out[t] += ref.topk_weights[t, k][:, None] * y
+    return out
+
+
+@pytest.mark.parametrize("tokens", [4, 40])     # the vector-ALU kernels, the persistent ones
+@pytest.mark.parametrize("where", ["up_inf_first", "up_inf_last", "up_overflow", "up_overflow_far", "down_inf", "down_neg_inf"])
+def test_fp32_sum_that_overflows_is_infinite(dev, tokens, where):  # noqa: F811
+    """One infinite weight, or two finite ones whose products overflow (in one 32-wide step, or in two), in the first,
+    a middle or the last step of the contraction: the sums are infinite, with the sign of the exact sum."""
+    dh, M, K, dm = 1472, 3, 3, 192
+    spec = wk.custom_spec("nonfinite", wk.F32, dh, M, K, dm, 0, tokens, 7300, calib_batches=1, calib_tokens=4)
+    wl = wk.make_workload(spec)
+    up, down = wl.w_gate_up[2][dm:], wl.w_down[2]
+    if where == "up_inf_first":
+        up[7, 3] = np.inf
+    elif where == "up_inf_last":
+        up[7, dh - 1] = np.inf
+    elif where == "up_overflow":
+        up[7, 640] = up[7, 641] = HUGE
+        wl.hidden[:, 640:642] = 1.0
+    elif where == "up_overflow_far":
+        up[7, 5] = up[7, dh - 2] = HUGE
+        wl.hidden[:, [5, dh - 2]] = 1.0
+    else:
+        down[11, dm // 2] = np.inf if where == "down_inf" else -np.inf
+    sim = pins.rand_sim(7300, M)
+    layer = dev.DeviceLayer.from_workload(wl, sim, K, 0.0)
+    ref = oracle.route(wl.hidden, wl.router_w, wk.F32, K, sim, K, 0.0)
+    assert (ref.rerouted_ids == 2).any()
+    print(f"nonfinite {where} {tokens}", flush=True)
+    layer.run_decode()
+    got, want = layer.out_to_host_f64(), f32_layer(wl, ref)
+    assert np.isinf(want).any() and not np.isnan(want).any()
+    assert not np.isnan(got).any(), np.argwhere(np.isnan(got))[:4]
+    assert np.array_equal(np.isinf(got), np.isinf(want)) and np.array_equal(np.signbit(got), np.signbit(want))
+    fin = np.isfinite(want)
+    # as in the finite fp32 tests: compensated sums stay near 2e-7
+    assert np.linalg.norm(got[fin] - want[fin]) <= 1e-6 * np.linalg.norm(want[fin])
