@@ -50,10 +50,10 @@ __device__ __forceinline__ int scalar_load(const int32_t* p, int i) {
 // They are asm so that the compiler does not wait for them on its own; nothing else of these kernels'
 // main loop counts in vmcnt but them and the result stores.
 __device__ __forceinline__ void lds_load_weights(uint32_t lds, uint32_t lane_off, const char* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_load_tokens(uint32_t lds, const char* addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
 }
 // all but the youngest N vector memory operations, and this wavefront's LDS reads
 template <int N>

@@ -2,7 +2,10 @@
 their descriptions (the device code is not run here): the XCD-aware numbering of the wide FFN
 kernels' workgroups must be a one-to-one map onto the (item, part) pairs, and the cut of a long
 expert into equal work items must give positive, tile-sized items that add up to the expert's rows."""
+import glob
+import os
 import random
+import re
 
 
 def xcd_virtual_id(wg: int, total: int, xcds: int = 8) -> int:
@@ -45,3 +48,15 @@ def test_long_experts_are_cut_into_positive_tile_sized_items():
             assert sum(items) == rows
             assert all(0 < c <= item_rows for c in items), (rows, item_rows, items)
             assert all(c % 16 == 0 for c in items[:-1]) or item_rows < 128 or len(items) > 4
+
+
+def test_inline_assembly_declares_the_registers_it_writes():
+    """An asm statement that writes m0 has to say so: the compiler may keep a value of its own there."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_07616_amd", "csrc")
+    found = 0
+    for path in glob.glob(os.path.join(csrc, "*.h*")):
+        for text in re.findall(r"asm volatile\((.*?)\);", open(path).read(), re.S):
+            if re.search(r"\bs_mov_b32 m0\b", text):
+                found += 1
+                assert '"m0"' in text.rsplit(":", 1)[1], (path, text)
+    assert found == 2
