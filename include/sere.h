@@ -236,8 +236,8 @@ int sere_moe_decode_static(const sere_config *cfg, const void *hidden, const voi
  * With SERE_FLAG_SIM_COSINE in cfg->flags the metric is the cosine one of the
  * appendix "Cosine Similarity" instead: Sim(p,q) = the mean over the batch's
  * tokens of the cosine between the two experts' outputs for that token (a
- * token where either output is the zero vector contributes 0); values lie in
- * [-1, 1].  With SERE_FLAG_SIM_CKA_LINEAR it is centered kernel alignment with
+ * token where either output is the zero vector, or has a NaN, contributes 0);
+ * values lie in [-1, 1].  With SERE_FLAG_SIM_CKA_LINEAR it is centered kernel alignment with
  * the linear kernel (appendix "Centered Kernel Alignment"): K_p = A_p A_p^T
  * [batch_tokens, batch_tokens] per expert, Sim(p,q) = HSIC(K_p,K_q) /
  * sqrt(HSIC(K_p,K_p) HSIC(K_q,K_q)) with the unbiased O(n^2) estimator of HSIC

@@ -616,7 +616,8 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
     launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(entries, kGramGroups, g), dim3(256),
                  static_cast<const double*>(part), l.gram_splits, M, gram);
     if (metric == kMetricCosine)
-      hipLaunchKernelGGL(cosine_mean_kernel, dim3(entries, g), dim3(256), 0, s, gram, n, M, dist);
+      hipLaunchKernelGGL(cosine_mean_kernel, dim3(entries, g), dim3(256), 0, s, gram,
+                         reinterpret_cast<const double*>(ws + l.inv_norm), n, M, dist);
     else
       launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
                    static_cast<const double*>(gram), static_cast<const float*>(f.y), f.ksplit, l.rows, n, dh, M, dist, max_bits);

@@ -75,7 +75,7 @@ __device__ __forceinline__ void gram_block_of(int index, int nb, int& bp, int& b
 // Serves the cosine metric, up to 64 experts, and y in slices.  43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us
 // a batch; the fp64 matrix cores reach 69 in a large product).  Neither more workgroups (three for every compute unit instead of one and a half) nor four
 // independent sums between two products of one changed that: it waits for its operands.
-// COSINE: every row of A is divided by its length first (inv_norm[row], 0 for a zero row), so the entries
+// COSINE: every row of A is divided by its length first (inv_norm[row]; see row_norm_kernel), so the entries
 // are sums over tokens of cosines.
 template <bool COSINE>
 __global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n,
@@ -424,18 +424,21 @@ __global__ __launch_bounds__(256) void frobenius_distance_kernel(const double* _
 }
 
 // Cosine metric (appendix "Cosine Similarity"): Sim(p, q) = (1/n) sum over tokens i of <A_p[i], A_q[i]> /
-// (|A_p[i]| |A_q[i]|); a token where either output is the zero vector contributes 0.  With every row divided
-// by its length that sum is an entry of the Gram matrix of the flattened outputs, so it takes the Frobenius
-// metric's kernels: M * M / 2 products on the fp64 matrix cores instead of a workgroup per ordered pair that
-// reads both experts' outputs from cache (two batches of 32 tokens, 128 experts, d_h 2048, forward pass
-// included: 1278 -> 358 us).
-// inv_norm[row] = 1 / |y[row]|, 0 for a zero row; grid ceil(rows / 4), 256 threads: a wavefront per row.
-__global__ __launch_bounds__(256) void row_norm_kernel(const float* __restrict__ y, int ksplit, int rows, int dh,
+// (|A_p[i]| |A_q[i]|); a token where the product of the two lengths is not positive (either output is the
+// zero vector, or has a NaN) contributes 0.  With every row divided by its length that sum is an entry of the Gram
+// matrix of the flattened outputs, so it takes the Frobenius metric's kernels: M * M / 2 products on the fp64
+// matrix cores instead of a workgroup per ordered pair that reads both experts' outputs from cache (two batches of
+// 32 tokens, 128 experts, d_h 2048, forward pass included: 1278 -> 329 us).
+// A sum over tokens cannot leave one out after the fact (NaN * 0 is NaN), so rows without a finite positive
+// length are set to zero here, before the Gram kernel reads them:
+// inv_norm[row] = 1 / |y[row]|, 0 for a zero row and one with a NaN, -1 for an infinite one.
+// grid ceil(rows / 4), 256 threads: a wavefront per row.
+__global__ __launch_bounds__(256) void row_norm_kernel(float* __restrict__ y, int ksplit, int rows, int dh,
                                                        double* __restrict__ inv_norm) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= rows) return;
   const size_t slice = static_cast<size_t>(rows) * dh;
-  const float* a = y + static_cast<size_t>(row) * dh;
+  float* a = y + static_cast<size_t>(row) * dh;
   double sum = 0.0;
   for (int c = lane * 4; c < dh; c += 256) {
     float4 v = *reinterpret_cast<const float4*>(a + c);
@@ -447,18 +450,36 @@ __global__ __launch_bounds__(256) void row_norm_kernel(const float* __restrict__
     sum += x * x + yy * yy + z * z + w * w;
   }
   sum = wave_sum(sum);
-  if (lane == 0) inv_norm[row] = sum > 0.0 ? 1.0 / sqrt(sum) : 0.0;
+  const bool normal = sum > 0.0 && sum < INFINITY;
+  if (!normal)   // wave-uniform
+    for (int s = 0; s < ksplit; ++s)
+      for (int c = lane * 4; c < dh; c += 256) *reinterpret_cast<float4*>(a + s * slice + c) = float4{0.0f, 0.0f, 0.0f, 0.0f};
+  if (lane == 0) inv_norm[row] = normal ? 1.0 / sqrt(sum) : sum > 0.0 ? -1.0 : 0.0;
 }
 
-// dist[batch][p][q] = (1/n) sum of the group sums; grid (ceil(M * M / 256), g), 256 threads
-__global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restrict__ gram, int n, int M,
+// dist[batch][p][q] = (1/n) sum of the group sums; grid (ceil(M * M / 256), g), 256 threads.  A token whose output
+// is infinite makes the quotient NaN, unless the other expert's is zero or has a NaN there.  Such tokens
+// are missing from an expert's sum with itself, which otherwise is n, so few pairs look for them.
+__global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restrict__ gram,
+                                                          const double* __restrict__ inv_norm, int n, int M,
                                                           double* __restrict__ dist) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (idx >= M * M) return;
-  double sum = 0.0;
+  const int g = gridDim.y, batch = blockIdx.y, p = idx / M, q = idx % M;
+  auto entry = [&](int at) {   // the group sums of one entry, in fixed order
+    double sum = 0.0;
 #pragma unroll
-  for (int r = 0; r < kGramGroups; ++r) sum += gram[(static_cast<size_t>(blockIdx.y) * kGramGroups + r) * M * M + idx];
-  dist[static_cast<size_t>(blockIdx.y) * M * M + idx] = sum / n;
+    for (int r = 0; r < kGramGroups; ++r) sum += gram[(static_cast<size_t>(batch) * kGramGroups + r) * M * M + at];
+    return sum;
+  };
+  double sum = entry(idx);
+  if (entry(p * M + p) < n - 0.5 || entry(q * M + q) < n - 0.5) {
+    const double* a = inv_norm + (static_cast<size_t>(p) * g + batch) * n;
+    const double* b = inv_norm + (static_cast<size_t>(q) * g + batch) * n;
+    for (int i = 0; i < n; ++i)
+      if ((a[i] < 0.0 && b[i] != 0.0) || (b[i] < 0.0 && a[i] != 0.0)) sum = NAN;
+  }
+  dist[static_cast<size_t>(batch) * M * M + idx] = sum / n;
 }
 
 // Linear CKA (appendix "Centered Kernel Alignment"), step 1: the Gram matrix of every expert's

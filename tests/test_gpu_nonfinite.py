@@ -1,5 +1,5 @@
-"""Infinities and NaN in the experts' weights or from overflow: what a layer returns where a plain sum gives one.
-(Hidden states, router and similarities have to be finite; expert weights need not be.)"""
+"""Infinities and NaN in the experts' weights or from overflow: what a layer or a similarity estimation returns where
+a plain sum gives one.  (Hidden states, router and similarities have to be finite; expert weights need not be.)"""
 import numpy as np
 import pytest
 
@@ -65,3 +65,36 @@ def test_fp32_sum_that_overflows_is_infinite(dev, tokens, where):  # noqa: F811
     fin = np.isfinite(want)
     # as in the finite fp32 tests: compensated sums stay near 2e-7
     assert np.linalg.norm(got[fin] - want[fin]) <= 1e-6 * np.linalg.norm(want[fin])
+
+
+@pytest.mark.parametrize("dtype", [wk.F32, wk.BF16])
+def test_cosine_of_nonfinite_outputs(dev, dtype):  # noqa: F811
+    """A token contributes the quotient where the product of the two norms is positive (that is NaN if one of them is
+    infinite), and 0 where it is not: a zero output or one with a NaN, whatever the other one is."""
+    spec = wk.custom_spec("cosnan", dtype, 320, 70, 2, 64, 0, 4, 6960, calib_batches=2, calib_tokens=17)
+    wl = wk.make_workload(spec)
+    zero, nan, inf = 5, 7, 9
+    wl.w_down[zero] = 0
+    wl.w_down[nan, 100, 3] = wk.to_storage(np.float32([np.nan]), dtype)[0]
+    wl.w_down[inf, 200, 60] = wk.to_storage(np.float32([np.inf]), dtype)[0]
+    print(f"cosine nonfinite dtype {dtype}", flush=True)
+    got = dev.similarity_on_device(wl, metric="cosine").cpu().numpy()
+    want = oracle.similarity_cosine(wl.calib, wl.w_gate_up, wl.w_down, dtype)
+    assert (want[nan] == 0).all() and np.isnan(want[inf]).sum() == 68       # the oracle has the same reading
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    fin = ~np.isnan(want)
+    assert (got[[zero, nan]] == 0).all() and (got[:, [zero, nan]] == 0).all()
+    # as in the finite cosine tests
+    assert np.abs(got[fin] - want[fin]).max() <= (1e-5 if dtype == wk.F32 else 5e-3)
+
+
+def test_cosine_of_one_token_with_nan_outputs(dev):  # noqa: F811
+    """A token whose outputs overflow to NaN in fp32 contributes 0: the others' mean is left, over all tokens."""
+    n = 20
+    spec = wk.custom_spec("costoken", wk.F32, 320, 33, 2, 64, 0, 4, 6970, calib_batches=1, calib_tokens=n)
+    wl = wk.make_workload(spec)
+    others = np.delete(wl.calib, 6, axis=1)
+    want = oracle.similarity_cosine(others, wl.w_gate_up, wl.w_down, wk.F32) * (n - 1) / n
+    wl.calib[0, 6] *= np.float32(1e30)
+    got = dev.similarity_on_device(wl, metric="cosine").cpu().numpy()
+    assert np.abs(got - want).max() <= 1e-5
