@@ -291,7 +291,9 @@ int sere_similarity_cka(const sere_config *cfg, const void *calib, int32_t num_b
  * the caller's stream: they take the kernel's start and end time stamps, so
  * the elapsed time is the kernel's duration as a profiler's kernel trace
  * reports it, without the gap to its neighbours (at most
- * SERE_TIMING_MAX_RECORDS launches are kept, later ones are not recorded).
+ * SERE_TIMING_MAX_RECORDS launches are kept, later ones are not recorded; the
+ * few microseconds that write the work list of a similarity estimation belong
+ * to no stage).
  * Do not enable it on a stream that is being captured into a HIP graph.
  * sere_stage_timing_read waits for the recorded events, adds the elapsed
  * milliseconds and launch counts per stage into the two arrays of

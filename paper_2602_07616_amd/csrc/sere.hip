@@ -587,40 +587,43 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
   double* gram = reinterpret_cast<double*>(ws + l.gram);
   unsigned long long* max_bits = reinterpret_cast<unsigned long long*>(ws + l.max_bits);
   const unsigned entries = (M * M + 255) / 256;
+  const float* y = f.y;
   if (metric == kMetricCkaLinear) {
     double* rowsum = reinterpret_cast<double*>(ws + l.rowsum);
     const bool linear = cka_kernel == kCkaLinear;
     double* diag = linear ? nullptr : reinterpret_cast<double*>(ws + l.diag);
-    hipLaunchKernelGGL(gram_kernel, dim3(n, M * g), dim3(256), 0, s, f.y, f.ksplit, l.rows, n, dh, gram,
-                       linear ? rowsum : static_cast<double*>(nullptr), diag);
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_kernel, dim3(n, M * g), dim3(256), y, f.ksplit, l.rows, n, dh, gram,
+                 linear ? rowsum : static_cast<double*>(nullptr), diag);
     if (!linear)
-      hipLaunchKernelGGL(gram_transform_kernel, dim3(n, M * g), dim3(256), 0, s, gram, diag, n, cka_kernel, p0,
-                         static_cast<int>(p1), rowsum);
-    hipLaunchKernelGGL(pair_hsic_kernel, dim3(M, M, g), dim3(256), 0, s, gram, rowsum, n, M, dist);
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_transform_kernel, dim3(n, M * g), dim3(256), gram,
+                   static_cast<const double*>(diag), n, cka_kernel, p0, static_cast<int>(p1), rowsum);
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_hsic_kernel, dim3(M, M, g), dim3(256), static_cast<const double*>(gram),
+                 static_cast<const double*>(rowsum), n, M, dist);
   } else {
     double* part = reinterpret_cast<double*>(ws + l.gram_part);
+    const double* inv_norm = metric == kMetricCosine ? reinterpret_cast<const double*>(ws + l.inv_norm) : nullptr;
     const int nb = (M + kGramBlock - 1) / kGramBlock;
     const dim3 blocks(nb * (nb + 1) / 2, l.gram_splits, g);
     if (metric == kMetricCosine) {
-      double* inv_norm = reinterpret_cast<double*>(ws + l.inv_norm);
-      hipLaunchKernelGGL(row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), 0, s, f.y, f.ksplit, l.rows, dh, inv_norm);
-      hipLaunchKernelGGL(pair_gram_kernel<true>, blocks, dim3(256), 0, s, f.y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part,
-                         inv_norm, max_bits);
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), f.y, f.ksplit, l.rows, dh,
+                   const_cast<double*>(inv_norm));
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<true>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
+                   l.gram_chunk, part, inv_norm, max_bits);
     } else if (l.gram_staged) {
       launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_staged_kernel, dim3(gram_triangles(M) + gram_squares(M), l.gram_splits, g),
-                   dim3(kGramStagedThreads), static_cast<const float*>(f.y), n, dh, M, l.gram_chunk, part, max_bits);
+                   dim3(kGramStagedThreads), y, n, dh, M, l.gram_chunk, part, max_bits);
     } else {
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<false>, blocks, dim3(256), f.y, f.ksplit, l.rows, n, dh, M,
-                   l.gram_chunk, part, static_cast<const double*>(nullptr), max_bits);
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<false>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
+                   l.gram_chunk, part, inv_norm, max_bits);
     }
     launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(entries, kGramGroups, g), dim3(256),
                  static_cast<const double*>(part), l.gram_splits, M, gram);
     if (metric == kMetricCosine)
-      hipLaunchKernelGGL(cosine_mean_kernel, dim3(entries, g), dim3(256), 0, s, gram,
-                         reinterpret_cast<const double*>(ws + l.inv_norm), n, M, dist);
+      launch_stage(SERE_STAGE_SIM_PAIRS, s, cosine_mean_kernel, dim3(entries, g), dim3(256), static_cast<const double*>(gram),
+                   inv_norm, n, M, dist);
     else
       launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
-                   static_cast<const double*>(gram), static_cast<const float*>(f.y), f.ksplit, l.rows, n, dh, M, dist, max_bits);
+                   static_cast<const double*>(gram), y, f.ksplit, l.rows, n, dh, M, dist, max_bits);
   }
   launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), M,
                b0, g, num_batches, metric, static_cast<const unsigned long long*>(max_bits),

@@ -146,6 +146,21 @@ def test_similarity_groups_of_batches(dev, metric):  # noqa: F811
     assert err.value.status == B.SERE_ERR_WORKSPACE_TOO_SMALL
 
 
+def test_every_launch_of_the_pair_stage_is_timed(dev):  # noqa: F811
+    """The reported stage is everything after the experts' forward pass, for every metric."""
+    from paper_2602_07616_amd import binding as B
+    spec = wk.custom_spec("simtimed", wk.BF16, 320, 20, 2, 192, 0, 4, 6980, calib_batches=3, calib_tokens=12)
+    wl = wk.make_workload(spec)
+    weights = (None, dev.to_device(wl.w_gate_up, wk.BF16), dev.to_device(wl.w_down, wk.BF16))
+    for kwargs, launches in (({"metric": "frobenius"}, 4), ({"metric": "cosine"}, 5), ({"metric": "cka_linear"}, 3),
+                             ({"cka": ("rbf", 1.0, 0.0)}, 4)):
+        B.sere_stage_timing(True)
+        dev.similarity_on_device(wl, weights, **kwargs)
+        ms, n = B.sere_stage_timing_read()
+        B.sere_stage_timing(False)
+        assert n["gate_up"] == 3 and n["sim_pairs"] == 3 * launches, (kwargs, n)
+
+
 def test_cosine_of_zero_outputs_and_group_in_place_of_h(dev):  # noqa: F811
     """An expert whose down projection is zero has cosine 0 with every expert, itself included; d_m = 64 makes
     the Gram buffers larger than the place of h that they start in."""
