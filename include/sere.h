@@ -254,8 +254,10 @@ int sere_moe_decode_static(const sere_config *cfg, const void *hidden, const voi
  * bf16 model forward does); similarities agree with an fp64 evaluation to a
  * few 1e-3.  batch_tokens: 1 .. 4096, num_batches: 1 .. 4096.
  * Workspace: sere_similarity_workspace_bytes(cfg, batch_tokens), which has room
- * for several batches at once (the experts' weights are then streamed once for
- * all of them); a smaller one is accepted as long as one batch fits.
+ * for several batches at once, up to 1 GiB of them (the experts' weights are
+ * then streamed once for all of them), whatever num_batches is; a smaller one
+ * is accepted as long as one batch fits, and changes nothing but the time
+ * (sums in fp64 are split differently: the last place of an entry at most).
  */
 size_t sere_similarity_workspace_bytes(const sere_config *cfg, int32_t batch_tokens);
 int sere_similarity(const sere_config *cfg, const void *calib, int32_t num_batches,

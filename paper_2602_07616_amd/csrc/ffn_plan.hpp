@@ -92,12 +92,13 @@ inline double row_cost(const FfnShape& s, double weight_bytes, double near_rate,
   return stream_us(weight_bytes, near_rate, far_rate) + again * weight_bytes / again_rate + fixed;
 }
 
-// Smallest number of slices up to max_ksplit that wastes the fewest rounds; no slice may be empty.
-inline int tile_ksplit(const FfnShape& s, double units, double step_us, double weight_bytes, double* cost) {
+// Smallest number of slices up to max_ksplit that wastes the fewest rounds; no slice may be empty.  `ksplit`: that
+// many and no other.
+inline int tile_ksplit(const FfnShape& s, double units, double step_us, double weight_bytes, int ksplit, double* cost) {
   const int blocks = s.inter / 64;
   int best = 1;
   *cost = 1e30;
-  for (int k = 1; k <= s.max_ksplit; ++k) {
+  for (int k = ksplit > 0 ? ksplit : 1; k <= (ksplit > 0 ? ksplit : s.max_ksplit); ++k) {
     const int per = (blocks + k - 1) / k;
     if ((k - 1) * per >= blocks) continue;
     const double c = tile_cost(units * k, per, step_us, 4.4, weight_bytes) + 0.55 * (k - 1);
@@ -109,8 +110,22 @@ inline int tile_ksplit(const FfnShape& s, double units, double step_us, double w
   return best;
 }
 
+// us of the two launches of the persistent kernels with items of v.rows, and the slices of the second
+struct TileCost {
+  double gate_up, down;
+  int ksplit;
+};
+inline TileCost tile_costs(const FfnShape& s, const TileVariant& v, double gu_bytes, int ksplit = 0) {
+  TileCost t;
+  const double items = total_items(s, v.rows);
+  t.gate_up = tile_cost(items * std::ceil(static_cast<double>(s.inter) / v.gate_up_out), s.hidden / 64, v.gate_up_step, 0.9, gu_bytes);
+  t.ksplit = tile_ksplit(s, items * std::ceil(static_cast<double>(s.hidden) / v.down_out), v.down_step, 0.5 * gu_bytes, ksplit, &t.down);
+  return t;
+}
+inline double gate_up_bytes(const FfnShape& s) { return (s.experts + s.num_shared) * 4.0 * s.hidden * s.inter; }
+
 inline FfnPlan plan_ffn(const FfnShape& s) {
-  const double gu_bytes = (s.experts + s.num_shared) * 4.0 * s.hidden * s.inter, dn_bytes = 0.5 * gu_bytes;
+  const double gu_bytes = gate_up_bytes(s), dn_bytes = 0.5 * gu_bytes;
   FfnPlan best;
   best.ksplit = s.max_ksplit;
   // from 8 rows per expert on the token rows that the gate/up kernel stages slow the weights down
@@ -121,23 +136,39 @@ inline FfnPlan plan_ffn(const FfnShape& s) {
   int n = 0;
   const TileVariant* v = tile_variants(s.split_h, &n);
   for (int i = 0; i < n; ++i) {
-    const double items = total_items(s, v[i].rows);
-    const double gu = tile_cost(items * std::ceil(static_cast<double>(s.inter) / v[i].gate_up_out), s.hidden / 64,
-                                v[i].gate_up_step, 0.9, gu_bytes);
-    double dn;
-    const int ksplit = tile_ksplit(s, items * std::ceil(static_cast<double>(s.hidden) / v[i].down_out), v[i].down_step, dn_bytes, &dn);
+    const TileCost t = tile_costs(s, v[i], gu_bytes);
     FfnPlan p;
     p.item_rows = v[i].rows;
-    p.tile_gate_up = v[i].rows != kItemRows || gu < kMargin * row_gu;   // the other kernels take items of kItemRows
-    p.tile_down = v[i].rows != kItemRows || dn < kMargin * row_dn;
-    p.ksplit = p.tile_down ? ksplit : s.max_ksplit;
-    const double cost = (p.tile_gate_up ? gu : row_gu) + (p.tile_down ? dn : row_dn);
+    p.tile_gate_up = v[i].rows != kItemRows || t.gate_up < kMargin * row_gu;   // the other kernels take items of kItemRows
+    p.tile_down = v[i].rows != kItemRows || t.down < kMargin * row_dn;
+    p.ksplit = p.tile_down ? t.ksplit : s.max_ksplit;
+    const double cost = (p.tile_gate_up ? t.gate_up : row_gu) + (p.tile_down ? t.down : row_dn);
     // larger items leave no choice for either kernel: gate/up, two thirds of the bytes, has to promise it by itself
     // (64 experts, d_m 1408, 46 active of 56 expected: promised 0.94 + 0.80, measured 104 + 52 us against 96 + 52)
-    if (v[i].rows != kItemRows && gu >= kMargin * row_gu) continue;
+    if (v[i].rows != kItemRows && t.gate_up >= kMargin * row_gu) continue;
     if (cost < best_cost * (best.tile_gate_up || best.tile_down ? 1.0 : kMargin)) {
       best_cost = cost;
       best = p;
+    }
+  }
+  return best;
+}
+
+// The persistent kernels whatever the others cost, with `ksplit` slices (0: the best number), for callers whose sums must
+// not depend on the number of rows: with equal slices these kernels add up an output in the same order for every
+// item size.
+inline FfnPlan plan_ffn_tile(const FfnShape& s, int ksplit) {
+  FfnPlan best;
+  best.tile_gate_up = best.tile_down = true;
+  double best_cost = 1e30;
+  int n = 0;
+  const TileVariant* v = tile_variants(s.split_h, &n);
+  for (int i = 0; i < n; ++i) {
+    const TileCost t = tile_costs(s, v[i], gate_up_bytes(s), ksplit);
+    if (t.gate_up + t.down < best_cost) {
+      best_cost = t.gate_up + t.down;
+      best.item_rows = v[i].rows;
+      best.ksplit = t.ksplit;
     }
   }
   return best;

@@ -173,7 +173,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     }
     pbeg = min(slice * per, blocks);
     pnk = min((slice + 1) * per, blocks) - pbeg;
-    pk = (part * 5) % pnk;
+    // Units of 128 bf16 weight rows start where the unit of 256 that covers them would: with the same slices of d_m
+    // the sums then have the same order whatever the item size, which calibration batches in groups rely on.
+    constexpr int kShared = DT == SERE_BF16 ? 256 / BM : 1;
+    pk = (slab / kShared * ksplit + slice) * 5 % pnk;
     pleft = pnk;
   };
   auto issue = [&](int slot) {

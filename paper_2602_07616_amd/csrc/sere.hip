@@ -645,13 +645,14 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   if (pc.status != SERE_OK) return pc.status;
   if (workspace == nullptr) return SERE_ERR_NULL_PTR;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return SERE_ERR_MISALIGNED;
-  int group = std::min(sim_group(*cfg, batch_tokens), num_batches);
-  while (group > 1 && make_sim_layout(*cfg, batch_tokens, group).total > workspace_bytes) --group;
-  const SimLayout l = make_sim_layout(*cfg, batch_tokens, group);
+  const int whole = std::min(sim_group(*cfg, batch_tokens), num_batches);
+  int group = whole;
+  while (group > 1 && make_sim_layout(*cfg, batch_tokens, group, whole).total > workspace_bytes) --group;
+  const SimLayout l = make_sim_layout(*cfg, batch_tokens, group, whole);
   if (workspace_bytes < l.total) return SERE_ERR_WORKSPACE_TOO_SMALL;
 
   const int rest = num_batches % group;
-  const SimLayout last = rest != 0 ? make_sim_layout(*cfg, batch_tokens, rest) : l;
+  const SimLayout last = rest != 0 ? make_sim_layout(*cfg, batch_tokens, rest, whole) : l;
   for (int b = 0; b < num_batches; b += group) {
     const bool whole = b + group <= num_batches;
     similarity_group(*cfg, whole ? l : last, static_cast<const char*>(calib), b, whole ? group : rest, b == 0 || !whole, num_batches, batch_tokens,
@@ -744,7 +745,8 @@ int sere_moe_decode_baseline(const sere_config* cfg, const void* hidden, const v
 
 size_t sere_similarity_workspace_bytes(const sere_config* cfg, int32_t batch_tokens) {
   if (check_config(cfg) != SERE_OK || check_similarity_sizes(*cfg, 1, batch_tokens) != SERE_OK) return 0;
-  return make_sim_layout(*cfg, batch_tokens, sim_group(*cfg, batch_tokens)).total;
+  const int group = sim_group(*cfg, batch_tokens);
+  return make_sim_layout(*cfg, batch_tokens, group, group).total;
 }
 
 int sere_similarity(const sere_config* cfg, const void* calib, int32_t num_batches, int32_t batch_tokens,

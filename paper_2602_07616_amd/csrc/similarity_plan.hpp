@@ -45,23 +45,43 @@ struct SimLayout {
   long long gram_chunk; // ... and their length
 };
 
+inline FfnShape sim_ffn_shape(const sere_config& c, int rows) {
+  FfnShape s{};
+  s.hidden = c.hidden;
+  s.inter = c.inter;
+  s.tokens = rows;
+  s.experts = c.num_experts;
+  s.rows = rows;
+  s.slots_per_expert = rows;
+  s.split_h = wants_split_h(c) != 0;
+  s.max_ksplit = down_ksplit(c);
+  return s;
+}
+
+// The kernels of a group of g batches, of a call whose groups would hold `whole` batches if the workspace had room for
+// them.  What decides the order of a sum follows from `whole`, so that neither the size of the workspace nor a shorter
+// last group changes a batch's outputs: for bf16 layers the persistent kernels and their slices of d_m, for fp32 layers one
+// kernel or the other.  The item size follows the group's own rows.
+// (Not from the layer and the batch size alone, which would free them from the number of batches, too: single batches of
+// layers with few, wide experts want other kernels than large groups.  4 experts, d_h and d_m 4096, one batch of 20 tokens:
+// 113 -> 123 us; 12 experts, d_h and d_m 3072, 8 batches of 16: 257 -> 290.  As it is, two batches of 8 tokens of 8
+// experts, d_h 4096, d_m 14336, lose 468 -> 480 and four gain 531 -> 512 against a choice for every group by itself.)
+inline FfnPlan sim_ffn_plan(const sere_config& c, int n, int g, int whole) {
+  const FfnShape all = sim_ffn_shape(c, n * whole);
+  if (c.dtype == SERE_F32) return plan_ffn_f32(all);
+  if (whole == 1) return plan_ffn(all);
+  return plan_ffn_tile(sim_ffn_shape(c, n * g), plan_ffn_tile(all, 0).ksplit);
+}
+
 // Layout of groups of g batches of n tokens.  A call checks its workspace against its largest group and launches
-// smaller ones in it (the last of a call), so no buffer's room may shrink as g grows, whatever is chosen by g.
-inline SimLayout make_sim_layout(const sere_config& c, int n, int g) {
+// smaller ones in it (the last of a call), so no buffer's room may shrink as g grows, whatever is chosen by g; and what is
+// chosen by `whole` changes nothing about the room, which a caller asks for without naming the number of batches.
+inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) {
   SimLayout l{};
   const size_t M = c.num_experts, R = M * static_cast<size_t>(n) * g;
   l.rows = static_cast<int>(R);
   l.ksplit = down_ksplit(c);
-  FfnShape s{};
-  s.hidden = c.hidden;
-  s.inter = c.inter;
-  s.tokens = n * g;
-  s.experts = M;
-  s.rows = n * g;
-  s.slots_per_expert = n * g;
-  s.split_h = wants_split_h(c) != 0;
-  s.max_ksplit = l.ksplit;
-  l.plan = c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
+  l.plan = sim_ffn_plan(c, n, g, whole);
   l.items = (n * g + l.plan.item_rows - 1) / l.plan.item_rows;
   const size_t W = M * ((static_cast<size_t>(n) * g + kItemRows - 1) / kItemRows);  // room: the shortest items
   size_t o = 0;
@@ -121,7 +141,7 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g) {
 inline int sim_group(const sere_config& c, int n) {
   const size_t weights = static_cast<size_t>(c.num_experts) * 3 * c.hidden * c.inter * (c.dtype == SERE_F32 ? 4 : 2);
   int g = weights <= kSimGroupWeights ? 1 : std::max(1, std::min(kSimGroupMax, kSimGroupRows / n));
-  while (g > 1 && make_sim_layout(c, n, g).total > kSimGroupBytes) --g;
+  while (g > 1 && make_sim_layout(c, n, g, g).total > kSimGroupBytes) --g;
   return g;
 }
 

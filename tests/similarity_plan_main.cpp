@@ -1,5 +1,5 @@
-// Reads "dtype hidden experts inter batch_tokens flags" lines and prints, for groups of 1 batch, 2 batches, ... up to
-// the largest that a workspace is sized for: "total items item_rows tile_gate_up tile_down ksplit gram_splits
+// Reads "dtype hidden experts inter batch_tokens flags batches" lines and prints, for groups of 1 batch, 2 batches, ... up
+// to the largest that a call with so many batches takes: "total items item_rows tile_gate_up tile_down ksplit gram_splits
 // gram_staged item_bytes part_bytes", the last two the room for an array of the work list and for the partial Gram
 // matrices; groups separated by ';'.  Host code only.
 #include <cstdio>
@@ -8,11 +8,12 @@
 
 int main() {
   sere_config c{};
-  int n = 0;
-  while (std::scanf("%d %d %d %d %d %d", &c.dtype, &c.hidden, &c.num_experts, &c.inter, &n, &c.flags) == 6) {
-    const int most = sere::sim_group(c, n);
-    for (int g = 1; g <= most; ++g) {
-      const sere::SimLayout l = sere::make_sim_layout(c, n, g);
+  int n = 0, batches = 0;
+  while (std::scanf("%d %d %d %d %d %d %d", &c.dtype, &c.hidden, &c.num_experts, &c.inter, &n, &c.flags,
+                    &batches) == 7) {
+    const int most = sere::sim_group(c, n), whole = batches < most ? batches : most;
+    for (int g = 1; g <= whole; ++g) {
+      const sere::SimLayout l = sere::make_sim_layout(c, n, g, whole);
       std::printf("%zu %d %d %d %d %d %d %d %zu %zu;", l.total, l.items, l.plan.item_rows, l.plan.tile_gate_up, l.plan.tile_down,
                   l.plan.ksplit, l.gram_splits, l.gram_staged, l.work_off - l.work_expert,
                   l.gram_splits > 0 ? l.gram - l.gram_part : 0);

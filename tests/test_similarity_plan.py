@@ -21,7 +21,7 @@ def layouts(tmp_path_factory):
                    check=True)
 
     def run(cases):
-        out = subprocess.run([exe], input="".join("%d %d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
+        out = subprocess.run([exe], input="".join("%d %d %d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
                              check=True).stdout.split("\n")
         return [[tuple(int(v) for v in g.split()) for g in line.split(";") if g] for line in out if line]
     return run
@@ -31,11 +31,11 @@ def draws(count, seed):
     rng = random.Random(seed)
     log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
     # the sizes at which a last group of 15 batches once needed more than a group of 16, for all metrics
-    cases = [(dtype, 768, M, 64, 7, f) for dtype in (B.SERE_F32, B.SERE_BF16) for M in range(120, 130) for f in METRICS]
+    cases = [(dtype, 768, M, 64, 7, f, 31) for dtype in (B.SERE_F32, B.SERE_BF16) for M in range(120, 130) for f in METRICS]
     for _ in range(count):
         f = rng.choice(METRICS)
         cases.append((rng.choice((B.SERE_F32, B.SERE_BF16)), 64 * log_int(1, 64), log_int(1, 256), 64 * log_int(1, 224),
-                      log_int(4 if f == B.SERE_FLAG_SIM_CKA_LINEAR else 1, 400), f))
+                      log_int(4 if f == B.SERE_FLAG_SIM_CKA_LINEAR else 1, 400), f, rng.choice((1, 2, 3, 7, 31, 31, 31))))
     return cases
 
 
@@ -60,3 +60,19 @@ def test_plans_of_groups_can_be_run(layouts):
             assert (items - 1) * rows < n * g <= items * rows, case
             assert rows == 32 or (tile_gu and tile_dn), case
             assert (ksplit - 1) * -(-blocks // ksplit) < blocks, case
+
+
+def test_the_room_does_not_depend_on_the_number_of_batches(layouts):
+    cases = draws(1500, 14)
+    for case, few, many in zip(cases, layouts(cases), layouts([c[:6] + (64,) for c in cases])):
+        assert [g[0] for g in few] == [g[0] for g in many][:len(few)], case
+
+
+def test_sums_do_not_depend_on_the_group(layouts):
+    """What decides the order of an expert's sums (the kernels, the slices of d_m) is the same for all groups of a call."""
+    cases = draws(3000, 13)
+    items = set()
+    for case, groups in zip(cases, layouts(cases)):
+        assert len({g[3:6] for g in groups}) == 1, case
+        items.add(len({g[2] for g in groups}))
+    assert max(items) > 3      # the item size does follow the group
