@@ -280,8 +280,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (fabsf(low[a][t][r]) < INFINITY) acc[a][t][r] += low[a][t][r];
+          for (int r = 0; r < 4; ++r) {
+            const float sum = acc[a][t][r] + low[a][t][r];
+            acc[a][t][r] = __builtin_amdgcn_fmed3f(sum, sum, acc[a][t][r]);   // acc where the sum is a NaN
+          }
     }
     const int slab = part / ksplit, slice = part % ksplit;
     if (GATEUP) {
