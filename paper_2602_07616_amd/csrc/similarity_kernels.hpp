@@ -473,7 +473,8 @@ __global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restri
     return sum;
   };
   double sum = entry(idx);
-  if (entry(p * M + p) < n - 0.5 || entry(q * M + q) < n - 0.5) {
+  const double pp = entry(p * M + p), qq = entry(q * M + q);   // (all three requested together)
+  if (fmin(pp, qq) < n - 0.5) {
     const double* a = inv_norm + (static_cast<size_t>(p) * g + batch) * n;
     const double* b = inv_norm + (static_cast<size_t>(q) * g + batch) * n;
     for (int i = 0; i < n; ++i)
