@@ -72,9 +72,10 @@ __device__ __forceinline__ void gram_block_of(int index, int nb, int& bp, int& b
 // 4 (l / 16) ... + 3 (the order of k inside the sum is free as long as both operands agree).
 // `chunk` (the split's length) is a multiple of 2 * 16 * kGramSteps (= 64, as L is).  blockIdx.z: batch of
 // the group.
-// Serves the cosine metric, up to 64 experts, and y in slices.  43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us
-// a batch; the fp64 matrix cores reach 69 in a large product).  Neither more workgroups (three for every compute unit instead of one and a half) nor four
-// independent sums between two products of one changed that: it waits for its operands.
+// Serves the cosine metric, y in slices, and the groups for which the staged kernel below is the slower one
+// (gram_staged_pays).  43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us a batch; the fp64 matrix cores reach
+// 69 in a large product).  Neither more workgroups (three for every compute unit instead of one and a half) nor
+// four independent sums between two products of one changed that: it waits for its operands.
 // COSINE: every row of A is divided by its length first (inv_norm[row]; see row_norm_kernel), so the entries
 // are sums over tokens of cosines.
 template <bool COSINE>
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict_
       }
 }
 
-// The same partial Gram matrices (Frobenius metric, more than 64 experts, y in one slice) with the operands
+// The same partial Gram matrices (Frobenius metric, y in one slice, where gram_staged_pays) with the operands
 // staged through LDS: a workgroup takes a triangle of 128 experts, or a square of 64 x 64 between two such
 // triangles, and a range of L, and reads each of its 128 rows once, in whole 128-byte lines that go straight to a
 // ring of kGramRing stages (128 rows x 32 k; 16-byte piece c of a row lies at c ^ (row & 7), so that the reads are
@@ -193,8 +194,8 @@ __global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict_
 // d = 4 (rows modulo 8), nine tiles each; of a square's 4 x 4 tiles row w & 3.  The two halves are added at the end.
 // Bound by the fp64 matrix cores and the conversions between their products: 128 experts, 128 tokens, d_h 2048 take
 // 91 us a batch (4.8 GFLOP of fp64: 53 TFLOP/s; the kernel above: 147 us for 6.4 GFLOP); reading a stage from LDS
-// while the one before it is multiplied changed nothing.  Up to 64 experts the kernel above has one block of 16
-// tiles where the triangle would compute 36; with the cosine metric or y in slices the loads need arithmetic.
+// while the one before it is multiplied changed nothing.  With the cosine metric or y in slices the loads need
+// arithmetic.
 constexpr int kGramRing = 8;
 constexpr int kGramRowsLds = 128;
 constexpr int kGramStageBytes = kGramRowsLds * kRowBytes;

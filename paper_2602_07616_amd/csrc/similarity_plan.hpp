@@ -73,6 +73,21 @@ inline FfnPlan sim_ffn_plan(const sere_config& c, int n, int g, int whole) {
   return plan_ffn_tile(sim_ffn_shape(c, n * g), plan_ffn_tile(all, 0).ksplit);
 }
 
+// Where pair_gram_staged_kernel is the faster one; it needs y in one slice.  `length`: numbers in the outputs of an expert,
+// all batches of a group.  us of the pair stage, kernel of 64 x 64 blocks against staged:
+//  - One triangle, 65 to 128 experts: a workgroup takes a whole compute unit, so short groups lose (length 8192:
+//    25 / 36, 32768: 1.05 times), longer ones gain (49152: 0.88 times, 128 experts: 65536 55 / 48, 262144 0.79 times,
+//    524288 300 / 180).  Up to 64 experts the triangle computes 36 tiles for 16 (102 / 164).
+//  - Beyond, two triangles and two squares take as long as four triangles (129 to 192 experts: 1.4 times), and two with
+//    all four squares 1.08 times.  But a row every multiple of 2 MiB puts the rows that the other kernel reads
+//    together on the same memory channels: 256 experts of length 524288 970 / 790, of 1048576 1890 / 1520 (of 518400
+//    724 / 782, of 557056 770 / 825); 193 experts 826 / 774, 192 still 605 / 637.
+constexpr long long kGramStagedLength = 40960;
+inline bool gram_staged_pays(int experts, long long length) {
+  if (experts <= 128) return experts > kGramBlock && length >= kGramStagedLength;
+  return experts > 192 && length * 4 % (2 << 20) == 0;
+}
+
 // Layout of groups of g batches of n tokens.  A call checks its workspace against its largest group and launches
 // smaller ones in it (the last of a call), so no buffer's room may shrink as g grows, whatever is chosen by g; and what is
 // chosen by `whole` changes nothing about the room, which a caller asks for without naming the number of batches.
@@ -114,21 +129,24 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) 
     }
     const long long L = static_cast<long long>(n) * c.hidden;
     // about three workgroups for every compute unit, 16 .. 256 splits, each a multiple of the Gram kernel's
-    // 64-wide load group
-    const int nb = static_cast<int>((M + kGramBlock - 1) / kGramBlock);
-    // (staged kernel: one workgroup to a compute unit at a time; a single triangle: one even wave of them)
-    l.gram_staged = !in_h && l.ksplit == 1 && M > kGramBlock;
-    const int blocks = l.gram_staged ? gram_triangles(static_cast<int>(M)) + gram_squares(static_cast<int>(M))
-                                     : nb * (nb + 1) / 2;
-    const int wave = l.gram_staged && blocks == 1 ? 256 : 768;
-    const int want = std::min(256, std::max(16, wave / (blocks * g)));
+    // 64-wide load group (staged kernel: one workgroup to a compute unit at a time; a single triangle: one even
+    // wave of them)
+    const auto splits = [&](bool staged) {   // of a group of one batch
+      const int m = static_cast<int>(M), nb = (m + kGramBlock - 1) / kGramBlock;
+      const int blocks = staged ? gram_triangles(m) + gram_squares(m) : nb * (nb + 1) / 2;
+      return (staged && blocks == 1 ? 256 : 768) / blocks;
+    };
+    l.gram_staged = !in_h && l.plan.ksplit == 1 && gram_staged_pays(static_cast<int>(M), g * L);
+    const int want = std::min(256, std::max(16, splits(l.gram_staged) / g));
     long long chunk = (L + want - 1) / want;
     chunk = std::max<long long>(256, (chunk + 63) / 64 * 64);
     l.gram_chunk = chunk;
     l.gram_splits = static_cast<int>((L + chunk - 1) / chunk);
-    // Room for g * gram_splits partial matrices of this group and of every smaller one: these are at most g * want
-    // and at most g * L / 256, but rounding the chunk may give a group of g - 1 batches more of them than one of g.
-    const long long room = std::min(g * ((L + 255) / 256), std::max<long long>(16 * g, std::min(256 * g, wave / blocks)));
+    // Room for g * gram_splits partial matrices of this group and of every smaller one, by either kernel: these are at
+    // most g * want and at most g * L / 256, but rounding the chunk may give a group of g - 1 batches more of them than
+    // one of g.
+    const int most = std::min(256 * g, std::max(splits(false), splits(true)));
+    const long long room = std::min(g * ((L + 255) / 256), std::max<long long>(16 * g, most));
     l.gram_part = take(static_cast<size_t>(room) * gram_part_stride(static_cast<int>(M)) * sizeof(double));
     l.gram = take(static_cast<size_t>(g) * kGramGroups * M * M * sizeof(double));
     if (in_h) o = std::max(end, o);

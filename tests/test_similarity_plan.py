@@ -76,3 +76,25 @@ def test_sums_do_not_depend_on_the_group(layouts):
         assert len({g[3:6] for g in groups}) == 1, case
         items.add(len({g[2] for g in groups}))
     assert max(items) > 3      # the item size does follow the group
+
+
+def test_choice_of_the_gram_kernel(layouts):
+    """Staged: Frobenius metric, outputs in one slice (by the slices that the plan takes, not by how many the layer's width
+    would allow), and sizes at which it was measured to be the faster one."""
+    cases = [c for c in draws(6000, 15)]
+    wide = 0
+    for case, groups in zip(cases, layouts(cases)):
+        M, length = case[2], case[1] * case[4]
+        for g, layout in enumerate(groups, 1):
+            pays = (64 < M <= 128 and g * length >= 40960) or (M > 192 and g * length % 524288 == 0)
+            assert layout[7] == (case[5] == 0 and layout[5] == 1 and pays), (case, g)
+            wide += layout[7] and case[0] == B.SERE_BF16 and case[3] > 2048
+    assert wide > 50
+
+
+def test_gpu_cases_of_the_gram_kernels_reach_them(layouts):
+    from . import test_gpu_pair_gram as gpu
+    for cases, staged in ((gpu.BLOCKS, 0), (gpu.STAGED, 1)):
+        plans = layouts([(c[4], c[1], c[0], (*c, 64)[5], c[2], 0, c[3]) for c in cases])
+        for case, groups in zip(cases, plans):
+            assert groups[-1][7] == staged, case
