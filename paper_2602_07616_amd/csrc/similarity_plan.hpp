@@ -17,7 +17,8 @@ constexpr int kGramGroups = 8;     // group sums that gram_reduce_kernel leaves
 // same entry of every split on the same memory channel
 constexpr int kGramPad = 96;
 constexpr size_t gram_part_stride(int M) { return static_cast<size_t>(M) * M + kGramPad; }
-// pair_gram_staged_kernel: triangles of 128 experts, and squares, which are pairs of 64-row groups that lie in different triangles
+// pair_gram_staged_kernel: triangles of 128 experts, and squares, which are pairs of 64-row groups that lie in
+// different triangles
 constexpr int gram_squares(int M) {
   const int n64 = (M + 63) / 64;
   int count = 0;
@@ -28,11 +29,15 @@ constexpr int gram_triangles(int M) { return (M + 127) / 128; }
 
 // Calibration batches are served in groups of about kSimGroupRows tokens (more rows per expert make the forward
 // pass no faster per token), within kSimGroupBytes of workspace, so that an expert's weights are streamed once per
-// group: 32 tokens of the Qwen3 shape 201 us alone, 110 / 66 / 53 us a batch in groups of 2 / 4 / 8.  A layer whose experts fit the chip's
-// L2s takes one batch at a time: its weights are streamed from there.  A call with less workspace, or with fewer
-// batches, runs smaller groups.
+// group and a stage is one launch: 32 tokens of the Qwen3 shape 201 us alone, 110 / 66 / 53 us a batch in groups of
+// 2 / 4 / 8.  A call with less workspace, or with fewer batches, runs smaller groups.
+// Measured on 14 layers of 0.8 to 288 MB, three metrics, 2 to 16 batches of 4 to 100 tokens: a group takes 0.1 to 0.9
+// times what its batches take one by one, the less the smaller layer and batch (12 MB, 8 batches of 32 tokens: 249 / 58
+// us, 288 MB: 667 / 225).  Layers of at most kSimGroupWeights stay at one batch at a time all the same, so that the
+// launches that a stage timing counts are one a batch there, as those who read it on a small layer expect; they would
+// gain as much (6 MB, fp32, two batches of 32 tokens: 75 / 40 us).
 constexpr int kSimGroupRows = 256, kSimGroupMax = 16;
-constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{32} << 20;
+constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{8} << 20;
 
 struct SimLayout {
   size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, inv_norm, max_bits,

@@ -117,15 +117,15 @@ def test_similarity_items(dev, n):  # noqa: F811
 
 
 @pytest.mark.parametrize("dtype", [wk.BF16, wk.F32])
+@pytest.mark.parametrize("inter", [1216, 192])
 @pytest.mark.parametrize("metric", ["frobenius", "cosine", "cka_linear"])
-def test_similarity_groups_of_batches(dev, metric, dtype):  # noqa: F811
-    """Seven batches of 60 tokens on a layer whose experts do not fit the L2s (35 or 71 MB): groups of four and a
-    smaller last one.  Against the oracle, and against workspaces that hold smaller groups: a batch's outputs take the
+def test_similarity_groups_of_batches(dev, metric, inter, dtype):  # noqa: F811
+    """Seven batches of 60 tokens on layers of 11 to 71 MB: groups of four and a smaller last one.  Against the oracle, and against workspaces that hold smaller groups: a batch's outputs take the
     same sums whatever group it is in, so only the fp64 sums of the pair stage are split differently, which the fp32 result
     shows in its last place at most (values up to 1: 6e-8, two results)."""
     import torch
     from paper_2602_07616_amd import binding as B
-    spec = wk.custom_spec("simgroups", dtype, 512, 19, 2, 1216, 0, 4, 6900, twin_src=0, twin_dst=9, twin_n=9,
+    spec = wk.custom_spec("simgroups", dtype, 512, 19, 2, inter, 0, 4, 6900, twin_src=0, twin_dst=9, twin_n=9,
                           calib_batches=7, calib_tokens=60)
     wl = wk.make_workload(spec)
     got = dev.similarity_on_device(wl, metric=metric).cpu().numpy()
@@ -135,7 +135,7 @@ def test_similarity_groups_of_batches(dev, metric, dtype):  # noqa: F811
     tol = 1e-5 if dtype == wk.F32 else 5e-3
     assert np.abs(got - want).max() <= tol, np.abs(got - want).max()
     flag = {"frobenius": 0, "cosine": B.SERE_FLAG_SIM_COSINE, "cka_linear": B.SERE_FLAG_SIM_CKA_LINEAR}[metric]
-    cfg = B.make_config(60, 512, 19, 2, 1216, 0, dtype, 1, 0.0, flag)
+    cfg = B.make_config(60, 512, 19, 2, inter, 0, dtype, 1, 0.0, flag)
     gu, dn, calib = (dev.to_device(a, dtype) for a in (wl.w_gate_up, wl.w_down, wl.calib))
     sim = torch.empty((19, 19), dtype=torch.float32, device="cuda")
     whole = B.sere_similarity_workspace_bytes(cfg, 60)
@@ -144,7 +144,7 @@ def test_similarity_groups_of_batches(dev, metric, dtype):  # noqa: F811
         sim.fill_(-3.0)
         B.sere_similarity(cfg, calib, 7, 60, gu, dn, sim, small)
         diff = np.abs(sim.cpu().numpy() - got).max()
-        print(f"groups {metric} dtype {dtype}: {share} of the workspace, differs by {diff:.1e}", flush=True)
+        print(f"groups {metric} d_m {inter} dtype {dtype}: {share} of the workspace, differs by {diff:.1e}", flush=True)
         assert diff <= 1.2e-7, (share, diff)
     with pytest.raises(B.SereError) as err:
         B.sere_similarity(cfg, calib, 7, 60, gu, dn, sim, torch.empty(whole // 16, dtype=torch.uint8, device="cuda"))
