@@ -1,5 +1,5 @@
-// Host side: which FFN kernels serve a bf16 call, with which work item size and how many slices of
-// the down projection's contraction.  A function of the sizes alone.
+// Host side: which FFN kernels serve a call (bf16: plan_ffn, fp32: plan_ffn_f32), with which work item size and how
+// many slices of the down projection's contraction.  A function of the sizes alone.
 #pragma once
 
 #include <algorithm>
@@ -47,8 +47,9 @@ struct TileVariant {
 
 // The constants of this file are fitted to measured launches of 300 layers (those of workloads.py at 4 to 4096
 // tokens and random ones: d_h 256 to 4096, d_m 128 to 14336, 2 to 160 experts, 1 to 4000 tokens), every item size
-// and both kinds of kernels timed on each.  What the rule picks takes 2.5 % longer than the best choice on average,
-// and 17 % less than one rule for all (items of 32 to 256 rows by rows per expert) with workgroup-staged kernels.
+// and both kinds of kernels timed on each.  Over these layers what plan_ffn picks, with all its rules, takes 2.6 %
+// longer than the best choice on average, 17 % less than the decode kernels alone, and 15 % less than one rule for
+// all (items of 32 to 256 rows by rows per expert) with the workgroup-staged kernels of earlier.
 inline const TileVariant* tile_variants(bool split_h, int* count) {
   // a step of a unit of 256 weight rows: 0.74 us and 2.6 ns for every token row; of 128 rows measured on its own
   static const TileVariant plain[] = {{32, 128, 256, 0.82, 0.82},  {64, 128, 256, 0.91, 0.91}, {96, 128, 256, 0.99, 0.99},
@@ -144,7 +145,8 @@ inline FfnPlan plan_ffn(const FfnShape& s) {
     p.ksplit = p.tile_down ? t.ksplit : s.max_ksplit;
     const double cost = (p.tile_gate_up ? t.gate_up : row_gu) + (p.tile_down ? t.down : row_dn);
     // larger items leave no choice for either kernel: gate/up, two thirds of the bytes, has to promise it by itself
-    // (64 experts, d_m 1408, 46 active of 56 expected: promised 0.94 + 0.80, measured 104 + 52 us against 96 + 52)
+    // (64 experts, d_m 1408, 46 active of 56 expected: promised 0.94 + 0.80, measured 104 + 52 us against 96 + 52; of
+    // the 300 layers above four get another plan by this, 9 % slower to 3 % faster: 0.03 % on average)
     if (v[i].rows != kItemRows && t.gate_up >= kMargin * row_gu) continue;
     if (cost < best_cost * (best.tile_gate_up || best.tile_down ? 1.0 : kMargin)) {
       best_cost = cost;
@@ -191,6 +193,26 @@ inline FfnPlan plan_ffn_f32(const FfnShape& s) {
   FfnPlan p;
   p.tile_gate_up = p.tile_down = s.tokens > 8 || tile < rows;
   return p;
+}
+
+// Work item size and kernels of a call whose experts own the slots of T tokens.  Which experts those are is
+// known on the device only; here it is what independent tokens give: an expert stays if some token has it among
+// its top S (its top K without re-routing or with a threshold).
+inline FfnPlan plan_decode(const sere_config& c, bool reroute) {
+  const double T = c.num_tokens, M = c.num_experts, K = c.top_k;
+  const double kept = reroute && !(c.threshold > 0.0f) ? c.select_top_k : K;
+  FfnShape s{};
+  s.hidden = c.hidden;
+  s.inter = c.inter;
+  s.num_shared = c.num_shared;
+  s.tokens = c.num_tokens;
+  s.experts = std::max(1.0, M * (1.0 - std::pow(1.0 - kept / M, T)));
+  s.rows = T * K / s.experts;
+  s.slots_per_expert = T * K / M;
+  s.spread = K < M ? 1.5 * std::sqrt(s.rows) : 0.0;  // tokens of a batch resemble each other: wider than by chance
+  s.split_h = wants_split_h(c) != 0;
+  s.max_ksplit = down_ksplit(c);
+  return c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
 }
 
 }  // namespace sere

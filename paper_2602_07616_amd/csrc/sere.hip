@@ -343,26 +343,6 @@ static void launch_combine(const sere_config& c, const Layout& l, const Pointers
 #undef SERE_LAUNCH_COMBINE
 }
 
-// Work item size and kernels of a call whose experts own the slots of T tokens.  Which experts those are is
-// known on the device only; here it is what independent tokens give: an expert stays if some token has it among
-// its top S (its top K without re-routing or with a threshold).
-static FfnPlan plan_decode(const sere_config& c, int ksplit, bool reroute) {
-  const double T = c.num_tokens, M = c.num_experts, K = c.top_k;
-  const double kept = reroute && !(c.threshold > 0.0f) ? c.select_top_k : K;
-  FfnShape s{};
-  s.hidden = c.hidden;
-  s.inter = c.inter;
-  s.num_shared = c.num_shared;
-  s.tokens = c.num_tokens;
-  s.experts = std::max(1.0, M * (1.0 - std::pow(1.0 - kept / M, T)));
-  s.rows = T * K / s.experts;
-  s.slots_per_expert = T * K / M;
-  s.spread = K < M ? 1.5 * std::sqrt(s.rows) : 0.0;  // tokens of a batch resemble each other: wider than by chance
-  s.split_h = wants_split_h(c) != 0;
-  s.max_ksplit = ksplit;
-  return c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
-}
-
 template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO = false>
 static void launch_tile_as(const FfnArgs& f, hipStream_t s) {
   launch_stage(GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, s, ffn_tile<DT, GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
@@ -479,7 +459,7 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   if (st != SERE_OK) return st;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const FfnPlan plan = plan_decode(*cfg, l.ksplit, reroute);
+  const FfnPlan plan = plan_decode(*cfg, reroute);
   Pointers p = bind(*cfg, l, workspace, dbg, true, plan.item_rows);
   p.route.sim = sim;
   p.route.reroute = reroute ? 1 : 0;

@@ -1,17 +1,28 @@
-// Reads "hidden inter shared tokens experts rows spread slots split max_ksplit" lines and prints the plan of each:
-// "item_rows tile_gate_up tile_down ksplit"; with an argument the plan of an fp32 layer.  Host code only.
+// Prints the plan of every input line, "item_rows tile_gate_up tile_down ksplit".  Lines without an argument, or with "f32" (an
+// fp32 layer): "hidden inter shared tokens experts rows spread slots split max_ksplit"; with "call":
+// "dtype tokens hidden experts top_k inter shared S rho reroute", a call of the library.  Host code only.
 #include <cstdio>
+#include <cstring>
 
 #include "../paper_2602_07616_amd/csrc/ffn_plan.hpp"
 
-int main(int argc, char**) {
+static void print(const sere::FfnPlan& p) { std::printf("%d %d %d %d\n", p.item_rows, p.tile_gate_up, p.tile_down, p.ksplit); }
+
+int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "call") == 0) {
+    sere_config c{};
+    int reroute = 0;
+    while (std::scanf("%d %d %d %d %d %d %d %d %f %d", &c.dtype, &c.num_tokens, &c.hidden, &c.num_experts, &c.top_k, &c.inter,
+                      &c.num_shared, &c.select_top_k, &c.threshold, &reroute) == 10)
+      print(sere::plan_decode(c, reroute != 0));
+    return 0;
+  }
   sere::FfnShape s{};
   int split = 0;
   while (std::scanf("%d %d %d %d %lf %lf %lf %lf %d %d", &s.hidden, &s.inter, &s.num_shared, &s.tokens, &s.experts, &s.rows,
                     &s.spread, &s.slots_per_expert, &split, &s.max_ksplit) == 10) {
     s.split_h = split != 0;
-    const sere::FfnPlan p = argc > 1 ? sere::plan_ffn_f32(s) : sere::plan_ffn(s);
-    std::printf("%d %d %d %d\n", p.item_rows, p.tile_gate_up, p.tile_down, p.ksplit);
+    print(argc > 1 ? sere::plan_ffn_f32(s) : sere::plan_ffn(s));
   }
   return 0;
 }

@@ -7,6 +7,9 @@ import subprocess
 
 import pytest
 
+from paper_2602_07616_amd import binding as B, workloads as wk
+from . import test_gpu_ffn_tile as gpu
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -16,7 +19,7 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "plan_main.cpp"), "-o", exe], check=True)
 
     def run(cases, *args):
-        text = "".join("%d %d %d %d %r %r %r %r %d %d\n" % c for c in cases)
+        text = "".join(" ".join(map(str, c)) + "\n" for c in cases)
         out = subprocess.run([exe, *args], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
         return [tuple(int(v) for v in line.split()) for line in out if line]
     return run
@@ -63,3 +66,41 @@ def test_fp32_plans(plans):
     for layer, (rows, tile_gu, tile_dn, ksplit) in zip(layers, plans(cases, "f32")):
         assert (rows, ksplit) == (32, 1) and tile_gu == tile_dn, layer
         assert tile_gu or layer[0] <= 8, layer
+
+
+def call(dtype, T, dh, M, K, dm, sh, S, rho=0.0):
+    return (dtype, T, dh, M, K, dm, sh, S, rho, 1)
+
+
+def test_gpu_cases_get_the_plans_they_are_there_for(plans):
+    for S in (lambda K: 1, lambda K: K):         # both settings that the GPU test runs
+        got = plans([call(B.SERE_BF16, *c, S(c[3])) for c in gpu.CASES], "call")
+        assert dict(zip(gpu.CASES, got)) == gpu.CASES
+    got = plans([call(B.SERE_F32, *c, 1, 0.3) for c in gpu.F32_CASES], "call")
+    assert [g[1:3] for g in got] == [(0, 0), (0, 0)] + [(1, 1)] * 5
+
+
+def test_gpu_cases_reach_every_kernel_of_a_plan(plans):
+    """Over a draw of all accepted layers no plan launches a kernel that the GPU cases (and the Mixtral-shaped layer of the
+    parity tests: gate/up by the decode kernels next to the persistent down kernel) do not."""
+    def kernels(inter, plan):
+        rows, tile_gu, tile_dn, _ = plan
+        split = inter >= 4096
+        return {("gate_up", rows if tile_gu else 0), ("down", rows if tile_dn else 0, split)}
+    spec = wk.SPECS["mixtral_b64"]
+    mixtral = plans([call(spec.dtype, spec.tokens, spec.hidden, spec.experts, spec.top_k, spec.inter, spec.shared, 1)], "call")[0]
+    assert mixtral == (32, 0, 1, 2)
+    tested = kernels(spec.inter, mixtral).union(*(kernels(c[4], p) for c, p in gpu.CASES.items()))
+    rng = random.Random(6)
+    log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    cases = []
+    for _ in range(20000):
+        M = log_int(1, 256)
+        K = rng.randint(1, min(M, 12))
+        cases.append(call(B.SERE_BF16, log_int(1, 65536), 64 * log_int(1, 256), M, K, 64 * log_int(1, 512),
+                          rng.choice([0, 0, 1, 4]), rng.randint(1, K), rng.choice([0.0, 0.3])))
+    reached = set()
+    for c, p in zip(cases, plans(cases, "call")):
+        reached |= kernels(c[5], p)
+    assert reached - tested <= {("down", 0, False), ("down", 0, True)}    # the decode kernels, which most other tests run
+    assert {("gate_up", r) for r in (32, 64, 96, 128, 160, 192, 256)} <= reached

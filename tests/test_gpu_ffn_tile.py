@@ -1,7 +1,9 @@
 """The persistent FFN kernels (csrc/ffn_tile.hpp) against the oracle, at sizes where they can go
-wrong: every work item size the host chooses, rows per expert around multiples of a 16-row tile and
+wrong: every kernel that a plan can launch, rows per expert around multiples of a 16-row tile and
 of the item size, d_h and d_m that end inside a unit (64 mod 128, 64 mod 256), shared experts, two
-slices of d_m, both planes of h.  Tolerances are those of the other bf16 parity tests."""
+slices of d_m, both planes of h.  Tolerances are those of the other bf16 parity tests.  The plan that a case
+is there for stands beside it; tests/test_ffn_plan.py checks on the CPU that the host's rule gives that plan, and that
+the cases reach every kernel."""
 import numpy as np
 import pytest
 
@@ -12,21 +14,25 @@ from .test_gpu_parity import check_output, check_routing, dev, pairs_with_counts
 
 pytestmark = pytest.mark.gpu
 
-CASES = [
-    # T, d_h, M, K, d_m, shared     item rows chosen (d_m >= 4096: both planes)
-    (33, 320, 2, 2, 1472, 1),     # 32 (gate/up; down by the other kernels)
-    (230, 704, 33, 4, 704, 1),    # 64
-    (230, 320, 17, 4, 2112, 1),   # 64, two slices of d_m offered
-    (500, 320, 33, 4, 704, 1),    # 96
-    (777, 704, 33, 4, 704, 0),    # 128
-    (1100, 320, 33, 4, 2112, 1),  # 160
-    (330, 320, 17, 4, 704, 0),    # 192
-    (500, 320, 5, 4, 1472, 0),    # 256
-    (33, 320, 2, 2, 4160, 0),     # 32, both planes
-    (230, 320, 2, 2, 4160, 1),    # 128, both planes
-    (1600, 320, 5, 4, 4160, 1),   # 128, both planes, one slice
-    (700, 64, 4, 4, 64, 0),       # a single k step per unit, every expert sees every token
-]
+# (T, d_h, M, K, d_m, shared): (item rows, gate/up and down by the persistent kernels, slices of d_m); d_m >= 4096: both planes
+CASES = {
+    (33, 320, 2, 2, 1472, 1): (32, 1, 0, 1),     # down by the other kernels
+    (500, 1024, 42, 2, 320, 1): (32, 1, 1, 1),
+    (230, 704, 33, 4, 704, 1): (64, 1, 1, 1),
+    (230, 320, 17, 4, 2112, 1): (64, 1, 1, 2),
+    (500, 320, 33, 4, 704, 1): (96, 1, 1, 1),
+    (777, 704, 33, 4, 704, 0): (128, 1, 1, 1),
+    (1100, 320, 33, 4, 2112, 1): (160, 1, 1, 2),
+    (330, 320, 17, 4, 704, 0): (192, 1, 1, 1),
+    (500, 320, 5, 4, 1472, 0): (256, 1, 1, 1),
+    (33, 320, 2, 2, 4160, 0): (32, 1, 0, 3),
+    (300, 512, 23, 1, 4160, 1): (32, 1, 1, 3),
+    (230, 320, 26, 4, 4160, 0): (64, 1, 1, 3),
+    (230, 320, 2, 2, 4160, 1): (128, 1, 1, 3),
+    (1600, 320, 5, 4, 4160, 1): (128, 1, 1, 1),  # one slice
+    (700, 64, 4, 4, 64, 0): (32, 1, 0, 1),       # a single k step per gate/up unit, every expert sees every token
+    (1200, 64, 226, 1, 64, 1): (192, 1, 1, 1),   # a single k step per unit of both kernels
+}
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c))
