@@ -5,8 +5,8 @@
 // from HBM at about 3 us of latency under load, so 27 GB/s per compute unit (7 TB/s for the chip)
 // needs some 80 KB on their way at all times, next to the token rows, which come from L2.  Loads
 // into registers cannot hold that; the 160 KB of LDS can: global_load_lds writes a stage of weight
-// and token rows straight into a ring of three or four stages (36 to 52 KB each), nothing passes
-// through registers until the matrix cores read it.
+// and token rows straight into a ring of three or four stages (36 to 52 KB each; fp32: eight of
+// 20 KB), nothing passes through registers until the matrix cores read it.
 //
 //  - A unit of work is BM weight rows x all token rows of a work item (at most BN) over the whole
 //    contraction, 128 bytes of every row a step.  256 workgroups, one per compute unit, walk their units without a gap: the ring

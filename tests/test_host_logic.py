@@ -1,6 +1,6 @@
-"""CPU-only checks of two index rules that the kernels rely on, written out again in Python from
-their descriptions (the device code is not run here): the XCD-aware numbering of the wide FFN
-kernels' workgroups must be a one-to-one map onto the (item, part) pairs, and the cut of a long
+"""CPU-only checks of rules that the kernels rely on, written out again in Python from
+their descriptions (the device code is not run here): the XCD-aware numbering of the persistent FFN
+kernels' units must give every unit of (item, part) to one workgroup, and the cut of a long
 expert into equal work items must give positive, tile-sized items that add up to the expert's rows."""
 import glob
 import os
@@ -8,27 +8,28 @@ import random
 import re
 
 
-def xcd_virtual_id(wg: int, total: int, xcds: int = 8) -> int:
-    """Workgroups go to the XCDs round-robin by linear id; XCD x gets the contiguous range of
-    virtual ids that starts after the ranges of the XCDs before it."""
-    x, q, r = wg % xcds, total // xcds, total % xcds
-    return x * q + min(x, r) + wg // xcds
+def units_of(group: int, total: int, groups: int = 256, xcds: int = 8):
+    """Workgroups go to the XCDs round-robin; each XCD has a contiguous range of the units, which its workgroups take in
+    turn."""
+    x, q, r = group % xcds, total // xcds, total % xcds
+    first = x * q + min(x, r)
+    return list(range(first + group // xcds, first + q + (1 if x < r else 0), groups // xcds))
 
 
-def test_xcd_numbering_is_a_bijection_and_keeps_an_item_on_one_xcd():
+def test_every_unit_has_one_workgroup_and_an_item_stays_on_one_xcd():
     rng = random.Random(7)
     for _ in range(300):
         items, parts = rng.randint(1, 700), rng.choice([1, 2, 3, 6, 8, 11, 12, 16, 24])
         total = items * parts
-        seen = [xcd_virtual_id(w, total) for w in range(total)]
+        owner, seen = {}, []
+        for g in range(256):
+            units = units_of(g, total)
+            seen += units
+            for u in units:
+                owner.setdefault(u // parts, set()).add(g % 8)
         assert sorted(seen) == list(range(total))
-        # consecutive virtual ids of one XCD are consecutive: an item's parts meet on one XCD
-        # except where an XCD's range ends inside an item (at most 7 items in all)
-        owner = {}
-        for w, v in enumerate(seen):
-            owner.setdefault(v // parts, set()).add(w % 8)
-        split = sum(1 for xs in owner.values() if len(xs) > 1)
-        assert split <= 7, (items, parts, split)
+        # an item's parts meet on one XCD except where an XCD's range ends inside an item (at most 7 items in all)
+        assert sum(1 for xs in owner.values() if len(xs) > 1) <= 7, (items, parts)
 
 
 def cut_expert(rows: int, item_rows: int):
@@ -42,7 +43,7 @@ def cut_expert(rows: int, item_rows: int):
 
 
 def test_long_experts_are_cut_into_positive_tile_sized_items():
-    for item_rows in (32, 64, 128, 256):
+    for item_rows in (32, 64, 96, 128, 160, 192, 256):
         for rows in range(1, 4 * item_rows + 40):
             items = cut_expert(rows, item_rows)
             assert sum(items) == rows
