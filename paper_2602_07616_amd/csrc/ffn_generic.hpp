@@ -208,8 +208,8 @@ __global__ __launch_bounds__(256) void combine_columns_kernel(CombineArgs p) {
 
 // The same for batches of more than kCombineColumns / d_h tokens: a thread owns four consecutive columns of a token
 // (128-bit loads of y), the threads of the launch are numbered along (token, column), so that ragged d_h leaves no
-// lane idle.  Bound by y, which is read once: 777 tokens, d_h 2880, 4 + 1 experts 29 -> 10 us, 2048 tokens, d_h
-// 2048, 8 experts 33 -> 26 us against the kernel above.  On small batches it is the slower one (one token, d_h
+// lane idle.  Bound by y, which is read once: 777 tokens, d_h 2880, 4 + 1 experts 28 -> 10 us, 2048 tokens, d_h
+// 2048, 8 experts 30 -> 22 us against the kernel above.  On small batches it is the slower one (one token, d_h
 // 2048: 29.6 -> 31.5 us for the whole step, 64 tokens 153.4 -> 154.4, also with scalar positions and with
 // workgroups of one wavefront).  grid ceil(T * d_h / 1024), 256 threads.
 constexpr int kCombineColumns = 128 * 2048;

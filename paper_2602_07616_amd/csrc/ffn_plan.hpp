@@ -181,7 +181,7 @@ inline FfnPlan plan_ffn_tile(const FfnShape& s, int ksplit) {
 // would gain nothing (measured with 256 x 64 units: 54 + 38 -> 93 + 65 us at 96 tokens of a 1024-wide layer).  The
 // vector-ALU kernels serve 8 rows in one pass and start faster: they keep batches of at most 8 tokens whose
 // contractions are long and whose experts are few (one token, d_h 1472: 27 against 37 us; 8 tokens, d_h 256: 24
-// against 14 us; 96 tokens, d_h 1024: 264 against 108 us).  Both sides fitted to 45 measured layers.
+// against 14 us; 96 tokens, d_h 1024: 260 against 103 us).  Both sides fitted to 45 measured layers.
 constexpr int kTileF32Rows = 128;
 inline FfnPlan plan_ffn_f32(const FfnShape& s) {
   const double experts = s.experts + s.num_shared;

@@ -9,9 +9,9 @@
 // 20 KB), nothing passes through registers until the matrix cores read it.
 //
 //  - A unit of work is BM weight rows x all token rows of a work item (at most BN) over the whole
-//    contraction, 128 bytes of every row a step.  256 workgroups, one per compute unit, walk their units without a gap: the ring
-//    is a single sequence of (unit, 64-wide k step), so the next unit's loads are in flight while
-//    the last one is finished and stored.
+//    contraction, 128 bytes of every row a step.  256 workgroups, one per compute unit, walk their units
+//    without a gap: the ring is a single sequence of (unit, 64-wide k step), so the next unit's loads are in
+//    flight while the last one is finished and stored.
 //  - A row of a stage is 128 bytes, eight 16-byte pieces; piece c of row r lies at position
 //    c ^ (r & 7).  The loads put it there by having each lane fetch the piece that belongs at its
 //    place, still eight whole 128-byte lines per instruction, and a matrix operand (16 rows x 16
@@ -19,20 +19,21 @@
 //  - Eight wavefronts share a stage as 8 / WN x WN: 64 (or 32) weight rows and every WN-th token
 //    tile each.  While the second half of a stage is multiplied the first half of the next one is read
 //    from LDS, so that reads and products overlap inside a wavefront (gate/up at 2048 tokens of
-//    the Qwen3 shape: 165 -> 151 us).
+//    the Qwen3 shape, one launch over and over: 165 -> 151 us).
 //  - Workgroups are handed to the 8 XCDs round-robin; each XCD walks a contiguous range of units,
-//    so the parts of one item run side by side and share its token rows in one L2.  Every part
-//    starts at another k step (not the same offset of every row at once, that is, not the same
-//    memory channels: 115 -> 107 us at 128 tokens).
+//    so the parts of one item run side by side and share its token rows in one L2.  Every part of
+//    256 weight rows starts at another k step (not the same offset of every row at once, that is, not
+//    the same memory channels: 115 -> 107 us at 128 tokens).
 //
-// Measured on the Qwen3 shape (d_h 2048, d_m 768, 128 experts), us per launch, gate/up + down,
-// against the kernels with eight wavefronts that staged token rows through registers:
-//   tokens   128: 113 + 60 -> 106 + 59     512: 140 + 82 -> 129 + 75    1024: 164 + 97 -> 136 + 85
-//           2048: 233 + 128 -> 151 + 111   3072: 260 + 155 -> 223 + 143   4096: 392 + 209 -> 273 + 179
-// fp32 layers against the vector-ALU kernels: 154 + 110 -> 66 + 42 us at 96 tokens (d_h 1024, d_m 704, 32 experts),
-// 182 + 130 -> 35 + 18 at 180 tokens (d_h 1024, d_m 192, 15 experts); relative error of the layer 1.8e-7 -> 1.4e-7.
-// Not faster: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens); the same
-// first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
+// Measured on the Qwen3 shape (d_h 2048, d_m 768, 128 experts), us per launch, gate/up + down, within steps on four
+// copies of the weights in turn, against the kernels with eight wavefronts that staged token rows through registers,
+// both on one card that has been busy for some 20 ms (from idle the first steps take a tenth longer):
+//   tokens   128: 111 + 60 -> 106 + 59     512: 140 + 81 -> 128 + 76    1024: 153 + 94 -> 136 + 86
+//           2048: 212 + 119 -> 155 + 112   3072: 242 + 145 -> 223 + 145   4096: 371 + 198 -> 290 + 186
+// fp32 layers against the vector-ALU kernels: 150 + 111 -> 64 + 39 us at 96 tokens (d_h 1024, d_m 704, 32 experts),
+// 67 + 49 -> 33 + 11 at 180 tokens (d_h 1024, d_m 192, 15 experts); relative error of the layer 1.8e-7 -> 1.4e-7.
+// Not faster, one launch over and over: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens);
+// the same first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
 #pragma once
 
 #include "common.hpp"

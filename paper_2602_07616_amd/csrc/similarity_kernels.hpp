@@ -9,7 +9,7 @@
 // averaged.
 //
 // Calibration batches are taken in groups of g: an expert's weights are streamed once for the g * n
-// tokens of a group (a batch of 32 tokens of the Qwen3 shape: forward pass 201 us alone, 66 us in a
+// tokens of a group (a batch of 32 tokens of the Qwen3 shape: forward pass 200 us alone, 66 us in a
 // group of four), and every kernel of the pair stage serves the whole group in one
 // launch.  Rows of y: expert-major, then batch, then token; V_e of a batch is n * d_h consecutive
 // numbers, and the same batch of the next expert lies g * n * d_h further.

@@ -29,7 +29,7 @@ constexpr int gram_triangles(int M) { return (M + 127) / 128; }
 
 // Calibration batches are served in groups of about kSimGroupRows tokens (more rows per expert make the forward
 // pass no faster per token), within kSimGroupBytes of workspace, so that an expert's weights are streamed once per
-// group and a stage is one launch: 32 tokens of the Qwen3 shape 201 us alone, 110 / 66 / 53 us a batch in groups of
+// group and a stage is one launch: 32 tokens of the Qwen3 shape 200 us alone, 110 / 66 / 50 us a batch in groups of
 // 2 / 4 / 8.  A call with less workspace, or with fewer batches, runs smaller groups.
 // Measured on 14 layers of 0.8 to 288 MB, three metrics, 2 to 16 batches of 4 to 100 tokens: a group takes 0.1 to 0.9
 // times what its batches take one by one, the less the smaller layer and batch (12 MB, 8 batches of 32 tokens: 249 / 58
