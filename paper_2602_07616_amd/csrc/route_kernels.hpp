@@ -760,9 +760,10 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
 // ---------------------------------------------------------------------------
 // The batch-wide step shared by many workgroups (batches of thousands of slots; top-K and re-routing of the
 // Qwen3 shape, us a step: 1024 tokens 27 -> 12, 2048 47 -> 14, 4096 89 -> 18).  Where a slot goes depends on its
-// expert and on whether it is a primary slot (k < S) only, so two counts per expert and chunk of tokens are all that workgroups have to tell each other: the launch before this one writes
-// them (chunk_hist), and every workgroup here derives the mask, the map, the new counts, the offsets
-// and its own chunk's starting positions from them, then regroups its own slots.
+// expert and on whether it is a primary slot (k < S) only, so two counts per expert and chunk of tokens are
+// all that workgroups have to tell each other: the launch before this one writes them (chunk_hist), and every
+// workgroup here derives the mask, the map, the new counts, the offsets and its own chunk's starting positions
+// from them, then regroups its own slots.
 // ---------------------------------------------------------------------------
 
 // counts of the slots whose ids are in s.ids8 (n tokens' worth): hist[0][e] primary slots, hist[1][e] secondary
