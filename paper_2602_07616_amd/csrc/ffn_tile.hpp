@@ -30,6 +30,8 @@
 // both on one card that has been busy for some 20 ms (from idle the first steps take a tenth longer):
 //   tokens   128: 111 + 60 -> 106 + 59     512: 140 + 81 -> 128 + 76    1024: 153 + 94 -> 136 + 86
 //           2048: 212 + 119 -> 155 + 112   3072: 242 + 145 -> 223 + 145   4096: 371 + 198 -> 290 + 186
+// (2048 tokens, items of 160 rows: while no expert has more.  Where one does, its second item makes the launch start a
+// fourth round of units on every compute unit: 190 + 129.)
 // fp32 layers against the vector-ALU kernels: 150 + 111 -> 64 + 39 us at 96 tokens (d_h 1024, d_m 704, 32 experts),
 // 67 + 49 -> 33 + 11 at 180 tokens (d_h 1024, d_m 192, 15 experts); relative error of the layer 1.8e-7 -> 1.4e-7.
 // Not faster, one launch over and over: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens);
