@@ -157,6 +157,25 @@ def test_similarity_groups_of_batches(dev, metric, inter, dtype):  # noqa: F811
     assert err.value.status == B.SERE_ERR_WORKSPACE_TOO_SMALL
 
 
+@pytest.mark.parametrize("metric", ["frobenius", "cosine", "cka_linear"])
+def test_similarity_stays_inside_its_workspace(dev, metric):  # noqa: F811
+    """31 batches of 7 tokens, groups of 16 and 15, at sizes where the smaller group has more Gram slices in all: nothing
+    behind exactly the bytes asked for changes."""
+    import torch
+    from paper_2602_07616_amd import binding as B
+    flag = {"frobenius": 0, "cosine": B.SERE_FLAG_SIM_COSINE, "cka_linear": B.SERE_FLAG_SIM_CKA_LINEAR}[metric]
+    cfg = B.make_config(7, 768, 128, 1, 64, 0, B.SERE_F32, 1, 0.0, flag)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    gu, dn, calib = (torch.empty(shape, device="cuda").normal_(0.0, std, generator=g)
+                     for shape, std in (((128, 128, 768), 0.02), ((128, 768, 64), 0.02), ((31, 7, 768), 1.0)))
+    sim = torch.full((128, 128), -3.0, device="cuda")
+    need = B.sere_similarity_workspace_bytes(cfg, 7)
+    room = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    B.sere_similarity(cfg, calib, 31, 7, gu, dn, sim, room[:need])
+    assert (room[need:] == 0x5A).all()
+    assert (torch.diagonal(sim) - 1.0).abs().max() <= 1e-6 and torch.isfinite(sim).all()
+
+
 def test_every_launch_of_the_pair_stage_is_timed(dev):  # noqa: F811
     """The reported stage is everything after the experts' forward pass, for every metric."""
     from paper_2602_07616_amd import binding as B
