@@ -20,6 +20,10 @@
 //    tile each.  While the second half of a stage is multiplied the first half of the next one is read
 //    from LDS, so that reads and products overlap inside a wavefront (gate/up at 2048 tokens of
 //    the Qwen3 shape, one launch over and over: 165 -> 151 us).
+//  - A compute unit takes in 64 bytes a cycle at best and its queue is short: eight wavefronts that issue a
+//    stage's 40 to 56 loads at once stand still until they are accepted.  So the loads go out one by one among the
+//    products (us, gate/up + down: 777 tokens of d_h 2880, d_m 1472 170 + 97 -> 161 + 93, 2048 tokens of the Qwen3
+//    shape 156 + 112 -> 150 + 109, 256 rows an expert 231 + 166 -> 231 + 158; fp32 below 63 + 39 -> 57 + 37).
 //  - Workgroups are handed to the 8 XCDs round-robin; each XCD walks a contiguous range of units,
 //    so the parts of one item run side by side and share its token rows in one L2.  Every part of
 //    256 weight rows starts at another k step (not the same offset of every row at once, that is, not
@@ -38,6 +42,9 @@
 // the same first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
 #pragma once
 
+#include <algorithm>
+#include <utility>
+
 #include "common.hpp"
 #include "ffn_generic.hpp"
 #include "ffn_mfma.hpp"
@@ -47,6 +54,14 @@ namespace sere {
 // uniform load through the scalar cache (of arrays that earlier kernels wrote)
 __device__ __forceinline__ int scalar_load(const int32_t* p, int i) {
   return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
+// the value of the first lane, for operands that have to be in scalar registers wherever the compiler kept them
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const uint64_t a = reinterpret_cast<uintptr_t>(p);
+  return reinterpret_cast<const char*>(static_cast<uintptr_t>(static_cast<uint64_t>(uniform(static_cast<uint32_t>(a >> 32))) << 32 |
+                                                             uniform(static_cast<uint32_t>(a))));
 }
 
 // 64 lanes x 16 bytes from memory to 1 KB of LDS at byte `lds` (lane l's bytes land at lds + 16 l).
@@ -90,6 +105,11 @@ struct TileShape {
   static_assert(kRealRows % (kTile * WN) == 0 && kStages >= 3, "the ring holds a stage in use and two on their way");
 };
 
+template <int... I, typename F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
 // h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of every unit.  Items have at most
 // TileShape::kRealRows rows; p.ksplit slices of d_m (down), none of them empty.  grid kTileGroups, 512 threads.
 template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO>
@@ -132,7 +152,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   const char* wbase[NQ];
   const char* tptr[NI];
   int pk = 0, pbeg = 0, pnk = 0, pleft = 0;
-  auto open_load_unit = [&](unsigned u) {
+  auto open_load_unit = [&](unsigned u) __attribute__((always_inline)) {
     const int item = u / parts, part = u % parts;
     const int e = scalar_load(p.work_expert, item), off = scalar_load(p.work_off, item), cnt = scalar_load(p.work_cnt, item);
     const int slab = part / ksplit, slice = part % ksplit;
@@ -182,14 +202,20 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     pk = (slab / kShared * ksplit + slice) * 5 % pnk;
     pleft = pnk;
   };
-  auto issue = [&](int slot) {
+  constexpr int P = NQ + NI;                             // loads of a stage
+  auto issue_some = [&](int slot, auto from, auto to) __attribute__((always_inline)) {  // loads from .. to - 1 of the next stage, into `slot`
     const size_t koff = static_cast<size_t>(pbeg + pk) * kRowBytes;
     const uint32_t at = lds0 + slot * Sh::kStageBytes;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) lds_load_weights(at + (wave * NQ + q) * 1024, lane_off, wbase[q] + koff);
-#pragma unroll
-    for (int n = 0; n < NI; ++n)
-      if (n + 1 < NI || wave < Sh::kFullWaves) lds_load_tokens(at + BM * kRowBytes + (wave + kTileWaves * n) * 1024, tptr[n] + koff);
+    for (int n = decltype(from)::value; n < decltype(to)::value; ++n) {
+      if (n < NQ) {
+        lds_load_weights(uniform(at + (wave * NQ + n) * 1024), lane_off, uniform(wbase[n < NQ ? n : 0] + koff));
+      } else if (n + 1 < P || wave < Sh::kFullWaves) {
+        lds_load_tokens(uniform(at + BM * kRowBytes + (wave + kTileWaves * (n - NQ)) * 1024), tptr[n - NQ < 0 ? 0 : n - NQ] + koff);
+      }
+    }
+  };
+  auto next_load_step = [&]() __attribute__((always_inline)) {
     if (++pk == pnk) pk = 0;
     if (--pleft == 0) {
       pu += kStride;
@@ -202,7 +228,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   f32x4 acc[NA][NT];
   f32x4 low[DT == SERE_F32 ? NA : 1][DT == SERE_F32 ? NT : 1];   // what acc has lost (fp32)
   int cnt = 0, off = 0, part = 0, left = 0;
-  auto open_unit = [&](unsigned u) {
+  auto open_unit = [&](unsigned u) __attribute__((always_inline)) {
     const int item = u / parts;
     part = u % parts;
     off = scalar_load(p.work_off, item);
@@ -220,7 +246,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   struct Frags {
     u32x4 w[NA], x[NT], y[LO ? NT : 1];
   };
-  auto fetch = [&](Frags& f, int slot, int h) {          // operands of one 32-wide half of a stage
+  auto fetch = [&](Frags& f, int slot, int h) __attribute__((always_inline)) {          // operands of one 32-wide half of a stage
     const unsigned char* st = lds + slot * Sh::kStageBytes + (frag ^ (h << 6));
 #pragma unroll
     for (int a = 0; a < NA; ++a) f.w[a] = *reinterpret_cast<const u32x4*>(st + (wm * RW + a * 16) * kRowBytes);
@@ -232,8 +258,8 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     }
   };
   f32x4 sums[4][DT == SERE_F32 ? NA : 1][DT == SERE_F32 ? NT : 1];
-  auto multiply = [&](const Frags& f, auto which) {
-    auto tile_of = [&](int t) {
+  auto multiply = [&](const Frags& f, auto which, auto&& between) __attribute__((always_inline)) {
+    auto tile_of = [&](int t) __attribute__((always_inline)) {
       if constexpr (DT == SERE_F32) {
         // 16 of the step's 32 k: lane (g, i) has four consecutive k of its rows, one product each.  The matrix
         // cores add one after the other; a chain over the whole contraction would round more than a sum over
@@ -267,16 +293,12 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         for (int a = 0; a < NA; ++a) acc[a][t] = mfma_bf16(f.w[a], f.y[t], acc[a][t]);
       }
     };
-    if ((wn + WN * (NT - 1)) * kTile < cnt) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t) tile_of(t);
-    } else {
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if ((wn + WN * t) * kTile < cnt) tile_of(t);
-    }
+    unrolled(std::make_integer_sequence<int, NT>{}, [&](auto t) __attribute__((always_inline)) {
+      if ((wn + WN * decltype(t)::value) * kTile < cnt) tile_of(decltype(t)::value);
+      between(t);
+    });
   };
-  auto store = [&]() {
+  auto store = [&]() __attribute__((always_inline)) {
     if constexpr (DT == SERE_F32) {
 #pragma unroll
       for (int a = 0; a < NA; ++a)
@@ -321,7 +343,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   // half of the next one is read from LDS, so that reads and products overlap within a wavefront.
   open_load_unit(pu);
   int ahead = 0, slot = 0;                               // stages issued and not yet waited for; slot in use
-  for (; ahead < S && pu < hi; ++ahead) issue(ahead);
+  for (; ahead < S && pu < hi; ++ahead) {
+    issue_some(ahead, std::integral_constant<int, 0>{}, std::integral_constant<int, P>{});
+    next_load_step();
+  }
   open_unit(cu);
   auto wait_stage = [&](auto issued) {                   // the oldest of the stages issued, by all wavefronts
     constexpr int D = decltype(issued)::value;           // how many there are while units are left to load
@@ -336,30 +361,44 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     --ahead;
   };
   Frags f0, f1;
-  wait_stage(std::integral_constant<int, S>{});
-  fetch(f0, 0, 0);
-  for (;;) {
-    fetch(f1, slot, 1);
-    multiply(f0, std::integral_constant<int, 0>{});
-    if (ahead > 0) {
-      // the wait also covers this wavefront's reads of the stage in use, whose slot is then free
-      const int used = slot;
-      slot = slot + 1 == S ? 0 : slot + 1;
-      wait_stage(std::integral_constant<int, S - 1>{});
-      if (pu < hi) {
-        issue(used);
-        ++ahead;
-      }
-      fetch(f0, slot, 0);
-    }
-    multiply(f1, std::integral_constant<int, 1>{});
+  // One stage: the second half of the products of the stage before it, then the first half of its own.
+  auto step = [&](bool more) __attribute__((always_inline)) { // more: a stage is left to load
+    const int used = slot;
+    slot = slot + 1 == S ? 0 : slot + 1;
+    fetch(f0, slot, 0);
+    // the loads of a stage, spread over the first three quarters of the products (one token tile: before them all)
+    auto loads = [&](auto half) __attribute__((always_inline)) {
+      return [&](auto t) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value * NT + decltype(t)::value, groups = NT == 1 ? 1 : (3 * NT + 1) / 2;
+        constexpr int n0 = std::min(P, h * P / groups), n1 = std::min(P, (h + 1) * P / groups);
+        if (n0 < n1 && more) issue_some(used, std::integral_constant<int, n0>{}, std::integral_constant<int, n1>{});
+      };
+    };
+    multiply(f1, std::integral_constant<int, 1>{}, loads(std::integral_constant<int, 0>{}));
     if (--left == 0) {
       store();
       cu += kStride;
-      if (cu >= hi) break;
       open_unit(cu);
     }
+    fetch(f1, slot, 1);
+    multiply(f0, std::integral_constant<int, 0>{}, loads(std::integral_constant<int, 1>{}));
+    if (more) {
+      next_load_step();
+      ++ahead;
+    }
+  };
+  const auto nothing = [](auto) __attribute__((always_inline)) {};
+  wait_stage(std::integral_constant<int, S>{});
+  fetch(f0, 0, 0);
+  fetch(f1, 0, 1);
+  multiply(f0, std::integral_constant<int, 0>{}, nothing);
+  while (ahead > 0) {
+    // the wait also covers this wavefront's reads of the stage in use, whose slot is then free
+    wait_stage(std::integral_constant<int, S - 1>{});
+    step(pu < hi);
   }
+  multiply(f1, std::integral_constant<int, 1>{}, nothing);
+  store();
 }
 
 }  // namespace sere
