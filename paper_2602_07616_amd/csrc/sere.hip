@@ -568,17 +568,23 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
   unsigned long long* max_bits = reinterpret_cast<unsigned long long*>(ws + l.max_bits);
   const unsigned entries = (M * M + 255) / 256;
   const float* y = f.y;
+  int parts = 1;   // summands that an entry of dist comes in
   if (metric == kMetricCkaLinear) {
-    double* rowsum = reinterpret_cast<double*>(ws + l.rowsum);
     const bool linear = cka_kernel == kCkaLinear;
+    // linear kernel: row sums in blocks, where h was; the other kernels need the diagonal and leave whole row sums
+    const int side = cka_block(n), nb = (n + side - 1) / side;
+    double* rowsum = reinterpret_cast<double*>(ws + (linear ? l.h : l.rowsum));
     double* diag = linear ? nullptr : reinterpret_cast<double*>(ws + l.diag);
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_kernel, dim3(n, M * g), dim3(256), y, f.ksplit, l.rows, n, dh, gram,
-                 linear ? rowsum : static_cast<double*>(nullptr), diag);
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, side == 16 ? cka_gram_kernel<1> : cka_gram_kernel<2>, dim3(nb * (nb + 1) / 2, M * g),
+                 dim3(256), y, f.ksplit, l.rows, n, dh, gram, rowsum, diag);
     if (!linear)
       launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_transform_kernel, dim3(n, M * g), dim3(256), gram,
                    static_cast<const double*>(diag), n, cka_kernel, p0, static_cast<int>(p1), rowsum);
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_hsic_kernel, dim3(M, M, g), dim3(256), static_cast<const double*>(gram),
-                 static_cast<const double*>(rowsum), n, M, dist);
+    const int mb = (M + 15) / 16;
+    parts = cka_parts(n, dh, M);
+    if (parts > 1) dist = reinterpret_cast<double*>(ws + l.y);   // no longer needed
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, cka_pair_kernel, dim3(mb * (mb + 1) / 2, parts, g), dim3(256),
+                 static_cast<const double*>(gram), static_cast<const double*>(rowsum), linear ? nb : 1, n, M, dist);
   } else {
     double* part = reinterpret_cast<double*>(ws + l.gram_part);
     const double* inv_norm = metric == kMetricCosine ? reinterpret_cast<const double*>(ws + l.inv_norm) : nullptr;
@@ -605,7 +611,7 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
       launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
                    static_cast<const double*>(gram), y, f.ksplit, l.rows, n, dh, M, dist, max_bits);
   }
-  launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), M,
+  launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), parts, M,
                b0, g, num_batches, metric, static_cast<const unsigned long long*>(max_bits),
                reinterpret_cast<double*>(ws + l.acc), sim);
 }

@@ -485,47 +485,133 @@ __global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restri
 }
 
 // Linear CKA (appendix "Centered Kernel Alignment"), step 1: the Gram matrix of every expert's
-// outputs with its diagonal set to zero, gram[e][i][j] = <A_e[i], A_e[j]> (i != j), and its row
-// sums.  Entries (i, j) and (j, i) are formed by the same operations in the same order, so the
-// matrix is symmetric to the bit.  grid (n, M * g), 256 threads (e: expert and batch): wavefront w takes j = w, w+4, ...;
-// fp64 accumulation.
+// outputs with its diagonal set to zero, gram[e][i][j] = <A_e[i], A_e[j]> (i != j), and the sums of its
+// rows, block by block: rowsum[e][bj][i] = sum of row i over the columns of block bj.  (e: expert and batch.)
+// A workgroup takes a block of 16 B x 16 B entries of the upper triangle over the whole d_h on the fp64 matrix cores
+// (operands as in pair_gram_kernel: 16 rows x 64 bytes an instruction, the next group of loads in flight while one is
+// multiplied); its four wavefronts take every fourth group of k and their sums are added in a fixed order through LDS.
+// Entries below the diagonal are copies, so the matrix is symmetric to the bit.  Bound by the rows' way from cache, which
+// B = 2 halves; B = 1 gives batches of up to kCkaSmallTokens tokens three times as many workgroups (us, launch: 60
+// experts, d_h 2048, two batches of 32 tokens B = 1 20, of 64 tokens B = 1 55, B = 2 49, of 128 B = 2 115, 70 TFLOP/s;
+// 128 experts, d_h 512, 60 tokens B = 1 54, B = 2 23).  With a wavefront per entry on the vector ALU: 77 us at 32 tokens.
+// More groups in flight or eight wavefronts changed nothing at 32 tokens and lost on short rows (d_h 512: 19 -> 32 us).
 // With `diag` (RBF and polynomial kernels) the diagonal <A_e[i], A_e[i]> goes there and the row
-// sums are left to gram_transform_kernel (rowsum == nullptr).
-__global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n, int dh,
-                                                   double* __restrict__ gram, double* __restrict__ rowsum,
-                                                   double* __restrict__ diag) {
-  __shared__ double part[4];
-  const int i = blockIdx.x, e = blockIdx.y;
+// sums are left to gram_transform_kernel.  grid (nb (nb + 1) / 2, M * g), nb = ceil(n / (16 B)), 256 threads.
+constexpr int kCkaSmallTokens = 48;
+constexpr int cka_block(int n) { return n <= kCkaSmallTokens ? 16 : 32; }
+template <int B>
+__global__ __launch_bounds__(256) void cka_gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n, int dh,
+                                                       double* __restrict__ gram, double* __restrict__ rowsum,
+                                                       double* __restrict__ diag) {
+  constexpr int W = 4, kSide = 16 * B, kAhead = 2, kSteps = B == 1 ? 4 : 2, kGroup = 16 * kSteps;   // d_h is a multiple of 64
+  __shared__ double s_part[W][B * B * 4][kWave];
+  __shared__ double s_tile[kSide][kSide + 1];
+  const int nb = (n + kSide - 1) / kSide, e = blockIdx.y;
+  int bi, bj;
+  gram_block_of(blockIdx.x, nb, bi, bj);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r16 = lane & 15, kq = lane >> 4;
   const size_t slice = static_cast<size_t>(rows) * dh;
-  const float* ai = y + (static_cast<size_t>(e) * n + i) * dh;
-  double row = 0.0;
-  for (int j = wave; j < n; j += 4) {
-    const float* aj = y + (static_cast<size_t>(e) * n + j) * dh;
-    double dot = 0.0;
-    for (int c = lane * 4; c < dh; c += 256) {
-      float4 a = *reinterpret_cast<const float4*>(ai + c), b = *reinterpret_cast<const float4*>(aj + c);
-      for (int s = 1; s < ksplit; ++s) {
-        const float4 a2 = *reinterpret_cast<const float4*>(ai + s * slice + c);
-        const float4 b2 = *reinterpret_cast<const float4*>(aj + s * slice + c);
-        a.x += a2.x; a.y += a2.y; a.z += a2.z; a.w += a2.w;
-        b.x += b2.x; b.y += b2.y; b.z += b2.z; b.w += b2.w;
-      }
-      const double ax = a.x, ay = a.y, az = a.z, aw = a.w, bx = b.x, by = b.y, bz = b.z, bw = b.w;
-      dot += (ax * bx + ay * by) + (az * bz + aw * bw);
-    }
-    dot = wave_sum(dot);
-    if (j == i) {
-      if (diag != nullptr && lane == 0) diag[static_cast<size_t>(e) * n + i] = dot;
-      dot = 0.0;
-    }
-    if (lane == 0) gram[(static_cast<size_t>(e) * n + i) * n + j] = dot;
-    row += dot;
+  const float* ai[B];
+  const float* aj[B];
+#pragma unroll
+  for (int t = 0; t < B; ++t) {   // rows beyond n repeat the last one (their results are not stored)
+    ai[t] = y + (static_cast<size_t>(e) * n + min(bi * kSide + 16 * t + r16, n - 1)) * dh + 4 * kq;
+    aj[t] = y + (static_cast<size_t>(e) * n + min(bj * kSide + 16 * t + r16, n - 1)) * dh + 4 * kq;
   }
-  if (lane == 0) part[wave] = row;
+  auto fetch = [&](const float* row, int k) {
+    float4 v = *reinterpret_cast<const float4*>(row + k);
+    for (int s = 1; s < ksplit; ++s) {
+      const float4 v2 = *reinterpret_cast<const float4*>(row + s * slice + k);
+      v.x += v2.x; v.y += v2.y; v.z += v2.z; v.w += v2.w;
+    }
+    return v;
+  };
+  f64x4 acc[B][B];
+#pragma unroll
+  for (int a = 0; a < B; ++a)
+#pragma unroll
+    for (int b = 0; b < B; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  float4 va[kAhead][kSteps][B], vb[kAhead][kSteps][B];   // groups whose loads are in flight
+  auto fetch_group = [&](int buf, int group) {
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st)
+#pragma unroll
+      for (int t = 0; t < B; ++t) {
+        va[buf][st][t] = fetch(ai[t], group * kGroup + 16 * st);
+        vb[buf][st][t] = fetch(aj[t], group * kGroup + 16 * st);
+      }
+  };
+  auto multiply_group = [&](int buf) {
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int a = 0; a < B; ++a)
+#pragma unroll
+          for (int b = 0; b < B; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(reinterpret_cast<const float*>(&va[buf][st][a])[j]),
+                                                             static_cast<double>(reinterpret_cast<const float*>(&vb[buf][st][b])[j]),
+                                                             acc[a][b], 0, 0, 0);
+  };
+  const int groups = dh / kGroup;
+#pragma unroll
+  for (int d = 0; d < kAhead; ++d)
+    if (wave + d * W < groups) fetch_group(d, wave + d * W);
+  for (int i = wave; i < groups; i += kAhead * W) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) {
+      if (i + d * W < groups) multiply_group(d);
+      if (i + (d + kAhead) * W < groups) fetch_group(d, i + (d + kAhead) * W);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < B; ++a)
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_part[wave][(a * B + b) * 4 + r][lane] = acc[a][b][r];
   __syncthreads();
-  if (threadIdx.x == 0 && rowsum != nullptr)
-    rowsum[static_cast<size_t>(e) * n + i] = (part[0] + part[1]) + (part[2] + part[3]);
+  // a wavefront finishes one register of a tile at a time: lane l holds D[l / 16 + 4 r][l % 16]
+  gram += static_cast<size_t>(e) * n * n;
+  for (int at = wave; at < 4 * B * B; at += W) {
+    const int t = at / 4;
+    double v = s_part[0][at][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += s_part[w][at][lane];
+    const int li = 16 * (t / B) + kq + 4 * (at % 4), lj = 16 * (t % B) + r16;
+    const int i = bi * kSide + li, j = bj * kSide + lj;
+    const bool inside = i < n && j < n;
+    if (bi == bj && li > lj) continue;        // written by its mirror entry
+    if (i == j) {
+      if (diag != nullptr && inside) diag[static_cast<size_t>(e) * n + i] = v;
+      v = 0.0;
+    }
+    if (!inside) v = 0.0;
+    s_tile[li][lj] = v;
+    if (bi == bj) s_tile[lj][li] = v;
+    if (inside) {
+      gram[static_cast<size_t>(i) * n + j] = v;
+      gram[static_cast<size_t>(j) * n + i] = v;
+    }
+  }
+  if (diag != nullptr) return;
+  __syncthreads();
+  rowsum += static_cast<size_t>(e) * nb * n;
+  if (threadIdx.x < kSide) {
+    const int i = bi * kSide + threadIdx.x;
+    double sum = 0.0;
+#pragma unroll
+    for (int j = 0; j < kSide; ++j) sum += s_tile[threadIdx.x][j];
+    if (i < n) rowsum[static_cast<size_t>(bj) * n + i] = sum;
+  } else if (threadIdx.x >= kWave && threadIdx.x < kWave + kSide && bi != bj) {   // the mirror block's rows
+    const int c = threadIdx.x - kWave, j = bj * kSide + c;
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSide; ++i) sum += s_tile[i][c];
+    if (j < n) rowsum[static_cast<size_t>(bi) * n + j] = sum;
+  }
 }
 
 constexpr int kCkaLinear = 0, kCkaRbf = 1, kCkaPoly = 2;  // SERE_CKA_* of the header
@@ -567,56 +653,122 @@ __global__ __launch_bounds__(256) void gram_transform_kernel(double* __restrict_
   if (threadIdx.x == 0) rowsum[static_cast<size_t>(e) * n + i] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
-// Linear CKA, step 2: the unbiased estimator of HSIC for every pair of experts (Song et al. 2012,
+// CKA, step 2: the unbiased estimator of HSIC for every pair of experts (Song et al. 2012,
 // the O(n^2) estimator the appendix refers to), from the zero-diagonal Gram matrices Kt_p, Kt_q:
 //   hsic[p][q] = [ tr(Kt_p Kt_q) + (1'Kt_p 1)(1'Kt_q 1) / ((n-1)(n-2)) - 2 (1'Kt_p Kt_q 1) / (n-2) ] / (n (n-3))
 // with tr(Kt_p Kt_q) = sum_ij Kt_p[i][j] Kt_q[i][j] (symmetric matrices) and 1'Kt_p Kt_q 1 = the
-// dot product of the two row-sum vectors.  grid (M, M, g), 256 threads; n >= 4.
-__global__ __launch_bounds__(256) void pair_hsic_kernel(const double* __restrict__ gram,
-                                                        const double* __restrict__ rowsum, int n, int M,
-                                                        double* __restrict__ hsic) {
-  __shared__ double part[4][4];
-  const int batch = blockIdx.z;
-  const size_t p = static_cast<size_t>(blockIdx.y) * gridDim.z + batch, q = static_cast<size_t>(blockIdx.x) * gridDim.z + batch;
+// dot product of the two row-sum vectors.  Traces and dot products are Gram matrices again, of the M flattened
+// matrices and the M row-sum vectors: 16 x 16 pairs a workgroup on the fp64 matrix cores, the upper triangle of the
+// pairs only (60 experts, two batches of 32 tokens: 7 us; a workgroup for every ordered pair that reads both
+// matrices from cache: 20).  n * n is cut into gridDim.y parts, hsic[batch][part][p][q]; the last one has
+// the terms of the row sums (in `nb` blocks a row), alone if there are several.  grid (mb (mb + 1) / 2, parts, g), mb = ceil(M / 16), 256 threads; n >= 4.
+typedef double f64x2_unaligned __attribute__((ext_vector_type(2), aligned(8)));
+__global__ __launch_bounds__(256) void cka_pair_kernel(const double* __restrict__ gram, const double* __restrict__ rowsum,
+                                                       int nb, int n, int M, double* __restrict__ hsic) {
+  __shared__ double s_part[4][4][4][kWave];   // [wavefront][trace, cross, sum of p, sum of q][register][lane]
+  int bp, bq;
+  gram_block_of(blockIdx.x, (M + 15) / 16, bp, bq);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const double* kp = gram + p * n * n;
-  const double* kq = gram + q * n * n;
-  double tr = 0.0, cross = 0.0, sp = 0.0, sq = 0.0;
-  for (int i = threadIdx.x; i < n * n; i += 256) tr += kp[i] * kq[i];
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const double rp = rowsum[p * n + i], rq = rowsum[q * n + i];
-    cross += rp * rq;
-    sp += rp;
-    sq += rq;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int g = gridDim.z, batch = blockIdx.z, part = blockIdx.y;
+  // rows beyond M repeat the last one (their results are not stored)
+  const size_t p = static_cast<size_t>(min(16 * bp + r16, M - 1)) * g + batch, q = static_cast<size_t>(min(16 * bq + r16, M - 1)) * g + batch;
+  const int parts = max(static_cast<int>(gridDim.y) - 1, 1);          // of the products
+  const int K = n * n, groups = (K + 15) / 16, per = (groups + parts - 1) / parts;
+  const int gend = min((part + 1) * per, groups);
+  const double* kp = gram + p * K;
+  const double* kv = gram + q * K;
+  f64x4 trace = {0.0, 0.0, 0.0, 0.0}, cross = trace, sp = trace, sq = trace;
+  constexpr int kAhead = 2;    // groups of 16 k whose loads are issued together
+  struct Operands {
+    double a[kAhead][4], b[kAhead][4];
+  };
+  auto fetch = [&](Operands& o, int group) {   // lane (r16, kq): k = 16 group + 4 kq .. + 3 of its rows
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int k0 = 16 * min(group + 4 * u, groups - 1), k = k0 + 4 * kq;
+      if (k0 + 16 <= K) {   // wave-uniform; all but the last group of an n that is no multiple of 4
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f64x2_unaligned x = *reinterpret_cast<const f64x2_unaligned*>(kp + k + 2 * h);
+          const f64x2_unaligned w = *reinterpret_cast<const f64x2_unaligned*>(kv + k + 2 * h);
+          o.a[u][2 * h] = x[0];
+          o.a[u][2 * h + 1] = x[1];
+          o.b[u][2 * h] = w[0];
+          o.b[u][2 * h + 1] = w[1];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          o.a[u][j] = k + j < K ? kp[k + j] : 0.0;
+          o.b[u][j] = k + j < K ? kv[k + j] : 0.0;
+        }
+      }
+    }
+  };
+  auto multiply = [&](const Operands& o, int group) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (group + 4 * u < gend) {   // wave-uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j) trace = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[u][j], o.b[u][j], trace, 0, 0, 0);
+      }
+  };
+  Operands o0, o1;
+  int at = part * per + wave;
+  if (at < gend) fetch(o0, at);
+  for (; at < gend; at += 8 * kAhead) {
+    fetch(o1, at + 4 * kAhead);
+    multiply(o0, at);
+    fetch(o0, at + 8 * kAhead);
+    multiply(o1, at + 4 * kAhead);
   }
-  tr = wave_sum(tr);
-  cross = wave_sum(cross);
-  sp = wave_sum(sp);
-  sq = wave_sum(sq);
-  if (lane == 0) {
-    part[0][wave] = tr;
-    part[1][wave] = cross;
-    part[2][wave] = sp;
-    part[3][wave] = sq;
+  if (part == static_cast<int>(gridDim.y) - 1) {
+    const double* rp = rowsum + p * nb * n;
+    const double* rq = rowsum + q * nb * n;
+    for (int st = wave; st * 4 < n; st += 4) {
+      const int i = 4 * st + kq;
+      double x = 0.0, w = 0.0;
+      if (i < n)
+#pragma unroll 4
+        for (int b = 0; b < nb; ++b) {
+          x += rp[static_cast<size_t>(b) * n + i];
+          w += rq[static_cast<size_t>(b) * n + i];
+        }
+      cross = __builtin_amdgcn_mfma_f64_16x16x4f64(x, w, cross, 0, 0, 0);
+      sp = __builtin_amdgcn_mfma_f64_16x16x4f64(x, 1.0, sp, 0, 0, 0);
+      sq = __builtin_amdgcn_mfma_f64_16x16x4f64(1.0, w, sq, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    s_part[wave][0][r][lane] = trace[r];
+    s_part[wave][1][r][lane] = cross[r];
+    s_part[wave][2][r][lane] = sp[r];
+    s_part[wave][3][r][lane] = sq[r];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double v[4];
-    for (int k = 0; k < 4; ++k) v[k] = (part[k][0] + part[k][1]) + (part[k][2] + part[k][3]);
-    const double dn = n;
-    hsic[(static_cast<size_t>(batch) * M + blockIdx.y) * M + blockIdx.x] =
-        (v[0] + v[2] * v[3] / ((dn - 1.0) * (dn - 2.0)) - 2.0 * v[1] / (dn - 2.0)) / (dn * (dn - 3.0));
-  }
+  double v[4];   // wavefront w finishes register w
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    v[c] = ((s_part[0][c][wave][lane] + s_part[1][c][wave][lane]) + s_part[2][c][wave][lane]) + s_part[3][c][wave][lane];
+  const int pp = 16 * bp + kq + 4 * wave, qq = 16 * bq + r16;
+  if (pp > qq || qq >= M) return;   // below the diagonal: written by the mirror entry
+  const double dn = n;
+  const double h = (v[0] + v[2] * v[3] / ((dn - 1.0) * (dn - 2.0)) - 2.0 * v[1] / (dn - 2.0)) / (dn * (dn - 3.0));
+  hsic += (static_cast<size_t>(batch) * gridDim.y + part) * M * M;
+  hsic[static_cast<size_t>(pp) * M + qq] = h;
+  hsic[static_cast<size_t>(qq) * M + pp] = h;
 }
 
 constexpr int kMetricFrobenius = 0, kMetricCosine = 1, kMetricCkaLinear = 2;
 
 // Frobenius: acc[p][q] (+)= 1 - dist/max(dist), the maximum of the batch given as the bits of a
 // double in *max_bits; cosine: acc[p][q] (+)= dist[p][q] (the pair kernel's value as it is); linear
-// CKA: acc[p][q] (+)= dist[p][q] / sqrt(dist[p][p] dist[q][q]), dist holding the HSIC estimates (0
+// CKA: acc[p][q] (+)= dist[p][q] / sqrt(dist[p][p] dist[q][q]), dist holding the HSIC estimates in `parts` summands (0
 // where a self-term is not positive: the quotient is undefined there).  The g batches of the group are added
 // in order.  With the last batch sim = acc / N.  grid ceil(M * M / 256), 256 threads.
-__global__ __launch_bounds__(256) void similarity_accumulate_kernel(const double* __restrict__ dist, int M,
+__global__ __launch_bounds__(256) void similarity_accumulate_kernel(const double* __restrict__ dist, int parts, int M,
                                                                     int batch0, int g, int num_batches, int metric,
                                                                     const unsigned long long* __restrict__ max_bits,
                                                                     double* __restrict__ acc,
@@ -624,13 +776,20 @@ __global__ __launch_bounds__(256) void similarity_accumulate_kernel(const double
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= M * M) return;
   double a = batch0 == 0 ? 0.0 : acc[i];
-  for (int b = 0; b < g; ++b, dist += static_cast<size_t>(M) * M) {
+  for (int b = 0; b < g; ++b, dist += static_cast<size_t>(parts) * M * M) {
     double sv;
     if (metric == kMetricCosine) {
       sv = dist[i];
     } else if (metric == kMetricCkaLinear) {
-      const double hp = dist[static_cast<size_t>(i / M) * M + i / M], hq = dist[static_cast<size_t>(i % M) * M + i % M];
-      sv = (hp > 0.0 && hq > 0.0) ? dist[i] / sqrt(hp * hq) : 0.0;
+      double h = 0.0, hp = 0.0, hq = 0.0;
+#pragma unroll 4
+      for (int s = 0; s < parts; ++s) {
+        const double* d = dist + static_cast<size_t>(s) * M * M;
+        h += d[i];
+        hp += d[static_cast<size_t>(i / M) * M + i / M];
+        hq += d[static_cast<size_t>(i % M) * M + i % M];
+      }
+      sv = (hp > 0.0 && hq > 0.0) ? h / sqrt(hp * hq) : 0.0;
     } else {
       const double mx = __longlong_as_double(static_cast<long long>(max_bits[b]));
       sv = mx > 0.0 ? 1.0 - dist[i] / mx : 1.0;  // all pairs identical: Sim = 1

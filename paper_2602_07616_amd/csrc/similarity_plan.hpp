@@ -93,6 +93,14 @@ inline bool gram_staged_pays(int experts, long long length) {
   return experts > 192 && length * 4 % (2 << 20) == 0;
 }
 
+// Parts of a batch's n * n products in cka_pair_kernel, 512 products and more each, and one more for its row sums: a
+// wavefront's products wait for their operands one after the other (60 experts, 64 tokens: one part 23 us, eight 8), while
+// similarity_accumulate_kernel adds up an entry's parts (32 of them: 7 -> 25 us).  The parts lie where y was: there
+// has to be room.
+inline int cka_parts(int n, int hidden, int experts) {
+  return std::max(1, std::min(1 + std::min(8, (n * n + 511) / 512), static_cast<int>(static_cast<long long>(n) * hidden / (2 * experts))));
+}
+
 // Layout of groups of g batches of n tokens.  A call checks its workspace against its largest group and launches
 // smaller ones in it (the last of a call), so no buffer's room may shrink as g grows, whatever is chosen by g; and what is
 // chosen by `whole` changes nothing about the room, which a caller asks for without naming the number of batches.
