@@ -278,9 +278,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs p) {
       acc.z += __uint_as_float(x.y << 16);
       acc.w += __uint_as_float(x.y & 0xffff0000u);
     }
-    uint2 packed;
-    packed.x = static_cast<uint32_t>(f32_to_bf16(acc.x)) | (static_cast<uint32_t>(f32_to_bf16(acc.y)) << 16);
-    packed.y = static_cast<uint32_t>(f32_to_bf16(acc.z)) | (static_cast<uint32_t>(f32_to_bf16(acc.w)) << 16);
+    const uint2 packed = {f32_to_bf16x2(acc.x, acc.y), f32_to_bf16x2(acc.z, acc.w)};
     *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + at) = packed;
   }
 }

@@ -91,22 +91,16 @@ __device__ __forceinline__ void store_h4(const FfnArgs& p, size_t at, f32x4 gate
     *reinterpret_cast<f32x4*>(p.h + at) = v;
     return;
   }
-  uint16_t hi[4], lo[4];
+  float hv[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const float hv = silu(gate[r]) * up[r];
-    hi[r] = f32_to_bf16(hv);
-    lo[r] = f32_to_bf16(hv - bf16_to_f32(hi[r]));
-  }
+  for (int r = 0; r < 4; ++r) hv[r] = silu_for_bf16(gate[r]) * up[r];
   uint16_t* h = reinterpret_cast<uint16_t*>(p.h);
-  uint2 packed;
-  packed.x = static_cast<uint32_t>(hi[0]) | (static_cast<uint32_t>(hi[1]) << 16);
-  packed.y = static_cast<uint32_t>(hi[2]) | (static_cast<uint32_t>(hi[3]) << 16);
-  *reinterpret_cast<uint2*>(h + at) = packed;
+  const uint2 high = {f32_to_bf16x2(hv[0], hv[1]), f32_to_bf16x2(hv[2], hv[3])};
+  *reinterpret_cast<uint2*>(h + at) = high;
   if (p.split_h) {
-    packed.x = static_cast<uint32_t>(lo[0]) | (static_cast<uint32_t>(lo[1]) << 16);
-    packed.y = static_cast<uint32_t>(lo[2]) | (static_cast<uint32_t>(lo[3]) << 16);
-    *reinterpret_cast<uint2*>(h + static_cast<size_t>(p.rows) * p.dm + at) = packed;
+    const uint2 low = {f32_to_bf16x2(hv[0] - __uint_as_float(high.x << 16), hv[1] - __uint_as_float(high.x & 0xffff0000u)),
+                       f32_to_bf16x2(hv[2] - __uint_as_float(high.y << 16), hv[3] - __uint_as_float(high.y & 0xffff0000u))};
+    *reinterpret_cast<uint2*>(h + static_cast<size_t>(p.rows) * p.dm + at) = low;
   }
 }
 
