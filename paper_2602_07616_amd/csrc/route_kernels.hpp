@@ -364,32 +364,40 @@ __device__ __forceinline__ double group_sum(double v) {
 
 // KEEP (8 or 16, >= min(K, 16)): list entries held per lane; a sorted list cannot
 // contribute more than K entries to the top K, so for K <= 8 half a list is enough.
-template <int LP, int KS, int KEEP>
-__device__ __forceinline__ void topk_merge(const uint64_t* __restrict__ list_key,
-                                           const uint8_t* __restrict__ list_id, bool active, int nlists,
-                                           int32_t* __restrict__ ids, float* __restrict__ w, uint8_t* ids8, int K) {
-  const int l = threadIdx.x & (LP - 1);
-  const bool has_list = active && l < nlists;
-  static_assert(KEEP == 8 || KEEP == 16, "half a list or a whole one");
+template <int KEEP>
+struct ListHead {
   uint64_t key[KEEP];
   uint32_t idw[4];  // expert ids, one byte each (the upper two words stay 0 for KEEP == 8)
-  idw[0] = idw[1] = idw[2] = idw[3] = 0;
-  if (has_list) {
-    const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(list_key + static_cast<size_t>(l) * 16);
+};
+// lane l's list of a token's (without a condition: a lane without a list reads the first one and drops it in topk_merge)
+template <int LP, int KEEP>
+__device__ __forceinline__ void load_lists(const uint64_t* __restrict__ list_key, const uint8_t* __restrict__ list_id,
+                                           int nlists, ListHead<KEEP>& h) {
+  static_assert(KEEP == 8 || KEEP == 16, "half a list or a whole one");
+  const int l = threadIdx.x & (LP - 1), at = l < nlists ? l : 0;
+  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(list_key + static_cast<size_t>(at) * 16);
 #pragma unroll
-    for (int j = 0; j < KEEP / 2; ++j) {
-      const ulonglong2 v = kp[j];
-      key[2 * j] = v.x;
-      key[2 * j + 1] = v.y;
-    }
-    if (KEEP == 16) {
-      const uint4 iv = *reinterpret_cast<const uint4*>(list_id + static_cast<size_t>(l) * 16);
-      idw[0] = iv.x; idw[1] = iv.y; idw[2] = iv.z; idw[3] = iv.w;
-    } else {
-      const uint2 iv = *reinterpret_cast<const uint2*>(list_id + static_cast<size_t>(l) * 16);
-      idw[0] = iv.x; idw[1] = iv.y;
-    }
+  for (int j = 0; j < KEEP / 2; ++j) {
+    const ulonglong2 v = kp[j];
+    h.key[2 * j] = v.x;
+    h.key[2 * j + 1] = v.y;
+  }
+  if (KEEP == 16) {
+    const uint4 iv = *reinterpret_cast<const uint4*>(list_id + static_cast<size_t>(at) * 16);
+    h.idw[0] = iv.x; h.idw[1] = iv.y; h.idw[2] = iv.z; h.idw[3] = iv.w;
   } else {
+    const uint2 iv = *reinterpret_cast<const uint2*>(list_id + static_cast<size_t>(at) * 16);
+    h.idw[0] = iv.x; h.idw[1] = iv.y; h.idw[2] = 0; h.idw[3] = 0;
+  }
+}
+
+// `chosen(k, id)` is called by one lane of the group for the expert of rank k.
+template <int LP, int KS, int KEEP, typename Chosen>
+__device__ __forceinline__ void topk_merge(ListHead<KEEP>& h, bool active, int nlists, float* __restrict__ w, int K, Chosen&& chosen) {
+  const int l = threadIdx.x & (LP - 1);
+  uint64_t (&key)[KEEP] = h.key;
+  uint32_t (&idw)[4] = h.idw;
+  if (!active || l >= nlists) {
 #pragma unroll
     for (int j = 0; j < KEEP; ++j) key[j] = 0;
   }
@@ -419,11 +427,7 @@ __device__ __forceinline__ void topk_merge(const uint64_t* __restrict__ list_key
 #pragma unroll
     for (int c = 0; c < KS; ++c)
       if (k == l + LP * c) mysel[c] = val;
-    if (l == 0 && active) {
-      // a device-scope store: with several workgroups the ids are read by another one of this launch
-      __hip_atomic_store(ids + k, static_cast<int32_t>(wid), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (ids8 != nullptr) ids8[k] = static_cast<uint8_t>(wid);
-    }
+    if (l == 0 && active) chosen(k, static_cast<int>(wid));
   }
   double ex[KS];
   double part = 0.0;
@@ -443,7 +447,9 @@ __device__ __forceinline__ void topk_merge(const uint64_t* __restrict__ list_key
 
 // ---------------------------------------------------------------------------
 // Batch-wide re-routing and compaction by ONE workgroup of 1024 threads (smaller batches), and the
-// parts of it that the shared form uses too.
+// parts of it that the shared form uses too.  A chain of short steps between barriers: counting by expert instead of
+// by slot, sums over lanes by DPP and clearing LDS before the top-K took the launch from 9.0 to 8.7 us at 32 tokens, 11.1 to
+// 10.6 at 128 (128 experts), 7.2 to 6.9 at 64 tokens of 64 experts.
 // ---------------------------------------------------------------------------
 struct RouteArgs {
   const int32_t* topk_ids;  // [A]  I
@@ -499,7 +505,7 @@ struct RouteShared {
   int scan_before[SERE_MAX_EXPERTS / kWave];
   int scan_items[SERE_MAX_EXPERTS / kWave];
   int cursor[SERE_MAX_EXPERTS];
-  int round_cnt[kRouteWaves][SERE_MAX_EXPERTS];
+  __attribute__((aligned(16))) int round_cnt[kRouteWaves][SERE_MAX_EXPERTS];
   uint8_t ids8[kIdsInLds];
   int flag;
 };
@@ -517,16 +523,20 @@ struct SimPrefetch {
   static constexpr int PR = NC == 16 ? 1 : NR;   // rounds fetched ahead (at most 16 values per lane)
   float v[PR * NC];
 };
+// No load under a condition, or its wait would cover every load before it: values that remap_secondary does not ask for are
+// another place of the matrix, or of `any` (readable) where there is nothing to prefetch.
 template <int NC>
-__device__ __forceinline__ void prefetch_sim(const RouteArgs& p, SimPrefetch<NC>& pf, bool enabled = true) {
+__device__ __forceinline__ void prefetch_sim(const RouteArgs& p, SimPrefetch<NC>& pf, const void* any, bool enabled = true) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int q = lane >> 4, i = lane & 15;
+  const bool on = enabled && p.reroute;
+  const float* base = on ? p.sim : static_cast<const float*>(any);
 #pragma unroll
   for (int r = 0; r < SimPrefetch<NC>::PR; ++r) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int u = 4 * wave + q + 64 * r, v = i + 16 * c;
-      pf.v[r * NC + c] = (enabled && p.reroute && u < p.M && v < p.M) ? p.sim[static_cast<size_t>(u) * p.M + v] : 0.0f;
+      const int u = min(4 * wave + q + 64 * r, p.M - 1), v = min(i + 16 * c, p.M - 1);
+      pf.v[r * NC + c] = base[on ? u * p.M + v : 0];
     }
   }
 }
@@ -548,39 +558,61 @@ __device__ __forceinline__ void simmax_step(float& sv, int& iv) {
 // merged preferring the larger similarity, then the lower index: together
 // the first maximum of an ascending scan, as the paper's algorithm finds it.
 // The expert is kept as critical iff rho > 0 and sim* < rho.
-template <int NC>
-__device__ __forceinline__ void remap_secondary(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf, bool prefetched) {
-  if (!p.reroute) return;
+// target(u, v) is called by one thread for every expert u < M, v being where its secondary slots go.
+template <int NC, typename Target>
+__device__ __forceinline__ void remap_secondary(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf, bool prefetched,
+                                                Target&& target) {
+  if (!p.reroute) {
+    if (static_cast<int>(threadIdx.x) < p.M) target(static_cast<int>(threadIdx.x), static_cast<int>(threadIdx.x));
+    return;
+  }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, M = p.M;
   const int q = lane >> 4, i = lane & 15;
 #pragma unroll
   for (int r = 0; r < SimPrefetch<NC>::NR; ++r) {
     const int u = 4 * wave + q + 64 * r;
     const bool sec = u < M && s.cnt_b[u] > 0 && !s.prim[u];
-    if (__ballot(sec) == 0) continue;  // wave-uniform
-    float bs = -INFINITY;
-    int bv = 0;
+    int to = u;
+    if (__ballot(sec) != 0) {  // wave-uniform
+      float bs = -INFINITY;
+      int bv = 0;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int v = i + 16 * c;
-      if (v < M) {
-        float sv;
-        if (r < SimPrefetch<NC>::PR && prefetched)   // prefetched: uniform over the workgroup
-          sv = pf.v[(r < SimPrefetch<NC>::PR ? r : 0) * NC + c];
-        else
-          sv = sec ? p.sim[static_cast<size_t>(u) * M + v] : 0.0f;
-        if (s.prim[v] && sv > bs) {
-          bs = sv;
-          bv = v;
+      for (int c = 0; c < NC; ++c) {
+        const int v = i + 16 * c;
+        if (v < M) {
+          float sv;
+          if (r < SimPrefetch<NC>::PR && prefetched)   // prefetched: uniform over the workgroup
+            sv = pf.v[(r < SimPrefetch<NC>::PR ? r : 0) * NC + c];
+          else
+            sv = sec ? p.sim[static_cast<size_t>(u) * M + v] : 0.0f;
+          if (s.prim[v] && sv > bs) {
+            bs = sv;
+            bv = v;
+          }
         }
       }
+      simmax_step<0>(bs, bv);
+      simmax_step<1>(bs, bv);
+      simmax_step<2>(bs, bv);
+      simmax_step<3>(bs, bv);
+      if (sec) {
+        to = (p.rho > 0.0f && bs < p.rho) ? u : bv;
+        if (i == 0) s.remap[u] = to;
+      }
     }
-    simmax_step<0>(bs, bv);
-    simmax_step<1>(bs, bv);
-    simmax_step<2>(bs, bv);
-    simmax_step<3>(bs, bv);
-    if (sec && i == 0) s.remap[u] = (p.rho > 0.0f && bs < p.rho) ? u : bv;
+    if (i == 0 && u < M) target(u, to);
   }
+}
+
+// inclusive sum over the wavefront's lanes (DPP row shifts, then the row totals into the rows behind)
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /*row_shr:1*/, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /*row_bcast:15*/, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /*row_bcast:31*/, 0xC, 0xF, false);
+  return v;
 }
 
 // Per-expert results from the counts in s.cnt_b, s.cnt_a and the mask in s.prim: s.cursor[e] = offset of expert e
@@ -588,7 +620,7 @@ __device__ __forceinline__ void remap_secondary(const RouteArgs& p, RouteShared&
 // inclusive scans over experts: slots (-> offsets), activity (-> active
 // count) and work items (an expert's rows are cut into items of at most
 // item_rows rows, so that one long expert cannot hold up the FFN kernels);
-// inside each of the first four wavefronts by shuffles, across them through
+// inside each of the first four wavefronts by DPP, across them through
 // four totals in LDS
 __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s, bool write) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -600,16 +632,9 @@ __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s,
   const int my_items = (my_cnt + item_rows - 1) / item_rows;
   int inc_cnt = my_cnt, inc_act = my_act, inc_items = my_items;
   if (is_e) {  // wave-uniform (waves 0-3)
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int uc = __shfl_up(inc_cnt, d, kWave), ua = __shfl_up(inc_act, d, kWave);
-      const int ui = __shfl_up(inc_items, d, kWave);
-      if (lane >= d) {
-        inc_cnt += uc;
-        inc_act += ua;
-        inc_items += ui;
-      }
-    }
+    inc_cnt = wave_scan(inc_cnt);
+    inc_act = wave_scan(inc_act);
+    inc_items = wave_scan(inc_items);
     if (lane == kWave - 1) {
       s.scan_cnt[wave] = inc_cnt;
       s.scan_act[wave] = inc_act;
@@ -727,6 +752,21 @@ __device__ __forceinline__ void regroup_slots(const RouteArgs& p, RouteShared& s
   }
 }
 
+// what route_phase finds cleared: all threads, before a barrier
+__device__ __forceinline__ void clear_counts(RouteShared& s) {
+  const int tid = threadIdx.x;
+  if (tid < SERE_MAX_EXPERTS) {
+    s.cnt_b[tid] = 0;
+    s.cnt_a[tid] = 0;
+    s.cursor[tid] = 0;
+    s.prim[tid] = 0;
+    s.remap[tid] = tid;
+  }
+  static_assert(kRouteWaves * SERE_MAX_EXPERTS == 4 * kRouteThreads, "four counters a thread");
+  *reinterpret_cast<int4*>(&s.round_cnt[0][0] + 4 * tid) = int4{0, 0, 0, 0};
+}
+// (s.cursor: secondary slots of an expert, until scan_experts puts the offsets there; counting them while the lists are
+// merged was slower, 8.7 -> 10.5 us at 32 tokens: the atomics lengthen the one chain that everything waits for)
 template <bool IDS_IN_LDS, int NC>
 __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, const SimPrefetch<NC>& pf,
                                             bool prefetched = true) {
@@ -741,38 +781,29 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
                       : min(max(__hip_atomic_load(p.topk_ids + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0), M - 1);
   };
 
-  if (tid < SERE_MAX_EXPERTS) {
-    s.cnt_b[tid] = 0;
-    s.cnt_a[tid] = 0;
-    s.prim[tid] = 0;
-    s.remap[tid] = tid;
-  }
-  for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
-  lds_barrier();
-
   // Step 1: activation histogram and primary mask (union of every token's top-S)
   for (int a = tid; a < A; a += kRouteThreads) {
     const int e = id_at(a);
     atomicAdd(&s.cnt_b[e], 1);
-    if (a % K < S) s.prim[e] = 1;
+    if (a % K < S)
+      s.prim[e] = 1;
+    else
+      atomicAdd(&s.cursor[e], 1);
   }
   lds_barrier();
-  remap_secondary(p, s, pf, prefetched);
+  // Step 2, and the new map's counts: an expert's primary slots stay, its secondary ones all go to one expert
+  remap_secondary(p, s, pf, prefetched, [&](int u, int v) {
+    const int secondary = s.cursor[u], primary = s.cnt_b[u] - secondary;
+    if (primary > 0) atomicAdd(&s.cnt_a[u], primary);
+    if (secondary > 0) atomicAdd(&s.cnt_a[v], secondary);
+  });
   lds_barrier();
 
-  // Step 3: rewrite secondary slots, count the new map
-  for (int a = tid; a < A; a += kRouteThreads) {
-    const int e = id_at(a);
-    const int e2 = (a % K >= S) ? s.remap[e] : e;
-    p.rerouted_ids[a] = e2;
-    atomicAdd(&s.cnt_a[e2], 1);
-  }
-  lds_barrier();
-
+  // Step 3: offsets, then the slots regrouped and rewritten
   scan_experts(p, s, true);
   for (int i = tid; i < p.n_sh * p.T; i += kRouteThreads) p.sorted_token[A + i] = i % p.T;
   lds_barrier();
-  regroup_slots(p, s, 0, A, id_at, false);
+  regroup_slots(p, s, 0, A, id_at, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -814,7 +845,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p
   __shared__ int s_total[2 * SERE_MAX_EXPERTS], s_before[2 * SERE_MAX_EXPERTS];  // of all chunks / of the chunks before this one
   const int tid = threadIdx.x, M = p.M, chunks = gridDim.x, chunk = blockIdx.x;
   SimPrefetch<NC> pf;
-  prefetch_sim(p, pf);
+  prefetch_sim(p, pf, p.topk_ids);
   for (int i = tid; i < 2 * SERE_MAX_EXPERTS; i += kRouteThreads) s_total[i] = s_before[i] = 0;
   for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
   lds_barrier();
@@ -840,13 +871,11 @@ __global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p
     s.cnt_a[tid] = is_e ? s_total[tid] : 0;   // primary slots stay; the secondary ones are added below
   }
   lds_barrier();
-  remap_secondary(p, s, pf, true);
-  lds_barrier();
-  if (tid < M) {  // an expert's secondary slots all go to remap[e]
-    const int v = s.remap[tid], n = s_total[M + tid], b = s_before[M + tid];
+  remap_secondary(p, s, pf, true, [&](int u, int v) {  // an expert's secondary slots all go to v
+    const int n = s_total[M + u], b = s_before[M + u];
     if (n > 0) atomicAdd(&s.cnt_a[v], n);
     if (b > 0) atomicAdd(&s_before[v], b);
-  }
+  });
   lds_barrier();
   scan_experts(p, s, chunk == 0);
   lds_barrier();
@@ -862,7 +891,9 @@ __global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs p) {
   __shared__ RouteShared s;
   SimPrefetch<16> pf;  // any M up to 256
-  prefetch_sim(p, pf);
+  prefetch_sim(p, pf, p.topk_ids);
+  clear_counts(s);
+  lds_barrier();
   route_phase<false>(p, s, pf);
 }
 
@@ -883,24 +914,30 @@ __global__ __launch_bounds__(kRouteThreads) void topk_route_kernel(const uint64_
   // or 256 -- one wavefront per SIMD, the merge being bound by the vector ALU -- so that a batch
   // shared by several workgroups spreads over more compute units)
   const int group_tokens = p.topk_threads / LP;
-  // The similarity rows are requested before the top-K so that their latency hides behind it.
-  // Only the workgroup that runs the batch-wide step uses them, and which one that is is not
-  // known yet: with a handful of workgroups every one of them asks (the lines come from L2), with
-  // many the step is long anyway and the rows are loaded where they are needed instead.
-  SimPrefetch<NC> pf;
-  prefetch_sim(p, pf, gridDim.x <= kSimPrefetchMaxGroups && p.chunk_hist == nullptr);
   const int nlists = (p.M + 15) >> 4;
   const int t = blockIdx.x * group_tokens + threadIdx.x / LP;
   const bool lone = gridDim.x == 1 && p.T * p.K <= kIdsInLds;
   const bool in_group = static_cast<int>(threadIdx.x) < group_tokens * LP;
   const bool has = in_group && t < p.T;
   const int first_of_wave = blockIdx.x * group_tokens + (threadIdx.x >> 6) * (kWave / LP);
-  if (static_cast<int>(threadIdx.x & ~63u) < group_tokens * LP && first_of_wave < p.T) {  // wave-uniform: the wavefront has a token
-    const size_t tt = has ? t : 0;
-    topk_merge<LP, KS, KEEP>(list_key + tt * nlists * 16, list_id + tt * nlists * 16, has, nlists, topk_ids + tt * p.K,
-                       topk_w + tt * p.K,
-                       lone ? s.ids8 + tt * p.K
-                            : (p.chunk_hist != nullptr ? s.ids8 + (threadIdx.x / LP) * p.K : nullptr), p.K);
+  const bool merges = static_cast<int>(threadIdx.x & ~63u) < group_tokens * LP && first_of_wave < p.T;  // wave-uniform: the wavefront has a token
+  const size_t tt = has ? t : 0;
+  ListHead<KEEP> head;
+  load_lists<LP, KEEP>(list_key + tt * nlists * 16, list_id + tt * nlists * 16, nlists, head);
+  // The similarity rows are requested before the top-K so that their latency hides behind it, and after its lists, which the
+  // merge waits for (the other way round the launch takes 9.5 us instead of 9.0 at 32 tokens, 128 experts).  Only the workgroup that runs the batch-wide step uses
+  // them, and which one that is is not known yet: with a handful of workgroups every one of them asks (the lines come
+  // from L2), with many the step is long anyway and the rows are loaded where they are needed instead.
+  SimPrefetch<NC> pf;
+  prefetch_sim(p, pf, list_key, gridDim.x <= kSimPrefetchMaxGroups && p.chunk_hist == nullptr);
+  if (p.chunk_hist == nullptr) clear_counts(s);   // while the loads are on their way
+  if (merges) {
+    uint8_t* ids8 = lone ? s.ids8 + tt * p.K : (p.chunk_hist != nullptr ? s.ids8 + (threadIdx.x / LP) * p.K : nullptr);
+    topk_merge<LP, KS, KEEP>(head, has, nlists, topk_w + tt * p.K, p.K, [&](int k, int id) {
+      // a device-scope store: with several workgroups the ids are read by another one of this launch
+      __hip_atomic_store(topk_ids + tt * p.K + k, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (ids8 != nullptr) ids8[k] = static_cast<uint8_t>(id);
+    });
   }
   if (p.chunk_hist != nullptr) {  // the batch-wide step is a launch of its own: leave this chunk's counts
     __syncthreads();
