@@ -35,6 +35,7 @@ struct FfnShape {
 struct FfnPlan {
   int item_rows = kItemRows;
   bool tile_gate_up = false, tile_down = false;   // the persistent kernels of ffn_tile.hpp
+  bool wide_gate_up = false;                      // items of 256 rows: gate/up units of 256 weight rows instead of 128
   int ksplit = 1;                                 // slices of d_m in the down projection
 };
 
@@ -125,6 +126,19 @@ inline TileCost tile_costs(const FfnShape& s, const TileVariant& v, double gu_by
 }
 inline double gate_up_bytes(const FfnShape& s) { return (s.experts + s.num_shared) * 4.0 * s.hidden * s.inter; }
 
+// Items of 256 rows: a gate/up unit of 256 weight rows takes less of a compute unit's intake per product than two of 128, 2.2
+// us a step against 2.4, but half as many units fill a round less evenly (us a launch, 256 rows an expert: 128 experts of the
+// Qwen3 shape 210 -> 199, 60 experts of d_m 1408 206 -> 190, 40 of d_h 1024, d_m 768 86 -> 77; 60 experts of d_m 768, 1.4
+// rounds for 2.8, 213 -> 241).  For items that are known (spread 0): where the rows per expert are only expected it lost as
+// often as it gained (130 decode layers).  Down units of that size gained nothing (157 -> 156, 128 experts; 155 -> 158).
+inline bool wide_gate_up_pays(const FfnShape& s, const FfnPlan& p) {
+  constexpr double kWideStep = 1.5;
+  if (s.split_h || s.spread > 0.0 || p.item_rows != 256 || !p.tile_gate_up) return false;
+  const TileVariant wide{256, 128, 256, kWideStep, kWideStep}, narrow{256, 64, 128, 0.84, 0.84};
+  const double bytes = gate_up_bytes(s);
+  return tile_costs(s, wide, bytes).gate_up < 0.95 * tile_costs(s, narrow, bytes).gate_up;
+}
+
 inline FfnPlan plan_ffn(const FfnShape& s) {
   const double gu_bytes = gate_up_bytes(s), dn_bytes = 0.5 * gu_bytes;
   FfnPlan best;
@@ -153,6 +167,7 @@ inline FfnPlan plan_ffn(const FfnShape& s) {
       best = p;
     }
   }
+  best.wide_gate_up = wide_gate_up_pays(s, best);
   return best;
 }
 
@@ -173,6 +188,7 @@ inline FfnPlan plan_ffn_tile(const FfnShape& s, int ksplit) {
       best.ksplit = t.ksplit;
     }
   }
+  best.wide_gate_up = wide_gate_up_pays(s, best);
   return best;
 }
 

@@ -5,7 +5,7 @@
 // from HBM at about 3 us of latency under load, so 27 GB/s per compute unit (7 TB/s for the chip)
 // needs some 80 KB on their way at all times, next to the token rows, which come from L2.  Loads
 // into registers cannot hold that; the 160 KB of LDS can: global_load_lds writes a stage of weight
-// and token rows straight into a ring of three or four stages (36 to 52 KB each; fp32: eight of
+// and token rows straight into a ring of two to four stages (36 to 64 KB each; fp32: eight of
 // 20 KB), nothing passes through registers until the matrix cores read it.
 //
 //  - A unit of work is BM weight rows x all token rows of a work item (at most BN) over the whole
@@ -102,7 +102,7 @@ struct TileShape {
   static constexpr int kWaveRows = BM * WN / kTileWaves;            // weight rows of a wavefront
   static constexpr int kWeightTiles = kWaveRows / kTile;
   static_assert(kWeightTiles % 2 == 0 && BM % (kLoadRows * kTileWaves) == 0, "gate and up rows pair up inside a wavefront");
-  static_assert(kRealRows % (kTile * WN) == 0 && kStages >= 3, "the ring holds a stage in use and two on their way");
+  static_assert(kRealRows % (kTile * WN) == 0 && kStages >= 2, "the ring holds a stage in use and one on its way");
 };
 
 template <int... I, typename F>
@@ -366,10 +366,11 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     const int used = slot;
     slot = slot + 1 == S ? 0 : slot + 1;
     fetch(f0, slot, 0);
-    // the loads of a stage, spread over the first three quarters of the products (one token tile: before them all)
+    // the loads of a stage, spread over the first three quarters of the products (one token tile: before them all; two
+    // stages: over the first quarter, they are waited for at the end of the same products)
     auto loads = [&](auto half) __attribute__((always_inline)) {
       return [&](auto t) __attribute__((always_inline)) {
-        constexpr int h = decltype(half)::value * NT + decltype(t)::value, groups = NT == 1 ? 1 : (3 * NT + 1) / 2;
+        constexpr int h = decltype(half)::value * NT + decltype(t)::value, groups = NT == 1 ? 1 : S == 2 ? NT / 2 : (3 * NT + 1) / 2;
         constexpr int n0 = std::min(P, h * P / groups), n1 = std::min(P, (h + 1) * P / groups);
         if (n0 < n1 && more) issue_some(used, std::integral_constant<int, n0>{}, std::integral_constant<int, n1>{});
       };

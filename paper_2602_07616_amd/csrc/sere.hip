@@ -349,22 +349,29 @@ static void launch_tile_as(const FfnArgs& f, hipStream_t s) {
                dim3(kTileThreads), f);
 }
 template <bool GATEUP>
-static void launch_tile(int item_rows, const FfnArgs& f, hipStream_t s) {
+static void launch_tile(const FfnPlan& plan, const FfnArgs& f, hipStream_t s) {
   if (!GATEUP && f.split_h) {  // both planes of the token rows count in the second size
-    switch (item_rows) {
+    switch (plan.item_rows) {
       case 32: launch_tile_as<SERE_BF16, false, 256, 64, 2, true>(f, s); return;
       case 64: launch_tile_as<SERE_BF16, false, 256, 128, 2, true>(f, s); return;
       default: launch_tile_as<SERE_BF16, false, 128, 256, 4, true>(f, s); return;
     }
   }
-  switch (item_rows) {
+  switch (plan.item_rows) {
     case 32: launch_tile_as<SERE_BF16, GATEUP, 256, 32, 2>(f, s); return;
     case 64: launch_tile_as<SERE_BF16, GATEUP, 256, 64, 2>(f, s); return;
     case 96: launch_tile_as<SERE_BF16, GATEUP, 256, 96, 2>(f, s); return;
     case 128: launch_tile_as<SERE_BF16, GATEUP, 256, 128, 2>(f, s); return;
     case 160: launch_tile_as<SERE_BF16, GATEUP, 256, 160, 2>(f, s); return;
     case 192: launch_tile_as<SERE_BF16, GATEUP, 128, 192, 4>(f, s); return;
-    default: launch_tile_as<SERE_BF16, GATEUP, 128, 256, 4>(f, s); return;
+    default:
+      if constexpr (GATEUP) {
+        if (plan.wide_gate_up) {
+          launch_tile_as<SERE_BF16, true, 256, 256, 4>(f, s);
+          return;
+        }
+      }
+      launch_tile_as<SERE_BF16, GATEUP, 128, 256, 4>(f, s);
   }
 }
 
@@ -384,13 +391,13 @@ static void launch_gateup_down(int dtype, int inter, int hidden, int max_work, c
     return;
   }
   if (plan.tile_gate_up)
-    launch_tile<true>(plan.item_rows, f, s);
+    launch_tile<true>(plan, f, s);
   else if (waves8)
     launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<8>, dim3(inter / (kGateUpJ * 8), max_work), dim3(512), f);
   else
     launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<4>, dim3(inter / (kGateUpJ * 4), max_work), dim3(256), f);
   if (plan.tile_down)
-    launch_tile<false>(plan.item_rows, f, s);
+    launch_tile<false>(plan, f, s);
   else
     launch_stage(SERE_STAGE_DOWN, s, ffn_down_mfma,
                  dim3(((hidden + kDownRows * kWavesPerBlock - 1) / (kDownRows * kWavesPerBlock)) * plan.ksplit, max_work),
