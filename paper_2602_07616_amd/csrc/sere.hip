@@ -536,6 +536,28 @@ static int check_similarity_sizes(const sere_config& c, int32_t num_batches, int
   return SERE_OK;
 }
 
+// up to 64 experts, in tiles of 16
+static void launch_pair_gram_few(bool cosine, dim3 grid, const float* y, int ksplit, int rows, int n, int dh, int M, long long chunk,
+                                 double* part, const double* inv_norm, unsigned long long* max_bits, hipStream_t s) {
+#define SERE_LAUNCH_FEW(TILES)                                                                                          \
+  if (cosine)                                                                                                           \
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_few_kernel<TILES, true>, grid, dim3(256), y, ksplit, rows, n, dh, M, \
+                 chunk, part, inv_norm, max_bits);                                                                      \
+  else                                                                                                                  \
+    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_few_kernel<TILES, false>, grid, dim3(256), y, ksplit, rows, n, dh,  \
+                 M, chunk, part, inv_norm, max_bits)
+  if (M <= 16) {
+    SERE_LAUNCH_FEW(1);
+  } else if (M <= 32) {
+    SERE_LAUNCH_FEW(2);
+  } else if (M <= 48) {
+    SERE_LAUNCH_FEW(3);
+  } else {
+    SERE_LAUNCH_FEW(4);
+  }
+#undef SERE_LAUNCH_FEW
+}
+
 // One group: g batches from calibration batch b0 on.
 static void similarity_group(const sere_config& c, const SimLayout& l, const char* calib, int b0, int g, bool new_list, int num_batches,
                              int n, const void* w_gate_up, const void* w_down, int cka_kernel, double p0, double p1, float* sim,
@@ -600,6 +622,10 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
     if (metric == kMetricCosine) {
       launch_stage(SERE_STAGE_SIM_PAIRS, s, row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), f.y, f.ksplit, l.rows, dh,
                    const_cast<double*>(inv_norm));
+    }
+    if (M <= kGramBlock) {
+      launch_pair_gram_few(metric == kMetricCosine, blocks, y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part, inv_norm, max_bits, s);
+    } else if (metric == kMetricCosine) {
       launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<true>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
                    l.gram_chunk, part, inv_norm, max_bits);
     } else if (l.gram_staged) {

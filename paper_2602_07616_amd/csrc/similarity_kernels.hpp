@@ -72,7 +72,7 @@ __device__ __forceinline__ void gram_block_of(int index, int nb, int& bp, int& b
 // 4 (l / 16) ... + 3 (the order of k inside the sum is free as long as both operands agree).
 // `chunk` (the split's length) is a multiple of 2 * 16 * kGramSteps (= 64, as L is).  blockIdx.z: batch of
 // the group.
-// Serves the cosine metric, y in slices, and the groups for which the staged kernel below is the slower one
+// More than 64 experts: the cosine metric, y in slices, and the groups for which the staged kernel below is the slower one
 // (gram_staged_pays).  43 TFLOP/s at 128 experts, 128 tokens, d_h 2048 (147 us a batch; the fp64 matrix cores reach
 // 69 in a large product).  Neither more workgroups (three for every compute unit instead of one and a half) nor
 // four independent sums between two products of one changed that: it waits for its operands.
@@ -181,6 +181,108 @@ __global__ __launch_bounds__(256) void pair_gram_kernel(const float* __restrict_
         const int pp = p0 + 16 * a + kq + 4 * r, qq = q0 + 16 * b + r16;
         if (pp < M && qq < M) out[static_cast<size_t>(pp) * M + qq] = acc[a][b][r];
       }
+}
+
+// The same for up to 64 experts, 16 TILES of them: a wavefront holds all tiles of the upper triangle (10 at most, where the
+// kernel above computes 16 whatever M is) and reads every row once for them; the four wavefronts of a workgroup take every
+// fourth group of k and add up through LDS in a fixed order.  Bound by the fp64 matrix cores at 64 experts and by reading y at
+// 16.  us of the pair stage, 64 x 64 blocks against this (with the unrolled reduction below), four batches of 128 tokens, d_h
+// 2048: 60 experts 206 -> 131, 16 experts 184 -> 44, 8 experts with the cosine metric 198 -> 50; 40 experts, d_h 1024 116 -> 61;
+// 64 experts, four batches of 16 tokens 39 -> 32.
+// grid (1, nsplit, g), 256 threads.
+template <int TILES, bool COSINE>
+__global__ __launch_bounds__(256) void pair_gram_few_kernel(const float* __restrict__ y, int ksplit, int rows, int n, int dh, int M,
+                                                            long long chunk, double* __restrict__ part,
+                                                            const double* __restrict__ inv_norm,
+                                                            unsigned long long* __restrict__ max_bits) {
+  constexpr int kPairs = TILES * (TILES + 1) / 2;
+  // 16-wide k steps of a group: enough bytes in flight; with COSINE a group (64 k at most) lies in one token
+  constexpr int kSteps = TILES == 1 ? (COSINE ? 4 : 8) : TILES == 2 ? 4 : 2;
+  __shared__ double s_part[4][kPairs * 4][kWave];
+  if (!COSINE && blockIdx.y == 0 && threadIdx.x == 0) max_bits[blockIdx.z] = 0ull;   // for frobenius_distance_kernel
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const long long L = static_cast<long long>(n) * dh;             // multiple of 64
+  const size_t slice = static_cast<size_t>(rows) * dh;
+  const int g = gridDim.z, batch = blockIdx.z;
+  const long long kbeg = blockIdx.y * chunk, kend = min(kbeg + chunk, L);   // multiples of 64
+  const int steps = static_cast<int>((kend - kbeg) / 16);
+  const float* row[TILES];
+  const double* inv[TILES];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) {   // rows beyond M repeat the last one (their results are not stored)
+    const size_t r = static_cast<size_t>(min(16 * t + r16, M - 1)) * g + batch;
+    row[t] = y + r * L + kbeg + 4 * kq;
+    inv[t] = inv_norm + r * n;
+  }
+  f64x4 acc[kPairs];
+#pragma unroll
+  for (int c = 0; c < kPairs; ++c) acc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+  float4 v[2][kSteps][TILES];
+  double scale[2][TILES];
+  auto fetch = [&](int buf, int first) {   // a step beyond the last re-reads that one and is not used
+    if constexpr (COSINE) {
+      const int token = static_cast<int>(kbeg + 16 * min(first, steps - 1)) / dh;   // L is below 2^29
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) scale[buf][t] = inv[t][token];
+    }
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st)
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) {
+        const float* at = row[t] + 16 * min(first + st, steps - 1);
+        float4 x = *reinterpret_cast<const float4*>(at);
+        for (int s = 1; s < ksplit; ++s) {
+          const float4 x2 = *reinterpret_cast<const float4*>(at + s * slice);
+          x.x += x2.x; x.y += x2.y; x.z += x2.z; x.w += x2.w;
+        }
+        v[buf][st][t] = x;
+      }
+  };
+  auto multiply = [&](int buf, int first) {
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st)
+      if (first + st < steps) {   // wave-uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          double x[TILES];
+#pragma unroll
+          for (int t = 0; t < TILES; ++t) {
+            x[t] = static_cast<double>(reinterpret_cast<const float*>(&v[buf][st][t])[j]);
+            if constexpr (COSINE) x[t] *= scale[buf][t];
+          }
+          int c = 0;
+#pragma unroll
+          for (int a = 0; a < TILES; ++a)
+#pragma unroll
+            for (int b = a; b < TILES; ++b, ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a], x[b], acc[c], 0, 0, 0);
+        }
+      }
+  };
+  int at = wave * kSteps;
+  fetch(0, at);
+  for (; at < steps; at += 8 * kSteps) {
+    fetch(1, at + 4 * kSteps);
+    multiply(0, at);
+    fetch(0, at + 8 * kSteps);
+    multiply(1, at + 4 * kSteps);
+  }
+#pragma unroll
+  for (int c = 0; c < kPairs; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_part[wave][4 * c + r][lane] = acc[c][r];
+  __syncthreads();
+  // wavefront w finishes register w of every tile: lane l holds D[l / 16 + 4 r][l % 16]
+  double* out = part + (static_cast<size_t>(batch) * gridDim.y + blockIdx.y) * gram_part_stride(M);
+  int c = 0;
+#pragma unroll
+  for (int a = 0; a < TILES; ++a)
+#pragma unroll
+    for (int b = a; b < TILES; ++b, ++c) {
+      const int reg = 4 * c + wave, pp = 16 * a + kq + 4 * wave, qq = 16 * b + r16;
+      const double sum = ((s_part[0][reg][lane] + s_part[1][reg][lane]) + s_part[2][reg][lane]) + s_part[3][reg][lane];
+      if (pp < M && qq < M) out[static_cast<size_t>(pp) * M + qq] = sum;
+    }
 }
 
 // The same partial Gram matrices (Frobenius metric, y in one slice, where gram_staged_pays) with the operands
@@ -344,7 +446,8 @@ __global__ __launch_bounds__(kGramStagedThreads) void pair_gram_staged_kernel(co
 // splits r, r + kGramGroups, ... (this kernel; entries below the diagonal of 16 x 16 tiles are
 // copies of their mirror image), and the distance kernel adds the kGramGroups group sums.
 // Only the upper entries are summed, in rows, and written twice: 8 us for 128 experts and 256 splits, against 28 with
-// the lower entries read down the columns of their mirror image.
+// the lower entries read down the columns of their mirror image.  Eight splits are requested together: with one after the other
+// 40 experts took 10 us, 16 experts as long, now 5.
 // grid (ceil(M * M / 256), kGramGroups, g), 256 threads.
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, int nsplit, int M,
                                                           double* __restrict__ gram) {
@@ -355,6 +458,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
   const size_t mm = gram_part_stride(M);
   const double* src = part + static_cast<size_t>(blockIdx.z) * nsplit * mm + idx;
   double g = 0.0;
+#pragma unroll 8
   for (int s = blockIdx.y; s < nsplit; s += kGramGroups) g += src[s * mm];
   double* out = gram + (static_cast<size_t>(blockIdx.z) * kGramGroups + blockIdx.y) * M * M;
   out[idx] = g;

@@ -11,7 +11,8 @@
 
 namespace sere {
 
-constexpr int kGramBlock = 64;     // experts per side of a block of pair_gram_kernel: 2 x 2 wavefronts, each 2 x 2 tiles of 16 x 16
+constexpr int kGramBlock = 64;     // experts per side of a block of pair_gram_kernel: 2 x 2 wavefronts, each 2 x 2 tiles of 16 x 16; up to
+                                   // that many experts pair_gram_few_kernel
 constexpr int kGramGroups = 8;     // group sums that gram_reduce_kernel leaves
 // partial Gram matrices lie M * M + kGramPad doubles apart: a power-of-two distance would put the
 // same entry of every split on the same memory channel
@@ -82,7 +83,7 @@ inline FfnPlan sim_ffn_plan(const sere_config& c, int n, int g, int whole) {
 // all batches of a group.  us of the pair stage, kernel of 64 x 64 blocks against staged:
 //  - One triangle, 65 to 128 experts: a workgroup takes a whole compute unit, so short groups lose (length 8192:
 //    25 / 36, 32768: 1.05 times), longer ones gain (49152: 0.88 times, 128 experts: 65536 55 / 48, 262144 0.79 times,
-//    524288 300 / 180).  Up to 64 experts the triangle computes 36 tiles for 16 (102 / 164).
+//    524288 300 / 180).  Up to 64 experts pair_gram_few_kernel computes no tile that is not needed.
 //  - Beyond, two triangles and two squares take as long as four triangles (129 to 192 experts: 1.4 times), and two with
 //    all four squares 1.08 times.  But a row every multiple of 2 MiB puts the rows that the other kernel reads
 //    together on the same memory channels: 256 experts of length 524288 970 / 790, of 1048576 1890 / 1520 (of 518400
