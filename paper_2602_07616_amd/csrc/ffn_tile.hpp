@@ -32,12 +32,12 @@
 // Measured on the Qwen3 shape (d_h 2048, d_m 768, 128 experts), us per launch, gate/up + down, within steps on four
 // copies of the weights in turn, against the kernels with eight wavefronts that staged token rows through registers,
 // both on one card that has been busy for some 20 ms (from idle the first steps take a tenth longer):
-//   tokens   128: 111 + 60 -> 106 + 59     512: 140 + 81 -> 128 + 76    1024: 153 + 94 -> 136 + 86
-//           2048: 212 + 119 -> 155 + 112   3072: 242 + 145 -> 223 + 145   4096: 371 + 198 -> 290 + 186
+//   tokens   128: 111 + 60 -> 104 + 58     512: 140 + 81 -> 127 + 75    1024: 153 + 94 -> 137 + 89
+//           2048: 212 + 119 -> 143 + 109   3072: 242 + 145 -> 208 + 140   4096: 371 + 198 -> 261 + 179
 // (2048 tokens, items of 160 rows: while no expert has more.  Where one does, its second item makes the launch start a
-// fourth round of units on every compute unit: 190 + 129.)
-// fp32 layers against the vector-ALU kernels: 150 + 111 -> 64 + 39 us at 96 tokens (d_h 1024, d_m 704, 32 experts),
-// 67 + 49 -> 33 + 11 at 180 tokens (d_h 1024, d_m 192, 15 experts); relative error of the layer 1.8e-7 -> 1.4e-7.
+// fourth round of units on every compute unit: 173 + 124.)
+// fp32 layers against the vector-ALU kernels: 150 + 111 -> 57 + 37 us at 96 tokens (d_h 1024, d_m 704, 32 experts);
+// relative error of the layer 1.8e-7 -> 1.4e-7.
 // Not faster, one launch over and over: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens);
 // the same first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
 #pragma once
