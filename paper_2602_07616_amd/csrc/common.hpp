@@ -119,10 +119,17 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
-// Where the result is rounded to bf16: v_rcp_f32 (1 ulp) in place of the dozen instructions of a division.  With the
-// conversion by v_cvt_pk_bf16_f32 instead of integer arithmetic the end of a unit of 128 weight rows x 256 tokens costs
-// less vector ALU time (us, gate/up: 256 rows an expert 222 -> 209, 2048 tokens of the Qwen3 shape 147 -> 142, 777 tokens of
-// d_h 2880 165 -> 161); the layer's error against 64 bits, that of the bf16 rounding, stays as it is.
-__device__ __forceinline__ float silu_for_bf16(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+// The same quotient for the kernels of bf16 layers (h, in one bf16 plane or two, is what it goes into): v_rcp_f32 and one step on the
+// quotient in place of a division's dozen instructions.  Of all 2^32 arguments only -0 gives other bits than the division (+0
+// for -0; a sum that starts at 0 is never -0).  Beyond 2^126 the reciprocal is below the normal numbers and v_rcp_f32 would
+// return 0, hence the scaling: z of -88.7 to -87.3, where silu is some 1e-37.  Where 1 + exp(-z) or z is infinite the step gives a
+// NaN and q is the answer.  With the conversion by v_cvt_pk_bf16_f32 instead of integer arithmetic the end of a unit of 128
+// weight rows x 256 tokens costs less vector ALU time (us, gate/up: 256 rows an expert 222 -> 209, 2048 tokens of the Qwen3
+// shape 147 -> 142, 777 tokens of d_h 2880 165 -> 161; without the step and the scaling within 0.2 % of that).
+__device__ __forceinline__ float silu_for_bf16(float z) {
+  const float d = 1.0f + __expf(-z), r = 0.25f * __builtin_amdgcn_rcpf(0.25f * d), q = z * r;
+  const float next = fmaf(fmaf(-d, q, z), r, q);
+  return __builtin_amdgcn_fmed3f(next, next, q);   // q where the step is a NaN
+}
 
 }  // namespace sere
