@@ -79,11 +79,12 @@ inline double stream_us(double bytes, double near_rate, double far_rate) {
   constexpr double kNear = 1.3e8;
   return std::min(bytes, kNear) / near_rate + std::max(0.0, bytes - kNear) / far_rate;
 }
+inline double unit_rounds(double units) { return std::max(1.0, std::ceil(units / kTileGroups - 0.02)); }
 // us of a launch of the persistent kernels: rounds of 256 units, each its k steps and `change` us to change units
 // (down stores y, four times the bytes of h), but no less than the weights take, and 2.8 us to fill the ring.
 // With few units a step is bound by latency alone and a little shorter.
 inline double tile_cost(double units, double steps, double step_us, double change, double weight_bytes) {
-  const double rounds = std::max(1.0, std::ceil(units / kTileGroups - 0.02));
+  const double rounds = unit_rounds(units);
   const double busy = std::min(1.0, std::max(0.8, units / rounds / kTileGroups));
   return std::max(rounds * (steps * step_us * busy + change), stream_us(weight_bytes, 9.8e6, 5.8e6)) + 2.8;
 }
@@ -112,6 +113,7 @@ inline int tile_ksplit(const FfnShape& s, double units, double step_us, double w
   return best;
 }
 
+constexpr double kGateUpChange = 0.9;   // us to change gate/up units
 // us of the two launches of the persistent kernels with items of v.rows, and the slices of the second
 struct TileCost {
   double gate_up, down;
@@ -120,23 +122,35 @@ struct TileCost {
 inline TileCost tile_costs(const FfnShape& s, const TileVariant& v, double gu_bytes, int ksplit = 0) {
   TileCost t;
   const double items = total_items(s, v.rows);
-  t.gate_up = tile_cost(items * std::ceil(static_cast<double>(s.inter) / v.gate_up_out), s.hidden / 64, v.gate_up_step, 0.9, gu_bytes);
+  t.gate_up = tile_cost(items * std::ceil(static_cast<double>(s.inter) / v.gate_up_out), s.hidden / 64, v.gate_up_step, kGateUpChange,
+                        gu_bytes);
   t.ksplit = tile_ksplit(s, items * std::ceil(static_cast<double>(s.hidden) / v.down_out), v.down_step, 0.5 * gu_bytes, ksplit, &t.down);
   return t;
 }
 inline double gate_up_bytes(const FfnShape& s) { return (s.experts + s.num_shared) * 4.0 * s.hidden * s.inter; }
 
-// Items of 256 rows: a gate/up unit of 256 weight rows takes less of a compute unit's intake per product than two of 128, 2.2
-// us a step against 2.4, but half as many units fill a round less evenly (us a launch, 256 rows an expert: 128 experts of the
-// Qwen3 shape 210 -> 199, 60 experts of d_m 1408 206 -> 190, 40 of d_h 1024, d_m 768 86 -> 77; 60 experts of d_m 768, 1.4
-// rounds for 2.8, 213 -> 241).  For items that are known (spread 0): where the rows per expert are only expected it lost as
-// often as it gained (130 decode layers).  Down units of that size gained nothing (157 -> 156, 128 experts; 155 -> 158).
+// Items of 256 rows: a gate/up unit of 256 weight rows takes less of a compute unit's intake per product than two of 128, but
+// half as many units fill a round less evenly (us a launch, 256 rows an expert: 128 experts of the Qwen3 shape 210 -> 199,
+// three rounds of 32 steps for six, 60 experts of d_m 1408 206 -> 190, 40 of d_h 1024, d_m 768 86 -> 77; 60 experts of d_m 768,
+// 1.4 rounds for 2.8, 213 -> 241).  The steps are those of weights that come from cache, like the ones of tile_variants.  A
+// part-filled round of these units is no shorter than a full one, as tile_cost takes it to be for the narrower ones, so their
+// rounds have to be the shorter ones without that, too.  us a call of 59 layers whose tokens select all 1 to 16 experts, by the
+// rounds' time against that of the units of 128: below 0.9 times 3 to 9 % less (157.6 -> 150.2; one layer the same), 0.9 to 1.0
+// times 1 % more to 6 % less, 1.0 to 1.04 times 2 % less to 2 % more, beyond 1 to 8 % more (127.8 -> 134.1).
+// For items that are known, or all but known (spread 0): similarity calls, where every expert has every token, and
+// layers whose tokens select every expert (K = M; re-routing that takes an expert out gives its rows to another, and the
+// number of items stays about the same: 12 layers with S = 1 gained as much as without re-routing).  Where the rows per
+// expert are only expected it lost as often as it gained (130 decode layers).  Down units of that size gained nothing
+// (157 -> 156, 128 experts; 155 -> 158).
 inline bool wide_gate_up_pays(const FfnShape& s, const FfnPlan& p) {
-  constexpr double kWideStep = 1.5;
   if (s.split_h || s.spread > 0.0 || p.item_rows != 256 || !p.tile_gate_up) return false;
-  const TileVariant wide{256, 128, 256, kWideStep, kWideStep}, narrow{256, 64, 128, 0.84, 0.84};
+  const TileVariant wide{256, 128, 256, 1.5, 1.5}, narrow{256, 64, 128, 0.84, 0.84};
+  const auto rounds_us = [&](const TileVariant& v) {
+    return unit_rounds(total_items(s, v.rows) * std::ceil(static_cast<double>(s.inter) / v.gate_up_out)) *
+           (s.hidden / 64 * v.gate_up_step + kGateUpChange);
+  };
   const double bytes = gate_up_bytes(s);
-  return tile_costs(s, wide, bytes).gate_up < 0.95 * tile_costs(s, narrow, bytes).gate_up;
+  return rounds_us(wide) < rounds_us(narrow) && tile_costs(s, wide, bytes).gate_up < 0.95 * tile_costs(s, narrow, bytes).gate_up;
 }
 
 inline FfnPlan plan_ffn(const FfnShape& s) {

@@ -1,12 +1,14 @@
-// Prints the plan of every input line, "item_rows tile_gate_up tile_down ksplit".  Lines without an argument, or with "f32" (an
-// fp32 layer): "hidden inter shared tokens experts rows spread slots split max_ksplit"; with "call":
+// Prints the plan of every input line, "item_rows tile_gate_up tile_down ksplit wide_gate_up".  Lines without an argument, or
+// with "f32" (an fp32 layer): "hidden inter shared tokens experts rows spread slots split max_ksplit"; with "call":
 // "dtype tokens hidden experts top_k inter shared S rho reroute", a call of the library.  Host code only.
 #include <cstdio>
 #include <cstring>
 
 #include "../paper_2602_07616_amd/csrc/ffn_plan.hpp"
 
-static void print(const sere::FfnPlan& p) { std::printf("%d %d %d %d\n", p.item_rows, p.tile_gate_up, p.tile_down, p.ksplit); }
+static void print(const sere::FfnPlan& p) {
+  std::printf("%d %d %d %d %d\n", p.item_rows, p.tile_gate_up, p.tile_down, p.ksplit, p.wide_gate_up);
+}
 
 int main(int argc, char** argv) {
   if (argc > 1 && std::strcmp(argv[1], "call") == 0) {

@@ -8,7 +8,7 @@ import subprocess
 import pytest
 
 from paper_2602_07616_amd import binding as B, workloads as wk
-from . import test_gpu_ffn_tile as gpu
+from . import test_gpu_ffn_tile as gpu, test_gpu_wide_gate_up as gpu_wide
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -41,7 +41,7 @@ def test_every_plan_can_be_run(plans):
         layer = (log_int(1, 65536), 64 * log_int(1, 1024), M, K, 64 * log_int(1, 4096), rng.choice([0, 0, 1, 4, 16]), rng.randint(1, K))
         layers.append(layer)
         cases.append(shape(*layer))
-    for layer, case, (rows, tile_gu, tile_dn, ksplit) in zip(layers, cases, plans(cases)):
+    for layer, case, (rows, tile_gu, tile_dn, ksplit, wide) in zip(layers, cases, plans(cases)):
         blocks, split, max_ksplit = layer[4] // 64, case[8], case[9]
         assert rows in ((32, 64, 128) if split else (32, 64, 96, 128, 160, 192, 256)), layer
         if not (tile_gu and tile_dn):
@@ -50,6 +50,7 @@ def test_every_plan_can_be_run(plans):
         assert (ksplit - 1) * -(-blocks // ksplit) < blocks, layer   # no slice of d_m is empty
         if not tile_dn:
             assert ksplit == max_ksplit, layer
+        assert not wide or (rows == 256 and tile_gu and not split), layer
 
 
 def test_choices_on_the_layers_the_rule_was_measured_on(plans):
@@ -63,13 +64,35 @@ def test_fp32_plans(plans):
     """fp32 layers: items of 32 rows, no slices; batches of more than 8 tokens run on the persistent kernels."""
     layers = [(T, dh, 17, 4, dm, sh, 4) for T in (1, 2, 8, 9, 96, 4096) for dh in (64, 256, 1472) for dm in (64, 704) for sh in (0, 2)]
     cases = [shape(*layer)[:9] + (1,) for layer in layers]
-    for layer, (rows, tile_gu, tile_dn, ksplit) in zip(layers, plans(cases, "f32")):
-        assert (rows, ksplit) == (32, 1) and tile_gu == tile_dn, layer
+    for layer, (rows, tile_gu, tile_dn, ksplit, wide) in zip(layers, plans(cases, "f32")):
+        assert (rows, ksplit, wide) == (32, 1, 0) and tile_gu == tile_dn, layer
         assert tile_gu or layer[0] <= 8, layer
 
 
 def call(dtype, T, dh, M, K, dm, sh, S, rho=0.0):
     return (dtype, T, dh, M, K, dm, sh, S, rho, 1)
+
+
+# (T, d_h, M, d_m, shared) with K = M: the gate/up units of 256 weight rows took 4 % to 6 % less time for the whole call, or more
+WIDE_IS_FASTER = [(1000, 2048, 5, 1536, 0), (1000, 512, 8, 2560, 1), (1000, 4096, 3, 1408, 1), (1500, 2048, 8, 512, 1),
+                  (397, 1536, 3, 3584, 1), (200, 1024, 5, 3584, 1), (1137, 384, 10, 1216, 0)]
+WIDE_IS_SLOWER = [(1500, 1024, 8, 1024, 0), (873, 1088, 10, 1216, 0), (2426, 384, 2, 3264, 1), (459, 512, 14, 1600, 1),
+                  (1789, 576, 4, 1728, 0), (1475, 384, 3, 2624, 0)]
+
+
+def test_wide_gate_up_units_only_where_their_rounds_are_shorter(plans):
+    for layers, wide in ((WIDE_IS_FASTER, 1), (WIDE_IS_SLOWER, 0)):
+        for reroute, S in ((0, 1), (1, 1)):
+            cases = [(B.SERE_BF16, T, dh, M, M, dm, sh, S, 0.0, reroute) for T, dh, M, dm, sh in layers]
+            assert [p[0] for p in plans(cases, "call")] == [256] * len(cases)
+            assert [p[4] for p in plans(cases, "call")] == [wide] * len(cases), (layers, reroute)
+
+
+def test_pairs_of_the_wide_kernel_and_the_narrow_one(plans):
+    """What the comparison of their bits takes for granted: the longer batch by units of 128, all else alike."""
+    for (dh, M, dm, sh), batches in gpu_wide.PAIRS:
+        few, many = plans([(B.SERE_BF16, T, dh, M, M, dm, sh, M, 0.0, 0) for T in batches], "call")
+        assert (few[4], many[4]) == (1, 0) and few[:4] == many[:4], (dh, M, dm, sh)
 
 
 def test_gpu_cases_get_the_plans_they_are_there_for(plans):
@@ -84,12 +107,12 @@ def test_gpu_cases_reach_every_kernel_of_a_plan(plans):
     """Over a draw of all accepted layers no plan launches a kernel that the GPU cases (and the Mixtral-shaped layer of the
     parity tests: gate/up by the decode kernels next to the persistent down kernel) do not."""
     def kernels(inter, plan):
-        rows, tile_gu, tile_dn, _ = plan
+        rows, tile_gu, tile_dn, _, wide = plan
         split = inter >= 4096
-        return {("gate_up", rows if tile_gu else 0), ("down", rows if tile_dn else 0, split)}
+        return {("gate_up", rows if tile_gu else 0, wide), ("down", rows if tile_dn else 0, split)}
     spec = wk.SPECS["mixtral_b64"]
     mixtral = plans([call(spec.dtype, spec.tokens, spec.hidden, spec.experts, spec.top_k, spec.inter, spec.shared, 1)], "call")[0]
-    assert mixtral == (32, 0, 1, 2)
+    assert mixtral == (32, 0, 1, 2, 0)
     tested = kernels(spec.inter, mixtral).union(*(kernels(c[4], p) for c, p in gpu.CASES.items()))
     rng = random.Random(6)
     log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
@@ -103,4 +126,4 @@ def test_gpu_cases_reach_every_kernel_of_a_plan(plans):
     for c, p in zip(cases, plans(cases, "call")):
         reached |= kernels(c[5], p)
     assert reached - tested <= {("down", 0, False), ("down", 0, True)}    # the decode kernels, which most other tests run
-    assert {("gate_up", r) for r in (32, 64, 96, 128, 160, 192, 256)} <= reached
+    assert {("gate_up", r, 0) for r in (32, 64, 96, 128, 160, 192, 256)} | {("gate_up", 256, 1)} <= reached

@@ -14,24 +14,28 @@ from .test_gpu_parity import check_output, check_routing, dev, pairs_with_counts
 
 pytestmark = pytest.mark.gpu
 
-# (T, d_h, M, K, d_m, shared): (item rows, gate/up and down by the persistent kernels, slices of d_m); d_m >= 4096: both planes
+# (T, d_h, M, K, d_m, shared): (item rows, gate/up and down by the persistent kernels, slices of d_m, gate/up in units of
+# 256 weight rows although the items have 256); d_m >= 4096: both planes
 CASES = {
-    (33, 320, 2, 2, 1472, 1): (32, 1, 0, 1),     # down by the other kernels
-    (500, 1024, 42, 2, 320, 1): (32, 1, 1, 1),
-    (230, 704, 33, 4, 704, 1): (64, 1, 1, 1),
-    (230, 320, 17, 4, 2112, 1): (64, 1, 1, 2),
-    (500, 320, 33, 4, 704, 1): (96, 1, 1, 1),
-    (777, 704, 33, 4, 704, 0): (128, 1, 1, 1),
-    (1100, 320, 33, 4, 2112, 1): (160, 1, 1, 2),
-    (330, 320, 17, 4, 704, 0): (192, 1, 1, 1),
-    (500, 320, 5, 4, 1472, 0): (256, 1, 1, 1),
-    (33, 320, 2, 2, 4160, 0): (32, 1, 0, 3),
-    (300, 512, 23, 1, 4160, 1): (32, 1, 1, 3),
-    (230, 320, 26, 4, 4160, 0): (64, 1, 1, 3),
-    (230, 320, 2, 2, 4160, 1): (128, 1, 1, 3),
-    (1600, 320, 5, 4, 4160, 1): (128, 1, 1, 1),  # one slice
-    (700, 64, 4, 4, 64, 0): (32, 1, 0, 1),       # a single k step per gate/up unit, every expert sees every token
-    (1200, 64, 226, 1, 64, 1): (192, 1, 1, 1),   # a single k step per unit of both kernels
+    (33, 320, 2, 2, 1472, 1): (32, 1, 0, 1, 0),     # down by the other kernels
+    (500, 1024, 42, 2, 320, 1): (32, 1, 1, 1, 0),
+    (230, 704, 33, 4, 704, 1): (64, 1, 1, 1, 0),
+    (230, 320, 17, 4, 2112, 1): (64, 1, 1, 2, 0),
+    (500, 320, 33, 4, 704, 1): (96, 1, 1, 1, 0),
+    (777, 704, 33, 4, 704, 0): (128, 1, 1, 1, 0),
+    (1100, 320, 33, 4, 2112, 1): (160, 1, 1, 2, 0),
+    (330, 320, 17, 4, 704, 0): (192, 1, 1, 1, 0),
+    (500, 320, 5, 4, 1472, 0): (256, 1, 1, 1, 0),
+    (33, 320, 2, 2, 4160, 0): (32, 1, 0, 3, 0),
+    (300, 512, 23, 1, 4160, 1): (32, 1, 1, 3, 0),
+    (230, 320, 26, 4, 4160, 0): (64, 1, 1, 3, 0),
+    (230, 320, 2, 2, 4160, 1): (128, 1, 1, 3, 0),
+    (1600, 320, 5, 4, 4160, 1): (128, 1, 1, 1, 0),  # one slice
+    (700, 64, 4, 4, 64, 0): (32, 1, 0, 1, 0),       # a single k step per gate/up unit, every expert sees every token
+    (1200, 64, 226, 1, 64, 1): (192, 1, 1, 1, 0),   # a single k step per unit of both kernels
+    (241, 192, 8, 8, 2112, 1): (256, 1, 1, 2, 1),  # gate/up units of 256 weight rows: the last block half empty, a token tile of one row
+    (753, 64, 8, 8, 2112, 1): (256, 1, 1, 2, 1),   # ... a single k step, more units than workgroups
+    (1009, 192, 6, 6, 1088, 0): (256, 1, 1, 1, 1),
 }
 
 

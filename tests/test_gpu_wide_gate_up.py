@@ -1,15 +1,16 @@
-"""The gate/up kernel with units of 256 weight rows x 256 token rows and two stages, which similarity calls take for items of
-256 rows: whole and part-filled token tiles, a last block of weight rows that is half empty, one k step and several, more
-units than workgroups."""
-import os
-import subprocess
-
+"""The gate/up kernel with units of 256 weight rows x 256 token rows and two stages, which similarity calls and layers whose
+tokens select every expert take for items of 256 rows: whole and part-filled token tiles, a last block of weight rows
+that is half empty, one k step and several, more units than workgroups.  tests/test_similarity_plan.py and
+tests/test_ffn_plan.py check on the CPU that the cases take it."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2602_07616_amd import workloads as wk
+from . import pins
 from .test_gpu_parity import dev  # noqa: F401
+
+pytestmark = pytest.mark.gpu
 
 # M, d_h, d_m, tokens, batches
 CASES = [
@@ -19,33 +20,8 @@ CASES = [
     (40, 64, 512, 241, 1),     # whole blocks
     (100, 128, 576, 256, 1),   # 500 units
 ]
-MAIN = """
-#include <cstdio>
-#include "csrc/similarity_plan.hpp"
-int main() {
-  sere_config c{};
-  int n = 0, batches = 0;
-  c.dtype = SERE_BF16;
-  while (std::scanf("%d %d %d %d %d", &c.num_experts, &c.hidden, &c.inter, &n, &batches) == 5) {
-    const int most = sere::sim_group(c, n), g = batches < most ? batches : most;
-    const sere::SimLayout l = sere::make_sim_layout(c, n, g, g);
-    std::printf("%d %d\\n", l.plan.item_rows, l.plan.wide_gate_up);
-  }
-}
-"""
 
 
-def test_the_cases_take_the_wide_kernel(tmp_path):
-    src, exe = str(tmp_path / "main.cpp"), str(tmp_path / "main")
-    with open(src, "w") as f:
-        f.write(MAIN)
-    pkg = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_07616_amd")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-I", pkg, src, "-o", exe], check=True)
-    out = subprocess.run([exe], input="".join("%d %d %d %d %d\n" % c for c in CASES), capture_output=True, text=True, check=True)
-    assert out.stdout.split("\n")[:-1] == ["256 1"] * len(CASES)
-
-
-@pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c))
 def test_wide_gate_up(dev, case):  # noqa: F811
     M, dh, dm, n, batches = case
@@ -58,3 +34,31 @@ def test_wide_gate_up(dev, case):  # noqa: F811
     # the experts' outputs carry the rounding of h to bf16; everything after them is fp64
     assert np.abs(got - want).max() <= 5e-3, np.abs(got - want).max()
     assert np.array_equal(got, got.T)
+
+
+# (d_h, M, d_m, shared), K = M: a batch that takes the kernel and a longer one that takes units of 128 weight rows, the same
+# item size and the same slices of d_m
+PAIRS = [
+    ((192, 8, 2112, 1), (241, 389)),     # a last token tile of one row, the last block half empty
+    ((320, 8, 1472, 1), (1009, 1157)),   # more units than workgroups
+    ((64, 8, 704, 1), (1009, 1031)),     # one k step
+    ((320, 5, 2240, 0), (500, 774)),
+]
+
+
+@pytest.mark.parametrize("layer, batches", PAIRS, ids=lambda v: "x".join(str(i) for i in v))
+def test_the_bits_of_the_narrow_kernel(dev, layer, batches):  # noqa: F811
+    """A token's output in both batches: the same sums in the same order."""
+    dh, M, dm, sh = layer
+    few, many = batches
+    spec = wk.custom_spec("widebits", wk.BF16, dh, M, M, dm, sh, many, 5800 + many, calib_batches=1, calib_tokens=4)
+    wl = wk.make_workload(spec)
+    print(f"wide bits {layer} {batches}", flush=True)
+    sim = pins.rand_sim(5800, M)
+    whole = dev.DeviceLayer.from_workload(wl, sim, M, 0.0)
+    whole.run_baseline()
+    want = whole.out[:few].clone()
+    wl.hidden = np.ascontiguousarray(wl.hidden[:few])
+    part = dev.DeviceLayer.from_workload(wl, sim, M, 0.0, weights=whole.weights())
+    part.run_baseline()
+    assert want.abs().max() > 0 and (part.out == want).all()

@@ -63,7 +63,7 @@ def test_plans_of_groups_can_be_run(layouts):
     cases = draws(2000, 12)
     for case, groups in zip(cases, layouts(cases)):
         M, n, blocks = case[2], case[4], case[3] // 64
-        for g, (_, items, rows, tile_gu, tile_dn, ksplit, splits, _, item_bytes, part_bytes) in enumerate(groups, 1):
+        for g, (_, items, rows, tile_gu, tile_dn, ksplit, splits, _, item_bytes, part_bytes, _) in enumerate(groups, 1):
             assert M * items * 4 <= item_bytes and g * splits * (M * M + 96) * 8 <= part_bytes, case
             assert (items - 1) * rows < n * g <= items * rows, case
             assert rows == 32 or (tile_gu and tile_dn), case
@@ -98,6 +98,12 @@ def test_choice_of_the_gram_kernel(layouts):
             assert layout[7] == (case[5] == 0 and layout[5] == 1 and pays), (case, g)
             wide += layout[7] and case[0] == B.SERE_BF16 and case[3] > 2048
     assert wide > 50
+
+
+def test_gpu_cases_of_the_wide_gate_up_kernel_take_it(layouts):
+    from . import test_gpu_wide_gate_up as gpu
+    for case, groups in zip(gpu.CASES, layouts([(B.SERE_BF16, dh, M, dm, n, 0, b) for M, dh, dm, n, b in gpu.CASES])):
+        assert (len(groups), groups[-1][2], groups[-1][10]) == (case[4], 256, 1), case
 
 
 def test_gpu_cases_of_the_gram_kernels_reach_them(layouts):
