@@ -528,8 +528,6 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* __restric
 }
 
 // ------------------------------------------------------------- similarity ---
-constexpr int kCkaMinTokens = 4, kCkaMaxTokens = 512;  // the estimator's lower limit; M*n*n doubles of workspace
-
 static int check_similarity_sizes(const sere_config& c, int32_t num_batches, int32_t n) {
   if (num_batches < 1 || num_batches > 4096 || n < 1 || n > 4096) return SERE_ERR_BAD_SHAPE;
   if ((c.flags & SERE_FLAG_SIM_CKA_LINEAR) && (n < kCkaMinTokens || n > kCkaMaxTokens)) return SERE_ERR_BAD_SHAPE;
@@ -601,8 +599,8 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
   if (metric == kMetricCkaLinear) {
     const bool linear = cka_kernel == kCkaLinear;
     // linear kernel: row sums in blocks, where h was; the other kernels need the diagonal and leave whole row sums
-    const int side = cka_block(n), nb = (n + side - 1) / side;
-    double* rowsum = reinterpret_cast<double*>(ws + (linear ? l.h : l.rowsum));
+    const int side = cka_block(n), nb = cka_blocks(n);
+    double* rowsum = reinterpret_cast<double*>(ws + (linear ? l.block_sums : l.rowsum));
     double* diag = linear ? nullptr : reinterpret_cast<double*>(ws + l.diag);
     launch_stage(SERE_STAGE_SIM_PAIRS, s, side == 16 ? cka_gram_kernel<1> : cka_gram_kernel<2>, dim3(nb * (nb + 1) / 2, M * g),
                  dim3(256), y, f.ksplit, l.rows, n, dh, gram, rowsum, diag);
@@ -610,7 +608,7 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
       launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_transform_kernel, dim3(n, M * g), dim3(256), gram,
                    static_cast<const double*>(diag), n, cka_kernel, p0, static_cast<int>(p1), rowsum);
     const int mb = (M + 15) / 16;
-    parts = cka_parts(n, dh, M);
+    parts = l.cka_parts;
     if (parts > 1) dist = reinterpret_cast<double*>(ws + l.y);   // no longer needed
     launch_stage(SERE_STAGE_SIM_PAIRS, s, cka_pair_kernel, dim3(mb * (mb + 1) / 2, parts, g), dim3(256),
                  static_cast<const double*>(gram), static_cast<const double*>(rowsum), linear ? nb : 1, n, M, dist);

@@ -601,8 +601,6 @@ __global__ __launch_bounds__(256) void cosine_mean_kernel(const double* __restri
 // More groups in flight or eight wavefronts changed nothing at 32 tokens and lost on short rows (d_h 512: 19 -> 32 us).
 // With `diag` (RBF and polynomial kernels) the diagonal <A_e[i], A_e[i]> goes there and the row
 // sums are left to gram_transform_kernel.  grid (nb (nb + 1) / 2, M * g), nb = ceil(n / (16 B)), 256 threads.
-constexpr int kCkaSmallTokens = 48;
-constexpr int cka_block(int n) { return n <= kCkaSmallTokens ? 16 : 32; }
 template <int B>
 __global__ __launch_bounds__(256) void cka_gram_kernel(const float* __restrict__ y, int ksplit, int rows, int n, int dh,
                                                        double* __restrict__ gram, double* __restrict__ rowsum,

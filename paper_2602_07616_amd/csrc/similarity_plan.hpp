@@ -43,6 +43,8 @@ constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{8} 
 struct SimLayout {
   size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, inv_norm, max_bits,
       total;
+  size_t block_sums;    // linear CKA: the Gram matrices' row sums block by block, in the place of h
+  int cka_parts;        // summands of a pair's estimate (CKA); several lie in the place of y
   int rows, ksplit;
   FfnPlan plan;
   int items;            // work items of an expert
@@ -94,6 +96,13 @@ inline bool gram_staged_pays(int experts, long long length) {
   return experts > 192 && length * 4 % (2 << 20) == 0;
 }
 
+// Centered kernel alignment: the estimator's lower limit; M * n * n doubles of workspace
+constexpr int kCkaMinTokens = 4, kCkaMaxTokens = 512;
+// side of cka_gram_kernel's blocks (why 48 stands at the kernel), and blocks of a row of a batch's n tokens
+constexpr int kCkaSmallTokens = 48;
+constexpr int cka_block(int n) { return n <= kCkaSmallTokens ? 16 : 32; }
+constexpr int cka_blocks(int n) { return (n + cka_block(n) - 1) / cka_block(n); }
+
 // Parts of a batch's n * n products in cka_pair_kernel, 512 products and more each, and one more for its row sums: a
 // wavefront's products wait for their operands one after the other (60 experts, 64 tokens: one part 23 us, eight 8), while
 // similarity_accumulate_kernel adds up an entry's parts (32 of them: 7 -> 25 us).  The parts lie where y was: there
@@ -128,8 +137,12 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) 
   l.dist = take(g * M * M * sizeof(double));
   l.max_bits = take(g * 8);
   l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
-  l.h = take(R * c.inter * sizeof(float));
-  if (c.flags & SERE_FLAG_SIM_CKA_LINEAR) {  // Gram matrix and its row sums per expert
+  const bool cka = (c.flags & SERE_FLAG_SIM_CKA_LINEAR) != 0;
+  const size_t sums = cka ? R * cka_blocks(n) * sizeof(double) : 0;   // no more than h at today's limits (d_m of 64 and more)
+  l.h = take(std::max(R * c.inter * sizeof(float), sums));
+  if (cka) {  // Gram matrix per expert; its row sums and diagonal for the kernels with parameters
+    l.block_sums = l.h;
+    l.cka_parts = cka_parts(n, c.hidden, c.num_experts);
     l.gram = take(R * n * sizeof(double));
     l.rowsum = take(R * sizeof(double));
     l.diag = take(R * sizeof(double));

@@ -23,6 +23,7 @@ CASES = [
     (5, 192, 65, 1, wk.F32, 64),
     (20, 128, 100, 1, wk.BF16, 2112),  # two slices of d_m
     (3, 64, 129, 1, wk.F32, 64),
+    (3, 64, 512, 1, wk.F32, 64),       # the most tokens: sixteen blocks of row sums to a row, in the place of a narrow h
 ]
 
 

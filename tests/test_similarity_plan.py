@@ -63,11 +63,28 @@ def test_plans_of_groups_can_be_run(layouts):
     cases = draws(2000, 12)
     for case, groups in zip(cases, layouts(cases)):
         M, n, blocks = case[2], case[4], case[3] // 64
-        for g, (_, items, rows, tile_gu, tile_dn, ksplit, splits, _, item_bytes, part_bytes, _) in enumerate(groups, 1):
+        for g, (_, items, rows, tile_gu, tile_dn, ksplit, splits, _, item_bytes, part_bytes, *_) in enumerate(groups, 1):
             assert M * items * 4 <= item_bytes and g * splits * (M * M + 96) * 8 <= part_bytes, case
             assert (items - 1) * rows < n * g <= items * rows, case
             assert rows == 32 or (tile_gu and tile_dn), case
             assert (ksplit - 1) * -(-blocks // ksplit) < blocks, case
+
+
+def test_sums_of_alignment_fit_where_h_and_y_were(layouts):
+    """The blocks of row sums of every expert's Gram matrix and the summands of every pair, 8 bytes each; 512 tokens and
+    d_m = 64 have the least room."""
+    cases = [(dtype, 64 * k, M, 64, n, B.SERE_FLAG_SIM_CKA_LINEAR, 3) for dtype in (B.SERE_F32, B.SERE_BF16) for k in (1, 2, 20)
+             for M in (1, 2, 16, 17, 100, 256) for n in (4, 5, 16, 47, 48, 49, 100, 511, 512)]
+    cases += [c for c in draws(6000, 16) if c[5] == B.SERE_FLAG_SIM_CKA_LINEAR]
+    several = 0
+    for case, groups in zip(cases, layouts(cases)):
+        M, n = case[2], case[4]
+        for g, (*_, y_bytes, h_bytes, parts, blocks) in enumerate(groups, 1):
+            assert (blocks - 1) * (16 if n <= 48 else 32) < n <= blocks * (16 if n <= 48 else 32), case
+            assert M * g * blocks * n * 8 <= h_bytes, case
+            assert 1 <= parts <= 9 and (parts == 1 or g * parts * M * M * 8 <= y_bytes), case
+            several += parts > 1
+    assert several > 1000
 
 
 def test_the_room_does_not_depend_on_the_number_of_batches(layouts):
