@@ -196,8 +196,7 @@ __global__ __launch_bounds__(256) void pair_gram_few_kernel(const float* __restr
                                                             const double* __restrict__ inv_norm,
                                                             unsigned long long* __restrict__ max_bits) {
   constexpr int kPairs = TILES * (TILES + 1) / 2;
-  // 16-wide k steps of a group: enough bytes in flight; with COSINE a group (64 k at most) lies in one token
-  constexpr int kSteps = TILES == 1 ? (COSINE ? 4 : 8) : TILES == 2 ? 4 : 2;
+  constexpr int kSteps = gram_few_steps(TILES, COSINE);
   __shared__ double s_part[4][kPairs * 4][kWave];
   if (!COSINE && blockIdx.y == 0 && threadIdx.x == 0) max_bits[blockIdx.z] = 0ull;   // for frobenius_distance_kernel
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;

@@ -14,6 +14,9 @@ namespace sere {
 constexpr int kGramBlock = 64;     // experts per side of a block of pair_gram_kernel: 2 x 2 wavefronts, each 2 x 2 tiles of 16 x 16; up to
                                    // that many experts pair_gram_few_kernel
 constexpr int kGramGroups = 8;     // group sums that gram_reduce_kernel leaves
+// 16-wide k steps of a load group of pair_gram_few_kernel (16 `tiles` experts): enough bytes in flight; with the cosine metric a
+// group, 64 k at most, lies in one token
+constexpr int gram_few_steps(int tiles, bool cosine) { return tiles == 1 ? (cosine ? 4 : 8) : tiles == 2 ? 4 : 2; }
 // partial Gram matrices lie M * M + kGramPad doubles apart: a power-of-two distance would put the
 // same entry of every split on the same memory channel
 constexpr int kGramPad = 96;

@@ -1,5 +1,6 @@
 """Frobenius and cosine similarity of up to 64 experts: every tile count of the Gram kernel, expert counts around the tiles,
-outputs shorter than a group of loads and longer than one, groups of batches, y in slices."""
+outputs shorter than a group of loads and longer than one, groups of batches, y in slices; splits that take the kernel's loop
+around more than once."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (2, 64, 1, 1, wk.F32, 64),         # four k steps, less than a wavefront's group
     (16, 192, 3, 2, wk.F32, 64),       # 36 steps, a whole tile
-    (15, 448, 33, 1, wk.BF16, 192),    # splits of several groups, tokens that change inside them
+    (15, 448, 33, 1, wk.BF16, 192),    # a split is two groups with the cosine metric; tokens that change inside it
     (17, 64, 5, 3, wk.F32, 64),        # a second tile of one row; a token is one group
     (32, 320, 7, 1, wk.BF16, 64),
     (33, 128, 20, 1, wk.F32, 128),
@@ -23,10 +24,19 @@ CASES = [
     (20, 256, 30, 2, wk.BF16, 2112),   # two slices of d_m, a group of two batches
     (12, 512, 128, 2, wk.BF16, 256),
 ]
+# splits of more than one turn of the loop, and a part of one (tests/test_similarity_plan.py), over several tokens
+LONG = [
+    (5, 320, 1275, 1, wk.F32, 64),     # 100 steps, 20 a token; a turn is 64, 32 with the cosine metric
+    (19, 192, 700, 1, wk.F32, 64),     # 36 steps, 12 a token; 32 a turn
+    (37, 192, 400, 1, wk.BF16, 64),    # 20 steps; 16 a turn
+    (61, 128, 700, 1, wk.F32, 64),     # 24 steps, 8 a token
+    (40, 1024, 64, 4, wk.BF16, 64),    # 24 steps, a group of four batches
+    (50, 1024, 64, 4, wk.BF16, 64),
+]
 
 
 @pytest.mark.parametrize("metric", ["frobenius", "cosine"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c))
+@pytest.mark.parametrize("case", CASES + LONG, ids=lambda c: "x".join(str(v) for v in c))
 def test_few_experts(dev, case, metric):  # noqa: F811
     M, dh, n, batches, dtype, dm = case
     print(f"pair gram few {metric} {case}", flush=True)

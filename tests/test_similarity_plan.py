@@ -79,7 +79,7 @@ def test_sums_of_alignment_fit_where_h_and_y_were(layouts):
     several = 0
     for case, groups in zip(cases, layouts(cases)):
         M, n = case[2], case[4]
-        for g, (*_, y_bytes, h_bytes, parts, blocks) in enumerate(groups, 1):
+        for g, (*_, y_bytes, h_bytes, parts, blocks, _, _) in enumerate(groups, 1):
             assert (blocks - 1) * (16 if n <= 48 else 32) < n <= blocks * (16 if n <= 48 else 32), case
             assert M * g * blocks * n * 8 <= h_bytes, case
             assert 1 <= parts <= 9 and (parts == 1 or g * parts * M * M * 8 <= y_bytes), case
@@ -121,6 +121,19 @@ def test_gpu_cases_of_the_wide_gate_up_kernel_take_it(layouts):
     from . import test_gpu_wide_gate_up as gpu
     for case, groups in zip(gpu.CASES, layouts([(B.SERE_BF16, dh, M, dm, n, 0, b) for M, dh, dm, n, b in gpu.CASES])):
         assert (len(groups), groups[-1][2], groups[-1][10]) == (case[4], 256, 1), case
+
+
+def test_gpu_cases_of_up_to_64_experts_run_the_loop_of_their_kernel(layouts):
+    """More than one turn and a part of one, for every number of tiles and both metrics, and in groups of batches."""
+    from . import test_gpu_pair_gram_few as gpu
+    for flag in (0, B.SERE_FLAG_SIM_COSINE):
+        tiles, grouped = set(), set()
+        for (M, dh, n, batches, dtype, dm), groups in zip(gpu.LONG, layouts([(dtype, dh, M, dm, n, flag, b) for M, dh, n, b, dtype, dm in gpu.LONG])):
+            *_, steps, turn = groups[-1]
+            assert steps > turn and steps % turn != 0 and len(groups) == batches, (M, dh, n)
+            tiles.add(-(-M // 16))
+            grouped |= {-(-M // 16)} if batches > 1 else set()
+        assert tiles == {1, 2, 3, 4} and grouped >= {3, 4}
 
 
 def test_gpu_cases_of_the_gram_kernels_reach_them(layouts):
