@@ -15,16 +15,21 @@ CASES = [
     (2, 64, 5, 1, wk.F32, 64),         # fewer groups of k than wavefronts
     (17, 64, 4, 2, wk.F32, 64),        # the fewest tokens; a second tile of one expert
     (16, 192, 15, 1, wk.F32, 64),
-    (15, 128, 17, 3, wk.F32, 128),     # a second block of one token, groups of batches
+    (15, 128, 17, 3, wk.F32, 384),     # a second block of one token, a group of batches
     (33, 256, 31, 2, wk.BF16, 192),
     (200, 64, 9, 1, wk.F32, 64),       # no room for more than one part
     (9, 320, 48, 2, wk.F32, 64),       # the last count with blocks of 16
     (9, 320, 49, 2, wk.F32, 64),       # the first with blocks of 32
+    (9, 320, 60, 3, wk.F32, 256),      # blocks of 32 in a group of batches
     (5, 192, 65, 1, wk.F32, 64),
     (20, 128, 100, 1, wk.BF16, 2112),  # two slices of d_m
     (3, 64, 129, 1, wk.F32, 64),
     (3, 64, 512, 1, wk.F32, 64),       # the most tokens: sixteen blocks of row sums to a row, in the place of a narrow h
 ]
+
+
+# batches that a group holds (tests/test_similarity_plan.py)
+GROUPED = {(15, 128, 17, 3, wk.F32, 384): 3, (33, 256, 31, 2, wk.BF16, 192): 2, (9, 320, 60, 3, wk.F32, 256): 3}
 
 
 @pytest.mark.parametrize("kernel", ["linear", "rbf", "poly"])

@@ -136,6 +136,15 @@ def test_gpu_cases_of_up_to_64_experts_run_the_loop_of_their_kernel(layouts):
         assert tiles == {1, 2, 3, 4} and grouped >= {3, 4}
 
 
+def test_gpu_cases_of_alignment_are_grouped(layouts):
+    from . import test_gpu_cka as gpu
+    for case, groups in gpu.GROUPED.items():
+        M, dh, n, batches, dtype, dm = case
+        assert case in gpu.CASES
+        assert len(layouts([(dtype, dh, M, dm, n, B.SERE_FLAG_SIM_CKA_LINEAR, batches)])[0]) == groups, case
+    assert {n > 48 for _, _, n, _, _, _ in gpu.GROUPED} == {False, True}
+
+
 def test_gpu_cases_of_the_gram_kernels_reach_them(layouts):
     from . import test_gpu_pair_gram as gpu
     for cases, staged in ((gpu.BLOCKS, 0), (gpu.STAGED, 1)):
