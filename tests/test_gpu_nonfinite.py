@@ -67,20 +67,21 @@ def test_fp32_sum_that_overflows_is_infinite(dev, tokens, where):  # noqa: F811
     assert np.linalg.norm(got[fin] - want[fin]) <= 1e-6 * np.linalg.norm(want[fin])
 
 
+@pytest.mark.parametrize("M", [70, 60, 12])     # blocks of 64 x 64 experts; 16 tiles of the kernel of up to 64 experts, one
 @pytest.mark.parametrize("dtype", [wk.F32, wk.BF16])
-def test_cosine_of_nonfinite_outputs(dev, dtype):  # noqa: F811
+def test_cosine_of_nonfinite_outputs(dev, dtype, M):  # noqa: F811
     """A token contributes the quotient where the product of the two norms is positive (that is NaN if one of them is
     infinite), and 0 where it is not: a zero output or one with a NaN, whatever the other one is."""
-    spec = wk.custom_spec("cosnan", dtype, 320, 70, 2, 64, 0, 4, 6960, calib_batches=2, calib_tokens=17)
+    spec = wk.custom_spec("cosnan", dtype, 320, M, 2, 64, 0, 4, 6960, calib_batches=2, calib_tokens=17)
     wl = wk.make_workload(spec)
     zero, nan, inf = 5, 7, 9
     wl.w_down[zero] = 0
     wl.w_down[nan, 100, 3] = wk.to_storage(np.float32([np.nan]), dtype)[0]
     wl.w_down[inf, 200, 60] = wk.to_storage(np.float32([np.inf]), dtype)[0]
-    print(f"cosine nonfinite dtype {dtype}", flush=True)
+    print(f"cosine nonfinite dtype {dtype}, {M} experts", flush=True)
     got = dev.similarity_on_device(wl, metric="cosine").cpu().numpy()
     want = oracle.similarity_cosine(wl.calib, wl.w_gate_up, wl.w_down, dtype)
-    assert (want[nan] == 0).all() and np.isnan(want[inf]).sum() == 68       # the oracle has the same reading
+    assert (want[nan] == 0).all() and np.isnan(want[inf]).sum() == M - 2       # the oracle has the same reading
     assert np.array_equal(np.isnan(got), np.isnan(want))
     fin = ~np.isnan(want)
     assert (got[[zero, nan]] == 0).all() and (got[:, [zero, nan]] == 0).all()
@@ -98,3 +99,30 @@ def test_cosine_of_one_token_with_nan_outputs(dev):  # noqa: F811
     wl.calib[0, 6] *= np.float32(1e30)
     got = dev.similarity_on_device(wl, metric="cosine").cpu().numpy()
     assert np.abs(got - want).max() <= 1e-5
+
+
+@pytest.mark.parametrize("kernel", ["linear", "rbf", "poly"])
+@pytest.mark.parametrize("n", [17, 60])     # blocks of 16 and of 32 rows
+def test_alignment_with_nonfinite_outputs(dev, n, kernel):  # noqa: F811
+    """An expert whose outputs are zero, infinite or NaN has no positive self-term, so its similarities are 0; the others' are
+    what they are without it."""
+    spec = wk.custom_spec("ckanan", wk.F32, 320, 20, 2, 64, 0, 4, 6975, calib_batches=2, calib_tokens=n)
+    wl = wk.make_workload(spec)
+    zero, nan, inf = 5, 7, 18
+    finite = [e for e in range(20) if e not in (nan, inf)]
+    outs = oracle.moe_layer(wl.calib[0], wl.w_gate_up, wl.w_down, None, None, wk.F32, np.zeros((n, 1), dtype=np.int32), np.ones((n, 1)))
+    norm2 = float(np.mean(np.sum(outs * outs, axis=1)))
+    p0, p1 = {"linear": (0.0, 0.0), "rbf": (np.sqrt(2.0 * norm2), 0.0), "poly": (norm2, 3.0)}[kernel]
+    wl.w_down[zero] = 0
+    wl.w_down[nan, 100, 3] = np.nan
+    wl.w_down[inf, 200, 60] = np.inf
+    print(f"alignment nonfinite {kernel}, {n} tokens", flush=True)
+    got = dev.similarity_on_device(wl, cka=(kernel, p0, p1)).cpu().numpy()
+    want = oracle.similarity_cka(wl.calib, wl.w_gate_up[finite], wl.w_down[finite], wk.F32, kernel, p0, p1)
+    assert (got[[nan, inf]] == 0).all() and (got[:, [nan, inf]] == 0).all()
+    # as in the finite tests; the zero expert's kernels are constant, so its self-term is 0 but for rounding
+    rest = [e for e in finite if e != zero]
+    at = [finite.index(e) for e in rest]
+    assert np.abs(got[np.ix_(rest, rest)] - want[np.ix_(at, at)]).max() <= 1e-5
+    if kernel == "linear":
+        assert (got[zero] == 0).all() and (got[:, zero] == 0).all()
