@@ -16,12 +16,12 @@
 //    c ^ (r & 7).  The loads put it there by having each lane fetch the piece that belongs at its
 //    place, still eight whole 128-byte lines per instruction, and a matrix operand (16 rows x 16
 //    bytes, rows in the wavefront's lane order) then reads every LDS bank once.
-//  - Eight wavefronts share a stage as 8 / WN x WN: 64 (or 32) weight rows and every WN-th token
+//  - Eight wavefronts share a stage as 8 / WN x WN: 32, 64 or 128 weight rows and every WN-th token
 //    tile each.  While the second half of a stage is multiplied the first half of the next one is read
 //    from LDS, so that reads and products overlap inside a wavefront (gate/up at 2048 tokens of
 //    the Qwen3 shape, one launch over and over: 165 -> 151 us).
 //  - A compute unit takes in 64 bytes a cycle at best and its queue is short: eight wavefronts that issue a
-//    stage's 40 to 56 loads at once stand still until they are accepted.  So the loads go out one by one among the
+//    stage's 36 to 64 loads (fp32: 20) at once stand still until they are accepted.  So the loads go out one by one among the
 //    products (us, gate/up + down: 777 tokens of d_h 2880, d_m 1472 170 + 97 -> 161 + 93, 2048 tokens of the Qwen3
 //    shape 156 + 112 -> 150 + 109, 256 rows an expert 231 + 166 -> 231 + 158; fp32 below 63 + 39 -> 57 + 37).
 //  - Workgroups are handed to the 8 XCDs round-robin; each XCD walks a contiguous range of units,
@@ -366,8 +366,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     const int used = slot;
     slot = slot + 1 == S ? 0 : slot + 1;
     fetch(f0, slot, 0);
-    // the loads of a stage, spread over the first three quarters of the products (one token tile: before them all; two
-    // stages: over the first quarter, they are waited for at the end of the same products)
+    // the loads of a stage, spread over the first three quarters of the products, each after a token tile's (one token tile:
+    // all of them after the first half; two stages: over the first quarter, they are waited for at the end of the same
+    // products)
     auto loads = [&](auto half) __attribute__((always_inline)) {
       return [&](auto t) __attribute__((always_inline)) {
         constexpr int h = decltype(half)::value * NT + decltype(t)::value, groups = NT == 1 ? 1 : S == 2 ? NT / 2 : (3 * NT + 1) / 2;
