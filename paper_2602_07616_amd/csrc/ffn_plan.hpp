@@ -19,6 +19,8 @@ inline int down_ksplit(const sere_config& c) { return c.dtype == SERE_BF16 ? (c.
 // wide experts: h keeps its bf16 rounding residual in a second plane (see decode())
 inline int wants_split_h(const sere_config& c) { return (c.dtype == SERE_BF16 && c.inter >= 4096) ? 1 : 0; }
 
+constexpr int kSmallSlots = 64;   // slots of a call that the kernels of ffn_small.hpp serve: one to a lane
+
 constexpr int kItemRows = 32;     // rows of the sorted slot list per FFN work item (FfnPlan::item_rows may be larger)
 constexpr int kTileGroups = 256;  // persistent workgroups of the kernels of ffn_tile.hpp: one per compute unit
 
@@ -243,6 +245,57 @@ inline FfnPlan plan_decode(const sere_config& c, bool reroute) {
   s.split_h = wants_split_h(c) != 0;
   s.max_ksplit = down_ksplit(c);
   return c.dtype == SERE_F32 ? plan_ffn_f32(s) : plan_ffn(s);
+}
+
+// ---- calls of at most kSmallSlots slots: the two launches of ffn_small.hpp behind the router logits
+constexpr int kSmallOut = 8;             // intermediate indices of a wavefront (gate/up), output rows of a workgroup (down)
+constexpr int kSmallBlock = 128;         // bytes of every row that a step takes: 64 bf16 or 32 fp32
+constexpr int kSmallAhead = 4;           // blocks whose loads are issued together
+constexpr int kSmallWaves = 8;           // wavefronts of a workgroup
+constexpr int kSmallGroups = 511;        // gate/up workgroups that run side by side, without the one that writes
+constexpr int kSmallTile = 16;           // rows that an item's weights are read for at a time
+
+// A wavefront ranks the upper halves of a token's lists and holds all slots, a shared expert's rows are one tile, and a
+// workgroup of the down launch holds the rows of y for its columns.
+inline bool small_call_fits(const sere_config& c) {
+  const long long T = c.num_tokens, slots = T * c.top_k;
+  return c.top_k <= 8 && T <= kSmallTile && slots + c.num_shared <= kSmallSlots && slots + T * c.num_shared <= 2 * kSmallSlots && !wants_split_h(c);
+}
+
+// Gate/up: wavefronts that share a contraction (1, 2, 4 or 8): as many as have kSmallAhead blocks each, more while all `rows`
+// rows of h still fit one round of units.  A unit costs some 3 us of latencies whatever it holds, so that a contraction of few
+// blocks leaves room for more weight rows in it.
+inline int small_units(int rows, int split) { return rows / (kSmallOut * kSmallWaves / split); }
+inline int small_split(int blocks, int rows) {
+  int split = 1;
+  while (split < kSmallWaves && (split * kSmallAhead < blocks || small_units(rows, 2 * split) <= kSmallGroups)) split *= 2;
+  return split;
+}
+
+// Whether these launches are the faster ones: us of a call by either way, both fitted to 370 layers that small_call_fits, timed
+// with both (d_h 256 to 4096, d_m 128 to 4032, 2 to 160 experts, 1 to 16 tokens, 1 to 740 MB of weights).  What costs
+// most here is rounds of units and, in a long contraction, of loads; the other launches start at 23 us (fp32 26 and more) and take the
+// weights as they come.  bf16: 0.83 to 1.9 times as fast where this rule takes them, 1.2 on average, and what it leaves out
+// would be 0.5 to 1.2 times; fp32: 1.05 to 2.1 times.
+inline bool small_call_pays(const sere_config& c, bool reroute) {
+  if (!small_call_fits(c)) return false;
+  const auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
+  const double T = c.num_tokens, M = c.num_experts, slots = T * c.top_k, bytes = c.dtype == SERE_F32 ? 4.0 : 2.0;
+  const double kept = reroute && !(c.threshold > 0.0f) ? c.select_top_k : c.top_k;
+  const double routed = std::max(1.0, M * (1.0 - std::pow(1.0 - kept / M, T))), items = routed + c.num_shared;
+  const double mb = items * 3e-6 * c.hidden * c.inter * bytes;
+  const int gu_blocks = static_cast<int>(c.hidden * bytes) / kSmallBlock, dn_blocks = static_cast<int>(c.inter * bytes) / kSmallBlock;
+  const int most = static_cast<int>(std::min(T * kept, M)) + c.num_shared;
+  const int split = small_split(gu_blocks, most * c.inter), slices = std::max(1, std::min(static_cast<int>(kSmallWaves / items), dn_blocks));
+  // an expert with more rows than a tile has its weights read twice
+  const double passes = slots > 10.0 * routed ? 2.0 : 1.0;
+  const double gu = std::max(1.0, std::ceil(items * c.inter * split / (kSmallOut * kSmallWaves) / kSmallGroups - 0.02)) *
+                    ceil_div(ceil_div(gu_blocks, split), kSmallAhead);
+  const double dn = std::ceil(items * slices / kSmallWaves) * ceil_div(ceil_div(dn_blocks, slices), kSmallAhead) *
+                    std::max(1.0, c.hidden / (256.0 * kSmallOut));
+  const double small = 13.3 + passes * (3.3 * gu + 0.66 * dn) + 0.105 * slots + 0.057 * mb;
+  const double other = c.dtype == SERE_F32 ? 26.5 + 0.196 * mb + 0.0087 * c.hidden : 23.2 + 0.133 * mb;
+  return small < 0.96 * other;
 }
 
 }  // namespace sere

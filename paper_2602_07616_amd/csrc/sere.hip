@@ -12,6 +12,7 @@
 #include "common.hpp"
 #include "ffn_generic.hpp"
 #include "ffn_mfma.hpp"
+#include "ffn_small.hpp"
 #include "ffn_tile.hpp"
 #include "route_kernels.hpp"
 #include "similarity_kernels.hpp"
@@ -323,10 +324,14 @@ static int launch_route(const sere_config& c, const Pointers& p, bool with_topk,
   return hip_status();
 }
 
+static CombineArgs combine_args(const sere_config& c, const Layout& l, const Pointers& p, int ksplit, const void* hidden, void* out) {
+  return CombineArgs{p.y, p.topk_w, p.route.slot_pos, (c.flags & SERE_FLAG_RESIDUAL) ? hidden : nullptr, out,
+                     c.num_tokens, c.hidden, c.top_k, c.num_shared, ksplit, l.rows};
+}
+
 static void launch_combine(const sere_config& c, const Layout& l, const Pointers& p, int ksplit, const void* hidden,
                            void* out, hipStream_t s) {
-  CombineArgs ca{p.y, p.topk_w, p.route.slot_pos, (c.flags & SERE_FLAG_RESIDUAL) ? hidden : nullptr, out,
-                 c.num_tokens, c.hidden, c.top_k, c.num_shared, ksplit, l.rows};
+  const CombineArgs ca = combine_args(c, l, p, ksplit, hidden, out);
   const bool small = static_cast<int64_t>(c.num_tokens) * c.hidden <= kCombineColumns;
   const dim3 grid(small ? static_cast<unsigned>((c.hidden + 255) / 256) * c.num_tokens
                         : (static_cast<unsigned>(c.num_tokens) * (c.hidden / 4) + 255) / 256);
@@ -413,6 +418,35 @@ static void launch_ffn(const sere_config& c, const Layout& l, const Pointers& p,
   launch_combine(c, l, p, plan.ksplit, f.hidden, out, s);
 }
 
+// Everything behind the router logits of a call that small_call_fits.
+static void launch_small(const sere_config& c, const Layout& l, const Pointers& p, const FfnArgs& f, void* out, hipStream_t s) {
+  const int lists = (c.num_experts + 15) / 16;
+  // as many items as there can be (a threshold keeps secondary experts); the workgroups take any number
+  const int kept = p.route.reroute && !(c.threshold > 0.0f) ? p.route.S : c.top_k;
+  const int rows = (std::min(c.num_tokens * kept, c.num_experts) + c.num_shared) * c.inter;
+  const int split = small_split(c.hidden * (c.dtype == SERE_F32 ? 4 : 2) / kSmallBlock, rows);
+  const dim3 grid(1 + std::min(small_units(rows, split), kSmallGroups));
+#define SERE_LAUNCH_SMALL(DT, LISTS)                                                                                               \
+  launch_stage(SERE_STAGE_GATE_UP, s, ffn_small_gate_up<DT, LISTS>, grid, dim3(kSmallThreads), f, p.route, p.list_key, \
+               p.list_id, p.topk_ids, p.topk_w, split)
+#define SERE_LAUNCH_SMALL_LISTS(DT) \
+  if (lists <= 8)                   \
+    SERE_LAUNCH_SMALL(DT, 1);       \
+  else                              \
+    SERE_LAUNCH_SMALL(DT, 2)
+  const CombineArgs ca = combine_args(c, l, p, 1, f.hidden, out);
+  const dim3 down(c.hidden / kSmallOut);
+  if (c.dtype == SERE_F32) {
+    SERE_LAUNCH_SMALL_LISTS(SERE_F32);
+    launch_stage(SERE_STAGE_DOWN, s, ffn_small_down<SERE_F32>, down, dim3(kSmallThreads), f, ca);
+  } else {
+    SERE_LAUNCH_SMALL_LISTS(SERE_BF16);
+    launch_stage(SERE_STAGE_DOWN, s, ffn_small_down<SERE_BF16>, down, dim3(kSmallThreads), f, ca);
+  }
+#undef SERE_LAUNCH_SMALL_LISTS
+#undef SERE_LAUNCH_SMALL
+}
+
 // --------------------------------------------------------- static scratch ---
 // Workspace of sere_moe_decode_static: part of the library image, one copy per GPU.  In host code
 // the array's name is only a handle for the runtime; the device address of the current GPU's copy
@@ -473,7 +507,9 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   if (!reroute) p.route.S = cfg->top_k;  // every slot is a primary slot: identity map
   st = launch_router(*cfg, p, hidden, router_w, s);
   if (st != SERE_OK) return st;
-  st = launch_route(*cfg, p, true, s);
+  // (stage timing reports every stage, so each is a launch of its own while it is on)
+  const bool small = small_call_pays(*cfg, reroute) && !g_timing.enabled;
+  if (!small) st = launch_route(*cfg, p, true, s);
   if (st != SERE_OK) return st;
 
   FfnArgs f{};
@@ -503,7 +539,10 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   // reach several units.  From d_m = 4096 on, h keeps its rounding residual in
   // a second bf16 plane and the down projection multiplies both.
   f.split_h = wants_split_h(*cfg);
-  launch_ffn(*cfg, l, p, plan, f, out, s);
+  if (small)
+    launch_small(*cfg, l, p, f, out, s);
+  else
+    launch_ffn(*cfg, l, p, plan, f, out, s);
   return hip_status();
 }
 
