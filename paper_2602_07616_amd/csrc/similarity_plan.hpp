@@ -31,16 +31,19 @@ constexpr int gram_squares(int M) {
 }
 constexpr int gram_triangles(int M) { return (M + 127) / 128; }
 
-// Calibration batches are served in groups of about kSimGroupRows tokens (more rows per expert make the forward
-// pass no faster per token), within kSimGroupBytes of workspace, so that an expert's weights are streamed once per
-// group and a stage is one launch: 32 tokens of the Qwen3 shape 200 us alone, 110 / 66 / 50 us a batch in groups of
-// 2 / 4 / 8.  A call with less workspace, or with fewer batches, runs smaller groups.
+// Calibration batches are served in groups within kSimGroupBytes of workspace, so that an expert's weights are streamed once per group and
+// a stage is one launch: 32 tokens of the Qwen3 shape 200 us alone, 110 / 66 / 50 us a batch in groups of 2 / 4 / 8.  A call with
+// less workspace, or with fewer batches, runs smaller groups.  Groups are of kSimGroupMin batches, whatever
+// their length, up to kSimGroupRows tokens; short batches of kSimGroupShortRows tokens together.  us a call, groups of 256 tokens / of 512 /
+// of 1024 (the longest ones that the batches allow): Qwen3 shape, four batches of 128 1094 / 988, of 78 tokens, 94 experts, d_h 1664, d_m
+// 1088 758 / 632; 11 experts, d_h 2048, four of 83 258 / 212; eight of 114, 41 experts, d_h 832 395 / 308 / 262; twelve of 83, 5
+// experts, d_h 1920 450 / 288 / 249.  41 calls with more than 256 tokens: 1.45 / 1.47 times as fast on average, none slower.
 // Measured on 14 layers of 0.8 to 288 MB, three metrics, 2 to 16 batches of 4 to 100 tokens: a group takes 0.1 to 0.9
 // times what its batches take one by one, the less the smaller layer and batch (12 MB, 8 batches of 32 tokens: 249 / 58
 // us, 288 MB: 667 / 225).  Layers of at most kSimGroupWeights stay at one batch at a time all the same, so that the
 // launches that a stage timing counts are one a batch there, as those who read it on a small layer expect; they would
 // gain as much (6 MB, fp32, two batches of 32 tokens: 75 / 40 us).
-constexpr int kSimGroupRows = 256, kSimGroupMax = 16;
+constexpr int kSimGroupRows = 1024, kSimGroupShortRows = 256, kSimGroupMin = 8, kSimGroupMax = 16;
 constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{8} << 20;
 
 struct SimLayout {
@@ -188,7 +191,8 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) 
 // batches of a group that a workspace is sized for
 inline int sim_group(const sere_config& c, int n) {
   const size_t weights = static_cast<size_t>(c.num_experts) * 3 * c.hidden * c.inter * (c.dtype == SERE_F32 ? 4 : 2);
-  int g = weights <= kSimGroupWeights ? 1 : std::max(1, std::min(kSimGroupMax, kSimGroupRows / n));
+  const int batches = std::max(std::min(kSimGroupMin, kSimGroupRows / n), std::min(kSimGroupMax, kSimGroupShortRows / n));
+  int g = weights <= kSimGroupWeights ? 1 : std::max(1, batches);
   while (g > 1 && make_sim_layout(c, n, g, g).total > kSimGroupBytes) --g;
   return g;
 }
