@@ -298,7 +298,8 @@ int sere_similarity_cka(const sere_config *cfg, const void *calib, int32_t num_b
  * to no stage).
  * Calls of few slots, which otherwise run top-K to gate/up and down to combine as one launch
  * each, run a launch for every stage while it is enabled (the same routing, outputs alike to
- * the rounding of the sums).
+ * the rounding of the sums), and similarity estimations on layers of at most 8 MiB of weights
+ * take their batches one at a time.
  * Do not enable it on a stream that is being captured into a HIP graph.
  * sere_stage_timing_read waits for the recorded events, adds the elapsed
  * milliseconds and launch counts per stage into the two arrays of

@@ -701,7 +701,7 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   if (pc.status != SERE_OK) return pc.status;
   if (workspace == nullptr) return SERE_ERR_NULL_PTR;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return SERE_ERR_MISALIGNED;
-  const int whole = std::min(sim_group(*cfg, batch_tokens), num_batches);
+  const int whole = std::min(sim_group(*cfg, batch_tokens, g_timing.enabled), num_batches);
   int group = whole;
   while (group > 1 && make_sim_layout(*cfg, batch_tokens, group, whole).total > workspace_bytes) --group;
   const SimLayout l = make_sim_layout(*cfg, batch_tokens, group, whole);
@@ -801,7 +801,7 @@ int sere_moe_decode_baseline(const sere_config* cfg, const void* hidden, const v
 
 size_t sere_similarity_workspace_bytes(const sere_config* cfg, int32_t batch_tokens) {
   if (check_config(cfg) != SERE_OK || check_similarity_sizes(*cfg, 1, batch_tokens) != SERE_OK) return 0;
-  const int group = sim_group(*cfg, batch_tokens);
+  const int group = sim_group(*cfg, batch_tokens, false);
   return make_sim_layout(*cfg, batch_tokens, group, group).total;
 }
 
