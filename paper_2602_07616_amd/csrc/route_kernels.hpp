@@ -17,6 +17,8 @@
 // the batch-wide step is a launch of its own, shared by many workgroups.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace sere {
@@ -68,6 +70,15 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// f(std::integral_constant<int, 0>{}), ..., f(... N - 1)
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
 }
 
 // order-preserving map double -> uint64 (larger double <=> larger key; -0 == +0)
@@ -342,15 +353,9 @@ __global__ __launch_bounds__(256) void router_logits_mfma_kernel(
 // workgroup's own use.
 // ---------------------------------------------------------------------------
 template <int STEP>
-__device__ __forceinline__ void argmax_step(uint64_t& key, uint32_t& idx) {
-  const uint32_t ohi = row_xchg<STEP>(static_cast<uint32_t>(key >> 32));
-  const uint32_t olo = row_xchg<STEP>(static_cast<uint32_t>(key));
-  const uint32_t oidx = row_xchg<STEP>(idx);
-  const uint64_t okey = (static_cast<uint64_t>(ohi) << 32) | olo;
-  if (okey > key || (okey == key && oidx < idx)) {
-    key = okey;
-    idx = oidx;
-  }
+__device__ __forceinline__ uint64_t max_step(uint64_t key) {
+  const uint64_t other = (static_cast<uint64_t>(row_xchg<STEP>(static_cast<uint32_t>(key >> 32))) << 32) | row_xchg<STEP>(static_cast<uint32_t>(key));
+  return other > key ? other : key;
 }
 
 template <int LP>
@@ -391,43 +396,59 @@ __device__ __forceinline__ void load_lists(const uint64_t* __restrict__ list_key
   }
 }
 
-// `chosen(k, id)` is called by one lane of the group for the expert of rank k.
+// `chosen(k, id)` is called by one lane of the group for the expert of rank k.  Only the keys go round the group: the winner is the
+// first lane that holds the largest one (lists are in the order of the experts, so that is the lower expert among equals), and
+// after round k no list needs more than K - 1 - k entries (us a launch,
+// against keys and ids going round and whole lists moving up: 32 tokens of 128 experts, K = 8, 8.5 -> 7.7, 128 10.6 -> 9.8, 64 of 64
+// experts, K = 6, 6.6 -> 6.3).
 template <int LP, int KS, int KEEP, typename Chosen>
 __device__ __forceinline__ void topk_merge(ListHead<KEEP>& h, bool active, int nlists, float* __restrict__ w, int K, Chosen&& chosen) {
-  const int l = threadIdx.x & (LP - 1);
+  const int lane = threadIdx.x & 63, l = lane & (LP - 1);
   uint64_t (&key)[KEEP] = h.key;
   uint32_t (&idw)[4] = h.idw;
   if (!active || l >= nlists) {
 #pragma unroll
     for (int j = 0; j < KEEP; ++j) key[j] = 0;
   }
-  double mysel[KS];
+  const uint64_t before = (1ull << lane) - (1ull << (lane - l));   // lanes of the group before this one
+  uint64_t mysel[KS];
 #pragma unroll
-  for (int c = 0; c < KS; ++c) mysel[c] = 0.0;
-  double top = 0.0;
-  for (int k = 0; k < K; ++k) {
-    uint64_t wkey = key[0];
-    uint32_t wid = key[0] != 0 ? (idw[0] & 0xffu) : 0x7fffffffu;
-    argmax_step<0>(wkey, wid);
-    argmax_step<1>(wkey, wid);
-    if constexpr (LP >= 8) argmax_step<2>(wkey, wid);
-    if constexpr (LP >= 16) argmax_step<3>(wkey, wid);
-    // every lane of the group now holds the winner; its owner pops
-    if (key[0] != 0 && (idw[0] & 0xffu) == wid) {
+  for (int c = 0; c < KS; ++c) mysel[c] = 0;
+  uint64_t top = 0;
+  auto round = [&](int k, auto needed) __attribute__((always_inline)) {   // needed: entries of a list that may still be wanted, this round's too
+    uint64_t most = key[0];
+    most = max_step<0>(most);
+    most = max_step<1>(most);
+    if constexpr (LP >= 8) most = max_step<2>(most);
+    if constexpr (LP >= 16) most = max_step<3>(most);
+    const bool equal = key[0] == most;
+    const bool mine = equal && (__ballot(equal) & before) == 0 && most != 0;
+    const int id = static_cast<int>(idw[0] & 0xffu);
+    if (mine) {
+      chosen(k, id);
 #pragma unroll
-      for (int j = 0; j < KEEP - 1; ++j) key[j] = key[j + 1];
-      key[KEEP - 1] = 0;
+      for (int j = 0; j + 1 < decltype(needed)::value; ++j) key[j] = key[j + 1];
+      if (KEEP == 16) key[KEEP - 1] = 0;   // a list may be used up
       idw[0] = (idw[0] >> 8) | (idw[1] << 24);
       idw[1] = (idw[1] >> 8) | (idw[2] << 24);
-      idw[2] = (idw[2] >> 8) | (idw[3] << 24);
-      idw[3] >>= 8;
+      if (KEEP == 16) {
+        idw[2] = (idw[2] >> 8) | (idw[3] << 24);
+        idw[3] >>= 8;
+      }
     }
-    const double val = key_to_double(wkey);
-    if (k == 0) top = val;
+    if (k == 0) top = most;
 #pragma unroll
     for (int c = 0; c < KS; ++c)
-      if (k == l + LP * c) mysel[c] = val;
-    if (l == 0 && active) chosen(k, static_cast<int>(wid));
+      if (k == l + LP * c) mysel[c] = most;
+  };
+  if constexpr (KEEP == 8) {   // K <= 8
+    static_for<8>([&](auto k) __attribute__((always_inline)) {
+      if (decltype(k)::value < K) round(decltype(k)::value, std::integral_constant<int, 8 - decltype(k)::value>{});
+    });
+  } else {
+    for (int k = 0; k < K; ++k) {
+      round(k, std::integral_constant<int, KEEP>{});
+    }
   }
   double ex[KS];
   double part = 0.0;
@@ -435,7 +456,7 @@ __device__ __forceinline__ void topk_merge(ListHead<KEEP>& h, bool active, int n
   for (int c = 0; c < KS; ++c) {
     ex[c] = 0.0;
     if (LP * c < K) {  // uniform
-      ex[c] = (l + LP * c < K) ? exp(mysel[c] - top) : 0.0;
+      ex[c] = (l + LP * c < K) ? exp(key_to_double(mysel[c]) - key_to_double(top)) : 0.0;
       part += ex[c];
     }
   }
@@ -448,8 +469,8 @@ __device__ __forceinline__ void topk_merge(ListHead<KEEP>& h, bool active, int n
 // ---------------------------------------------------------------------------
 // Batch-wide re-routing and compaction by ONE workgroup of 1024 threads (smaller batches), and the
 // parts of it that the shared form uses too.  A chain of short steps between barriers: counting by expert instead of
-// by slot, sums over lanes by DPP and clearing LDS before the top-K took the launch from 9.0 to 8.7 us at 32 tokens, 11.1 to
-// 10.6 at 128 (128 experts), 7.2 to 6.9 at 64 tokens of 64 experts.
+// by slot, sums over lanes by DPP and clearing LDS before the top-K took the launch from 9.0 to 8.5 us at 32 tokens, 11.1 to
+// 10.6 at 128 (128 experts), 7.2 to 6.6 at 64 tokens of 64 experts.
 // ---------------------------------------------------------------------------
 struct RouteArgs {
   const int32_t* topk_ids;  // [A]  I
@@ -808,20 +829,22 @@ __device__ __forceinline__ void route_phase(const RouteArgs& p, RouteShared& s, 
 
 // ---------------------------------------------------------------------------
 // The batch-wide step shared by many workgroups (batches of thousands of slots; top-K and re-routing of the
-// Qwen3 shape, us a step: 1024 tokens 27 -> 12, 2048 47 -> 14, 4096 89 -> 18).  Where a slot goes depends on its
+// Qwen3 shape, us a step: 1024 tokens 27 -> 11, 2048 47 -> 11, 4096 89 -> 18).  Where a slot goes depends on its
 // expert and on whether it is a primary slot (k < S) only, so two counts per expert and chunk of tokens are
 // all that workgroups have to tell each other: the launch before this one writes them (chunk_hist), and every
 // workgroup here derives the mask, the map, the new counts, the offsets and its own chunk's starting positions
 // from them, then regroups its own slots.
 // ---------------------------------------------------------------------------
 
-// counts of the slots whose ids are in s.ids8 (n tokens' worth): hist[0][e] primary slots, hist[1][e] secondary
-// ones; all threads of the workgroup
-__device__ __forceinline__ void write_chunk_hist(const RouteArgs& p, RouteShared& s, int slots, int32_t* hist) {
+// counts of the slots whose ids are in s.ids8: hist[0][e] primary slots, hist[1][e] secondary ones; all threads of the workgroup,
+// after clear_chunk_counts and a barrier.  (Barriers that order LDS only: the ids and gate weights are still on their way to
+// memory.)
+__device__ __forceinline__ void clear_chunk_counts(RouteShared& s) {
   for (int i = threadIdx.x; i < SERE_MAX_EXPERTS; i += blockDim.x) s.cnt_a[i] = s.cnt_b[i] = 0;
-  __syncthreads();
+}
+__device__ __forceinline__ void write_chunk_hist(const RouteArgs& p, RouteShared& s, int slots, int32_t* hist) {
   for (int a = threadIdx.x; a < slots; a += blockDim.x) atomicAdd((a % p.K < p.S) ? &s.cnt_a[s.ids8[a]] : &s.cnt_b[s.ids8[a]], 1);
-  __syncthreads();
+  lds_barrier();
   for (int i = threadIdx.x; i < p.M; i += blockDim.x) {
     hist[i] = s.cnt_a[i];
     hist[p.M + i] = s.cnt_b[i];
@@ -834,7 +857,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_hist_kernel(RouteArgs p) 
   const int begin = blockIdx.x * p.chunk_tokens * p.K, slots = min(p.chunk_tokens * p.K, p.T * p.K - begin);
   for (int a = threadIdx.x; a < slots; a += kRouteThreads)
     s.ids8[a] = static_cast<uint8_t>(min(max(p.topk_ids[begin + a], 0), p.M - 1));
-  __syncthreads();
+  clear_chunk_counts(s);
+  lds_barrier();
   write_chunk_hist(p, s, slots, p.chunk_hist + static_cast<size_t>(blockIdx.x) * 2 * p.M);
 }
 
@@ -844,20 +868,36 @@ __global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p
   __shared__ RouteShared s;
   __shared__ int s_total[2 * SERE_MAX_EXPERTS], s_before[2 * SERE_MAX_EXPERTS];  // of all chunks / of the chunks before this one
   const int tid = threadIdx.x, M = p.M, chunks = gridDim.x, chunk = blockIdx.x;
+  const int A = p.T * p.K, begin = chunk * p.chunk_tokens * p.K, end = min(begin + p.chunk_tokens * p.K, A);
+  // The 2 M counts of the chunks, kRouteThreads / (2 M) chunks at a time: kAhead passes are requested together, before the
+  // similarity rows, and so are the ids of the chunk's first slots (one pass after the other: both launches 13.4 us instead of 11.7 at
+  // 1000 tokens, 13.8 instead of 10.7 at 2048).
+  constexpr int kAhead = 8;
+  const int per_pass = kRouteThreads / (2 * M);  // >= 2
+  const int c = tid % (2 * M), first = tid / (2 * M);
+  int n[kAhead];
+  auto fetch = [&](int g) __attribute__((always_inline)) {   // a chunk beyond the last: that one again, not used
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (u * per_pass < chunks) n[u] = p.chunk_hist[static_cast<size_t>(min(g + u * per_pass, chunks - 1)) * 2 * M + c];   // uniform
+  };
+  fetch(first);
+  const int first_id = p.topk_ids[min(begin + tid, end - 1)];
   SimPrefetch<NC> pf;
   prefetch_sim(p, pf, p.topk_ids);
   for (int i = tid; i < 2 * SERE_MAX_EXPERTS; i += kRouteThreads) s_total[i] = s_before[i] = 0;
-  for (int i = tid; i < kRouteWaves * SERE_MAX_EXPERTS; i += kRouteThreads) (&s.round_cnt[0][0])[i] = 0;
+  *reinterpret_cast<int4*>(&s.round_cnt[0][0] + 4 * tid) = int4{0, 0, 0, 0};
   lds_barrier();
-  // the 2 M counts of the chunks, kRouteThreads / (2 M) chunks at a time
-  const int per_pass = kRouteThreads / (2 * M);  // >= 2
-  const int c = tid % (2 * M);
   if (tid < per_pass * 2 * M) {
     int total = 0, before = 0;
-    for (int g = tid / (2 * M); g < chunks; g += per_pass) {
-      const int n = p.chunk_hist[static_cast<size_t>(g) * 2 * M + c];
-      total += n;
-      before += g < chunk ? n : 0;
+    for (int g = first; g < chunks; g += kAhead * per_pass) {
+      if (g != first) fetch(g);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int at = g + u * per_pass, add = at < chunks ? n[u] : 0;
+        total += add;
+        before += at < chunk ? add : 0;
+      }
     }
     atomicAdd(&s_total[c], total);
     atomicAdd(&s_before[c], before);
@@ -881,9 +921,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_chunks_kernel(RouteArgs p
   lds_barrier();
   if (tid < M) s.cursor[tid] += s_before[tid];
   lds_barrier();
-  const int A = p.T * p.K, begin = chunk * p.chunk_tokens * p.K;
-  regroup_slots(p, s, begin, min(begin + p.chunk_tokens * p.K, A),
-                [&](int a) { return min(max(p.topk_ids[a], 0), M - 1); }, true);
+  regroup_slots(p, s, begin, end, [&](int a) { return min(max(a == begin + tid ? first_id : p.topk_ids[a], 0), M - 1); }, true);
   for (int i = chunk * kRouteThreads + tid; i < p.n_sh * p.T; i += chunks * kRouteThreads) p.sorted_token[A + i] = i % p.T;
 }
 
@@ -930,7 +968,7 @@ __global__ __launch_bounds__(kRouteThreads) void topk_route_kernel(const uint64_
   // from L2), with many the step is long anyway and the rows are loaded where they are needed instead.
   SimPrefetch<NC> pf;
   prefetch_sim(p, pf, list_key, gridDim.x <= kSimPrefetchMaxGroups && p.chunk_hist == nullptr);
-  if (p.chunk_hist == nullptr) clear_counts(s);   // while the loads are on their way
+  if (p.chunk_hist == nullptr) clear_counts(s); else clear_chunk_counts(s);   // while the loads are on their way
   if (merges) {
     uint8_t* ids8 = lone ? s.ids8 + tt * p.K : (p.chunk_hist != nullptr ? s.ids8 + (threadIdx.x / LP) * p.K : nullptr);
     topk_merge<LP, KS, KEEP>(head, has, nlists, topk_w + tt * p.K, p.K, [&](int k, int id) {
@@ -940,13 +978,13 @@ __global__ __launch_bounds__(kRouteThreads) void topk_route_kernel(const uint64_
     });
   }
   if (p.chunk_hist != nullptr) {  // the batch-wide step is a launch of its own: leave this chunk's counts
-    __syncthreads();
+    lds_barrier();
     const int tokens = min(group_tokens, p.T - static_cast<int>(blockIdx.x) * group_tokens);
     write_chunk_hist(p, s, tokens * p.K, p.chunk_hist + static_cast<size_t>(blockIdx.x) * 2 * p.M);
     return;
   }
   if (lone) {
-    __syncthreads();
+    lds_barrier();   // the ids go on through LDS; what was stored and requested need not have arrived
     route_phase<true>(p, s, pf);
     return;
   }
