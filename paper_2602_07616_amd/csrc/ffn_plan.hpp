@@ -255,11 +255,12 @@ constexpr int kSmallWaves = 8;           // wavefronts of a workgroup
 constexpr int kSmallGroups = 511;        // gate/up workgroups that run side by side, without the one that writes
 constexpr int kSmallTile = 16;           // rows that an item's weights are read for at a time
 
-// A wavefront ranks the upper halves of a token's lists and holds all slots, a shared expert's rows are one tile, and a
-// workgroup of the down launch holds the rows of y for its columns.
+// A wavefront ranks the upper halves of a token's lists and holds all slots, and a workgroup of the down launch holds the
+// rows of y for its columns.  bf16: up to a tile of tokens (238 layers of 17 to 64 tokens: the median 0.81 times as fast by these
+// launches, 9 more than 1.1 times).
 inline bool small_call_fits(const sere_config& c) {
   const long long T = c.num_tokens, slots = T * c.top_k;
-  return c.top_k <= 8 && T <= kSmallTile && slots + c.num_shared <= kSmallSlots && slots + T * c.num_shared <= 2 * kSmallSlots && !wants_split_h(c);
+  return c.top_k <= 8 && (T <= kSmallTile || c.dtype == SERE_F32) && slots + c.num_shared <= kSmallSlots && slots + T * c.num_shared <= 2 * kSmallSlots && !wants_split_h(c);
 }
 
 // Gate/up: wavefronts that share a contraction (1, 2, 4 or 8): as many as have kSmallAhead blocks each, more while all `rows`
@@ -276,7 +277,9 @@ inline int small_split(int blocks, int rows) {
 // with both (d_h 256 to 4096, d_m 128 to 4032, 2 to 160 experts, 1 to 16 tokens, 1 to 740 MB of weights).  What costs
 // most here is rounds of units and, in a long contraction, of loads; the other launches start at 23 us (fp32 26 and more) and take the
 // weights as they come.  bf16: 0.83 to 1.9 times as fast where this rule takes them, 1.2 on average, and what it leaves out
-// would be 0.5 to 1.2 times; fp32: 1.05 to 2.1 times.
+// would be 0.5 to 1.2 times; fp32: 1.05 to 2.1 times.  More than 16 tokens (fp32): with up to a dozen items, of which 85 of 172
+// more layers were taken, 1.01 to 2.19 times as fast, 1.47 on average (25 tokens of three experts of 960 x 1024 54.1 -> 27.2); with
+// more items 0.7 to 1.6 times, and what the rule reads of a layer does not tell which.
 inline bool small_call_pays(const sere_config& c, bool reroute) {
   if (!small_call_fits(c)) return false;
   const auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
@@ -287,15 +290,17 @@ inline bool small_call_pays(const sere_config& c, bool reroute) {
   const int gu_blocks = static_cast<int>(c.hidden * bytes) / kSmallBlock, dn_blocks = static_cast<int>(c.inter * bytes) / kSmallBlock;
   const int most = static_cast<int>(std::min(T * kept, M)) + c.num_shared;
   const int split = small_split(gu_blocks, most * c.inter), slices = std::max(1, std::min(static_cast<int>(kSmallWaves / items), dn_blocks));
-  // an expert with more rows than a tile has its weights read twice
-  const double passes = slots > 10.0 * routed ? 2.0 : 1.0;
+  if (c.num_tokens > kSmallTile && items > 12.0) return false;
+  // the weights of an item with more rows than a tile are read for every tile
+  double passes = slots > 10.0 * routed ? 2.0 : 1.0;
+  if (c.num_tokens > kSmallTile) passes = std::max({passes, std::ceil((slots / routed + 6.0) / kSmallTile), c.num_shared > 0 ? std::ceil(T / kSmallTile) : 1.0});
   const double gu = std::max(1.0, std::ceil(items * c.inter * split / (kSmallOut * kSmallWaves) / kSmallGroups - 0.02)) *
                     ceil_div(ceil_div(gu_blocks, split), kSmallAhead);
   const double dn = std::ceil(items * slices / kSmallWaves) * ceil_div(ceil_div(dn_blocks, slices), kSmallAhead) *
                     std::max(1.0, c.hidden / (256.0 * kSmallOut));
   const double small = 13.3 + passes * (3.3 * gu + 0.66 * dn) + 0.105 * slots + 0.057 * mb;
   const double other = c.dtype == SERE_F32 ? 26.5 + 0.196 * mb + 0.0087 * c.hidden : 23.2 + 0.133 * mb;
-  return small < 0.96 * other;
+  return small < (c.num_tokens > kSmallTile ? 1.0 : 0.96) * other;   // (the other launches' start was fitted to 16 tokens)
 }
 
 }  // namespace sere

@@ -26,6 +26,11 @@ CASES = [
     (wk.BF16, 3, 4096, 20, 5, 320, 0, 2, 0.6),      # two rounds of loads
     (wk.F32, 2, 512, 60, 4, 1088, 0, 1, 0.0),       # more units than workgroups without re-routing
     (wk.F32, 9, 1024, 64, 7, 128, 1, 3, 0.5),       # 63 slots and a shared expert: the longest work list
+    (wk.F32, 17, 768, 9, 1, 320, 0, 1, 0.0),        # a tile and a row of tokens
+    (wk.F32, 32, 1024, 1, 1, 256, 0, 1, 0.0),       # two whole tiles of one expert
+    (wk.F32, 64, 1024, 3, 1, 256, 0, 1, 0.0),       # an output element of every thread
+    (wk.F32, 32, 1024, 2, 1, 128, 3, 1, 0.0),       # two tiles of every shared expert, 128 rows in all
+    (wk.F32, 32, 1088, 5, 2, 256, 0, 1, 0.6),       # 32 primary slots
 ]
 
 

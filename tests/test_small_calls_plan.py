@@ -35,12 +35,12 @@ def test_what_fits_is_what_the_kernels_hold(small):
     for _ in range(5000):
         M = rng.choice([1, 2, 8, 16, 17, 64, 128, 129, 256])
         K = rng.randint(1, min(M, 12))
-        calls.append((rng.randint(0, 1), rng.randint(1, 40), 64 * rng.randint(1, 70), M, K, 64 * rng.randint(1, 80), rng.choice([0, 0, 1, 2, 4, 16]),
+        calls.append((rng.randint(0, 1), rng.randint(1, 70), 64 * rng.randint(1, 70), M, K, 64 * rng.randint(1, 80), rng.choice([0, 0, 1, 2, 4, 16]),
                       rng.randint(1, K), rng.choice([0.0, 0.5]), rng.randint(0, 1)))
     taken = 0
     for (dt, T, dh, M, K, dm, sh, S, rho, re), (fits, pays, split, units) in zip(calls, small(calls)):
         if pays:
             taken += 1
-            assert fits and K <= 8 and T <= 16 and T * K + sh <= 64 and T * (K + sh) <= 128 and (dt == 0 or dm < 4096)
+            assert fits and K <= 8 and T <= (64 if dt == 0 else 16) and T * K + sh <= 64 and T * (K + sh) <= 128 and (dt == 0 or dm < 4096)
         assert split in (1, 2, 4, 8) and dm % (64 // split) == 0 and units * (64 // split) == dm
     assert taken > 300
