@@ -252,6 +252,7 @@ __device__ __forceinline__ void write_small_route(const RouteArgs& p, const Smal
     p.num_active[1] = r.active;
     p.n_work[0] = r.active + p.n_sh;
     p.n_work[1] = 0;
+    p.n_work[2] = 0;
   }
 }
 

@@ -29,6 +29,15 @@
 //    256 weight rows starts at another k step (not the same offset of every row at once, that is, not
 //    the same memory channels: 115 -> 107 us at 128 tokens).
 //
+//  - fp32: an item of more than 16 rows takes half as long again as a shorter one (31 against 23 us a gate/up unit in a first
+//    round, 25 against 17 in a second; d_h 1024), and few layers have more than two rounds of units.  The work list then has
+//    the long items first, every XCD gets an eighth of their units, and a workgroup that starts with one is the
+//    last to get a second unit (96 tokens of 32 experts and a shared one, d_h 1024, d_m 704: the XCD with the shared expert's rows ended
+//    after 56 us, the others after 41; now all after 44.  Down 34 -> 30.  All calls of that size 111 -> 91).
+//  - fp32: matrix cores and vector ALU take turns (16x16x4 products and seven additions in one wavefront: 65 cycles, 32 + 28 alone), so
+//    that the additions of a step are kept behind its products, where the compiler otherwise starts the first ones between products and
+//    waits for these, and one of the two wavefronts of a SIMD goes first: 1 to 3 % of a call, 91 -> 88 us of the one above.
+//
 // Measured on the Qwen3 shape (d_h 2048, d_m 768, 128 experts), us per launch, gate/up + down, within steps on four
 // copies of the weights in turn, against the kernels with eight wavefronts that staged token rows through registers,
 // both on one card that has been busy for some 20 ms (from idle the first steps take a tenth longer):
@@ -36,7 +45,7 @@
 //           2048: 212 + 119 -> 143 + 109   3072: 242 + 145 -> 208 + 140   4096: 371 + 198 -> 261 + 179
 // (2048 tokens, items of 160 rows: while no expert has more.  Where one does, its second item makes the launch start a
 // fourth round of units on every compute unit: 173 + 124.)
-// fp32 layers against the vector-ALU kernels: 150 + 111 -> 57 + 37 us at 96 tokens (d_h 1024, d_m 704, 32 experts);
+// fp32 layers against the vector-ALU kernels: 150 + 111 -> 42 + 31 us at 96 tokens (d_h 1024, d_m 704, 32 experts);
 // relative error of the layer 1.8e-7 -> 1.4e-7.
 // Not faster, one launch over and over: 32-wide steps with more stages (64-byte rows: 165 -> 236 us at 2048 tokens);
 // the same first step for all parts of an item; plain instead of non-temporal weight loads (151 -> 162 us).
@@ -136,12 +145,30 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   const int parts = (outs + kOut - 1) / kOut * ksplit;
   const int blocks = ld * EB / kRowBytes, per = (blocks + ksplit - 1) / ksplit;
 
-  // this workgroup's units: every 32nd of its XCD's contiguous range
-  const unsigned total = static_cast<unsigned>(items) * parts;
-  const unsigned xcd = blockIdx.x % kXcds, q8 = total / kXcds, r8 = total % kXcds;
-  const unsigned lo = xcd * q8 + min(xcd, r8), hi = lo + q8 + (xcd < r8 ? 1u : 0u);
+  // This workgroup's units: one of every round of its XCD's contiguous range.  fp32: that is an eighth of the units of the
+  // long items and then an eighth of the others; the rounds that hold long ones go round the XCD's workgroups one way, the
+  // ones behind them the other way, so that those without a long unit get the one more that a last round has for some.
+  constexpr bool kLongFirst = DT == SERE_F32;
   constexpr unsigned kStride = kTileGroups / kXcds;
-  unsigned pu = lo + blockIdx.x / kXcds;                 // unit being loaded
+  const unsigned total = static_cast<unsigned>(items) * parts;
+  const unsigned xcd = blockIdx.x % kXcds, turn = blockIdx.x / kXcds;
+  const auto share = [](unsigned n, unsigned x) { return n / kXcds * x + min(x, n % kXcds); };   // units before XCD x's
+  unsigned lo = share(total, xcd), hi = share(total, xcd + 1);
+  unsigned longs = 0, to_long = 0, to_other = 0, back = 0;   // long units; from place to unit, of these and of the others; last round of theirs
+  if constexpr (kLongFirst) {
+    const unsigned total_long = static_cast<unsigned>(scalar_load(p.n_work, 2)) * parts, others = total - total_long;
+    to_long = share(total_long, xcd);
+    longs = share(total_long, xcd + 1) - to_long;
+    to_other = total - share(others, kXcds - xcd) - longs;
+    lo = 0;
+    hi = longs + share(others, kXcds - xcd) - share(others, kXcds - 1 - xcd);
+    back = longs / kStride;
+  }
+  const auto next_unit = [&](unsigned u) __attribute__((always_inline)) {
+    return u + kStride + (kLongFirst && u / kStride == back ? kStride - 1 - 2 * turn : 0u);
+  };
+  const auto unit_at = [&](unsigned u) __attribute__((always_inline)) { return kLongFirst ? u + (u < longs ? to_long : to_other) : u; };
+  unsigned pu = lo + turn;                               // unit being loaded
   unsigned cu = pu;                                      // unit being multiplied
   if (pu >= hi) return;
 
@@ -218,8 +245,8 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   auto next_load_step = [&]() __attribute__((always_inline)) {
     if (++pk == pnk) pk = 0;
     if (--pleft == 0) {
-      pu += kStride;
-      if (pu < hi) open_load_unit(pu);
+      pu = next_unit(pu);
+      if (pu < hi) open_load_unit(unit_at(pu));
     }
   };
 
@@ -276,6 +303,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
                                                        j % 2 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
           }
         if constexpr (decltype(which)::value == 1) {
+          __builtin_amdgcn_sched_barrier(0);   // the additions behind all products
 #pragma unroll
           for (int a = 0; a < NA; ++a) {
             const f32x4 add = (sums[0][a][t] + sums[1][a][t]) + (sums[2][a][t] + sums[3][a][t]);
@@ -341,13 +369,14 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
 
   // Steps run half a step out of phase with the stages: while a stage's second half is multiplied, the first
   // half of the next one is read from LDS, so that reads and products overlap within a wavefront.
-  open_load_unit(pu);
+  if (DT == SERE_F32 && wn == 0) __builtin_amdgcn_s_setprio(1);   // of the two wavefronts of a SIMD
+  open_load_unit(unit_at(pu));
   int ahead = 0, slot = 0;                               // stages issued and not yet waited for; slot in use
   for (; ahead < S && pu < hi; ++ahead) {
     issue_some(ahead, std::integral_constant<int, 0>{}, std::integral_constant<int, P>{});
     next_load_step();
   }
-  open_unit(cu);
+  open_unit(unit_at(cu));
   auto wait_stage = [&](auto issued) {                   // the oldest of the stages issued, by all wavefronts
     constexpr int D = decltype(issued)::value;           // how many there are while units are left to load
     if (ahead == D) {
@@ -379,8 +408,8 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     multiply(f1, std::integral_constant<int, 1>{}, loads(std::integral_constant<int, 0>{}));
     if (--left == 0) {
       store();
-      cu += kStride;
-      open_unit(cu);
+      cu = next_unit(cu);
+      if (!kLongFirst || cu < hi) open_unit(unit_at(cu));
     }
     fetch(f1, slot, 1);
     multiply(f0, std::integral_constant<int, 0>{}, loads(std::integral_constant<int, 1>{}));

@@ -489,16 +489,19 @@ struct RouteArgs {
   int32_t* sorted_token_out; // [A]  the caller's copy of the routed part of sorted_token, or NULL
   int32_t* slot_pos;        // [A]  position of slot a = t*K+k in the sorted list
   int32_t* work_expert;     // [max items] expert of each work item (M+s for shared expert s); experts
-                            //             ascending, an expert's rows cut into items of <= item_rows
+                            //             ascending, an expert's rows cut into items of <= item_rows; the ones of
+                            //             more than long_rows before the others
   int32_t* work_off;        // [max items] first row of the item in the sorted list
   int32_t* work_cnt;        // [max items] rows of the item (1 .. item_rows)
-  int32_t* n_work;          // [2]: number of items; 1 if the FFN kernels are to cut them fine
+  int32_t* n_work;          // [3]: number of items; 1 if the FFN kernels are to cut them fine; items that come first
   int fine_items;           // ... which they do while there are at most this many items
   int topk_threads;         // threads of a workgroup that take part in the top-K merge (256 or 1024)
   int32_t* chunk_hist;      // [chunks][2][M] slots per expert of every chunk of tokens, primary / secondary slots
                             //             (NULL: the batch-wide step runs in the last workgroup of the top-K)
   int chunk_tokens;         // tokens of a chunk
   int item_rows;            // rows per work item, at most: kItemRows and more, the host's choice
+  int long_rows;            // items of more rows than this come first in the work list (0: all in order)
+  int long_parts;           // gate/up units of an item
 };
 
 constexpr int kRouteThreads = 1024;
@@ -525,6 +528,7 @@ struct RouteShared {
   int scan_act[SERE_MAX_EXPERTS / kWave];
   int scan_before[SERE_MAX_EXPERTS / kWave];
   int scan_items[SERE_MAX_EXPERTS / kWave];
+  int scan_long[SERE_MAX_EXPERTS / kWave];
   int cursor[SERE_MAX_EXPERTS];
   __attribute__((aligned(16))) int round_cnt[kRouteWaves][SERE_MAX_EXPERTS];
   uint8_t ids8[kIdsInLds];
@@ -651,12 +655,16 @@ __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s,
   const int my_act = my_cnt > 0 ? 1 : 0;
   const int item_rows = p.item_rows;
   const int my_items = (my_cnt + item_rows - 1) / item_rows;
-  int inc_cnt = my_cnt, inc_act = my_act, inc_items = my_items;
+  // all items but the last one have item_rows rows
+  int my_long = p.long_rows > 0 && my_items > 0 ? my_items - (my_cnt - (my_items - 1) * item_rows <= p.long_rows ? 1 : 0) : 0;
+  int inc_cnt = my_cnt, inc_act = my_act, inc_items = my_items, inc_long = 0;
   if (is_e) {  // wave-uniform (waves 0-3)
     inc_cnt = wave_scan(inc_cnt);
     inc_act = wave_scan(inc_act);
     inc_items = wave_scan(inc_items);
+    if (p.long_rows > 0) inc_long = wave_scan(my_long);
     if (lane == kWave - 1) {
+      s.scan_long[wave] = inc_long;
       s.scan_cnt[wave] = inc_cnt;
       s.scan_act[wave] = inc_act;
       s.scan_items[wave] = inc_items;
@@ -665,17 +673,27 @@ __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s,
     if (lane == 0) s.scan_before[wave] = nb;
   }
   lds_barrier();
-  int n_after = 0, n_before = 0, n_items = 0;
+  int n_after = 0, n_before = 0, n_items = 0, n_long = 0;
 #pragma unroll
   for (int w = 0; w < SERE_MAX_EXPERTS / kWave; ++w) {
     if (is_e && w < wave) {
       inc_cnt += s.scan_cnt[w];
       inc_items += s.scan_items[w];
+      inc_long += s.scan_long[w];
     }
     n_after += s.scan_act[w];
     n_before += s.scan_before[w];
     n_items += s.scan_items[w];
+    n_long += s.scan_long[w];
   }
+  const int sh_items = (p.T + item_rows - 1) / item_rows;  // per shared expert
+  // long items first where there is more than one round of units; in one round all start together, and an expert's
+  // items next to each other share its weights in one L2
+  const bool long_first = p.long_rows > 0 && (n_items + p.n_sh * sh_items) * p.long_parts > kTileGroups;
+  const int sh_long = long_first ? sh_items - (p.T - (sh_items - 1) * item_rows <= p.long_rows ? 1 : 0) : 0;
+  if (!long_first) my_long = inc_long = n_long = 0;
+  const int routed_long = n_long;
+  n_long += p.n_sh * sh_long;
   if (is_e && tid < M) {
     const int off = inc_cnt - my_cnt;
     s.cursor[tid] = off;
@@ -684,7 +702,7 @@ __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s,
       p.count_before[tid] = s.cnt_b[tid];
       p.count_after[tid] = my_cnt;
       p.primary_mask[tid] = s.prim[tid];
-      const int first = inc_items - my_items;
+      const int first = inc_long - my_long, then = n_long + (inc_items - inc_long) - my_items;   // of the long ones, of the others (from my_long on)
       // Items of 128 rows and more (prefill-sized batches): an expert with a few rows more than one item
       // holds is cut into items of about equal size (multiples of a 16-row tile) instead of a full
       // one and a remnant: its items then take about equally long, and as they are numbered next
@@ -693,26 +711,28 @@ __device__ __forceinline__ void scan_experts(const RouteArgs& p, RouteShared& s,
       if (item_rows >= 4 * kItemRows && my_items >= 2 && my_items <= 4)
         per = ((my_cnt + my_items - 1) / my_items + 15) & ~15;
       for (int j = 0; j < my_items; ++j) {
-        p.work_expert[first + j] = tid;
-        p.work_off[first + j] = off + j * per;
-        p.work_cnt[first + j] = min(per, my_cnt - j * per);
+        const int at = (j < my_long ? first : then) + j;
+        p.work_expert[at] = tid;
+        p.work_off[at] = off + j * per;
+        p.work_cnt[at] = min(per, my_cnt - j * per);
       }
     }
   }
   if (!write) return;
-  const int sh_items = (p.T + item_rows - 1) / item_rows;  // per shared expert
   if (tid == 0) {
     p.expert_offsets[M] = A;
     p.num_active[0] = n_before;
     p.num_active[1] = n_after;
     p.n_work[0] = n_items + p.n_sh * sh_items;
     p.n_work[1] = (item_rows == kItemRows && n_items + p.n_sh * sh_items <= p.fine_items) ? 1 : 0;
+    p.n_work[2] = n_long;
   }
   for (int i = tid; i < p.n_sh * sh_items; i += kRouteThreads) {
     const int sh = i / sh_items, j = i % sh_items;
-    p.work_expert[n_items + i] = M + sh;
-    p.work_off[n_items + i] = A + sh * p.T + j * item_rows;
-    p.work_cnt[n_items + i] = min(item_rows, p.T - j * item_rows);
+    const int at = j < sh_long ? routed_long + sh * sh_long + j : n_items + p.n_sh * sh_long + sh * (sh_items - sh_long) + j - sh_long;
+    p.work_expert[at] = M + sh;
+    p.work_off[at] = A + sh * p.T + j * item_rows;
+    p.work_cnt[at] = min(item_rows, p.T - j * item_rows);
   }
 }
 

@@ -63,7 +63,7 @@ static Layout make_layout(const sere_config& c) {
   l.work_expert = take(W * 4);
   l.work_off = take(W * 4);
   l.work_cnt = take(W * 4);
-  l.n_work = take(8);
+  l.n_work = take(12);
   l.ticket = take(4);
   l.h = take(R * c.inter * sizeof(float));
   l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
@@ -187,7 +187,7 @@ struct Pointers {
 constexpr int kRerouteChunkSlots = 1024;  // slots of a chunk when the ids are given (sere_reroute): one regrouping round
 
 static Pointers bind(const sere_config& c, const Layout& l, void* workspace, const sere_route_out* o,
-                     bool with_topk = true, int item_rows = kItemRows) {
+                     bool with_topk = true, int item_rows = kItemRows, int long_rows = 0) {
   char* ws = static_cast<char*>(workspace);
   auto pick = [&](void* user, size_t off) { return user != nullptr ? user : static_cast<void*>(ws + off); };
   static const sere_route_out none{};
@@ -237,6 +237,8 @@ static Pointers bind(const sere_config& c, const Layout& l, void* workspace, con
   r.chunk_hist = chunked ? reinterpret_cast<int32_t*>(ws + l.y) : nullptr;
   r.fine_items = kFineCutBlocks / (c.inter / (2 * kGateUpJ * kWavesPerBlock));
   r.item_rows = item_rows;
+  r.long_rows = long_rows;
+  r.long_parts = (c.inter + kTileF32Rows / 2 - 1) / (kTileF32Rows / 2);
   p.h = reinterpret_cast<float*>(ws + l.h);
   p.y = reinterpret_cast<float*>(ws + l.y);
   return p;
@@ -501,7 +503,8 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const FfnPlan plan = plan_decode(*cfg, reroute);
-  Pointers p = bind(*cfg, l, workspace, dbg, true, plan.item_rows);
+  // fp32: items with a second tile of rows take half as long again (ffn_tile.hpp)
+  Pointers p = bind(*cfg, l, workspace, dbg, true, plan.item_rows, cfg->dtype == SERE_F32 && plan.tile_gate_up ? kTile : 0);
   p.route.sim = sim;
   p.route.reroute = reroute ? 1 : 0;
   if (!reroute) p.route.S = cfg->top_k;  // every slot is a primary slot: identity map

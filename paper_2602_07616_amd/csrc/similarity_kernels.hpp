@@ -40,6 +40,7 @@ __global__ __launch_bounds__(256) void similarity_worklist_kernel(int M, int n, 
   if (i == 0) {
     n_work[0] = M * items;
     n_work[1] = 0;  // many long items: coarse cut
+    n_work[2] = 0;
   }
 }
 

@@ -140,7 +140,7 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) 
   l.work_expert = take(W * 4);
   l.work_off = take(W * 4);
   l.work_cnt = take(W * 4);
-  l.n_work = take(8);
+  l.n_work = take(12);
   l.dist = take(g * M * M * sizeof(double));
   l.max_bits = take(g * 8);
   l.y = take(static_cast<size_t>(l.ksplit) * R * c.hidden * sizeof(float));
