@@ -29,6 +29,11 @@
 //    256 weight rows starts at another k step (not the same offset of every row at once, that is, not
 //    the same memory channels: 115 -> 107 us at 128 tokens).
 //
+//  - Where at most half of an XCD's workgroups would get one more unit, these units are cut into halves of their weight rows, one for
+//    every workgroup: half the weights and the same token rows are some two thirds of the time, less 2 us to start again (us, gate/up +
+//    down: 777 tokens of d_h 2880, d_m 1472, 2.3 rounds each, 156 + 92 -> 149 + 88, a call 279 -> 263; 2048 tokens of the Qwen3
+//    shape, items in excess of three and four rounds, 175 + 121 -> 166 + 117; 128 tokens, down 59.6 -> 57.7).  The sums are the same ones.
+//    (Not for gate/up units of 256 weight rows x 256 token rows, whose wavefronts have no registers to spare.)
 //  - fp32: an item of more than 16 rows takes half as long again as a shorter one (31 against 23 us a gate/up unit in a first
 //    round, 25 against 17 in a second; d_h 1024), and few layers have more than two rounds of units.  The work list then has
 //    the long items first, every XCD gets an eighth of their units, and a workgroup that starts with one is the
@@ -119,15 +124,24 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F&& f
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-// h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of every unit.  Items have at most
-// TileShape::kRealRows rows; p.ksplit slices of d_m (down), none of them empty.  grid kTileGroups, 512 threads.
-template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO>
-__global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
+constexpr unsigned kStride = kTileGroups / kXcds;   // workgroups of an XCD
+
+// units of an item
+template <bool GATEUP, int BM>
+__device__ __forceinline__ int tile_parts(const FfnArgs& p) {
+  constexpr int kOut = GATEUP ? BM / 2 : BM;
+  return ((GATEUP ? p.dm : p.dh) + kOut - 1) / kOut * (GATEUP ? 1 : p.ksplit);
+}
+
+// h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of the units of an XCD from place `lo` up to `hi`, of which
+// this workgroup takes one of every kStride.  Items have at most TileShape::kRealRows rows; p.ksplit slices of d_m (down), none
+// of them empty.  SPLIT = 2: halves of units of 2 BM weight rows, and at most one for a workgroup.
+template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO, int SPLIT>
+__device__ __forceinline__ void tile_units(const FfnArgs& p, unsigned char* lds, unsigned lo, unsigned hi, unsigned longs, unsigned to_long,
+                                           unsigned to_other) {
   using Sh = TileShape<BM, BN, WN, LO>;
-  static_assert(DT == SERE_BF16 || !LO, "fp32 keeps h as it is");
   constexpr int EB = Store<DT>::bytes;
   constexpr int S = Sh::kStages, NQ = Sh::kWeightLoads, NI = Sh::kTokenLoads, NT = Sh::kTilesPerWave;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[S * Sh::kStageBytes];
   const uint32_t lds0 = static_cast<uint32_t>(
       reinterpret_cast<uintptr_t>(reinterpret_cast<__attribute__((address_space(3))) unsigned char*>(
           reinterpret_cast<uintptr_t>(lds))));
@@ -138,39 +152,28 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   const int wm = wave % WM, wn = wave / WM;
   const int dh = p.dh, dm = p.dm;
   const int ld = GATEUP ? dh : dm;                       // row length of both operands
-  const int items = scalar_load(p.n_work, 0);
   const int outs = GATEUP ? dm : dh;
   constexpr int kOut = GATEUP ? BM / 2 : BM;             // output columns of a unit
   const int ksplit = GATEUP ? 1 : p.ksplit;
-  const int parts = (outs + kOut - 1) / kOut * ksplit;
+  const int parts = tile_parts<GATEUP, BM * SPLIT>(p);
   const int blocks = ld * EB / kRowBytes, per = (blocks + ksplit - 1) / ksplit;
-
-  // This workgroup's units: one of every round of its XCD's contiguous range.  fp32: that is an eighth of the units of the
-  // long items and then an eighth of the others; the rounds that hold long ones go round the XCD's workgroups one way, the
-  // ones behind them the other way, so that those without a long unit get the one more that a last round has for some.
   constexpr bool kLongFirst = DT == SERE_F32;
-  constexpr unsigned kStride = kTileGroups / kXcds;
-  const unsigned total = static_cast<unsigned>(items) * parts;
-  const unsigned xcd = blockIdx.x % kXcds, turn = blockIdx.x / kXcds;
-  const auto share = [](unsigned n, unsigned x) { return n / kXcds * x + min(x, n % kXcds); };   // units before XCD x's
-  unsigned lo = share(total, xcd), hi = share(total, xcd + 1);
-  unsigned longs = 0, to_long = 0, to_other = 0, back = 0;   // long units; from place to unit, of these and of the others; last round of theirs
-  if constexpr (kLongFirst) {
-    const unsigned total_long = static_cast<unsigned>(scalar_load(p.n_work, 2)) * parts, others = total - total_long;
-    to_long = share(total_long, xcd);
-    longs = share(total_long, xcd + 1) - to_long;
-    to_other = total - share(others, kXcds - xcd) - longs;
-    lo = 0;
-    hi = longs + share(others, kXcds - xcd) - share(others, kXcds - 1 - xcd);
-    back = longs / kStride;
-  }
+  const unsigned turn = blockIdx.x / kXcds;
+  const unsigned back = longs / kStride;                 // last round that holds long units
   const auto next_unit = [&](unsigned u) __attribute__((always_inline)) {
-    return u + kStride + (kLongFirst && u / kStride == back ? kStride - 1 - 2 * turn : 0u);
+    if (!kLongFirst) return u + kStride;
+    const unsigned round = u / kStride + 1;
+    return round * kStride + (round > back ? kStride - 1 - turn : turn);
   };
   const auto unit_at = [&](unsigned u) __attribute__((always_inline)) { return kLongFirst ? u + (u < longs ? to_long : to_other) : u; };
   unsigned pu = lo + turn;                               // unit being loaded
   unsigned cu = pu;                                      // unit being multiplied
   if (pu >= hi) return;
+  // first output column; a last unit's second half may have none
+  const auto first_out = [&](unsigned u) __attribute__((always_inline)) {
+    return static_cast<int>(u / SPLIT % parts / ksplit * SPLIT + u % SPLIT) * kOut;
+  };
+  if (SPLIT > 1 && first_out(pu) >= outs) return;
 
   // ---- loading side
   constexpr int CH = kRowBytes / 16;                     // pieces of a row
@@ -180,13 +183,13 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   const char* tptr[NI];
   int pk = 0, pbeg = 0, pnk = 0, pleft = 0;
   auto open_load_unit = [&](unsigned u) __attribute__((always_inline)) {
-    const int item = u / parts, part = u % parts;
+    const int item = u / SPLIT / parts, part = u / SPLIT % parts;
     const int e = scalar_load(p.work_expert, item), off = scalar_load(p.work_off, item), cnt = scalar_load(p.work_cnt, item);
     const int slab = part / ksplit, slice = part % ksplit;
     const char* W = static_cast<const char*>(expert_base<DT>(GATEUP ? p.w_gate_up : p.w_down,
                                                              GATEUP ? p.shared_gate_up : p.shared_down, e, p.M,
                                                              static_cast<size_t>(GATEUP ? 2 : 1) * dm * dh));
-    const int o0 = slab * kOut;
+    const int o0 = (slab * SPLIT + u % SPLIT) * kOut;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int r = kLoadRows * (wave * NQ + q);                // first of the LDS rows of this load
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     pnk = min((slice + 1) * per, blocks) - pbeg;
     // Units of 128 bf16 weight rows start where the unit of 256 that covers them would: with the same slices of d_m
     // the sums then have the same order whatever the item size, which calibration batches in groups rely on.
-    constexpr int kShared = DT == SERE_BF16 ? 256 / BM : 1;
+    constexpr int kShared = DT == SERE_BF16 ? 256 / (BM * SPLIT) : 1;
     pk = (slab / kShared * ksplit + slice) * 5 % pnk;
     pleft = pnk;
   };
@@ -254,10 +257,11 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   const uint32_t frag = i * kRowBytes + ((g ^ (i & 7)) << 4);
   f32x4 acc[NA][NT];
   f32x4 low[DT == SERE_F32 ? NA : 1][DT == SERE_F32 ? NT : 1];   // what acc has lost (fp32)
-  int cnt = 0, off = 0, part = 0, left = 0;
+  int cnt = 0, off = 0, part = 0, half = 0, left = 0;
   auto open_unit = [&](unsigned u) __attribute__((always_inline)) {
-    const int item = u / parts;
-    part = u % parts;
+    const int item = u / SPLIT / parts;
+    part = u / SPLIT % parts;
+    half = u % SPLIT;
     off = scalar_load(p.work_off, item);
     cnt = scalar_load(p.work_cnt, item);
     const int slice = part % ksplit;
@@ -302,8 +306,8 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
             sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(f.w[a][j]), __uint_as_float(f.x[t][j]),
                                                        j % 2 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
           }
+        __builtin_amdgcn_sched_barrier(0);   // the additions behind all products
         if constexpr (decltype(which)::value == 1) {
-          __builtin_amdgcn_sched_barrier(0);   // the additions behind all products
 #pragma unroll
           for (int a = 0; a < NA; ++a) {
             const f32x4 add = (sums[0][a][t] + sums[1][a][t]) + (sums[2][a][t] + sums[3][a][t]);
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     }
     const int slab = part / ksplit, slice = part % ksplit;
     if (GATEUP) {
-      const int j0 = slab * kOut + wm * (RW / 2);
+      const int j0 = (slab * SPLIT + half) * kOut + wm * (RW / 2);
       if (j0 >= dm) return;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
         }
       }
     } else {
-      const int r0 = slab * kOut + wm * RW;
+      const int r0 = (slab * SPLIT + half) * kOut + wm * RW;
       if (r0 >= dh) return;
       float* y = p.y + static_cast<size_t>(slice) * p.rows * dh;
 #pragma unroll
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
     if (--left == 0) {
       store();
       cu = next_unit(cu);
-      if (!kLongFirst || cu < hi) open_unit(unit_at(cu));
+      open_unit(unit_at(cu));
     }
     fetch(f1, slot, 1);
     multiply(f0, std::integral_constant<int, 0>{}, loads(std::integral_constant<int, 1>{}));
@@ -430,6 +434,41 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   }
   multiply(f1, std::integral_constant<int, 1>{}, nothing);
   store();
+}
+
+// grid kTileGroups, 512 threads
+template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO>
+__global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
+  using Sh = TileShape<BM, BN, WN, LO>;
+  static_assert(DT == SERE_BF16 || !LO, "fp32 keeps h as it is");
+  constexpr bool kHalves = DT == SERE_BF16 && !(BM == 256 && BN == 256);
+  using Half = TileShape<kHalves ? BM / 2 : BM, BN, WN, LO>;
+  constexpr int kRing = Sh::kStages * Sh::kStageBytes, kHalfRing = Half::kStages * Half::kStageBytes;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kRing > kHalfRing ? kRing : kHalfRing];
+  const unsigned parts = tile_parts<GATEUP, BM>(p), total = static_cast<unsigned>(scalar_load(p.n_work, 0)) * parts;
+  const unsigned xcd = blockIdx.x % kXcds;
+  const auto share = [](unsigned n, unsigned x) { return n / kXcds * x + min(x, n % kXcds); };   // units before XCD x's
+  // This workgroup's units: one of every round of its XCD's contiguous range.
+  if constexpr (kHalves) {
+    const unsigned lo = share(total, xcd), hi = share(total, xcd + 1);
+    const unsigned rest = (hi - lo) % kStride, whole = rest <= kStride / 2 ? hi - rest : hi;
+    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, lo, whole, 0, 0, 0);
+    if (whole < hi) {
+      __builtin_amdgcn_s_barrier();                      // every wavefront has read its last stage
+      asm volatile("" ::: "memory");
+      tile_units<DT, GATEUP, BM / 2, BN, WN, LO, 2>(p, lds, 2 * whole, 2 * hi, 0, 0, 0);
+    }
+  } else if constexpr (DT == SERE_BF16) {
+    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, share(total, xcd), share(total, xcd + 1), 0, 0, 0);
+  } else {
+    // An eighth of the units of the long items and then an eighth of the others; the rounds that hold long ones go round the
+    // XCD's workgroups one way, the ones behind them the other way, so that those without a long unit get the one more
+    // that a last round has for some.
+    const unsigned total_long = static_cast<unsigned>(scalar_load(p.n_work, 2)) * parts, others = total - total_long;
+    const unsigned to_long = share(total_long, xcd), longs = share(total_long, xcd + 1) - to_long;
+    const unsigned before = share(others, kXcds - xcd), after = share(others, kXcds - 1 - xcd);
+    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, 0, longs + before - after, longs, to_long, total - before - longs);
+  }
 }
 
 }  // namespace sere
