@@ -21,6 +21,7 @@
 #include "ffn_generic.hpp"
 #include "ffn_mfma.hpp"
 #include "route_kernels.hpp"
+#include "rules.hpp"
 
 namespace sere {
 
@@ -54,7 +55,7 @@ struct SmallRouteShared {
 constexpr int kSmallPrimary = 0x100;
 
 // Top-K: a wavefront takes a token, a lane one of the first eight entries of each of its sorted lists (16 lists: of two).  An
-// entry's rank is the number of larger keys, counted by their upper halves; if two of these are equal, the whole keys are
+// entry's rank is the number of larger keys, counted by their upper halves (rules.hpp); if two of these are equal, the whole keys are
 // compared, and equal ones go in the order of the experts, which is the order of (list, place).  (A merge of the list heads,
 // one round after the other, takes 2.3 us for K = 8; comparing whole keys throughout 3.7; this 1.5.)
 template <int N>
@@ -63,7 +64,7 @@ __device__ __forceinline__ void small_topk(const uint64_t* __restrict__ list_key
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, K = p.K, nlists = (p.M + 15) >> 4;
   for (int t = wave; t < p.T; t += kSmallWaves) {
     uint64_t key[N];
-    uint32_t high[N], rank[N];
+    uint32_t word[N], rank[N];
     int id[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
@@ -75,10 +76,8 @@ __device__ __forceinline__ void small_topk(const uint64_t* __restrict__ list_key
     uint32_t sum = 0;
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      // places without an expert (key 0): below the others, one below the other
-      const bool real = lane / 8 + 8 * n < nlists && key[n] != 0;
-      if (!real) key[n] = static_cast<uint64_t>(64 * N - 1 - (lane + 64 * n)) << 32;
-      high[n] = static_cast<uint32_t>(key[n] >> 32);
+      if (lane / 8 + 8 * n >= nlists) key[n] = 0;
+      word[n] = rank_word(key[n], lane + 64 * n, 64 * N);
       rank[n] = 0;
     }
 #pragma unroll
@@ -86,9 +85,9 @@ __device__ __forceinline__ void small_topk(const uint64_t* __restrict__ list_key
       for (int l = 0; l < min(8, nlists - 8 * n); ++l)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const uint32_t other = read_lane(high[n], 8 * l + j);
+          const uint32_t other = read_lane(word[n], 8 * l + j);
 #pragma unroll
-          for (int m = 0; m < N; ++m) rank[m] += other > high[m] ? 1u : 0u;
+          for (int m = 0; m < N; ++m) rank[m] += other > word[m] ? 1u : 0u;
         }
     const int entries = 8 * nlists;
 #pragma unroll
@@ -101,7 +100,7 @@ __device__ __forceinline__ void small_topk(const uint64_t* __restrict__ list_key
         const uint64_t other = static_cast<uint64_t>(static_cast<uint32_t>(read_lane(static_cast<int>(mine >> 32), b & 63))) << 32 |
                                static_cast<uint32_t>(read_lane(static_cast<int>(mine), b & 63));
 #pragma unroll
-        for (int n = 0; n < N; ++n) rank[n] += other > key[n] || (other == key[n] && b < lane + 64 * n) ? 1u : 0u;
+        for (int n = 0; n < N; ++n) rank[n] += ranks_before(other, b, key[n], lane + 64 * n) ? 1u : 0u;
       }
     }
 #pragma unroll

@@ -118,3 +118,26 @@ def test_one_expert_has_every_slot(dev, case):  # noqa: F811
     layer.run_decode()
     check_routing(layer.routing_to_host(), ref, layer.cfg)
     check_output(layer.out_to_host_f64(), ref.out_sere, dtype, "one expert")
+
+
+@pytest.mark.parametrize("dtype", [wk.BF16, wk.F32])
+@pytest.mark.parametrize("M,K", [(3, 2), (19, 8), (130, 4)])
+def test_a_token_of_nan_chooses_experts(dev, dtype, M, K):  # noqa: F811
+    """Hidden states whose bits are all set (memory that nobody wrote; no precondition allows them): the smallest keys there
+    are.  The ids are those of the launches for larger calls, so experts, and the other token's output is what it is."""
+    def mutate(wl):
+        wl.hidden.view(np.uint32 if dtype == wk.F32 else np.uint16)[1] = 0xffffffff if dtype == wk.F32 else 0xffff
+    wl, layer, sim = small_case(dev, dtype, 2, 64, M, K, 64, 0, 9800 + M, K, 0.0, mutate=mutate)
+    print(f"small nan dtype {dtype} M {M}", flush=True)
+    layer.run_route()
+    want = layer.routing_to_host()
+    assert want["topk_ids"].max() < M and all(len(set(row)) == K for row in want["topk_ids"].tolist())
+    for run in (layer.run_decode, layer.run_baseline):
+        run()
+        got = layer.routing_to_host()
+        for name in want:
+            assert np.array_equal(got[name], want[name], equal_nan=True) or name == "topk_weights", name
+        out = layer.out_to_host_f64()
+        assert np.isnan(out[1]).all()
+        alone = oracle.layer(wl.hidden[:1], wl.router_w, wl.w_gate_up, wl.w_down, None, None, dtype, K, sim, K, 0.0)
+        check_output(out[:1], alone.out_base, dtype, "the other token")

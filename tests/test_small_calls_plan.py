@@ -25,6 +25,7 @@ def small(tmp_path_factory):
 def test_the_gpu_cases_take_them(small):
     calls = [(dt, T, dh, M, K, dm, sh, S, rho, reroute) for dt, T, dh, M, K, dm, sh, S, rho in gpu.CASES for reroute in (0, 1)]
     calls += [(*c, 1) for c in gpu.SAME] + [(dt, 4, 256, 40, 5, 64, 0, S, rho, 1) for dt in (0, 1) for S, rho in ((1, 0.0), (2, 0.25), (2, 0.0))]
+    calls += [(dt, 2, 64, M, K, 64, 0, K, 0.0, reroute) for dt in (0, 1) for M, K in ((3, 2), (19, 8), (130, 4)) for reroute in (0, 1)]
     for call, (fits, pays, _, _) in zip(calls, small(calls)):
         assert fits and pays, call
 
