@@ -296,10 +296,10 @@ int sere_similarity_cka(const sere_config *cfg, const void *calib, int32_t num_b
  * SERE_TIMING_MAX_RECORDS launches are kept, later ones are not recorded; the
  * few microseconds that write the work list of a similarity estimation belong
  * to no stage).
- * Calls of few slots, which otherwise run top-K to gate/up and down to combine as one launch
- * each, run a launch for every stage while it is enabled (the same routing, outputs alike to
- * the rounding of the sums), and similarity estimations on layers of at most 8 MiB of weights
- * take their batches one at a time.
+ * What is launched does not depend on whether it is timed.  A launch that does the work of two
+ * stages (calls of few slots: top-K to gate/up is one launch, down to combine another) is recorded
+ * for both, with its whole time in each; one that serves several calibration batches of a similarity
+ * estimation counts once for every batch.
  * Do not enable it on a stream that is being captured into a HIP graph.
  * sere_stage_timing_read waits for the recorded events, adds the elapsed
  * milliseconds and launch counts per stage into the two arrays of

@@ -260,7 +260,7 @@ def sere_stage_timing(enable: bool) -> None:
 
 
 def sere_stage_timing_read():
-    """-> ({stage: total ms}, {stage: launches}) since the last read."""
+    """-> ({stage: total ms}, {stage: launches}) since the last read; include/sere.h says what a launch counts as."""
     ms = (ctypes.c_double * len(STAGES))()
     n = (ctypes.c_int32 * len(STAGES))()
     _check(load().sere_stage_timing_read(ms, n))

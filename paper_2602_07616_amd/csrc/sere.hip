@@ -130,18 +130,25 @@ static int check_workspace(const Layout& l, const void* ws, size_t bytes) {
 }
 
 // ---------------------------------------------------------------- timing ---
+// What a launch is recorded as.  What is launched never depends on whether it is timed.
+struct StageMark {
+  int stage, also;   // the stages whose work it does: one, or two (else -1)
+  int times;         // calibration batches that it serves (similarity estimation; else 1)
+  StageMark(int stage_, int also_ = -1, int times_ = 1) : stage(stage_), also(also_), times(times_) {}
+};
+
 struct Timing {
   bool enabled = false;
   int n = 0;
   int created = 0;
   hipEvent_t start[SERE_TIMING_MAX_RECORDS];
   hipEvent_t stop[SERE_TIMING_MAX_RECORDS];
-  int stage[SERE_TIMING_MAX_RECORDS];
+  int stage[SERE_TIMING_MAX_RECORDS], also[SERE_TIMING_MAX_RECORDS], times[SERE_TIMING_MAX_RECORDS];
 };
 static Timing g_timing;
 
-// Event pair for the next launch of `stage`, if timing is on and a record is free.
-static bool timing_slot(int stage, hipEvent_t* start, hipEvent_t* stop) {
+// Event pair for the next launch, if timing is on and a record is free.
+static bool timing_slot(const StageMark& mark, hipEvent_t* start, hipEvent_t* stop) {
   Timing& t = g_timing;
   if (!t.enabled || t.n >= SERE_TIMING_MAX_RECORDS) return false;
   if (t.n >= t.created) {
@@ -152,19 +159,21 @@ static bool timing_slot(int stage, hipEvent_t* start, hipEvent_t* stop) {
     }
     ++t.created;
   }
-  t.stage[t.n] = stage;
+  t.stage[t.n] = mark.stage;
+  t.also[t.n] = mark.also;
+  t.times[t.n] = mark.times;
   *start = t.start[t.n];
   *stop = t.stop[t.n];
   return true;
 }
 
-// One kernel launch of a stage.  With timing on, the two events are attached to the dispatch
+// One kernel launch.  With timing on, the two events are attached to the dispatch
 // itself (they take the kernel's own start and end time stamps, as a profiler's kernel trace
 // does), not recorded around it on the stream.
 template <typename Kernel, typename... Args>
-static void launch_stage(int stage, hipStream_t s, Kernel kernel, dim3 grid, dim3 block, Args... args) {
+static void launch_stage(const StageMark& mark, hipStream_t s, Kernel kernel, dim3 grid, dim3 block, Args... args) {
   hipEvent_t e0, e1;
-  if (timing_slot(stage, &e0, &e1)) {
+  if (timing_slot(mark, &e0, &e1)) {
     hipExtLaunchKernelGGL(kernel, grid, block, 0, s, e0, e1, 0, args...);
     ++g_timing.n;
   } else {
@@ -351,62 +360,63 @@ static void launch_combine(const sere_config& c, const Layout& l, const Pointers
 }
 
 template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO = false>
-static void launch_tile_as(const FfnArgs& f, hipStream_t s) {
-  launch_stage(GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, s, ffn_tile<DT, GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
+static void launch_tile_as(const FfnArgs& f, hipStream_t s, int times) {
+  launch_stage({GATEUP ? SERE_STAGE_GATE_UP : SERE_STAGE_DOWN, -1, times}, s, ffn_tile<DT, GATEUP, BM, BN, WN, LO>, dim3(kTileGroups),
                dim3(kTileThreads), f);
 }
 template <bool GATEUP>
-static void launch_tile(const FfnPlan& plan, const FfnArgs& f, hipStream_t s) {
+static void launch_tile(const FfnPlan& plan, const FfnArgs& f, hipStream_t s, int times) {
   if (!GATEUP && f.split_h) {  // both planes of the token rows count in the second size
     switch (plan.item_rows) {
-      case 32: launch_tile_as<SERE_BF16, false, 256, 64, 2, true>(f, s); return;
-      case 64: launch_tile_as<SERE_BF16, false, 256, 128, 2, true>(f, s); return;
-      default: launch_tile_as<SERE_BF16, false, 128, 256, 4, true>(f, s); return;
+      case 32: launch_tile_as<SERE_BF16, false, 256, 64, 2, true>(f, s, times); return;
+      case 64: launch_tile_as<SERE_BF16, false, 256, 128, 2, true>(f, s, times); return;
+      default: launch_tile_as<SERE_BF16, false, 128, 256, 4, true>(f, s, times); return;
     }
   }
   switch (plan.item_rows) {
-    case 32: launch_tile_as<SERE_BF16, GATEUP, 256, 32, 2>(f, s); return;
-    case 64: launch_tile_as<SERE_BF16, GATEUP, 256, 64, 2>(f, s); return;
-    case 96: launch_tile_as<SERE_BF16, GATEUP, 256, 96, 2>(f, s); return;
-    case 128: launch_tile_as<SERE_BF16, GATEUP, 256, 128, 2>(f, s); return;
-    case 160: launch_tile_as<SERE_BF16, GATEUP, 256, 160, 2>(f, s); return;
-    case 192: launch_tile_as<SERE_BF16, GATEUP, 128, 192, 4>(f, s); return;
+    case 32: launch_tile_as<SERE_BF16, GATEUP, 256, 32, 2>(f, s, times); return;
+    case 64: launch_tile_as<SERE_BF16, GATEUP, 256, 64, 2>(f, s, times); return;
+    case 96: launch_tile_as<SERE_BF16, GATEUP, 256, 96, 2>(f, s, times); return;
+    case 128: launch_tile_as<SERE_BF16, GATEUP, 256, 128, 2>(f, s, times); return;
+    case 160: launch_tile_as<SERE_BF16, GATEUP, 256, 160, 2>(f, s, times); return;
+    case 192: launch_tile_as<SERE_BF16, GATEUP, 128, 192, 4>(f, s, times); return;
     default:
       if constexpr (GATEUP) {
         if (plan.wide_gate_up) {
-          launch_tile_as<SERE_BF16, true, 256, 256, 4>(f, s);
+          launch_tile_as<SERE_BF16, true, 256, 256, 4>(f, s, times);
           return;
         }
       }
-      launch_tile_as<SERE_BF16, GATEUP, 128, 256, 4>(f, s);
+      launch_tile_as<SERE_BF16, GATEUP, 128, 256, 4>(f, s, times);
   }
 }
 
-// fp32 layers: the persistent kernels, or the vector-ALU ones.  bf16 layers: matrix-core kernels.  As planned.
+// fp32 layers: the persistent kernels, or the vector-ALU ones.  bf16 layers: matrix-core kernels.  As planned.  `times`: see StageMark.
 static void launch_gateup_down(int dtype, int inter, int hidden, int max_work, const FfnPlan& plan, const FfnArgs& f,
-                               hipStream_t s, bool waves8 = false) {
+                               hipStream_t s, bool waves8 = false, int times = 1) {
+  const StageMark gate_up{SERE_STAGE_GATE_UP, -1, times}, down{SERE_STAGE_DOWN, -1, times};
   if (dtype == SERE_F32 && plan.tile_gate_up) {
-    launch_tile_as<SERE_F32, true, kTileF32Rows, kItemRows, 2>(f, s);
-    launch_tile_as<SERE_F32, false, kTileF32Rows, kItemRows, 2>(f, s);
+    launch_tile_as<SERE_F32, true, kTileF32Rows, kItemRows, 2>(f, s, times);
+    launch_tile_as<SERE_F32, false, kTileF32Rows, kItemRows, 2>(f, s, times);
     return;
   }
   if (dtype == SERE_F32) {
-    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_generic<SERE_F32>, dim3((inter + kGenJB - 1) / kGenJB, max_work),
+    launch_stage(gate_up, s, ffn_gateup_generic<SERE_F32>, dim3((inter + kGenJB - 1) / kGenJB, max_work),
                  dim3(256), f);
-    launch_stage(SERE_STAGE_DOWN, s, ffn_down_generic<SERE_F32>, dim3((hidden + kGenRB - 1) / kGenRB, max_work),
+    launch_stage(down, s, ffn_down_generic<SERE_F32>, dim3((hidden + kGenRB - 1) / kGenRB, max_work),
                  dim3(256), f);
     return;
   }
   if (plan.tile_gate_up)
-    launch_tile<true>(plan, f, s);
+    launch_tile<true>(plan, f, s, times);
   else if (waves8)
-    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<8>, dim3(inter / (kGateUpJ * 8), max_work), dim3(512), f);
+    launch_stage(gate_up, s, ffn_gateup_mfma<8>, dim3(inter / (kGateUpJ * 8), max_work), dim3(512), f);
   else
-    launch_stage(SERE_STAGE_GATE_UP, s, ffn_gateup_mfma<4>, dim3(inter / (kGateUpJ * 4), max_work), dim3(256), f);
+    launch_stage(gate_up, s, ffn_gateup_mfma<4>, dim3(inter / (kGateUpJ * 4), max_work), dim3(256), f);
   if (plan.tile_down)
-    launch_tile<false>(plan, f, s);
+    launch_tile<false>(plan, f, s, times);
   else
-    launch_stage(SERE_STAGE_DOWN, s, ffn_down_mfma,
+    launch_stage(down, s, ffn_down_mfma,
                  dim3(((hidden + kDownRows * kWavesPerBlock - 1) / (kDownRows * kWavesPerBlock)) * plan.ksplit, max_work),
                  dim3(256), f);
 }
@@ -429,7 +439,7 @@ static void launch_small(const sere_config& c, const Layout& l, const Pointers& 
   const int split = small_split(c.hidden * (c.dtype == SERE_F32 ? 4 : 2) / kSmallBlock, rows);
   const dim3 grid(1 + std::min(small_units(rows, split), kSmallGroups));
 #define SERE_LAUNCH_SMALL(DT, LISTS)                                                                                               \
-  launch_stage(SERE_STAGE_GATE_UP, s, ffn_small_gate_up<DT, LISTS>, grid, dim3(kSmallThreads), f, p.route, p.list_key, \
+  launch_stage({SERE_STAGE_ROUTE, SERE_STAGE_GATE_UP}, s, ffn_small_gate_up<DT, LISTS>, grid, dim3(kSmallThreads), f, p.route, p.list_key, \
                p.list_id, p.topk_ids, p.topk_w, split)
 #define SERE_LAUNCH_SMALL_LISTS(DT) \
   if (lists <= 8)                   \
@@ -440,10 +450,10 @@ static void launch_small(const sere_config& c, const Layout& l, const Pointers& 
   const dim3 down(c.hidden / kSmallOut);
   if (c.dtype == SERE_F32) {
     SERE_LAUNCH_SMALL_LISTS(SERE_F32);
-    launch_stage(SERE_STAGE_DOWN, s, ffn_small_down<SERE_F32>, down, dim3(kSmallThreads), f, ca);
+    launch_stage({SERE_STAGE_DOWN, SERE_STAGE_COMBINE}, s, ffn_small_down<SERE_F32>, down, dim3(kSmallThreads), f, ca);
   } else {
     SERE_LAUNCH_SMALL_LISTS(SERE_BF16);
-    launch_stage(SERE_STAGE_DOWN, s, ffn_small_down<SERE_BF16>, down, dim3(kSmallThreads), f, ca);
+    launch_stage({SERE_STAGE_DOWN, SERE_STAGE_COMBINE}, s, ffn_small_down<SERE_BF16>, down, dim3(kSmallThreads), f, ca);
   }
 #undef SERE_LAUNCH_SMALL_LISTS
 #undef SERE_LAUNCH_SMALL
@@ -510,8 +520,7 @@ static int decode(const sere_config* cfg, const void* hidden, const void* router
   if (!reroute) p.route.S = cfg->top_k;  // every slot is a primary slot: identity map
   st = launch_router(*cfg, p, hidden, router_w, s);
   if (st != SERE_OK) return st;
-  // (stage timing reports every stage, so each is a launch of its own while it is on)
-  const bool small = small_call_pays(*cfg, reroute) && !g_timing.enabled;
+  const bool small = small_call_pays(*cfg, reroute);
   if (!small) st = launch_route(*cfg, p, true, s);
   if (st != SERE_OK) return st;
 
@@ -577,14 +586,14 @@ static int check_similarity_sizes(const sere_config& c, int32_t num_batches, int
 }
 
 // up to 64 experts, in tiles of 16
-static void launch_pair_gram_few(bool cosine, dim3 grid, const float* y, int ksplit, int rows, int n, int dh, int M, long long chunk,
+static void launch_pair_gram_few(const StageMark& pairs, bool cosine, dim3 grid, const float* y, int ksplit, int rows, int n, int dh, int M, long long chunk,
                                  double* part, const double* inv_norm, unsigned long long* max_bits, hipStream_t s) {
 #define SERE_LAUNCH_FEW(TILES)                                                                                          \
   if (cosine)                                                                                                           \
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_few_kernel<TILES, true>, grid, dim3(256), y, ksplit, rows, n, dh, M, \
+    launch_stage(pairs, s, pair_gram_few_kernel<TILES, true>, grid, dim3(256), y, ksplit, rows, n, dh, M, \
                  chunk, part, inv_norm, max_bits);                                                                      \
   else                                                                                                                  \
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_few_kernel<TILES, false>, grid, dim3(256), y, ksplit, rows, n, dh,  \
+    launch_stage(pairs, s, pair_gram_few_kernel<TILES, false>, grid, dim3(256), y, ksplit, rows, n, dh,  \
                  M, chunk, part, inv_norm, max_bits)
   if (M <= 16) {
     SERE_LAUNCH_FEW(1);
@@ -627,7 +636,8 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
     hipLaunchKernelGGL(similarity_worklist_kernel, dim3((l.rows + 255) / 256), dim3(256), 0, s, M, n * g, l.plan.item_rows,
                        const_cast<int32_t*>(f.sorted_token), const_cast<int32_t*>(f.work_expert),
                        const_cast<int32_t*>(f.work_off), const_cast<int32_t*>(f.work_cnt), const_cast<int32_t*>(f.n_work));
-  launch_gateup_down(c.dtype, c.inter, dh, M * l.items, l.plan, f, s);
+  launch_gateup_down(c.dtype, c.inter, dh, M * l.items, l.plan, f, s, false, g);
+  const StageMark pairs{SERE_STAGE_SIM_PAIRS, -1, g};
 
   const int metric = (c.flags & SERE_FLAG_SIM_COSINE)
                          ? kMetricCosine
@@ -644,15 +654,15 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
     const int side = cka_block(n), nb = cka_blocks(n);
     double* rowsum = reinterpret_cast<double*>(ws + (linear ? l.block_sums : l.rowsum));
     double* diag = linear ? nullptr : reinterpret_cast<double*>(ws + l.diag);
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, side == 16 ? cka_gram_kernel<1> : cka_gram_kernel<2>, dim3(nb * (nb + 1) / 2, M * g),
+    launch_stage(pairs, s, side == 16 ? cka_gram_kernel<1> : cka_gram_kernel<2>, dim3(nb * (nb + 1) / 2, M * g),
                  dim3(256), y, f.ksplit, l.rows, n, dh, gram, rowsum, diag);
     if (!linear)
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_transform_kernel, dim3(n, M * g), dim3(256), gram,
+      launch_stage(pairs, s, gram_transform_kernel, dim3(n, M * g), dim3(256), gram,
                    static_cast<const double*>(diag), n, cka_kernel, p0, static_cast<int>(p1), rowsum);
     const int mb = (M + 15) / 16;
     parts = l.cka_parts;
     if (parts > 1) dist = reinterpret_cast<double*>(ws + l.y);   // no longer needed
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, cka_pair_kernel, dim3(mb * (mb + 1) / 2, parts, g), dim3(256),
+    launch_stage(pairs, s, cka_pair_kernel, dim3(mb * (mb + 1) / 2, parts, g), dim3(256),
                  static_cast<const double*>(gram), static_cast<const double*>(rowsum), linear ? nb : 1, n, M, dist);
   } else {
     double* part = reinterpret_cast<double*>(ws + l.gram_part);
@@ -660,31 +670,31 @@ static void similarity_group(const sere_config& c, const SimLayout& l, const cha
     const int nb = (M + kGramBlock - 1) / kGramBlock;
     const dim3 blocks(nb * (nb + 1) / 2, l.gram_splits, g);
     if (metric == kMetricCosine) {
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), f.y, f.ksplit, l.rows, dh,
+      launch_stage(pairs, s, row_norm_kernel, dim3((l.rows + 3) / 4), dim3(256), f.y, f.ksplit, l.rows, dh,
                    const_cast<double*>(inv_norm));
     }
     if (M <= kGramBlock) {
-      launch_pair_gram_few(metric == kMetricCosine, blocks, y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part, inv_norm, max_bits, s);
+      launch_pair_gram_few(pairs, metric == kMetricCosine, blocks, y, f.ksplit, l.rows, n, dh, M, l.gram_chunk, part, inv_norm, max_bits, s);
     } else if (metric == kMetricCosine) {
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<true>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
+      launch_stage(pairs, s, pair_gram_kernel<true>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
                    l.gram_chunk, part, inv_norm, max_bits);
     } else if (l.gram_staged) {
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_staged_kernel, dim3(gram_triangles(M) + gram_squares(M), l.gram_splits, g),
+      launch_stage(pairs, s, pair_gram_staged_kernel, dim3(gram_triangles(M) + gram_squares(M), l.gram_splits, g),
                    dim3(kGramStagedThreads), y, n, dh, M, l.gram_chunk, part, max_bits);
     } else {
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, pair_gram_kernel<false>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
+      launch_stage(pairs, s, pair_gram_kernel<false>, blocks, dim3(256), y, f.ksplit, l.rows, n, dh, M,
                    l.gram_chunk, part, inv_norm, max_bits);
     }
-    launch_stage(SERE_STAGE_SIM_PAIRS, s, gram_reduce_kernel, dim3(entries, kGramGroups, g), dim3(256),
+    launch_stage(pairs, s, gram_reduce_kernel, dim3(entries, kGramGroups, g), dim3(256),
                  static_cast<const double*>(part), l.gram_splits, M, gram);
     if (metric == kMetricCosine)
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, cosine_mean_kernel, dim3(entries, g), dim3(256), static_cast<const double*>(gram),
+      launch_stage(pairs, s, cosine_mean_kernel, dim3(entries, g), dim3(256), static_cast<const double*>(gram),
                    inv_norm, n, M, dist);
     else
-      launch_stage(SERE_STAGE_SIM_PAIRS, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
+      launch_stage(pairs, s, frobenius_distance_kernel, dim3(entries, g), dim3(256),
                    static_cast<const double*>(gram), y, f.ksplit, l.rows, n, dh, M, dist, max_bits);
   }
-  launch_stage(SERE_STAGE_SIM_PAIRS, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), parts, M,
+  launch_stage(pairs, s, similarity_accumulate_kernel, dim3(entries), dim3(256), static_cast<const double*>(dist), parts, M,
                b0, g, num_batches, metric, static_cast<const unsigned long long*>(max_bits),
                reinterpret_cast<double*>(ws + l.acc), sim);
 }
@@ -704,7 +714,7 @@ static int similarity(const sere_config* cfg, const void* calib, int32_t num_bat
   if (pc.status != SERE_OK) return pc.status;
   if (workspace == nullptr) return SERE_ERR_NULL_PTR;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return SERE_ERR_MISALIGNED;
-  const int whole = std::min(sim_group(*cfg, batch_tokens, g_timing.enabled), num_batches);
+  const int whole = std::min(sim_group(*cfg, batch_tokens), num_batches);
   int group = whole;
   while (group > 1 && make_sim_layout(*cfg, batch_tokens, group, whole).total > workspace_bytes) --group;
   const SimLayout l = make_sim_layout(*cfg, batch_tokens, group, whole);
@@ -804,7 +814,7 @@ int sere_moe_decode_baseline(const sere_config* cfg, const void* hidden, const v
 
 size_t sere_similarity_workspace_bytes(const sere_config* cfg, int32_t batch_tokens) {
   if (check_config(cfg) != SERE_OK || check_similarity_sizes(*cfg, 1, batch_tokens) != SERE_OK) return 0;
-  const int group = sim_group(*cfg, batch_tokens, false);
+  const int group = sim_group(*cfg, batch_tokens);
   return make_sim_layout(*cfg, batch_tokens, group, group).total;
 }
 
@@ -876,8 +886,11 @@ int sere_stage_timing_read(double* total_ms, int32_t* launches) {
       status = SERE_ERR_HIP;
       continue;
     }
-    total_ms[t.stage[i]] += ms;
-    launches[t.stage[i]] += 1;
+    for (const int stage : {t.stage[i], t.also[i]}) {
+      if (stage < 0) continue;
+      total_ms[stage] += ms;
+      launches[stage] += t.times[i];
+    }
   }
   t.n = 0;
   return status;

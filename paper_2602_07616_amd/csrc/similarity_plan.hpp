@@ -40,12 +40,11 @@ constexpr int gram_triangles(int M) { return (M + 127) / 128; }
 // experts, d_h 1920 450 / 288 / 249.  41 calls with more than 256 tokens: 1.45 / 1.47 times as fast on average, none slower.
 // Measured on 14 layers of 0.8 to 288 MB, three metrics, 2 to 16 batches of 4 to 100 tokens: a group takes 0.1 to 0.9
 // times what its batches take one by one, the less the smaller layer and batch (12 MB, 8 batches of 32 tokens: 249 / 58
-// us, 288 MB: 667 / 225).  While stages are timed layers of at most kSimGroupWeights stay at one batch at a time, so that the launches
-// that are counted are one a batch there, as those who read them on a small layer expect.  us a call of such layers, one batch at a
-// time / in a group: 3 batches of 66 tokens, 2 experts, d_h 576 109 / 47, 4 of 13, 4 experts of d_h 384 in fp32 116 / 38, 2 of 31, 19
-// experts of d_h 256 54 / 34; 13 calls 2.1 times as fast on average, none less than 1.35 times.
+// us, 288 MB: 667 / 225).  us a call of layers of at most 8 MiB, one batch at a time / in a group: 3 batches of 66 tokens, 2
+// experts, d_h 576 109 / 47, 4 of 13, 4 experts of d_h 384 in fp32 116 / 38, 2 of 31, 19 experts of d_h 256 54 / 34; 13 calls 2.1
+// times as fast on average, none less than 1.35 times.
 constexpr int kSimGroupRows = 1024, kSimGroupShortRows = 256, kSimGroupMin = 8, kSimGroupMax = 16;
-constexpr size_t kSimGroupBytes = size_t{1} << 30, kSimGroupWeights = size_t{8} << 20;
+constexpr size_t kSimGroupBytes = size_t{1} << 30;
 
 struct SimLayout {
   size_t sorted_token, work_expert, work_off, work_cnt, n_work, h, y, dist, acc, gram, rowsum, diag, gram_part, inv_norm, max_bits,
@@ -189,11 +188,10 @@ inline SimLayout make_sim_layout(const sere_config& c, int n, int g, int whole) 
   return l;
 }
 
-// Largest group of a call; `timed`: while stages are timed.  A workspace is sized for the other.
-inline int sim_group(const sere_config& c, int n, bool timed = true) {
-  const size_t weights = static_cast<size_t>(c.num_experts) * 3 * c.hidden * c.inter * (c.dtype == SERE_F32 ? 4 : 2);
+// Largest group of a call; a workspace is sized for it.
+inline int sim_group(const sere_config& c, int n) {
   const int batches = std::max(std::min(kSimGroupMin, kSimGroupRows / n), std::min(kSimGroupMax, kSimGroupShortRows / n));
-  int g = timed && weights <= kSimGroupWeights ? 1 : std::max(1, batches);
+  int g = std::max(1, batches);
   while (g > 1 && make_sim_layout(c, n, g, g).total > kSimGroupBytes) --g;
   return g;
 }

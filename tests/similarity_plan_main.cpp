@@ -3,17 +3,17 @@
 // gram_staged item_bytes part_bytes wide_gate_up y_bytes h_bytes cka_parts cka_blocks gram_steps few_steps", item_bytes,
 // part_bytes, y_bytes and h_bytes the room for an array of the work list, for the partial Gram matrices, for y and for h,
 // gram_steps the 16-wide steps of a slice and few_steps those that pair_gram_few_kernel takes a turn of its loop; groups separated
-// by ';'.  As while stages are timed or, with an argument, as otherwise.  Host code only.
+// by ';'.  Host code only.
 #include <cstdio>
 
 #include "../paper_2602_07616_amd/csrc/similarity_plan.hpp"
 
-int main(int argc, char**) {
+int main() {
   sere_config c{};
   int n = 0, batches = 0;
   while (std::scanf("%d %d %d %d %d %d %d", &c.dtype, &c.hidden, &c.num_experts, &c.inter, &n, &c.flags,
                     &batches) == 7) {
-    const int most = sere::sim_group(c, n, argc < 2), whole = batches < most ? batches : most;
+    const int most = sere::sim_group(c, n), whole = batches < most ? batches : most;
     for (int g = 1; g <= whole; ++g) {
       const sere::SimLayout l = sere::make_sim_layout(c, n, g, whole);
       std::printf("%zu %d %d %d %d %d %d %d %zu %zu %d %zu %zu %d %d %lld %d;", l.total, l.items, l.plan.item_rows,

@@ -1,5 +1,5 @@
-"""Similarity on layers of at most 8 MiB of weights, whose batches are taken in groups unless stages are timed: against the
-oracle, against smaller groups, and against one batch at a time.  The CPU test checks the groups' layouts."""
+"""Similarity on layers of at most 8 MiB of weights, whose batches are taken in groups as those of larger ones: against the
+oracle, against smaller groups, and while stages are timed.  The CPU test checks the groups' layouts."""
 import os
 import subprocess
 
@@ -43,21 +43,28 @@ def test_small_layers_in_groups(dev, case, metric):  # noqa: F811
     small = torch.empty(int(whole * 0.4), dtype=torch.uint8, device="cuda")
     B.sere_similarity(cfg, calib, batches, n, gu, dn, sim, small)
     assert np.abs(sim.cpu().numpy() - got).max() <= 1.2e-7       # the fp64 sums are split differently: values up to 1, two results
-    B.sere_stage_timing(True)
-    sim.fill_(-3.0)
-    B.sere_similarity(cfg, calib, batches, n, gu, dn, sim, small)
-    _, launches = B.sere_stage_timing_read()
-    B.sere_stage_timing(False)
-    assert launches["gate_up"] == batches
-    assert np.abs(sim.cpu().numpy() - want).max() <= tol
+    # stage timing changes nothing but what is recorded, and every batch counts
+    whole_ws = torch.empty(whole, dtype=torch.uint8, device="cuda")
+    pairs = {"frobenius": 4, "cosine": 5, "cka_linear": 3}[metric]
+    for ws in (small, whole_ws):
+        sim.fill_(-3.0)
+        B.sere_similarity(cfg, calib, batches, n, gu, dn, sim, ws)
+        untimed = sim.clone()
+        B.sere_stage_timing(True)
+        sim.fill_(-3.0)
+        B.sere_similarity(cfg, calib, batches, n, gu, dn, sim, ws)
+        ms, launches = B.sere_stage_timing_read()
+        B.sere_stage_timing(False)
+        assert launches["gate_up"] == launches["down"] == batches and launches["sim_pairs"] == pairs * batches and ms["sim_pairs"] > 0
+        assert torch.equal(sim, untimed)
 
 
-def test_layouts_of_groups_that_are_not_timed(tmp_path):
+def test_layouts_of_groups(tmp_path):
     exe = str(tmp_path / "plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "similarity_plan_main.cpp"), "-o", exe], check=True)
     cases = [c for c in draws(6000, 21) if c[2] * 3 * c[1] * c[3] * (4 if c[0] == B.SERE_F32 else 2) <= 8 << 20]
     cases += [(dt, dh, M, dm, n, f, b) for dt, dh, M, dm, n, b in CASES for f in METRICS]
-    out = subprocess.run([exe, "x"], input="".join("%d %d %d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
+    out = subprocess.run([exe], input="".join("%d %d %d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
                          check=True).stdout.split("\n")
     assert len(cases) > 1000
     for case, line in zip(cases, out):

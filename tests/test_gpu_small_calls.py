@@ -1,6 +1,8 @@
 """Calls of at most 64 slots that take two launches behind the router logits (csrc/ffn_small.hpp), at the edges of what they
-take: against the oracle, and against the launches for larger calls, which serve a call while stages are timed.
+take: against the oracle, and against the launches for larger calls, which serve the same tokens given several times over.
 tests/test_small_calls_plan.py checks on the CPU that the cases take them."""
+import copy
+
 import numpy as np
 import pytest
 
@@ -55,19 +57,32 @@ def test_small_calls(dev, case):  # noqa: F811
     layer.cfg.flags = 0
     layer.run_baseline()
     check_output(layer.out_to_host_f64(), ref.out_base, dtype, "baseline")
-    small = layer.out_to_host_f64()
-    before = layer.routing_to_host()
+    small, before = layer.out.clone(), layer.routing_to_host()
+    # while stages are timed the same launches run, each recorded for the stages that it does
     B.sere_stage_timing(True)
+    layer.out.zero_()
     layer.run_baseline()
-    _, launches = B.sere_stage_timing_read()
+    ms, launches = B.sere_stage_timing_read()
     B.sere_stage_timing(False)
-    assert launches["route"] == launches["combine"] == 1
-    after = layer.routing_to_host()
-    for name in before:
-        if name != "topk_weights":
-            assert np.array_equal(before[name], after[name]), name
+    assert all(launches[stage] == 1 and ms[stage] > 0 for stage in ("router", "route", "gate_up", "down", "combine"))
+    assert ms["route"] == ms["gate_up"] and ms["down"] == ms["combine"]
+    assert (layer.out == small).all()
+    # more than 64 slots
+    times = -(-65 // T)
+    again = copy.copy(wl)
+    again.hidden = np.concatenate([wl.hidden] * times)
+    large = dev.DeviceLayer.from_workload(again, sim, S, rho, weights=layer.weights())
+    large.run_baseline()
+    after = large.routing_to_host()
+    for name in ("topk_ids", "rerouted_ids"):
+        assert np.array_equal(after[name], np.concatenate([before[name]] * times)), name
+    for name in ("primary_mask", "num_active"):
+        assert np.array_equal(after[name], before[name]), name
+    for name in ("count_before", "count_after", "expert_offsets"):
+        assert np.array_equal(after[name], times * before[name]), name
     # both are within half the tolerance of the exact result's rounding, so within it of each other
-    assert np.abs(small - layer.out_to_host_f64()).max() <= max(TOL[dtype][0], np.abs(small).max() * 2.0 ** -7 if dtype == wk.BF16 else 0.0)
+    small, rest = small.double().cpu().numpy(), large.out_to_host_f64()[:T]
+    assert np.abs(small - rest).max() <= max(TOL[dtype][0], np.abs(small).max() * 2.0 ** -7 if dtype == wk.BF16 else 0.0)
 
 
 @pytest.mark.parametrize("dtype", [wk.BF16, wk.F32])

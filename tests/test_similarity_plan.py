@@ -49,12 +49,11 @@ def test_no_group_needs_more_than_a_larger_one(layouts):
     assert grouped > 1000      # otherwise the draw would say nothing
 
 
-def test_layers_of_more_than_8_mib_are_grouped(layouts):
+def test_layers_of_every_size_are_grouped(layouts):
     cases = [(B.SERE_BF16, 256, 16, 128 * k, 20, f, 64) for k in (1, 5, 6, 20) for f in METRICS]   # 3, 7.9, 9.4, 31 MB
     cases += [(B.SERE_F32, 256, 16, 128 * k, 20, f, 64) for k in (1, 2, 3, 10) for f in METRICS]   # 6, 13, 19, 63 MB
     for case, groups in zip(cases, layouts(cases)):
-        weights = case[2] * 3 * case[1] * case[3] * (4 if case[0] == B.SERE_F32 else 2)
-        assert len(groups) == (12 if weights > 8 << 20 else 1), case
+        assert len(groups) == 12, case
 
 
 def test_plans_of_groups_can_be_run(layouts):
