@@ -62,6 +62,7 @@
 #include "common.hpp"
 #include "ffn_generic.hpp"
 #include "ffn_mfma.hpp"
+#include "rules.hpp"
 
 namespace sere {
 
@@ -94,7 +95,6 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
-constexpr unsigned kXcds = 8;
 constexpr int kTileThreads = 512;
 constexpr int kTileWaves = kTileThreads / kWave;
 constexpr int kTileLds = 160 * 1024;
@@ -124,7 +124,7 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F&& f
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-constexpr unsigned kStride = kTileGroups / kXcds;   // workgroups of an XCD
+static_assert(kXcds * kXcdGroups == kTileGroups, "every workgroup has its turn on an XCD");
 
 // units of an item
 template <bool GATEUP, int BM>
@@ -134,7 +134,7 @@ __device__ __forceinline__ int tile_parts(const FfnArgs& p) {
 }
 
 // h[row, j] = silu(gate) * up, or y[slice][row][r] = partial down projection, of the units of an XCD from place `lo` up to `hi`, of which
-// this workgroup takes one of every kStride.  Items have at most TileShape::kRealRows rows; p.ksplit slices of d_m (down), none
+// this workgroup takes one of every kXcdGroups.  Items have at most TileShape::kRealRows rows; p.ksplit slices of d_m (down), none
 // of them empty.  SPLIT = 2: halves of units of 2 BM weight rows, and at most one for a workgroup.
 template <int DT, bool GATEUP, int BM, int BN, int WN, bool LO, int SPLIT>
 __device__ __forceinline__ void tile_units(const FfnArgs& p, unsigned char* lds, unsigned lo, unsigned hi, unsigned longs, unsigned to_long,
@@ -159,21 +159,14 @@ __device__ __forceinline__ void tile_units(const FfnArgs& p, unsigned char* lds,
   const int blocks = ld * EB / kRowBytes, per = (blocks + ksplit - 1) / ksplit;
   constexpr bool kLongFirst = DT == SERE_F32;
   const unsigned turn = blockIdx.x / kXcds;
-  const unsigned back = longs / kStride;                 // last round that holds long units
   const auto next_unit = [&](unsigned u) __attribute__((always_inline)) {
-    if (!kLongFirst) return u + kStride;
-    const unsigned round = u / kStride + 1;
-    return round * kStride + (round > back ? kStride - 1 - turn : turn);
+    return kLongFirst ? next_place_long_first(u, turn, longs) : u + kXcdGroups;
   };
-  const auto unit_at = [&](unsigned u) __attribute__((always_inline)) { return kLongFirst ? u + (u < longs ? to_long : to_other) : u; };
+  const auto unit_at = [&](unsigned u) __attribute__((always_inline)) { return kLongFirst ? unit_at_long_first(u, longs, to_long, to_other) : u; };
   unsigned pu = lo + turn;                               // unit being loaded
   unsigned cu = pu;                                      // unit being multiplied
   if (pu >= hi) return;
-  // first output column; a last unit's second half may have none
-  const auto first_out = [&](unsigned u) __attribute__((always_inline)) {
-    return static_cast<int>(u / SPLIT % parts / ksplit * SPLIT + u % SPLIT) * kOut;
-  };
-  if (SPLIT > 1 && first_out(pu) >= outs) return;
+  if (SPLIT > 1 && unit_first_out(pu, SPLIT, parts, ksplit, kOut) >= outs) return;
 
   // ---- loading side
   constexpr int CH = kRowBytes / 16;                     // pieces of a row
@@ -447,11 +440,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kRing > kHalfRing ? kRing : kHalfRing];
   const unsigned parts = tile_parts<GATEUP, BM>(p), total = static_cast<unsigned>(scalar_load(p.n_work, 0)) * parts;
   const unsigned xcd = blockIdx.x % kXcds;
-  const auto share = [](unsigned n, unsigned x) { return n / kXcds * x + min(x, n % kXcds); };   // units before XCD x's
   // This workgroup's units: one of every round of its XCD's contiguous range.
   if constexpr (kHalves) {
-    const unsigned lo = share(total, xcd), hi = share(total, xcd + 1);
-    const unsigned rest = (hi - lo) % kStride, whole = rest <= kStride / 2 ? hi - rest : hi;
+    const unsigned lo = xcd_share(total, xcd), hi = xcd_share(total, xcd + 1);
+    const unsigned whole = whole_units_end(lo, hi);
     tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, lo, whole, 0, 0, 0);
     if (whole < hi) {
       __builtin_amdgcn_s_barrier();                      // every wavefront has read its last stage
@@ -459,15 +451,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
       tile_units<DT, GATEUP, BM / 2, BN, WN, LO, 2>(p, lds, 2 * whole, 2 * hi, 0, 0, 0);
     }
   } else if constexpr (DT == SERE_BF16) {
-    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, share(total, xcd), share(total, xcd + 1), 0, 0, 0);
+    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, xcd_share(total, xcd), xcd_share(total, xcd + 1), 0, 0, 0);
   } else {
-    // An eighth of the units of the long items and then an eighth of the others; the rounds that hold long ones go round the
-    // XCD's workgroups one way, the ones behind them the other way, so that those without a long unit get the one more
-    // that a last round has for some.
-    const unsigned total_long = static_cast<unsigned>(scalar_load(p.n_work, 2)) * parts, others = total - total_long;
-    const unsigned to_long = share(total_long, xcd), longs = share(total_long, xcd + 1) - to_long;
-    const unsigned before = share(others, kXcds - xcd), after = share(others, kXcds - 1 - xcd);
-    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, 0, longs + before - after, longs, to_long, total - before - longs);
+    const LongFirst f = long_first(total, static_cast<unsigned>(scalar_load(p.n_work, 2)) * parts, xcd);
+    tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, 0, f.count, f.longs, f.to_long, f.to_other);
   }
 }
 

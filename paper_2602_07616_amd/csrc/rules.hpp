@@ -1,5 +1,5 @@
 // Integer rules that the kernels follow and that the tests run on the CPU: the ranking of a token's sorted lists in calls of few
-// slots.  constexpr, and so for host and device alike.
+// slots, and which workgroup of the persistent FFN kernels has which units.  constexpr, and so for host and device alike.
 #pragma once
 
 #include <cstdint>
@@ -17,6 +17,46 @@ constexpr uint32_t rank_word(uint64_t key, int place, int places) {
 }
 constexpr bool ranks_before(uint64_t other, int other_place, uint64_t key, int place) {
   return other > key || (other == key && other_place < place);
+}
+
+// ---- units of the persistent FFN kernels (ffn_tile.hpp).  Workgroup b is on XCD b % kXcds, the (b / kXcds)-th there (its turn).
+// An XCD has places [lo, hi) of the units, of which a workgroup starts at lo + turn.
+constexpr unsigned kXcds = 8;
+constexpr unsigned kXcdGroups = 32;   // workgroups of an XCD
+
+// units before XCD x's contiguous range of n
+constexpr unsigned xcd_share(unsigned n, unsigned x) { return n / kXcds * x + (x < n % kXcds ? x : n % kXcds); }
+
+// bf16: end of the whole units; the ones behind are cut into halves, one for every workgroup: places [2 whole, 2 hi).  Where at most
+// half of the workgroups would get one more unit.
+constexpr unsigned whole_units_end(unsigned lo, unsigned hi) {
+  const unsigned rest = (hi - lo) % kXcdGroups;
+  return rest <= kXcdGroups / 2 ? hi - rest : hi;
+}
+// first output column of place u; split: 1, or 2 for halves.  A last unit's second half may have none.
+constexpr int unit_first_out(unsigned u, unsigned split, int parts, int ksplit, int out) {
+  return static_cast<int>(u / split % parts / ksplit * split + u % split) * out;
+}
+
+// fp32: an XCD has an eighth of the units of the long items, which come first, and behind them an eighth of the others, counted
+// from the other end.
+struct LongFirst {
+  unsigned longs, count;          // places of long units; of all
+  unsigned to_long, to_other;     // from a place to the unit
+};
+constexpr LongFirst long_first(unsigned total, unsigned total_long, unsigned xcd) {
+  const unsigned others = total - total_long, to_long = xcd_share(total_long, xcd), longs = xcd_share(total_long, xcd + 1) - to_long;
+  const unsigned before = xcd_share(others, kXcds - xcd), after = xcd_share(others, kXcds - 1 - xcd);
+  return {longs, longs + before - after, to_long, total - before - longs};
+}
+// The place after u: the rounds that hold long units go round the workgroups one way, the ones behind them the other way, so
+// that those without a long unit get the one more that a last round has for some.
+constexpr unsigned next_place_long_first(unsigned u, unsigned turn, unsigned longs) {
+  const unsigned round = u / kXcdGroups + 1;
+  return round * kXcdGroups + (round > longs / kXcdGroups ? kXcdGroups - 1 - turn : turn);
+}
+constexpr unsigned unit_at_long_first(unsigned u, unsigned longs, unsigned to_long, unsigned to_other) {
+  return u + (u < longs ? to_long : to_other);
 }
 
 }  // namespace sere

@@ -1,6 +1,6 @@
 """CPU-only checks of rules that the kernels rely on, written out again in Python from
-their descriptions (the device code is not run here): the XCD-aware numbering of the persistent FFN
-kernels' units must give every unit of (item, part) to one workgroup, and the cut of a long
+their descriptions (the device code is not run here): an item of the persistent FFN kernels stays on one XCD as far
+as contiguous ranges let it (tests/test_tile_units.py walks the numbering itself), and the cut of a long
 expert into equal work items must give positive, tile-sized items that add up to the expert's rows."""
 import glob
 import os
