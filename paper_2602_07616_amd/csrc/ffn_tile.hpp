@@ -33,7 +33,8 @@
 //    every workgroup: half the weights and the same token rows are some two thirds of the time, less 2 us to start again (us, gate/up +
 //    down: 777 tokens of d_h 2880, d_m 1472, 2.3 rounds each, 156 + 92 -> 149 + 88, a call 279 -> 263; 2048 tokens of the Qwen3
 //    shape, items in excess of three and four rounds, 175 + 121 -> 166 + 117; 128 tokens, down 59.6 -> 57.7).  The sums are the same ones.
-//    (Not for gate/up units of 256 weight rows x 256 token rows, whose wavefronts have no registers to spare.)
+//    (Not for gate/up units of fewer than five k steps behind whole ones, halves_pay in rules.hpp, nor for those of 256 weight rows x 256
+//    token rows, whose wavefronts have no registers to spare.)
 //  - fp32: an item of more than 16 rows takes half as long again as a shorter one (31 against 23 us a gate/up unit in a first
 //    round, 25 against 17 in a second; d_h 1024), and few layers have more than two rounds of units.  The work list then has
 //    the long items first, every XCD gets an eighth of their units, and a workgroup that starts with one is the
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void ffn_tile(FfnArgs p) {
   // This workgroup's units: one of every round of its XCD's contiguous range.
   if constexpr (kHalves) {
     const unsigned lo = xcd_share(total, xcd), hi = xcd_share(total, xcd + 1);
-    const unsigned whole = whole_units_end(lo, hi);
+    const unsigned whole = whole_units_end(lo, hi, halves_pay(GATEUP, p.dh / 64));   // (p.dh: of gate/up)
     tile_units<DT, GATEUP, BM, BN, WN, LO, 1>(p, lds, lo, whole, 0, 0, 0);
     if (whole < hi) {
       __builtin_amdgcn_s_barrier();                      // every wavefront has read its last stage

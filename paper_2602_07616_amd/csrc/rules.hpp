@@ -28,11 +28,18 @@ constexpr unsigned kXcdGroups = 32;   // workgroups of an XCD
 constexpr unsigned xcd_share(unsigned n, unsigned x) { return n / kXcds * x + (x < n % kXcds ? x : n % kXcds); }
 
 // bf16: end of the whole units; the ones behind are cut into halves, one for every workgroup: places [2 whole, 2 hi).  Where at most
-// half of the workgroups would get one more unit.
-constexpr unsigned whole_units_end(unsigned lo, unsigned hi) {
+// half of the workgroups would get one more unit, and `pays` says so or there are no whole ones before.
+constexpr unsigned whole_units_end(unsigned lo, unsigned hi, bool pays) {
   const unsigned rest = (hi - lo) % kXcdGroups;
-  return rest <= kXcdGroups / 2 ? hi - rest : hi;
+  return rest <= kXcdGroups / 2 && (pays || rest == hi - lo) ? hi - rest : hi;
 }
+// Whether halves pay behind whole units.  They start a ring of their own, and a half is some two thirds of a unit: gate/up
+// needs some steps for that.  A down unit stores four times the bytes, half of which is worth it at any length.  us a launch with
+// halves by us without, over 170 launches of layers whose tokens select all experts, one to four whole rounds: gate/up of 1 to 3 steps
+// 1.04 on average (0.98 to 1.10), 4 1.01 to 1.02, 5 and 6 0.99 (0.95 to 1.05), 7 0.99 (0.97 to 1.01), 8 to 13 0.97 (0.91 to 1.01), more
+// 0.93; down of 2 to 5 steps 0.94 (0.82 to 1.00), of 7 to 13 0.96.
+constexpr int kHalvesGateUpSteps = 5;
+constexpr bool halves_pay(bool gate_up, int steps) { return !gate_up || steps >= kHalvesGateUpSteps; }
 // first output column of place u; split: 1, or 2 for halves.  A last unit's second half may have none.
 constexpr int unit_first_out(unsigned u, unsigned split, int parts, int ksplit, int out) {
   return static_cast<int>(u / split % parts / ksplit * split + u % split) * out;

@@ -24,7 +24,8 @@ def units(tmp_path_factory):
 def draw(rng, f32):
     items = rng.choice([1, 2, 3, 7, 8, 31, 32, 33, 64, rng.randint(1, 700)])
     longs = rng.choice([0, items, min(items, 32), rng.randint(0, items)]) if f32 else 0
-    return f32, items, longs, rng.choice([1, 2, 3, 5, 8, 11, 16, 32]), 1 if f32 else rng.choice([1, 1, 2, 3]), rng.randint(0, 1)
+    return (f32, rng.randint(0, 1), items, longs, rng.choice([1, 2, 3, 5, 8, 11, 16, 32]), 1 if f32 else rng.choice([1, 1, 2, 3]),
+            rng.randint(1, 20), rng.randint(0, 1))
 
 
 def test_every_unit_has_one_workgroup(units):
@@ -32,7 +33,7 @@ def test_every_unit_has_one_workgroup(units):
     cases = [draw(rng, f32) for f32 in (0, 1) for _ in range(1500)]
     cut = uncut = 0
     for case, (wrong, whole, halves, most, *_) in zip(cases, units(cases)):
-        f32, items, _, blocks, ksplit, tail = case
+        f32, gate_up, items, _, blocks, ksplit, steps, tail = case
         total = items * blocks * ksplit
         assert wrong == 0 and most <= 1, case
         if f32 or tail:
@@ -42,12 +43,24 @@ def test_every_unit_has_one_workgroup(units):
     assert cut > 300 and uncut > 300
 
 
+def test_halves_behind_whole_units_only_where_they_pay(units):
+    """A remainder of up to half of an XCD's workgroups; gate/up from five k steps on, down always.  With no whole units
+    before, always."""
+    for rest in range(1, 32):
+        for rounds in (0, 1, 3):
+            items = 8 * (32 * rounds + rest)
+            cases = [(0, gate_up, items, 0, 1, 1, steps, 1) for gate_up in (0, 1) for steps in (1, 3, 4, 5, 30)]
+            for case, (_, whole, halves, *_) in zip(cases, units(cases)):
+                pays = rest <= 16 and (rounds == 0 or case[1] == 0 or case[6] >= 5)
+                assert (whole, halves) == ((256 * rounds, 16 * rest) if pays else (items, 0)), case
+
+
 def test_workgroups_with_a_long_unit_get_a_further_one_last(units):
     """Every XCD has an eighth of the long units and of the others; the first round takes the long ones and the second goes the other
     way round the workgroups."""
-    cases = [(1, 8 * (longs + others), 8 * longs, 1, 1, 1) for longs in range(1, 33) for others in (32 - longs, 48 - longs, 64 - longs)]
+    cases = [(1, 1, 8 * (longs + others), 8 * longs, 1, 1, 8, 1) for longs in range(1, 33) for others in (32 - longs, 48 - longs, 64 - longs)]
     for case, (wrong, whole, _, _, both) in zip(cases, units(cases)):
-        longs, second = case[2] // 8, case[1] // 8 - 32
-        assert (wrong, whole) == (0, case[1])
+        longs, second = case[3] // 8, case[2] // 8 - 32
+        assert (wrong, whole) == (0, case[2])
         if longs < 32:
             assert both == 8 * max(0, longs + second - 32), case
