@@ -273,13 +273,15 @@ inline int small_split(int blocks, int rows) {
   return split;
 }
 
-// Whether these launches are the faster ones: us of a call by either way, both fitted to 370 layers that small_call_fits, timed
-// with both (d_h 256 to 4096, d_m 128 to 4032, 2 to 160 experts, 1 to 16 tokens, 1 to 740 MB of weights).  What costs
-// most here is rounds of units and, in a long contraction, of loads; the other launches start at 23 us (fp32 26 and more) and take the
-// weights as they come.  bf16: 0.83 to 1.9 times as fast where this rule takes them, 1.2 on average, and what it leaves out
-// would be 0.5 to 1.2 times; fp32: 1.05 to 2.1 times.  More than 16 tokens (fp32): with up to a dozen items, of which 85 of 172
-// more layers were taken, 1.01 to 2.19 times as fast, 1.47 on average (25 tokens of three experts of 960 x 1024 54.1 -> 27.2); with
-// more items 0.7 to 1.6 times, and what the rule reads of a layer does not tell which.
+// Whether these launches are the faster ones: us of a call by either way, both fitted to 885 bf16 and 495 fp32 layers that
+// small_call_fits, timed with both (d_h 256 to 4096, d_m 128 to 4032, 2 to 160 experts, 1 to 16 tokens, 1 to 740 MB of weights).
+// What costs most here is rounds of units and, in a long contraction, of loads; then the top-K, a wavefront's tokens one after the
+// other, the exchange between wavefronts that more than eight primary slots need, and the rows of h and y.  The other launches start at 23 us
+// (fp32 29 and more) and take the weights as they come.  The fits are within 5 to 15 % of a layer, hence the margin.  On these layers and
+// 650 others: bf16 674 of 1280 taken, 0.95 to 1.6 times as fast there, 1.2 on average, four of them less than 0.97 times (without
+// the top-K, the exchange and the rows 44 were, down to 0.68); fp32 0.95 to 2.3 times, three less than 0.97.  fp32 calls of more than 16
+// tokens: with up to a dozen items, 154 of 182 layers, 0.96 to 2.2 times as fast, 1.45 on average; with more items 0.7 to 1.6 times, and what
+// the rule reads of a layer does not tell which.
 inline bool small_call_pays(const sere_config& c, bool reroute) {
   if (!small_call_fits(c)) return false;
   const auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
@@ -298,9 +300,14 @@ inline bool small_call_pays(const sere_config& c, bool reroute) {
                     ceil_div(ceil_div(gu_blocks, split), kSmallAhead);
   const double dn = std::ceil(items * slices / kSmallWaves) * ceil_div(ceil_div(dn_blocks, slices), kSmallAhead) *
                     std::max(1.0, c.hidden / (256.0 * kSmallOut));
-  const double small = 13.3 + passes * (3.3 * gu + 0.66 * dn) + 0.105 * slots + 0.057 * mb;
-  const double other = c.dtype == SERE_F32 ? 26.5 + 0.196 * mb + 0.0087 * c.hidden : 23.2 + 0.133 * mb;
-  return small < (c.num_tokens > kSmallTile ? 1.0 : 0.96) * other;   // (the other launches' start was fitted to 16 tokens)
+  const double topk = std::ceil(T / kSmallWaves) * (M <= 128 ? std::ceil(M / 16.0) / 8.0 : 2.0);
+  const double exchange = reroute && c.select_top_k < c.top_k && T * c.select_top_k > 8 ? 1.0 : 0.0, rows = slots + T * c.num_shared;
+  const double small = c.dtype == SERE_F32
+                           ? 16.1 + passes * (0.55 * gu + 0.84 * dn) + 0.014 * slots + 0.175 * mb + 1.44 * topk + 0.94 * exchange + 0.027 * rows
+                           : 13.3 + passes * (3.18 * gu + 0.45 * dn) + 0.06 * slots + 0.098 * mb + 1.15 * topk + 0.82 * exchange + 0.019 * rows;
+  const double other = c.dtype == SERE_F32 ? 27.2 + 0.167 * mb + 0.0089 * c.hidden
+                                           : 22.7 + 0.156 * mb + 0.25 * std::ceil(M / 16.0) - 0.129 * items;
+  return small < 0.93 * other;
 }
 
 }  // namespace sere

@@ -20,12 +20,12 @@ CASES = [
     (wk.F32, 1, 64, 3, 3, 64, 4, 1, 0.5),           # one token, shared experts
     (wk.F32, 8, 1024, 8, 8, 256, 0, 8, 0.0),        # 64 slots, all primary
     (wk.F32, 3, 192, 256, 8, 64, 0, 3, 0.0),        # 16 lists of experts, nine primary slots
-    (wk.BF16, 4, 320, 129, 8, 128, 1, 2, 0.0),      # eight primary slots: every wavefront looks at all of them; nine lists
-    (wk.BF16, 5, 320, 113, 4, 128, 0, 2, 0.4),      # ten: each looks at some; the last list has one expert
+    (wk.BF16, 2, 320, 129, 5, 128, 1, 4, 0.0),      # eight primary slots: every wavefront looks at all of them; nine lists
+    (wk.BF16, 5, 320, 113, 3, 64, 0, 2, 0.4),       # ten: each looks at some; the last list has one expert
     (wk.F32, 16, 512, 16, 4, 256, 0, 3, 0.3),       # 64 slots
     (wk.F32, 16, 448, 2, 2, 192, 4, 1, 0.0),        # a whole tile of rows for every shared expert, 96 rows in all
     (wk.F32, 7, 1472, 33, 3, 320, 2, 1, 0.0),       # blocks that do not split evenly
-    (wk.BF16, 3, 4096, 20, 5, 320, 0, 2, 0.6),      # two rounds of loads
+    (wk.BF16, 3, 4096, 20, 3, 320, 0, 2, 0.6),      # two rounds of loads
     (wk.F32, 2, 512, 60, 4, 1088, 0, 1, 0.0),       # more units than workgroups without re-routing
     (wk.F32, 9, 1024, 64, 7, 128, 1, 3, 0.5),       # 63 slots and a shared expert: the longest work list
     (wk.F32, 17, 768, 9, 1, 320, 0, 1, 0.0),        # a tile and a row of tokens
