@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 # T, M, K
 CASES = [(33, 40, 1), (33, 40, 7), (20, 64, 12), (9, 128, 8), (70, 128, 8), (33, 113, 16), (300, 128, 5), (40, 256, 8), (17, 200, 30),
-         (5, 256, 256), (33, 17, 17)]
+         (5, 256, 256), (33, 17, 17),
+         (33, 64, 9), (21, 64, 16), (9, 50, 17), (400, 64, 17), (33, 64, 32), (6, 33, 33)]      # up to 4, 8 and 16 logits of a lane
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c))
