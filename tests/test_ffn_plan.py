@@ -8,7 +8,7 @@ import subprocess
 import pytest
 
 from paper_2602_07616_amd import binding as B, workloads as wk
-from . import test_gpu_ffn_tile as gpu, test_gpu_wide_gate_up as gpu_wide
+from . import test_gpu_ffn_tile as gpu, test_gpu_nonfinite as gpu_nonfinite, test_gpu_wide_gate_up as gpu_wide
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -99,8 +99,15 @@ def test_gpu_cases_get_the_plans_they_are_there_for(plans):
     for S in (lambda K: 1, lambda K: K):         # both settings that the GPU test runs
         got = plans([call(B.SERE_BF16, *c, S(c[3])) for c in gpu.CASES], "call")
         assert dict(zip(gpu.CASES, got)) == gpu.CASES
-    got = plans([call(B.SERE_F32, *c, 1, 0.3) for c in gpu.F32_CASES], "call")
-    assert [g[1:3] for g in got] == [(0, 0), (0, 0)] + [(1, 1)] * 5
+
+
+def test_gpu_cases_of_fp32_layers_reach_the_kernels_that_they_name(plans):
+    """What decode() does: the launches for few slots where they pay, else the plan's kernels."""
+    calls = {call(B.SERE_F32, *c, S, rho): kind for c, kind in gpu.F32_CASES.items() for S, rho in ((1, 0.3),)}
+    calls.update({call(B.SERE_F32, T, 1472, M, M, 192, 0, M): kind for (T, M), kind in gpu_nonfinite.F32_CALLS.items()})
+    for c, plan, (fits, pays, *_) in zip(calls, plans(calls, "call"), plans(calls, "small")):
+        assert ("few" if pays else "tile" if plan[1] else "alu") == calls[c] and plan[1] == plan[2], c
+    assert set(gpu.F32_CASES.values()) == set(gpu_nonfinite.F32_CALLS.values()) == {"few", "alu", "tile"}
 
 
 def test_gpu_cases_reach_every_kernel_of_a_plan(plans):

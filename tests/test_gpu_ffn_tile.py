@@ -67,11 +67,13 @@ def test_every_item_size(dev, case):  # noqa: F811
         assert (layer.out == first).all()          # the same bits again
 
 
-F32_CASES = [
-    # T, d_h, M, K, d_m, shared: the vector-ALU kernels below 9 tokens with long contractions, else the persistent ones
-    (1, 1472, 17, 4, 192, 1), (8, 1472, 5, 2, 704, 0), (8, 256, 16, 2, 128, 0), (9, 1472, 5, 2, 704, 1),
-    (33, 64, 2, 2, 64, 1), (70, 320, 3, 1, 448, 0), (300, 704, 8, 2, 1088, 2),
-]
+F32_CASES = {
+    # T, d_h, M, K, d_m, shared: the two launches of calls of few slots, the vector-ALU kernels (below 9 tokens, where those do not take the
+    # call) or the persistent ones
+    (1, 1472, 17, 4, 192, 1): "few", (8, 1472, 5, 2, 704, 0): "few", (8, 256, 16, 2, 128, 0): "few", (9, 1472, 5, 2, 704, 1): "few",
+    (1, 1472, 17, 9, 192, 1): "alu", (8, 1472, 8, 8, 64, 1): "alu", (6, 2880, 11, 9, 128, 0): "alu",
+    (33, 64, 2, 2, 64, 1): "tile", (70, 320, 3, 1, 448, 0): "tile", (300, 704, 8, 2, 1088, 2): "tile", (9, 1472, 9, 9, 192, 1): "tile",
+}
 
 
 @pytest.mark.parametrize("case", F32_CASES, ids=lambda c: "x".join(str(v) for v in c))

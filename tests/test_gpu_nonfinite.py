@@ -31,12 +31,16 @@ def f32_layer(wl, ref):
     return out
 
 
-@pytest.mark.parametrize("tokens", [4, 40])     # the vector-ALU kernels, the persistent ones
+# (tokens, experts = K): the two launches of calls of few slots, the vector-ALU kernels, the persistent ones
+F32_CALLS = {(4, 3): "few", (4, 9): "alu", (40, 3): "tile"}
+
+
+@pytest.mark.parametrize("tokens,M", F32_CALLS)
 @pytest.mark.parametrize("where", ["up_inf_first", "up_inf_last", "up_overflow", "up_overflow_far", "down_inf", "down_neg_inf"])
-def test_fp32_sum_that_overflows_is_infinite(dev, tokens, where):  # noqa: F811
+def test_fp32_sum_that_overflows_is_infinite(dev, tokens, M, where):  # noqa: F811
     """One infinite weight, or two finite ones whose products overflow (in one 32-wide step, or in two), in the first,
     a middle or the last step of the contraction: the sums are infinite, with the sign of the exact sum."""
-    dh, M, K, dm = 1472, 3, 3, 192
+    dh, K, dm = 1472, M, 192
     spec = wk.custom_spec("nonfinite", wk.F32, dh, M, K, dm, 0, tokens, 7300, calib_batches=1, calib_tokens=4)
     wl = wk.make_workload(spec)
     up, down = wl.w_gate_up[2][dm:], wl.w_down[2]
@@ -56,7 +60,7 @@ def test_fp32_sum_that_overflows_is_infinite(dev, tokens, where):  # noqa: F811
     layer = dev.DeviceLayer.from_workload(wl, sim, K, 0.0)
     ref = oracle.route(wl.hidden, wl.router_w, wk.F32, K, sim, K, 0.0)
     assert (ref.rerouted_ids == 2).any()
-    print(f"nonfinite {where} {tokens}", flush=True)
+    print(f"nonfinite {where} {tokens} {M}", flush=True)
     layer.run_decode()
     got, want = layer.out_to_host_f64(), f32_layer(wl, ref)
     assert np.isinf(want).any() and not np.isnan(want).any()
