@@ -52,7 +52,8 @@ struct TileVariant {
 // tokens and random ones: d_h 256 to 4096, d_m 128 to 14336, 2 to 160 experts, 1 to 4000 tokens), every item size
 // and both kinds of kernels timed on each.  Over these layers what plan_ffn picks, with all its rules, takes 2.6 %
 // longer than the best choice on average, 17 % less than the decode kernels alone, and 15 % less than one rule for
-// all (items of 32 to 256 rows by rows per expert) with the workgroup-staged kernels of earlier.
+// all (items of 32 to 256 rows by rows per expert) with the workgroup-staged kernels of earlier.  (Timed and fitted before last rounds
+// of units were cut into halves, rules.hpp: the costs charge a part-filled round as a whole one, where halves make it two thirds.)
 inline const TileVariant* tile_variants(bool split_h, int* count) {
   // a step of a unit of 256 weight rows: 0.74 us and 2.6 ns for every token row; of 128 rows measured on its own
   static const TileVariant plain[] = {{32, 128, 256, 0.82, 0.82},  {64, 128, 256, 0.91, 0.91}, {96, 128, 256, 0.99, 0.99},
@@ -138,7 +139,9 @@ inline double gate_up_bytes(const FfnShape& s) { return (s.experts + s.num_share
 // part-filled round of these units is no shorter than a full one, as tile_cost takes it to be for the narrower ones, so their
 // rounds have to be the shorter ones without that, too.  us a call of 59 layers whose tokens select all 1 to 16 experts, by the
 // rounds' time against that of the units of 128: below 0.9 times 3 to 9 % less (157.6 -> 150.2; one layer the same), 0.9 to 1.0
-// times 1 % more to 6 % less, 1.0 to 1.04 times 2 % less to 2 % more, beyond 1 to 8 % more (127.8 -> 134.1).
+// times 1 % more to 6 % less, 1.0 to 1.04 times 2 % less to 2 % more, beyond 1 to 8 % more (127.8 -> 134.1).  Where they are taken
+// they still pay now that last rounds of the narrower units are cut into halves: ten layers by these units / by those, 1 to 8 % less
+// (141 / 152, 158 / 165, 75.5 / 76.0).
 // For items that are known, or all but known (spread 0): similarity calls, where every expert has every token, and
 // layers whose tokens select every expert (K = M; re-routing that takes an expert out gives its rows to another, and the
 // number of items stays about the same: 12 layers with S = 1 gained as much as without re-routing).  Where the rows per
