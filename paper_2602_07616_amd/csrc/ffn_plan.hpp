@@ -281,9 +281,9 @@ inline int small_split(int blocks, int rows) {
 // What costs most here is rounds of units and, in a long contraction, of loads; then the top-K, a wavefront's tokens one after the
 // other, the exchange between wavefronts that more than eight primary slots need, and the rows of h and y.  The other launches start at 23 us
 // (fp32 29 and more) and take the weights as they come.  The fits are within 5 to 15 % of a layer, hence the margin.  On these layers and
-// 650 others: bf16 675 of 1280 taken, 0.95 to 1.6 times as fast there, 1.2 on average, four of them less than 0.97 times (without
-// the top-K, the exchange and the rows 44 were, down to 0.68); fp32 0.95 to 2.3 times, three less than 0.97.  fp32 calls of more than 16
-// tokens: with up to a dozen items, 154 of 182 layers, 0.96 to 2.2 times as fast, 1.45 on average; with more items 0.7 to 1.6 times, and what
+// 650 others: bf16 675 of 1280 taken, 0.95 to 1.7 times as fast there, 1.2 on average, four of them less than 0.97 times (without
+// the top-K, the exchange and the rows 44 were, down to 0.68); fp32 711 of 750, 0.95 to 2.6 times, three less than 0.97.  fp32 calls of more than 16
+// tokens: with up to a dozen items, 154 of 182 layers, 0.96 to 2.0 times as fast, 1.45 on average; with more items 0.7 to 1.6 times, and what
 // the rule reads of a layer does not tell which.
 inline bool small_call_pays(const sere_config& c, bool reroute) {
   if (!small_call_fits(c)) return false;
